@@ -1,18 +1,24 @@
-// bf16-input, fp32-accumulate members of the tiled GEMM family (paper Section II), MFMA only.
+// 16-bit-input, fp32-accumulate members of the tiled GEMM family (paper Section II), MFMA only: the
+// parts both operand paths share, and the register-staged path, which takes any operand.
 //
 // An instantiation fixes the work-group tile BM x BN, the K-step BK (multiple of 32), the wave
 // tile WM x WN and the MFMA fragment F (32: v_mfma_f32_32x32x16_bf16, 16: v_mfma_f32_16x16x32_bf16).
-// Both operand tiles are staged in LDS K-contiguous, tile[row][BK], in 16-byte chunks of eight
-// consecutive k, because every lane of these MFMAs consumes eight consecutive k of one row.
-// Chunk positions inside a row are XOR-swizzled so that the 16 lanes of one ds_read_b128 phase,
-// which read the same k-chunk of 16 consecutive rows, fall into 16 different bank groups.
 //
-//   AKC / BKC  operand is K-contiguous in memory (A: transA == 0, B: transB == 1): chunks are
-//              copied straight through.  Otherwise an 8(k) x 8(row) block is loaded along the
-//              contiguous row direction and transposed in registers before it is written.
-//   VEC        16-byte global accesses are legal (alignment, leading dimension and contiguous
-//              extent multiples of 8); otherwise scalar.  Every access is edge-predicated.
+// LDS layouts (both paths)
+//   K-contiguous operand (A not transposed, B transposed):  tile[row][BK] in 16-byte chunks of eight
+//     consecutive k; chunk c of row r sits at chunk position c ^ swz(r) (Bf16Lds), read with
+//     ds_read_b128: the 16 lanes of one read phase, which want the same k-chunk of 16 consecutive
+//     rows, fall into 16 different bank groups.
+//   row-contiguous operand (A transposed, B not transposed): tile[k][ROWS] exactly as in memory;
+//     32-byte units are XOR-swizzled by k (Bf16LdsT).  The MFMA operand (8 consecutive k of one row
+//     per lane) is produced by the transposing LDS read ds_read_b64_tr_b16: inside each group of 16
+//     lanes, lane s supplies the address of 4 consecutive rows at k = kb + s/4, and lane l
+//     receives the 4 values k = kb .. kb+3 of row l.
+//
+//   AKC / BKC  operand is K-contiguous in memory (A: transA == 0, B: transB == 1)
 #pragma once
+#include <type_traits>
+
 #include "ks_common.hpp"
 
 namespace ks {
@@ -20,6 +26,8 @@ namespace ks {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
 typedef unsigned int uintx4 __attribute__((ext_vector_type(4)));
+typedef short shortx4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) void *lds_void_ptr;
 
 // The 16-bit members move bit patterns; only the MFMA instruction knows whether they are bf16 or
 // IEEE binary16 (F16: v_mfma_f32_16x16x32_f16 / v_mfma_f32_32x32x16_f16).
@@ -49,104 +57,174 @@ struct Bf16Lds {
     }
 };
 
-template <int ROWS, int BK, int NT, bool KC, bool VEC>
-struct Bf16TileLoader {
-    using L = Bf16Lds<BK>;
-    static constexpr int CPR = BK / 8;
-    // KC: units are chunks, INNER = CPR along k.  !KC: units are 8x8 blocks, INNER = ROWS/8 along rows.
-    static constexpr int INNER = KC ? CPR : ROWS / 8;
-    static constexpr int OUTER = KC ? ROWS : CPR;
-    static constexpr int UNITS = INNER * OUTER;
-    static constexpr int ITERS = (UNITS + NT - 1) / NT;
-    static constexpr int REGS = KC ? 1 : 8;
-    static_assert((INNER <= NT && NT % INNER == 0) || (INNER > NT && INNER % NT == 0), "walk");
-
-    uintx4 reg[ITERS][REGS];
-
-    __device__ __forceinline__ static void unit(int tid, int it, int &inner, int &outer) {
-        if constexpr (INNER <= NT) {
-            inner = tid % INNER;
-            outer = tid / INNER + it * (NT / INNER);
-        } else {
-            inner = tid + (it % (INNER / NT)) * NT;
-            outer = it / (INNER / NT);
-        }
+// F: fragment edge of the MFMAs that read the tile (the unit swizzle of narrow tiles depends on it)
+template <int ROWS, int F = 32>
+struct Bf16LdsT {
+    static constexpr int CPR = ROWS / 8;                    // 16-byte chunks per k row
+    static constexpr int UPR = ROWS / 16;                   // 32-byte units per k row
+    // XOR applied to the 32-byte unit index of k row `k`.  A transposing read touches, per group of
+    // sixteen lanes, one or two units of four consecutive k rows, and two such groups (k and k + 8
+    // with 16 x 16 fragments, the next sixteen tile rows with 32 x 32 fragments) are served
+    // together: bits 0, 1 and 3 of k pick the unit, so that all eight land in different banks.
+    __device__ __forceinline__ static int swz(int k) {
+        if constexpr (UPR >= 8) return (k & 3) | ((k >> 1) & 4);
+        // narrower tiles: 16 x 16 fragments read k and k + 8 in the same pass, and a k row of 128 or
+        // 64 bytes already puts k and k + 1 into different banks: the units tell k from k + 2 and
+        // from k + 8.  32 x 32 fragments read two units of four consecutive k rows per pass and
+        // keep the pairing that measured fastest for them (the other one cost them 5 - 20 %).
+        else if constexpr (UPR == 4) return F == 16 ? ((k & 2) | ((k >> 3) & 1)) : ((k >> 1) & 3);
+        else if constexpr (UPR == 2) return F == 16 ? ((k >> 3) & 1) : ((k >> 2) & 1);
+        else return 0;
     }
-
-    // eight consecutive bf16 starting at src; element e is valid while e < nValid
-    __device__ __forceinline__ static uintx4 load8(const uint16_t *src, int nValid) {
-        uintx4 v = {0u, 0u, 0u, 0u};
-        if constexpr (VEC) {
-            if (nValid > 0) v = *reinterpret_cast<const uintx4 *>(src);
-        } else {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                unsigned x = e < nValid ? (unsigned)src[e] : 0u;
-                v[e >> 1] |= x << (16 * (e & 1));
-            }
-        }
-        return v;
+    // byte offset of element (k, row) for row a multiple of 4
+    __device__ __forceinline__ static int byte_of(int k, int row) {
+        return k * (ROWS * 2) + ((((row >> 4) ^ swz(k)) << 5) | ((row & 15) << 1));
     }
+};
 
-    __device__ __forceinline__ void load(const uint16_t *base, long long ld, int row0, int rowLimit,
-                                         int k0, int kEnd, int tid) {
-#pragma unroll
-        for (int it = 0; it < ITERS; ++it) {
-            int inner, outer;
-            unit(tid, it, inner, outer);
-            const bool live = UNITS % NT == 0 || outer < OUTER;
-            if constexpr (KC) {
-                const int r = row0 + outer, k = k0 + inner * 8;
-                const int nValid = (live && r < rowLimit) ? (kEnd - k) : 0;
-                reg[it][0] = load8(base + (long long)r * ld + k, nValid);
-            } else {
-                const int r = row0 + inner * 8;
-                const int nValid = live ? (rowLimit - r) : 0;
-#pragma unroll
-                for (int j = 0; j < 8; ++j) {
-                    const int k = k0 + outer * 8 + j;
-                    reg[it][j] = load8(base + (long long)k * ld + r, k < kEnd ? nValid : 0);
-                }
-            }
-        }
+// LDS -> registers: the MFMA operand of one fragment, i.e. for lane l the eight consecutive k
+// starting at kk + 8*(l / F) of tile row rowBase + l % F.  KC tiles ([row][BK], swizzled chunks)
+// need one ds_read_b128; row-contiguous tiles ([k][ROWS]) two transposing ds_read_b64_tr_b16, in
+// which lane s of a 16-lane group addresses rows 4*(s%4).. of k row s/4 and lane l receives the
+// four k values of row l.
+template <int F, int ROWS, int BK, bool KC>
+__device__ __forceinline__ bf16x8 read_fragment(const char *tile, int rowBase, int kk, int lane) {
+    const int lgrp = lane / F;
+    if constexpr (KC) {
+        return __builtin_bit_cast(bf16x8, *reinterpret_cast<const uintx4 *>(
+            tile + 16 * Bf16Lds<BK>::chunk(rowBase + lane % F, kk / 8 + lgrp)));
+    } else {
+        typedef short shortx8 __attribute__((ext_vector_type(8)));
+        using LT = Bf16LdsT<ROWS, F>;
+        const int trRow = 4 * (lane & 3) + (F == 32 ? 16 * ((lane >> 4) & 1) : 0);
+        const int kb = kk + 8 * lgrp + ((lane & 15) >> 2);
+        const shortx4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+            (__attribute__((address_space(3))) shortx4 *)(lds_void_ptr)(tile + LT::byte_of(kb, rowBase + trRow)));
+        const shortx4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+            (__attribute__((address_space(3))) shortx4 *)(lds_void_ptr)(tile + LT::byte_of(kb + 4, rowBase + trRow)));
+        const shortx8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+        return __builtin_bit_cast(bf16x8, v);
     }
+}
 
-    __device__ __forceinline__ void store(uintx4 *lds, int tid) const {
-#pragma unroll
-        for (int it = 0; it < ITERS; ++it) {
-            int inner, outer;
-            unit(tid, it, inner, outer);
-            if (UNITS % NT != 0 && outer >= OUTER) continue;
-            if constexpr (KC) {
-                lds[L::chunk(outer, inner)] = reg[it][0];
-            } else {
-                // reg[it][j] holds k = 8*outer + j, rows 8*inner .. +7; emit one chunk per row
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    uintx4 o;
-#pragma unroll
-                    for (int d = 0; d < 4; ++d) {
-                        const unsigned lo = (reg[it][2 * d][i >> 1] >> (16 * (i & 1))) & 0xffffu;
-                        const unsigned hi = (reg[it][2 * d + 1][i >> 1] >> (16 * (i & 1))) & 0xffffu;
-                        o[d] = lo | (hi << 16);
-                    }
-                    lds[L::chunk(inner * 8 + i, outer)] = o;
-                }
-            }
+// Scheduling hint for one k-substep: NM MFMAs with NR LDS reads spread evenly between them.
+template <int M, int NM, int NR>
+struct InterleaveHint {
+    __device__ __forceinline__ static void emit() {
+        if constexpr (M < NM) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                 // one MFMA
+            // all reads go behind the first NM-2 MFMAs; the last two cover the read latency
+            constexpr int SLOTS = NM > 2 ? NM - 2 : 1;
+            constexpr int reads = M < SLOTS ? (NR * (M + 1)) / SLOTS - (NR * M) / SLOTS : 0;
+            if constexpr (reads > 0) __builtin_amdgcn_sched_group_barrier(0x100, reads, 0);   // LDS reads
+            InterleaveHint<M + 1, NM, NR>::emit();
         }
     }
 };
 
-template <int F, int BM, int BN, int BK, int WM, int WN, bool SPLIT, bool AKC, bool BKC, bool VEC,
-          bool F16 = false>
+// Sixteen bytes at an address that only the element type aligns.  Global memory takes such accesses at
+// any byte (the target's unaligned access mode), so this is one global_load_dwordx4 like the aligned form.
+struct __attribute__((packed, aligned(2))) AnyUintx4 {
+    uintx4 v;
+};
+__device__ __forceinline__ uintx4 load16_any(const uint16_t *src) {
+    return reinterpret_cast<const AnyUintx4 *>(src)->v;
+}
+
+// Global memory -> registers -> LDS for one operand tile of a K-step, ROWS x BK in the layout above.
+// A thread moves the 16-byte chunks tid, tid + NT, ... of the LDS tile.
+//
+// load() is for K-steps in which every chunk may be read whole: the rows of a K-contiguous operand end
+// at or behind the step, or the step of a row-contiguous one ends before the last k (a chunk that
+// hangs over the right edge of row k then reads the beginning of row k + 1, and what it gets belongs to
+// rows of C that do not exist).  Rows beyond `limit` are clamped to valid ones for the same reason.
+// load_edge() is for the steps that are left, at most one for all but very narrow operands: it
+// reads inside the matrix only, and k beyond the end read as zero.
+template <int ROWS, int BK, int NT, bool KC, int F>
+struct Bf16Staging {
+    static constexpr int CPR = (KC ? BK : ROWS) / 8;         // chunks along the contiguous direction
+    static constexpr int CHUNKS = ROWS * BK / 8;
+    static constexpr int PER = (CHUNKS + NT - 1) / NT;
+    const uint16_t *src[PER];                                // this thread's chunks at the first K-step
+
+    __device__ __forceinline__ static bool has(int tid, int j) { return CHUNKS % NT == 0 || tid + j * NT < CHUNKS; }
+
+    __device__ __forceinline__ void init(const uint16_t *base, long long ld, int row0, int limit, int kBegin, int tid) {
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            const int L = tid + j * NT, outer = L / CPR, c = L % CPR;
+            if constexpr (KC) {
+                src[j] = base + (long long)min(row0 + outer, limit - 1) * ld + (kBegin + c * 8);
+            } else {
+                const int s = row0 + c * 8;
+                src[j] = base + (long long)(kBegin + outer) * ld + (s < limit ? s : max(limit - 8, 0));
+            }
+        }
+    }
+
+    // advance: elements from the first K-step to this one
+    __device__ __forceinline__ void load(uintx4 (&reg)[PER], long long advance, int tid) const {
+#pragma unroll
+        for (int j = 0; j < PER; ++j)
+            if (has(tid, j)) reg[j] = load16_any(src[j] + advance);
+    }
+
+    __device__ __forceinline__ static void load_edge(uintx4 (&reg)[PER], const uint16_t *base, long long ld, int row0,
+                                                     int limit, int k0, int kEnd, int tid) {
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            const int L = tid + j * NT, outer = L / CPR, c = L % CPR;
+            const int row = KC ? min(row0 + outer, limit - 1) : row0 + c * 8;
+            const int k = KC ? k0 + c * 8 : k0 + outer;
+            const int n = !has(tid, j) ? 0 : KC ? kEnd - k : k < kEnd ? limit - row : 0;   // elements that exist
+            const uint16_t *p = KC ? base + (long long)row * ld + k : base + (long long)k * ld + row;
+            uintx4 v = {0u, 0u, 0u, 0u};
+            if (n >= 8) {
+                v = load16_any(p);
+            } else if (n > 0) {
+                unsigned x[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) x[e] = p[min(e, n - 1)];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) v[e >> 1] |= (e < n ? x[e] : 0u) << (16 * (e & 1));
+            }
+            reg[j] = v;
+        }
+    }
+
+    __device__ __forceinline__ static void store(const uintx4 (&reg)[PER], char *lds, int tid) {
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            if (!has(tid, j)) continue;
+            const int L = tid + j * NT, outer = L / CPR, c = L % CPR;
+            const int at = KC ? Bf16Lds<BK>::chunk(outer, c) : outer * CPR + (c ^ (2 * Bf16LdsT<ROWS, F>::swz(outer)));
+            reinterpret_cast<uintx4 *>(lds)[at] = reg[j];
+        }
+    }
+};
+
+// Register-staged path: operands whose rows are not 16-byte aligned, ragged extents and ragged K, in
+// short everything the direct-to-LDS path does not take.  Same LDS tiles, same fragments, same order
+// along K as that path, so on operands both take the results are the same bits.
+//
+// What bounds it is the latency of the operand loads: a K-step of most members holds 0.1 - 0.4 us of
+// MFMAs against 1 - 2 us from memory.  Two K-steps are therefore in flight where two sets of staging
+// registers of at most 32 fit beside at most 64 accumulators, one otherwise.  Measured against the
+// element-wise loads (two bytes per lane, transposed in registers where row-contiguous) that this form
+// replaced: fp16 1000 x 777 x 1509 NN 116 -> 19.6 us, bf16 5120 x 6528 x 2560 NT with odd rows 1312 ->
+// 303 us (0.57 PFLOP/s), 4959 x 2007 x 1325 TN 713 -> 70 us.
+template <int F, int BM, int BN, int BK, int WM, int WN, bool SPLIT, bool AKC, bool BKC, bool F16 = false>
 __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) void gemm_bf16_kernel(const GemmParams p) {
     constexpr int NT = 64 * (BM / WM) * (BN / WN);
     constexpr int FM = WM / F, FN = WN / F;
     constexpr int KSTEP = F == 32 ? 16 : 32;          // k consumed by one MFMA
-    constexpr int LGRP = F == 32 ? 2 : 4;             // lane groups along k
-    using L = Bf16Lds<BK>;
-    __shared__ __attribute__((aligned(16))) uintx4 As[2][BM * BK / 8];
-    __shared__ __attribute__((aligned(16))) uintx4 Bs[2][BN * BK / 8];
+    using LoadA = Bf16Staging<BM, BK, NT, AKC, F>;
+    using LoadB = Bf16Staging<BN, BK, NT, BKC, F>;
+    constexpr int PF = 4 * (LoadA::PER + LoadB::PER) <= 32 && WM * WN <= 4096 ? 2 : 1;
+    __shared__ __attribute__((aligned(1024))) char As0[BM * BK * 2];
+    __shared__ __attribute__((aligned(1024))) char As1[BM * BK * 2];
+    __shared__ __attribute__((aligned(1024))) char Bs0[BN * BK * 2];
+    __shared__ __attribute__((aligned(1024))) char Bs1[BN * BK * 2];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const TileCoord tc = tile_of_block(p);
@@ -158,10 +236,19 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) void gemm_bf16_kernel(c
     const int kEnd = min(p.K, kBegin + p.kChunk);
     const int nk = (kEnd - kBegin + BK - 1) / BK;
     const int subM = (wave / (BN / WN)) * WM, subN = (wave % (BN / WN)) * WN;
-    const int lrow = lane % F, lgrp = lane / F;
 
-    Bf16TileLoader<BM, BK, NT, AKC, VEC> la;
-    Bf16TileLoader<BN, BK, NT, BKC, VEC> lb;
+    // K-steps whose chunks may all be read whole (see Bf16Staging).  A row-contiguous operand with rows
+    // of fewer than seven elements could reach beyond the row after next: it has none.
+    const int fullA = AKC ? (kEnd - kBegin) / BK : p.lda < 7 ? 0 : (min(kEnd, p.K - 1) - kBegin) / BK;
+    const int fullB = BKC ? (kEnd - kBegin) / BK : p.ldb < 7 ? 0 : (min(kEnd, p.K - 1) - kBegin) / BK;
+    const int full = max(min(fullA, fullB), 0);
+    const long long aStep = AKC ? (long long)BK : BK * p.lda, bStep = BKC ? (long long)BK : BK * p.ldb;
+
+    LoadA la;
+    LoadB lb;
+    la.init(Ab, p.lda, row0, p.M, kBegin, tid);
+    lb.init(Bb, p.ldb, col0, p.N, kBegin, tid);
+    uintx4 ra[PF][LoadA::PER], rb[PF][LoadB::PER];
 
     floatx4 acc16[F == 16 ? FM : 1][F == 16 ? FN : 1];
     floatx16 acc32[F == 32 ? FM : 1][F == 32 ? FN : 1];
@@ -175,33 +262,24 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) void gemm_bf16_kernel(c
                 for (int e = 0; e < 16; ++e) acc32[i][j][e] = 0.f;
         }
 
-    if (nk > 0) {
-        la.load(Ab, p.lda, row0, p.M, kBegin, kEnd, tid);
-        lb.load(Bb, p.ldb, col0, p.N, kBegin, kEnd, tid);
-        la.store(As[0], tid);
-        lb.store(Bs[0], tid);
-    }
-    __syncthreads();
-
-    for (int kt = 0; kt < nk; ++kt) {
-        const int cur = kt & 1;
-        const bool more = kt + 1 < nk;
-        if (more) {
-            const int k0 = kBegin + (kt + 1) * BK;
-            la.load(Ab, p.lda, row0, p.M, k0, kEnd, tid);
-            lb.load(Bb, p.ldb, col0, p.N, k0, kEnd, tid);
-        }
-        const uintx4 *as = As[cur], *bs = Bs[cur];
+    auto load = [&](int t, uintx4 (&a)[LoadA::PER], uintx4 (&b)[LoadB::PER]) {
+        la.load(a, t * aStep, tid);
+        lb.load(b, t * bStep, tid);
+    };
+    auto load_edge = [&](int t, uintx4 (&a)[LoadA::PER], uintx4 (&b)[LoadB::PER]) {
+        LoadA::load_edge(a, Ab, p.lda, row0, p.M, kBegin + t * BK, kEnd, tid);
+        LoadB::load_edge(b, Bb, p.ldb, col0, p.N, kBegin + t * BK, kEnd, tid);
+    };
+    auto compute = [&](const char *as, const char *bs) {
 #pragma unroll
         for (int kk = 0; kk < BK; kk += KSTEP) {
-            const int c = kk / 8 + lgrp;              // this lane's k-chunk
+            // large wave tiles have no registers for the fragments of two k-substeps at once
+            if constexpr (WM * WN >= 8192) __builtin_amdgcn_sched_barrier(0);
             bf16x8 a[FM], b[FN];
 #pragma unroll
-            for (int i = 0; i < FM; ++i)
-                a[i] = __builtin_bit_cast(bf16x8, as[L::chunk(subM + i * F + lrow, c)]);
+            for (int i = 0; i < FM; ++i) a[i] = read_fragment<F, BM, BK, AKC>(as, subM + i * F, kk, lane);
 #pragma unroll
-            for (int j = 0; j < FN; ++j)
-                b[j] = __builtin_bit_cast(bf16x8, bs[L::chunk(subN + j * F + lrow, c)]);
+            for (int j = 0; j < FN; ++j) b[j] = read_fragment<F, BN, BK, BKC>(bs, subN + j * F, kk, lane);
 #pragma unroll
             for (int i = 0; i < FM; ++i)
 #pragma unroll
@@ -212,13 +290,42 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) void gemm_bf16_kernel(c
                         acc32[i][j] = mfma_32x32x16<F16>(a[i], b[j], acc32[i][j]);
                 }
         }
-        if (more) {
-            la.store(As[cur ^ 1], tid);
-            lb.store(Bs[cur ^ 1], tid);
+    };
+    // K-step t sits in LDS stage t & 1 and came through register set t % PF; while it is consumed, that
+    // set is refilled with step t + PF and step t + 1 moves from its set to the other stage.
+    auto step = [&](int t, auto odd) {
+        constexpr int S = decltype(odd)::value;
+        constexpr int CUR = S % PF, NEXT = (S + 1) % PF;
+        if (t + PF < full) load(t + PF, ra[CUR], rb[CUR]);
+        compute(S ? As1 : As0, S ? Bs1 : Bs0);
+        if (t + 1 < full) {
+            LoadA::store(ra[NEXT], S ? As0 : As1, tid);
+            LoadB::store(rb[NEXT], S ? Bs0 : Bs1, tid);
         }
         __syncthreads();
+    };
+
+    if (full > 0) {
+        load(0, ra[0], rb[0]);
+        if (PF > 1 && full > 1) load(1, ra[PF - 1], rb[PF - 1]);
+        LoadA::store(ra[0], As0, tid);
+        LoadB::store(rb[0], Bs0, tid);
+        __syncthreads();
+        for (int t = 0; t < full; t += 2) {
+            step(t, std::integral_constant<int, 0>{});
+            if (t + 1 < full) step(t + 1, std::integral_constant<int, 1>{});
+        }
     }
-    (void)LGRP;
+    // what is left: as a rule the one K-step that holds the end of K.  Every step above ended with a
+    // barrier, so the first stage is free.
+    for (int t = full; t < nk; ++t) {
+        load_edge(t, ra[0], rb[0]);
+        LoadA::store(ra[0], As0, tid);
+        LoadB::store(rb[0], Bs0, tid);
+        __syncthreads();
+        compute(As0, Bs0);
+        __syncthreads();
+    }
 
     if constexpr (F == 16)
         write_tile_mfma16<SPLIT, FM, FN>(p, tc, Cb, row0 + subM, col0 + subN, lane, acc16);

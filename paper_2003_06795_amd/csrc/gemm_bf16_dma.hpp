@@ -3,56 +3,17 @@
 // operand tiles go from global memory straight into LDS (global_load_lds_dwordx4, 16 bytes per
 // lane, no staging registers) one K-step ahead of the MFMAs.
 //
-// Preconditions (checked by the host, which otherwise launches the generic kernel):
+// Preconditions (checked by the host, which otherwise launches the register-staged kernel):
 //   16-byte aligned operands, leading dimensions and contiguous extents multiples of 8,
 //   K a multiple of BK, tile-relative byte offsets below 2^31.
 // Rows beyond M / N are clamped to the last valid row (the results they feed are never stored).
 //
-// LDS layouts
-//   K-contiguous operand (A not transposed, B transposed):  tile[row][BK]; the 16-byte chunk c of
-//     row r sits at chunk position c ^ swz(r) (Bf16Lds), read with ds_read_b128.
-//   row-contiguous operand (A transposed, B not transposed): tile[k][ROWS] exactly as in memory;
-//     32-byte units are XOR-swizzled by k.  The MFMA operand (8 consecutive k of one row per
-//     lane) is produced by the transposing LDS read ds_read_b64_tr_b16: inside each group of 16
-//     lanes, lane s supplies the address of 4 consecutive rows at k = kb + s/4, and lane l
-//     receives the 4 values k = kb .. kb+3 of row l.
-//
 // A direct-to-LDS load writes LDS_base(wave-uniform) + lane * 16, i.e. one instruction fills 1 KiB
 // of the tile; the swizzle is applied by choosing which global chunk each lane fetches.
 #pragma once
-#include <type_traits>
-
 #include "gemm_bf16.hpp"
 
 namespace ks {
-
-typedef short shortx4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) void *lds_void_ptr;
-
-// F: fragment edge of the MFMAs that read the tile (the unit swizzle of narrow tiles depends on it)
-template <int ROWS, int F = 32>
-struct Bf16LdsT {
-    static constexpr int CPR = ROWS / 8;                    // 16-byte chunks per k row
-    static constexpr int UPR = ROWS / 16;                   // 32-byte units per k row
-    // XOR applied to the 32-byte unit index of k row `k`.  A transposing read touches, per group of
-    // sixteen lanes, one or two units of four consecutive k rows, and two such groups (k and k + 8
-    // with 16 x 16 fragments, the next sixteen tile rows with 32 x 32 fragments) are served
-    // together: bits 0, 1 and 3 of k pick the unit, so that all eight land in different banks.
-    __device__ __forceinline__ static int swz(int k) {
-        if constexpr (UPR >= 8) return (k & 3) | ((k >> 1) & 4);
-        // narrower tiles: 16 x 16 fragments read k and k + 8 in the same pass, and a k row of 128 or
-        // 64 bytes already puts k and k + 1 into different banks: the units tell k from k + 2 and
-        // from k + 8.  32 x 32 fragments read two units of four consecutive k rows per pass and
-        // keep the pairing that measured fastest for them (the other one cost them 5 - 20 %).
-        else if constexpr (UPR == 4) return F == 16 ? ((k & 2) | ((k >> 3) & 1)) : ((k >> 1) & 3);
-        else if constexpr (UPR == 2) return F == 16 ? ((k >> 3) & 1) : ((k >> 2) & 1);
-        else return 0;
-    }
-    // byte offset of element (k, row) for row a multiple of 4
-    __device__ __forceinline__ static int byte_of(int k, int row) {
-        return k * (ROWS * 2) + ((((row >> 4) ^ swz(k)) << 5) | ((row & 15) << 1));
-    }
-};
 
 // Per-lane source offsets of the direct-to-LDS loads of one operand tile.
 template <int ROWS, int BK, int NW, bool KC, int F = 32>
@@ -101,46 +62,6 @@ __device__ __forceinline__ void wait_vmcnt() {
     static_assert(N >= 0 && N < 64, "vmcnt range");
     __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
 }
-
-// LDS -> registers: the MFMA operand of one fragment, i.e. for lane l the eight consecutive k
-// starting at kk + 8*(l / F) of tile row rowBase + l % F.  KC tiles ([row][BK], swizzled chunks)
-// need one ds_read_b128; row-contiguous tiles ([k][ROWS]) two transposing ds_read_b64_tr_b16, in
-// which lane s of a 16-lane group addresses rows 4*(s%4).. of k row s/4 and lane l receives the
-// four k values of row l.
-template <int F, int ROWS, int BK, bool KC>
-__device__ __forceinline__ bf16x8 read_fragment(const char *tile, int rowBase, int kk, int lane) {
-    const int lgrp = lane / F;
-    if constexpr (KC) {
-        return __builtin_bit_cast(bf16x8, *reinterpret_cast<const uintx4 *>(
-            tile + 16 * Bf16Lds<BK>::chunk(rowBase + lane % F, kk / 8 + lgrp)));
-    } else {
-        typedef short shortx8 __attribute__((ext_vector_type(8)));
-        using LT = Bf16LdsT<ROWS, F>;
-        const int trRow = 4 * (lane & 3) + (F == 32 ? 16 * ((lane >> 4) & 1) : 0);
-        const int kb = kk + 8 * lgrp + ((lane & 15) >> 2);
-        const shortx4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-            (__attribute__((address_space(3))) shortx4 *)(lds_void_ptr)(tile + LT::byte_of(kb, rowBase + trRow)));
-        const shortx4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-            (__attribute__((address_space(3))) shortx4 *)(lds_void_ptr)(tile + LT::byte_of(kb + 4, rowBase + trRow)));
-        const shortx8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-        return __builtin_bit_cast(bf16x8, v);
-    }
-}
-
-// Scheduling hint for one k-substep: NM MFMAs with NR LDS reads spread evenly between them.
-template <int M, int NM, int NR>
-struct InterleaveHint {
-    __device__ __forceinline__ static void emit() {
-        if constexpr (M < NM) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                 // one MFMA
-            // all reads go behind the first NM-2 MFMAs; the last two cover the read latency
-            constexpr int SLOTS = NM > 2 ? NM - 2 : 1;
-            constexpr int reads = M < SLOTS ? (NR * (M + 1)) / SLOTS - (NR * M) / SLOTS : 0;
-            if constexpr (reads > 0) __builtin_amdgcn_sched_group_barrier(0x100, reads, 0);   // LDS reads
-            InterleaveHint<M + 1, NM, NR>::emit();
-        }
-    }
-};
 
 template <int F, int BM, int BN, int BK, int WM, int WN, int STAGES, bool SPLIT, bool AKC, bool BKC,
           bool F16 = false>

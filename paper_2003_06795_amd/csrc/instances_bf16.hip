@@ -15,22 +15,18 @@ static void launch_bf16_fixed(const GemmParams &p, int grid, int variant, hipStr
     constexpr int NT = 64 * (BM / WM) * (BN / WN);
     const dim3 g = launch_grid(p, grid), b(NT);
     // variant bit 4: the operands are IEEE binary16 instead of bf16
-#define KS_V(A, B, V)                                                                                        \
-    do {                                                                                                     \
-        if (variant & 16)                                                                                    \
-            hipLaunchKernelGGL((gemm_bf16_kernel<F, BM, BN, BK, WM, WN, SPLIT, A, B, V, true>), g, b, 0, s, p);  \
-        else                                                                                                 \
-            hipLaunchKernelGGL((gemm_bf16_kernel<F, BM, BN, BK, WM, WN, SPLIT, A, B, V, false>), g, b, 0, s, p); \
+#define KS_V(A, B)                                                                                        \
+    do {                                                                                                  \
+        if (variant & 16)                                                                                 \
+            hipLaunchKernelGGL((gemm_bf16_kernel<F, BM, BN, BK, WM, WN, SPLIT, A, B, true>), g, b, 0, s, p);  \
+        else                                                                                              \
+            hipLaunchKernelGGL((gemm_bf16_kernel<F, BM, BN, BK, WM, WN, SPLIT, A, B, false>), g, b, 0, s, p); \
     } while (0)
-    switch (variant & 7) {
-        case 0: KS_V(false, false, false); break;
-        case 1: KS_V(false, false, true); break;
-        case 2: KS_V(false, true, false); break;
-        case 3: KS_V(false, true, true); break;
-        case 4: KS_V(true, false, false); break;
-        case 5: KS_V(true, false, true); break;
-        case 6: KS_V(true, true, false); break;
-        default: KS_V(true, true, true); break;
+    switch ((variant >> 1) & 3) {
+        case 0: KS_V(false, false); break;
+        case 1: KS_V(false, true); break;
+        case 2: KS_V(true, false); break;
+        default: KS_V(true, true); break;
     }
 #undef KS_V
 }
