@@ -50,18 +50,18 @@ def kernel_symbol(ks, dt, plan, tA, tB):
     library says it would launch (ks_gemm_plan): member, split actually taken, code path."""
     ki = ks.kernel_info(dt, plan["kernel_id"])
     akc, bkc = int(not tA), int(bool(tB))
-    split, vec = plan["split_k"] > 1, plan["vector_loads"]
+    split = plan["split_k"] > 1
     b = lambda v: "true" if v else "false"
     if dt == ks.F32 and ki["core_name"] == "direct":
-        return "gemm_f32_direct_kernel<%d, %d, %d, %d, %d, %s, %s, %s, %s>" % (
-            ki["bm"], ki["bn"], ki["bk"], ki["wm"], ki["wn"], b(split), b(akc), b(bkc), b(vec))
+        return "gemm_f32_direct_kernel<%d, %d, %d, %d, %d, %s, %s, %s>" % (
+            ki["bm"], ki["bn"], ki["bk"], ki["wm"], ki["wn"], b(split), b(akc), b(bkc))
     if dt == ks.F32 and ki["core_name"] == "kslice":
-        return "gemm_f32_kslice_kernel<%d, %d, %d, %d, %d, %s, %s, %s, %s>" % (
-            ki["bm"], ki["bn"], ki["bk"], ki["k_waves"], ki["wm"], b(split), b(akc), b(bkc), b(vec))
+        return "gemm_f32_kslice_kernel<%d, %d, %d, %d, %d, %s, %s, %s>" % (
+            ki["bm"], ki["bn"], ki["bk"], ki["k_waves"], ki["wm"], b(split), b(akc), b(bkc))
     if dt == ks.F32:
         p1, p2 = (ki["tm"], ki["tn"]) if ki["core_name"] == "fma" else (ki["wm"], ki["wn"])
-        return "gemm_f32_kernel<%d, %d, %d, %d, %d, %d, %s, %s, %s, %s, %d, %s, %s>" % (
-            ki["core"], ki["bm"], ki["bn"], ki["bk"], p1, p2, b(split), b(akc), b(bkc), b(vec), ki["k_waves"],
+        return "gemm_f32_kernel<%d, %d, %d, %d, %d, %d, %s, %s, %s, %d, %s, %s>" % (
+            ki["core"], ki["bm"], ki["bn"], ki["bk"], p1, p2, b(split), b(akc), b(bkc), ki["k_waves"],
             b(plan["tiles_per_workgroup"] > 1), b(plan["balanced_groups"] > 0))
     f = 16 if ki["core_name"] == "mfma16" else 32
     if plan["path"] == 2:
@@ -70,8 +70,8 @@ def kernel_symbol(ks, dt, plan, tA, tB):
         stages = ki["lds_bytes"] // (ki["bk"] * (ki["bm"] + ki["bn"]) * 2)
         return "gemm_bf16_dma_kernel<%d, %d, %d, %d, %d, %d, %d, %s, %s, %s, false>" % (
             f, ki["bm"], ki["bn"], ki["bk"], ki["wm"], ki["wn"], stages, b(split), b(akc), b(bkc))
-    return "gemm_bf16_kernel<%d, %d, %d, %d, %d, %d, %s, %s, %s, %s, false>" % (
-        f, ki["bm"], ki["bn"], ki["bk"], ki["wm"], ki["wn"], b(split), b(akc), b(bkc), b(vec))
+    return "gemm_bf16_kernel<%d, %d, %d, %d, %d, %d, %s, %s, %s, false>" % (
+        f, ki["bm"], ki["bn"], ki["bk"], ki["wm"], ki["wn"], b(split), b(akc), b(bkc))
 
 
 def build_rows(workload):

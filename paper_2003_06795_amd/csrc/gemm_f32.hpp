@@ -12,9 +12,7 @@
 //   SPLIT     the instantiation is a split-K member: partial sums go to the workspace
 //   AKC/BKC   whether op(A)/op(B) is K-contiguous in memory (A: transA == 0, B: transB == 1);
 //             decides the coalescing direction of the global loads
-//   VEC       operands are 16-byte aligned with leading dimensions and contiguous extents that
-//             are multiples of 4, so global accesses are float4; otherwise scalar.  Both forms
-//             predicate every access against the matrix edges and zero-fill.
+// Operands are fetched sixteen bytes per lane at any element address (see TileLoader).
 //
 // LDS layout (both operands): tile[k][m or n] with the row padded by 4 floats.  All cores read
 // "one k, many m/n", so rows of consecutive m/n are conflict-free for them.
@@ -36,9 +34,14 @@ namespace ks {
 // Waves per SIMD the register allocation must leave room for (0 = no demand).  The multi-tile
 // forms keep the next tile's staging registers alive across the epilogue; the four-wave members
 // with 64 x 32 wave tiles then drift a few registers past the budget of three waves per SIMD (168
-// with the accumulators) that they met before, and lose a resident work-group.
+// with the accumulators) that they met before, and lose a resident work-group; the eight-wave members
+// need four.  The sixteen-wave 16x16 members hold two work-groups per compute unit with 64 registers
+// and would take 65 - 67 with both kinds of K-step in their loop.
 #ifndef KS_F32_MIN_WAVES
-#define KS_F32_MIN_WAVES(multi, core, bm, bn, bk, p1, p2) ((multi) && ((bm) / (p1)) * ((bn) / (p2)) <= 4 ? 3 : 0)
+#define KS_F32_MIN_WAVES(multi, core, bm, bn, bk, p1, p2, kw)                                        \
+    ((core) == CORE_MFMA16 && ((bm) / (p1)) * ((bn) / (p2)) * (kw) == 16                  ? 8 \
+     : !(multi)                                                                            ? 0 \
+     : ((bm) / (p1)) * ((bn) / (p2)) <= 4 ? 3 : 4)
 #endif
 // The balanced persistent form counts on a fixed number of resident work-groups per compute unit:
 // two of eight waves (four waves per SIMD, 128 registers) or three of four waves (three per SIMD),
@@ -47,23 +50,23 @@ namespace ks {
 #define KS_F32_SK_MIN_WAVES(bm, bn, p1, p2) (((bm) / (p1)) * ((bn) / (p2)) >= 8 ? 4 : 3)
 #endif
 
-// Row padding of the row-contiguous operand's LDS tile when the other operand is K-contiguous and
-// both are fetched as float4 (NN and TT layouts): the padding of its partner instead of its own 4
+// Row padding of the row-contiguous operand's LDS tile when the other operand is K-contiguous
+// (NN and TT layouts): the padding of its partner instead of its own 4
 // for the members named below.  With unequal row lengths (130 and 132 floats at BK = 32) the
 // compiler keeps separate sets of fragment addresses for the two tiles, 23 - 28 registers.  The
-// balanced persistent form of the 128 x 128 x 32 member does not have them inside its budget of 128
-// (it spilled 13 - 14 and ran 16 % slower in NN than in NT / TN; with equal rows it needs 110), and
+// balanced persistent form of the 128 x 128 x 32 member does not have them inside its budget of 128,
+// nor does its multi-tile form (the balanced one spilled 13 - 14 and ran 16 % slower in NN than in NT / TN; with equal rows it needs 110), and
 // the sixteen-wave 64 x 64 x 32 member on 16 x 16 wave tiles loses its second resident work-group
 // (75 registers against 52).  The tile is then written with 8-byte stores, which costs elsewhere:
 // measured on the NN and TT rows of the tuning set, the three members on 16 x 16 wave tiles with
 // square tiles, K-step 32 and at least 512 threads gain 2.5 - 9 %, every other member is level or
 // loses 1 - 9 % (among them the four-wave 64 x 64 x 32 balanced member), so only those get it.
 // -1 = no override.
-constexpr int f32_pad_of_partner(bool sk, int core, int bm, int bn, int p1, int p2, int kw, bool kc, bool partnerKc,
-                                 bool vec, int bk, int threads) {
-    const bool balancedLarge = sk && threads >= 512;
+constexpr int f32_pad_of_partner(bool persistent, int core, int bm, int bn, int p1, int p2, int kw, bool kc, bool partnerKc,
+                                 int bk, int threads) {
+    const bool persistentLarge = persistent && threads >= 512;
     const bool squareOn16 = core == 1 && bm == bn && p1 == 16 && p2 == 16 && bk == 32 && threads * kw >= 512;
-    return (balancedLarge || squareOn16) && vec && !kc && partnerKc && bk <= 32 && (64 / bk) % 2 == 0 ? 64 / bk : -1;
+    return (persistentLarge || squareOn16) && !kc && partnerKc && bk <= 32 && (64 / bk) % 2 == 0 ? 64 / bk : -1;
 }
 
 enum { CORE_FMA = 0, CORE_MFMA16 = 1, CORE_MFMA32 = 2, CORE_DIRECT = 3, CORE_KSLICE = 4 };
@@ -77,82 +80,123 @@ struct F32Shape {
 
 // ---- global -> registers -> LDS staging of one ROWS x BK operand tile ------------------------
 // KC:  memory is [row][k] (k contiguous);  !KC: memory is [k][row] (row contiguous).
-// Units are float4 (VEC) or single floats walked so that consecutive lanes touch consecutive
-// addresses.  INNER = units along the contiguous direction, OUTER = the other direction.
+// Units are four floats walked so that consecutive lanes touch consecutive addresses.  INNER = units
+// along the contiguous direction, OUTER = the other direction.
 // PAD >= 0 overrides the row padding chosen below (see f32_pad_of_partner).
-template <int ROWS, int BK, int NT, bool KC, bool VEC, int PAD = -1>
+//
+// load() is for K-steps in which every unit may be read whole (whole_steps() of them): the rows of a
+// K-contiguous operand end at or behind the step, or the step of a row-contiguous one ends before the
+// last k (a unit that hangs over the right edge of row k then reads the beginning of row k + 1, and
+// what it gets belongs to rows of C that do not exist).  Rows beyond `limit` are clamped to valid ones
+// for the same reason.  There is no predicate and no per-lane address arithmetic: a 32-bit lane
+// offset that stays the same for the whole tile on a scalar address that advances with K.
+// load_edge() is for the steps that are left, as a rule the one that holds the end of K: it reads
+// inside the matrix only, and k beyond the end read as zero.
+//
+// What it is there for: the large members wait for the issue of their loads, not for memory (a matrix
+// pipe kept busy by other waves holds up vector-memory issue), and four-byte loads took four times as
+// many of them.  Against scalar loads of unaligned operands and predicated ones of aligned operands:
+// 4095 x 3000 x 4089 NT 950 -> 805 us (TN 1020 -> 797), 1000^3 with padded rows NN 33.3 -> 26.2 us;
+// aligned 4096^3 TN 1058 -> 1006 us, 1024^3 NN 26.0 -> 24.5 us, im2col 25088 x 256 x 1152 149 -> 144 us.
+template <int ROWS, int BK, int NT, bool KC, int PAD = -1>
 struct TileLoader {
-    static constexpr int W = VEC ? 4 : 1;
+    static constexpr int W = 4;
     static constexpr int INNER = (KC ? BK : ROWS) / W;
     static constexpr int OUTER = KC ? ROWS : BK;
     static constexpr int UNITS = INNER * OUTER;
     static constexpr int ITERS = (UNITS + NT - 1) / NT;
-    // Row padding of the LDS tile.  A K-contiguous operand fetched as float4 is written as four
-    // scalars to rows k .. k+3; a wave's lanes then differ in k by multiples of 4 (BK/4 lanes)
-    // and in the row, and land in 64 different banks when 4 * LDS_LD = 256/BK (mod 64), i.e. a
-    // padding of 64/BK floats.  The other forms write along a row and take the padding of 4 that
-    // keeps their 16-byte writes aligned.  (Measured: bank-conflict cycles of the 128 x 128 x 32
-    // member fell to a third and the BK = 32 / 64 members gained 2 - 20 % on long K; giving the
-    // lane groups of an MFMA read rows 4 or 8 apart instead of adjacent ones changed nothing.)
-    static constexpr int LDS_LD = ROWS + (PAD >= 0 ? PAD : (KC && VEC) ? (BK >= 64 ? 1 : 64 / BK) : 4);
-    static_assert(!(VEC && !KC) || LDS_LD % 2 == 0, "row-contiguous vector writes need 8-byte alignment");
-    static_assert((INNER <= NT && NT % INNER == 0) || (INNER > NT && INNER % NT == 0), "walk");
+    static constexpr int STRIDE = NT / INNER;                // outer distance of a thread's units
+    // Row padding of the LDS tile.  A K-contiguous operand is written as four scalars to rows
+    // k .. k+3; a wave's lanes then differ in k by multiples of 4 (BK/4 lanes) and in the row, and
+    // land in 64 different banks when 4 * LDS_LD = 256/BK (mod 64), i.e. a padding of 64/BK floats.
+    // A row-contiguous one is written along a row and takes the padding of 4 that keeps its 16-byte
+    // writes aligned.  (Measured: bank-conflict cycles of the 128 x 128 x 32 member fell to a third
+    // and the BK = 32 / 64 members gained 2 - 20 % on long K; giving the lane groups of an MFMA read
+    // rows 4 or 8 apart instead of adjacent ones changed nothing.)
+    static constexpr int LDS_LD = ROWS + (PAD >= 0 ? PAD : KC ? (BK >= 64 ? 1 : 64 / BK) : 4);
+    static_assert(KC || LDS_LD % 2 == 0, "row-contiguous vector writes need 8-byte alignment");
+    static_assert(INNER <= NT && NT % INNER == 0, "walk");
 
-    float reg[ITERS][W];
+    // byte offsets of a thread's units from the tile origin (row0, first k of the step); the units of a
+    // row-contiguous operand differ by whole k rows, which the scalar address takes
+    struct Plan {
+        unsigned off[KC ? ITERS : 1];
+        __device__ __forceinline__ void init(long long ld, int row0, int limit, int tid) {
+#pragma unroll
+            for (int it = 0; it < (KC ? ITERS : 1); ++it) {
+                const int inner = tid % INNER, outer = tid / INNER + it * STRIDE;
+                if constexpr (KC)
+                    off[it] = ((unsigned)(min(row0 + outer, limit - 1) - row0) * (unsigned)ld + inner * W) * 4u;
+                else
+                    off[it] = (outer * (unsigned)ld + (row0 + inner * W < limit ? inner * W : 0)) * 4u;
+            }
+        }
+    };
 
-    __device__ __forceinline__ static void unit(int tid, int it, int &inner, int &outer) {
-        if constexpr (INNER <= NT) {
-            inner = tid % INNER;
-            outer = tid / INNER + it * (NT / INNER);
-        } else {
-            inner = tid + (it % (INNER / NT)) * NT;
-            outer = it / (INNER / NT);
+    floatx4 reg[ITERS];
+
+    __device__ __forceinline__ static bool has(int tid, int it) {
+        return UNITS % NT == 0 || tid / INNER + it * STRIDE < OUTER;
+    }
+
+    // leading K-steps of [kBegin, kEnd) that load() may take (lane offsets fit 32 bits below 2^22; a row
+    // of one or two elements could reach beyond the row after next)
+    __device__ __forceinline__ static int whole_steps(long long ld, int limit, int K, int kBegin, int kEnd) {
+        if (ld > (1LL << 22)) return 0;
+        if (KC || (limit & 3) == 0) return max((kEnd - kBegin) / BK, 0);
+        return ld < 3 ? 0 : max((min(kEnd, K - 1) - kBegin) / BK, 0);
+    }
+
+    // tile: address of the tile origin at this K-step (the same for all lanes)
+    __device__ __forceinline__ void load(const Plan &plan, const float *tile, long long ld, int tid) {
+#pragma unroll
+        for (int it = 0; it < ITERS; ++it) {
+            const char *t = reinterpret_cast<const char *>(tile + (KC ? 0 : it * STRIDE * ld));
+            if (has(tid, it)) reg[it] = load_float4_any(t + plan.off[KC ? it : 0]);
         }
     }
 
-    // rowLimit: number of valid rows from row0 on; k runs from k0, valid while < kEnd.
-    __device__ __forceinline__ void load(const float *base, long long ld, int row0, int rowLimit,
-                                         int k0, int kEnd, int tid) {
+    __device__ __forceinline__ void load_edge(const float *base, long long ld, int row0, int limit, int k0, int kEnd,
+                                              int tid) {
+        // (the addresses are recomputed here: the compiler would otherwise keep them in registers
+        // across the K loop)
+        asm volatile("" : "+v"(tid));
 #pragma unroll
         for (int it = 0; it < ITERS; ++it) {
-            int inner, outer;
-            unit(tid, it, inner, outer);
-            const int r = KC ? outer : inner * W;
-            const int k = KC ? inner * W : outer;
-            const bool ok = (UNITS % NT == 0 || outer < OUTER) && (row0 + r < rowLimit) && (k0 + k < kEnd);
-            const float *src = KC ? base + (long long)(row0 + r) * ld + (k0 + k)
-                                  : base + (long long)(k0 + k) * ld + (row0 + r);
-            if constexpr (VEC) {
-                floatx4 v = {0.f, 0.f, 0.f, 0.f};
-                if (ok) v = *reinterpret_cast<const floatx4 *>(src);
-                reg[it][0] = v.x; reg[it][1] = v.y; reg[it][2] = v.z; reg[it][3] = v.w;
+            const int inner = tid % INNER, outer = tid / INNER + it * STRIDE;
+            const int row = KC ? min(row0 + outer, limit - 1) : row0 + inner * W;
+            const int k = KC ? k0 + inner * W : k0 + outer;
+            const int n = !has(tid, it) ? 0 : KC ? kEnd - k : k < kEnd ? limit - row : 0;   // elements that exist
+            const float *src = KC ? base + (long long)row * ld + k : base + (long long)k * ld + row;
+            floatx4 v = {0.f, 0.f, 0.f, 0.f};
+            if (n >= W) {
+                v = load_float4_any(src);
             } else {
-                reg[it][0] = ok ? *src : 0.f;
+#pragma unroll
+                for (int e = 0; e < W - 1; ++e)
+                    if (e < n) v[e] = src[e];
             }
+            reg[it] = v;
         }
     }
 
     __device__ __forceinline__ void store(float *lds, int tid) const {
 #pragma unroll
         for (int it = 0; it < ITERS; ++it) {
-            int inner, outer;
-            unit(tid, it, inner, outer);
-            if (UNITS % NT != 0 && outer >= OUTER) continue;
+            if (!has(tid, it)) continue;
+            const int inner = tid % INNER, outer = tid / INNER + it * STRIDE;
             const int r = KC ? outer : inner * W;
             const int k = KC ? inner * W : outer;
-            if constexpr (VEC && !KC && LDS_LD % 4 == 0) {
-                floatx4 v = {reg[it][0], reg[it][1], reg[it][2], reg[it][3]};
-                *reinterpret_cast<floatx4 *>(lds + k * LDS_LD + r) = v;
-            } else if constexpr (VEC && !KC) {
+            if constexpr (KC) {
+#pragma unroll
+                for (int j = 0; j < W; ++j) lds[(k + j) * LDS_LD + r] = reg[it][j];
+            } else if constexpr (LDS_LD % 4 == 0) {
+                *reinterpret_cast<floatx4 *>(lds + k * LDS_LD + r) = reg[it];
+            } else {
                 typedef float floatx2 __attribute__((ext_vector_type(2)));
                 floatx2 *dst = reinterpret_cast<floatx2 *>(lds + k * LDS_LD + r);
                 dst[0] = floatx2{reg[it][0], reg[it][1]};
                 dst[1] = floatx2{reg[it][2], reg[it][3]};
-            } else if constexpr (VEC) {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) lds[(k + j) * LDS_LD + r] = reg[it][j];
-            } else {
-                lds[k * LDS_LD + r] = reg[it][0];
             }
         }
     }
@@ -178,29 +222,29 @@ struct TileLoader {
 // workspace as a raw accumulator tile (at most two per work-group: the head and the tail of its
 // share), and gemm_f32_sk_fixup_kernel adds the parts of every divided tile in K order and applies
 // the epilogue.  No work-group waits for another, so there is nothing to deadlock on.
-template <int CORE, int BM, int BN, int BK, int P1, int P2, bool SPLIT, bool AKC, bool BKC, bool VEC,
+template <int CORE, int BM, int BN, int BK, int P1, int P2, bool SPLIT, bool AKC, bool BKC,
           int KW = 1, bool MULTI = false, bool SK = false>
-__global__ __launch_bounds__((F32Shape<CORE, BM, BN, P1, P2>::threads * KW), (SK ? KS_F32_SK_MIN_WAVES(BM, BN, P1, P2) : KS_F32_MIN_WAVES(MULTI, CORE, BM, BN, BK, P1, P2))) void gemm_f32_kernel(
+__global__ __launch_bounds__((F32Shape<CORE, BM, BN, P1, P2>::threads * KW), (SK ? KS_F32_SK_MIN_WAVES(BM, BN, P1, P2) : KS_F32_MIN_WAVES(MULTI, CORE, BM, BN, BK, P1, P2, KW))) void gemm_f32_kernel(
     const GemmParams p) {
     static_assert(!MULTI || (f32_multi_tile(CORE, BM, BN, P1, P2, KW) && !SPLIT), "multi-tile form");
     static_assert(!SK || (CORE == CORE_MFMA32 && KW == 1 && !SPLIT && !MULTI), "balanced persistent form");
     using Shape = F32Shape<CORE, BM, BN, P1, P2>;
     constexpr int NT = Shape::threads;                        // threads of one group
     static_assert(KW == 1 || CORE != CORE_FMA, "K groups need an MFMA core");
-    constexpr int PADA = f32_pad_of_partner(SK, CORE, BM, BN, P1, P2, KW, AKC, BKC, VEC, BK, NT);
-    constexpr int PADB = f32_pad_of_partner(SK, CORE, BM, BN, P1, P2, KW, BKC, AKC, VEC, BK, NT);
-    constexpr int LDA = TileLoader<BM, BK, NT, AKC, VEC, PADA>::LDS_LD, LDB = TileLoader<BN, BK, NT, BKC, VEC, PADB>::LDS_LD;
+    constexpr int PADA = f32_pad_of_partner(SK || MULTI, CORE, BM, BN, P1, P2, KW, AKC, BKC, BK, NT);
+    constexpr int PADB = f32_pad_of_partner(SK || MULTI, CORE, BM, BN, P1, P2, KW, BKC, AKC, BK, NT);
+    constexpr int LDA = TileLoader<BM, BK, NT, AKC, PADA>::LDS_LD, LDB = TileLoader<BN, BK, NT, BKC, PADB>::LDS_LD;
     __shared__ __attribute__((aligned(16))) float AsAll[KW][2][BK * LDA];
     __shared__ __attribute__((aligned(16))) float BsAll[KW][2][BK * LDB];
 
-    const int grp = KW == 1 ? 0 : (int)threadIdx.x / NT;
+    const int grp = KW == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x / NT);
     const int tid = KW == 1 ? (int)threadIdx.x : (int)threadIdx.x % NT;
     float (*As)[BK * LDA] = AsAll[grp];
     float (*Bs)[BK * LDB] = BsAll[grp];
     // the (first) tile of this work-group
     const TileCoord tc = MULTI && !p.grid3d ? tile_of_logical(p, logical_of_block() * (unsigned)p.tilesPerWG)
                                             : tile_of_block(p);
-    const int row0 = tc.tm * BM, col0 = tc.tn * BN;
+    const int row0 = __builtin_amdgcn_readfirstlane(tc.tm) * BM, col0 = __builtin_amdgcn_readfirstlane(tc.tn) * BN;
     const float *Ab = static_cast<const float *>(p.A) + (long long)tc.batch * p.strideA;
     const float *Bb = static_cast<const float *>(p.B) + (long long)tc.batch * p.strideB;
     float *Cb = p.C + (long long)tc.batch * p.strideC;
@@ -213,12 +257,27 @@ __global__ __launch_bounds__((F32Shape<CORE, BM, BN, P1, P2>::threads * KW), (SK
     // K-steps in flight between global memory and LDS (each in its own set of staging registers):
     // small tiles are latency-bound - few waves per compute unit, short MFMA runs per K-step - and
     // afford several; large tiles hide the latency behind their MFMAs and keep the registers.
-    using LoaderA = TileLoader<BM, BK, NT, AKC, VEC, PADA>;
-    using LoaderB = TileLoader<BN, BK, NT, BKC, VEC, PADB>;
+    using LoaderA = TileLoader<BM, BK, NT, AKC, PADA>;
+    using LoaderB = TileLoader<BN, BK, NT, BKC, PADB>;
     constexpr int STAGE_REGS = (LoaderA::ITERS + LoaderB::ITERS) * LoaderA::W;
     constexpr int PF = KS_F32_PREFETCH(STAGE_REGS, NT);
     LoaderA la[PF];
     LoaderB lb[PF];
+    typename LoaderA::Plan pa;
+    typename LoaderB::Plan pb;
+    // one K-step, from k0 on, of the tile at (r, c) that pa and pb describe
+    auto load_step = [&](LoaderA &a, LoaderB &b, const float *A, const float *B, int r, int c, int k0, int kE, bool whole) {
+        if (whole) {
+            a.load(pa, AKC ? A + (long long)r * p.lda + k0 : A + (long long)k0 * p.lda + r, p.lda, tid);
+            b.load(pb, BKC ? B + (long long)c * p.ldb + k0 : B + (long long)k0 * p.ldb + c, p.ldb, tid);
+        } else {
+            a.load_edge(A, p.lda, r, p.M, k0, kE, tid);
+            b.load_edge(B, p.ldb, c, p.N, k0, kE, tid);
+        }
+    };
+    auto whole_steps = [&](int kB, int kE) {
+        return min(LoaderA::whole_steps(p.lda, p.M, p.K, kB, kE), LoaderB::whole_steps(p.ldb, p.N, p.K, kB, kE));
+    };
 
     // accumulators
     constexpr int FR = Shape::frag;
@@ -327,16 +386,20 @@ __global__ __launch_bounds__((F32Shape<CORE, BM, BN, P1, P2>::threads * KW), (SK
         TileCoord tcL = tc;
         int iL = 0, kL = 0, rowL = row0, colL = col0;
         const float *AbL = Ab, *BbL = Bb;
+        pa.init(p.lda, rowL, p.M, tid);
+        pb.init(p.ldb, colL, p.N, tid);
+        const int full = whole_steps(kBegin, kEnd);
         auto issue_load = [&](LoaderA &a, LoaderB &b) {
-            a.load(AbL, p.lda, rowL, p.M, kBegin + kL * BK, kEnd, tid);
-            b.load(BbL, p.ldb, colL, p.N, kBegin + kL * BK, kEnd, tid);
+            load_step(a, b, AbL, BbL, rowL, colL, kBegin + kL * BK, kEnd, kL < full);
             if (++kL == nkT) {
                 kL = 0;
                 if (++iL < nTiles) {
                     tcL = tile_of_logical(p, firstTile + (unsigned)iL);
-                    rowL = tcL.tm * BM; colL = tcL.tn * BN;
+                    rowL = __builtin_amdgcn_readfirstlane(tcL.tm) * BM; colL = __builtin_amdgcn_readfirstlane(tcL.tn) * BN;
                     AbL = static_cast<const float *>(p.A) + (long long)tcL.batch * p.strideA;
                     BbL = static_cast<const float *>(p.B) + (long long)tcL.batch * p.strideB;
+                    pa.init(p.lda, rowL, p.M, tid);
+                    pb.init(p.ldb, colL, p.N, tid);
                 }
             }
         };
@@ -416,13 +479,13 @@ __global__ __launch_bounds__((F32Shape<CORE, BM, BN, P1, P2>::threads * KW), (SK
             const float *AbS = static_cast<const float *>(p.A) + (long long)tcS.batch * p.strideA;
             const float *BbS = static_cast<const float *>(p.B) + (long long)tcS.batch * p.strideB;
             const int kB = ks0 * BK, kE = min(p.K, ks1 * BK), nkS = ks1 - ks0;
+            pa.init(p.lda, rowS, p.M, tid);
+            pb.init(p.ldb, colS, p.N, tid);
+            const int full = whole_steps(kB, kE);
             // every staging set is (re)defined here, so none stays alive across the epilogue of the
             // previous tile; steps past the end of the range are zero tiles that touch no memory
 #pragma unroll
-            for (int d = 0; d < PF; ++d) {
-                la[d].load(AbS, p.lda, rowS, p.M, kB + d * BK, kE, tid);
-                lb[d].load(BbS, p.ldb, colS, p.N, kB + d * BK, kE, tid);
-            }
+            for (int d = 0; d < PF; ++d) load_step(la[d], lb[d], AbS, BbS, rowS, colS, kB + d * BK, kE, d < full);
             la[0].store(As[0], tid);
             lb[0].store(Bs[0], tid);
             __syncthreads();
@@ -432,11 +495,8 @@ __global__ __launch_bounds__((F32Shape<CORE, BM, BN, P1, P2>::threads * KW), (SK
                     const int kt = kt0 + u;
                     if (kt >= nkS) break;
                     const int cur = kt & 1;
-                    if (kt + PF < nkS) {
-                        const int k0 = kB + (kt + PF) * BK;
-                        la[u].load(AbS, p.lda, rowS, p.M, k0, kE, tid);
-                        lb[u].load(BbS, p.ldb, colS, p.N, k0, kE, tid);
-                    }
+                    if (kt + PF < nkS)
+                        load_step(la[u], lb[u], AbS, BbS, rowS, colS, kB + (kt + PF) * BK, kE, kt + PF < full);
                     compute_step(As[cur], Bs[cur]);
                     if (kt + 1 < nkS) {
                         la[(u + 1) % PF].store(As[cur ^ 1], tid);
@@ -476,12 +536,12 @@ __global__ __launch_bounds__((F32Shape<CORE, BM, BN, P1, P2>::threads * KW), (SK
         return;
     }
 
+    pa.init(p.lda, row0, p.M, tid);
+    pb.init(p.ldb, col0, p.N, tid);
+    const int full = whole_steps(kBegin, kEnd);
 #pragma unroll
     for (int d = 0; d < PF; ++d)
-        if (d < nk) {
-            la[d].load(Ab, p.lda, row0, p.M, kBegin + d * BK, kEnd, tid);
-            lb[d].load(Bb, p.ldb, col0, p.N, kBegin + d * BK, kEnd, tid);
-        }
+        if (d < nk) load_step(la[d], lb[d], Ab, Bb, row0, col0, kBegin + d * BK, kEnd, d < full);
     if (nk > 0) {
         la[0].store(As[0], tid);
         lb[0].store(Bs[0], tid);
@@ -496,11 +556,7 @@ __global__ __launch_bounds__((F32Shape<CORE, BM, BN, P1, P2>::threads * KW), (SK
             const int kt = kt0 + u;
             if (kt >= nk) break;
             const int cur = kt & 1;
-            if (kt + PF < nk) {
-                const int k0 = kBegin + (kt + PF) * BK;
-                la[u].load(Ab, p.lda, row0, p.M, k0, kEnd, tid);
-                lb[u].load(Bb, p.ldb, col0, p.N, k0, kEnd, tid);
-            }
+            if (kt + PF < nk) load_step(la[u], lb[u], Ab, Bb, row0, col0, kBegin + (kt + PF) * BK, kEnd, kt + PF < full);
             const float *as = As[cur], *bs = Bs[cur];
             compute_step(as, bs);
             if (kt + 1 < nk) {

@@ -13,7 +13,6 @@
 //
 //   BK        k consumed per pipeline step (multiple of 16)
 //   AKC/BKC   operand is K-contiguous in memory (A: transA == 0, B: transB == 1)
-//   VEC       16-byte accesses are legal (see gemm_f32.hpp); otherwise scalar loads
 // Rows / columns beyond M / N are clamped to the last valid one (their results are never stored);
 // k beyond the end of the K range reads as zero.
 #pragma once
@@ -28,44 +27,31 @@
 
 namespace ks {
 
-template <bool KC, bool VEC>
+// Four consecutive k of row / column idx; k from the end of the range on read as zero.
+template <bool KC>
 __device__ __forceinline__ floatx4 direct_fetch(const float *base, long long ld, int idx, int k, int kEnd) {
     floatx4 v = {0.f, 0.f, 0.f, 0.f};
-    if constexpr (KC && VEC) {
-        if (k < kEnd) v = *reinterpret_cast<const floatx4 *>(base + (long long)idx * ld + k);
-    } else if constexpr (KC) {
-        const float *src = base + (long long)idx * ld + k;
+    const float *src = KC ? base + (long long)idx * ld + k : base + (long long)k * ld + idx;
+    if (KC && k + 4 <= kEnd) return load_float4_any(src);
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-            if (k + j < kEnd) v[j] = src[j];
-    } else {
-        const float *src = base + (long long)k * ld + idx;
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            if (k + j < kEnd) v[j] = src[(long long)j * ld];
-    }
+    for (int j = 0; j < 4; ++j)
+        if (k + j < kEnd) v[j] = src[KC ? j : (long long)j * ld];
     return v;
 }
 
 // The same four values when the whole K-step is known to lie inside the K range: no predicate,
 // so nothing between the loads of a step makes the wave wait for an earlier one.  `lanePtr` is the
 // lane's element at k = 0 (KC: &op[idx][kLane]; otherwise &op[kLane][idx]); k is wave-uniform.
-template <bool KC, bool VEC>
+template <bool KC>
 __device__ __forceinline__ floatx4 direct_fetch_full(const float *lanePtr, long long ld, int k) {
+    if constexpr (KC) return load_float4_any(lanePtr + k);
     floatx4 v;
-    if constexpr (KC && VEC) {
-        v = *reinterpret_cast<const floatx4 *>(lanePtr + k);
-    } else if constexpr (KC) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) v[j] = lanePtr[k + j];
-    } else {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) v[j] = lanePtr[(long long)(k + j) * ld];
-    }
+    for (int j = 0; j < 4; ++j) v[j] = lanePtr[(long long)(k + j) * ld];
     return v;
 }
 
-template <int BM, int BN, int BK, int WM, int WN, bool SPLIT, bool AKC, bool BKC, bool VEC>
+template <int BM, int BN, int BK, int WM, int WN, bool SPLIT, bool AKC, bool BKC>
 __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) void gemm_f32_direct_kernel(const GemmParams p) {
     constexpr int FM = WM / 16, FN = WN / 16, NG = BK / 16;       // fragments per wave; k-groups per step
     static_assert(BK % 16 == 0 && WM % 16 == 0 && WN % 16 == 0, "direct core shape");
@@ -113,20 +99,20 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) void gemm_f32_direct_ke
             for (int g = 0; g < NG; ++g) {
 #pragma unroll
                 for (int i = 0; i < FM; ++i)
-                    a[set][g][i] = direct_fetch_full<AKC, VEC>(aLane[i], p.lda, k0 + g * 16);
+                    a[set][g][i] = direct_fetch_full<AKC>(aLane[i], p.lda, k0 + g * 16);
 #pragma unroll
                 for (int j = 0; j < FN; ++j)
-                    b[set][g][j] = direct_fetch_full<BKC, VEC>(bLane[j], p.ldb, k0 + g * 16);
+                    b[set][g][j] = direct_fetch_full<BKC>(bLane[j], p.ldb, k0 + g * 16);
             }
         } else {
 #pragma unroll
             for (int g = 0; g < NG; ++g) {
 #pragma unroll
                 for (int i = 0; i < FM; ++i)
-                    a[set][g][i] = direct_fetch<AKC, VEC>(Ab, p.lda, rowIdx[i], k0 + g * 16 + kLane, kEnd);
+                    a[set][g][i] = direct_fetch<AKC>(Ab, p.lda, rowIdx[i], k0 + g * 16 + kLane, kEnd);
 #pragma unroll
                 for (int j = 0; j < FN; ++j)
-                    b[set][g][j] = direct_fetch<BKC, VEC>(Bb, p.ldb, colIdx[j], k0 + g * 16 + kLane, kEnd);
+                    b[set][g][j] = direct_fetch<BKC>(Bb, p.ldb, colIdx[j], k0 + g * 16 + kLane, kEnd);
             }
         }
     };

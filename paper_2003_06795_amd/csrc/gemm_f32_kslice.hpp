@@ -16,7 +16,7 @@
 
 namespace ks {
 
-template <int BM, int BN, int BK, int KW, int W, bool SPLIT, bool AKC, bool BKC, bool VEC>
+template <int BM, int BN, int BK, int KW, int W, bool SPLIT, bool AKC, bool BKC>
 __global__ __launch_bounds__(64 * KW * (BM / W) * (BN / W)) void gemm_f32_kslice_kernel(const GemmParams p) {
     constexpr int FM = W / 16, FN = W / 16, NG = BK / 16;
     constexpr int TW = (BM / W) * (BN / W);                   // wave tiles per work-group tile
@@ -70,20 +70,20 @@ __global__ __launch_bounds__(64 * KW * (BM / W) * (BN / W)) void gemm_f32_kslice
             for (int g = 0; g < NG; ++g) {
 #pragma unroll
                 for (int i = 0; i < FM; ++i)
-                    a[set][g][i] = direct_fetch_full<AKC, VEC>(aLane[i], p.lda, k0 + g * 16);
+                    a[set][g][i] = direct_fetch_full<AKC>(aLane[i], p.lda, k0 + g * 16);
 #pragma unroll
                 for (int j = 0; j < FN; ++j)
-                    b[set][g][j] = direct_fetch_full<BKC, VEC>(bLane[j], p.ldb, k0 + g * 16);
+                    b[set][g][j] = direct_fetch_full<BKC>(bLane[j], p.ldb, k0 + g * 16);
             }
         } else {
 #pragma unroll
             for (int g = 0; g < NG; ++g) {
 #pragma unroll
                 for (int i = 0; i < FM; ++i)
-                    a[set][g][i] = direct_fetch<AKC, VEC>(Ab, p.lda, rowIdx[i], k0 + g * 16 + kLane, kEnd);
+                    a[set][g][i] = direct_fetch<AKC>(Ab, p.lda, rowIdx[i], k0 + g * 16 + kLane, kEnd);
 #pragma unroll
                 for (int j = 0; j < FN; ++j)
-                    b[set][g][j] = direct_fetch<BKC, VEC>(Bb, p.ldb, colIdx[j], k0 + g * 16 + kLane, kEnd);
+                    b[set][g][j] = direct_fetch<BKC>(Bb, p.ldb, colIdx[j], k0 + g * 16 + kLane, kEnd);
             }
         }
     };

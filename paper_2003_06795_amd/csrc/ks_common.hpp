@@ -9,6 +9,14 @@ namespace ks {
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
+// Four floats at an address that only the element type aligns: global memory takes sixteen-byte accesses
+// at any element (the target's unaligned access mode), so this is one global_load_dwordx4 like the aligned form.
+struct __attribute__((packed, aligned(4))) AnyFloatx4 {
+    floatx4 v;
+};
+__device__ __forceinline__ floatx4 load_float4_any(const void *src) { return static_cast<const AnyFloatx4 *>(src)->v; }
+
+
 struct GemmParams {
     const void *A;
     const void *B;
