@@ -45,7 +45,7 @@ def attainable_tflops(dtype, M, N, K, batch=1, beta=0.0):
     return min(PEAK[dtype], 2.0 * M * N * K * batch / by * HBM_TBS)
 
 
-def kernel_symbol(ks, dt, plan, tA, tB):
+def kernel_symbol(ks, dt, plan, tA, tB, K):
     """Name of the device function a call resolves to (as rocprofv3 prints it), from what the
     library says it would launch (ks_gemm_plan): member, split actually taken, code path."""
     ki = ks.kernel_info(dt, plan["kernel_id"])
@@ -65,11 +65,12 @@ def kernel_symbol(ks, dt, plan, tA, tB):
             b(plan["tiles_per_workgroup"] > 1), b(plan["balanced_groups"] > 0))
     f = 16 if ki["core_name"] == "mfma16" else 32
     if plan["path"] == 2:
-        return "gemm_bf16_pp_kernel<%d, %s, %s, %s, false, 0, %d, %d>" % (f, b(split), b(akc), b(bkc), ki["bm"], ki["bk"])
+        return "gemm_bf16_pp_kernel<%d, %s, %s, %s, false, 0, %d, %d, %s>" % (f, b(split), b(akc), b(bkc), ki["bm"], ki["bk"],
+                                                                             b(K % ki["bk"] != 0))
     if plan["path"] == 1:
         stages = ki["lds_bytes"] // (ki["bk"] * (ki["bm"] + ki["bn"]) * 2)
-        return "gemm_bf16_dma_kernel<%d, %d, %d, %d, %d, %d, %d, %s, %s, %s, false>" % (
-            f, ki["bm"], ki["bn"], ki["bk"], ki["wm"], ki["wn"], stages, b(split), b(akc), b(bkc))
+        return "gemm_bf16_dma_kernel<%d, %d, %d, %d, %d, %d, %d, %s, %s, %s, false, %s>" % (
+            f, ki["bm"], ki["bn"], ki["bk"], ki["wm"], ki["wn"], stages, b(split), b(akc), b(bkc), b(K % ki["bk"] != 0))
     return "gemm_bf16_kernel<%d, %d, %d, %d, %d, %d, %s, %s, %s, false>" % (
         f, ki["bm"], ki["bn"], ki["bk"], ki["wm"], ki["wn"], b(split), b(akc), b(bkc))
 
@@ -537,7 +538,7 @@ def main():
                 f.write("%d,%d,%d,%d,%d,%d,%d,%d,%d,%.6g,%.6g\n" % (i, r["tA"], r["tB"], r["M"], r["N"], r["K"],
                                                                   chosen[i], plans[i]["split_k"], reps[i], med[i],
                                                                   tflops[i]))
-    sym = [kernel_symbol(ks, dt, p, r["tA"], r["tB"]) for p, r in zip(plans, rows)]
+    sym = [kernel_symbol(ks, dt, p, r["tA"], r["tB"], r["K"]) for p, r in zip(plans, rows)]
     # Per kernel symbol: `pass_*` counts every row once (one pass of the workload = one GEMM per
     # row); `all_*` counts every timed launch (rows of few flops are repeated up to 64 times per
     # sample, a measurement device), which is what a profiler's per-symbol average sees.

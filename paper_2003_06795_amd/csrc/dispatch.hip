@@ -65,6 +65,9 @@ const InstanceDesc kBf16[kNumBf16] = {
 #undef KS_BF16_INSTANCE_BAND
 };
 
+// granularity of K on the direct-to-LDS path: a member of K-step 128 takes half a step at the end
+constexpr int64_t dma_k_step(const InstanceDesc &d) { return d.bk == 128 ? 64 : d.bk; }
+
 LaunchFn g_f32[kNumF32];
 LaunchFn g_bf16[kNumBf16];
 LaunchFn g_bf16_dma[kNumBf16];
@@ -435,8 +438,8 @@ int run_ws(Workspace wsp, int dtype, int id, int transA, int transB, int64_t M, 
     // operand is not K-contiguous (NN, TN, TT; level at 2048^2 NN), while with both operands
     // K-contiguous (NT), where the general kernel is at its best, it loses 40 % at 2048^2, is level
     // at 1024^2 and gains 4 - 12 % from 4096^2 on: NT is cut only for outputs of at least 2^24 entries.
-    if (dtype != KS_F32 && !out16 && g_forceGeneric == 0 && K % d->bk != 0 && K % 8 == 0 && K >= 4LL * d->bk) {
-        const int64_t Kr = K % d->bk, Kh = K - Kr;
+    if (dtype != KS_F32 && !out16 && g_forceGeneric == 0 && K % dma_k_step(*d) != 0 && K % 8 == 0 && K >= 4LL * d->bk) {
+        const int64_t Kr = K % dma_k_step(*d), Kh = K - Kr;
         const bool akc = transA == 0, bkc = transB == 1;
         const bool pays = !(akc && bkc) || M * N >= (1LL << 24);
         const bool vecOk = pays && aligned(A, 16) && aligned(B, 16) && lda % 8 == 0 && ldb % 8 == 0 && (akc || M % 8 == 0) &&
@@ -550,7 +553,7 @@ int run_ws(Workspace wsp, int dtype, int id, int transA, int transB, int64_t M, 
     // bf16 fast path: operand tiles go global -> LDS directly.  Needs 16-byte accesses, whole
     // K-steps, and tile-relative byte offsets that fit 32 bits.
     const int f16Bit = dtype == KS_F16 ? 16 : 0;     // same 16-bit members, binary16 MFMA
-    const bool dma = dtype != KS_F32 && vec && g_forceGeneric == 0 && K % d->bk == 0 &&
+    const bool dma = dtype != KS_F32 && vec && g_forceGeneric == 0 && K % dma_k_step(*d) == 0 &&
                      lda <= (1LL << 22) && ldb <= (1LL << 22);
     // Hybrid launch of a 16-bit member whose split is chosen per call: whole rounds of work-groups
     // compute their tiles over all of K, the tiles of the last, partly filled round are cut along

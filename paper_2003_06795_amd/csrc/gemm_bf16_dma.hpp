@@ -6,6 +6,11 @@
 // Preconditions (checked by the host, which otherwise launches the register-staged kernel):
 //   16-byte aligned operands, leading dimensions and contiguous extents multiples of 8,
 //   K a multiple of BK, tile-relative byte offsets below 2^31.
+// CUT (BK = 128): K is an odd multiple of 64 and the last K-step half a one.  A form of its own, because the
+// branch at every load costs 1 - 5 % where K is whole (256 x 256 x 65536 on the 128 x 128 x 128 member 433 -> 450
+// us).  Measured against cutting K into two launches or, where that is not done, the register-staged path:
+// 64 x 64 x 128 member 1024 x 2368 x 3392 TN 45 -> 41 us, 192 x 768 x 3520 NN 15.7 -> 13.3, 64 x 448 x 1088 NN 11.2 ->
+// 9.2; 128 x 128 x 128 members 2112 x 1472 x 1984 NT 28.3 -> 22.1 and 26.2 -> 21.1.
 // Rows beyond M / N are clamped to the last valid row (the results they feed are never stored).
 //
 // A direct-to-LDS load writes LDS_base(wave-uniform) + lane * 16, i.e. one instruction fills 1 KiB
@@ -14,6 +19,19 @@
 #include "gemm_bf16.hpp"
 
 namespace ks {
+
+// Bytes by which the source of LDS chunk slot L lies behind the same place of the K-step's first half; 0 in
+// the first half.
+template <int ROWS, int BK, bool KC>
+__device__ __forceinline__ unsigned dma_half_back(int L, long long ld) {
+    if constexpr (KC) {
+        constexpr int CPR = BK / 8;
+        const int r = L / CPR, c = (L % CPR) ^ ((r / (16 / CPR)) & (CPR - 1));
+        return c >= CPR / 2 ? (unsigned)BK : 0u;
+    } else {
+        return L / (ROWS / 8) >= BK / 2 ? (unsigned)(BK * ld) : 0u;
+    }
+}
 
 // Per-lane source offsets of the direct-to-LDS loads of one operand tile.
 template <int ROWS, int BK, int NW, bool KC, int F = 32>
@@ -54,6 +72,18 @@ struct DmaPlan {
                     (lds_void_ptr)(lds + i * 1024), 16, 0, 0);
         }
     }
+
+    // the same for half a K-step: chunks of the second half, which nobody reads, repeat the first
+    __device__ __forceinline__ void issue_half(const char *tile, char *lds, int wave, int lane, long long ld) const {
+#pragma unroll
+        for (int j = 0; j < PER_WAVE; ++j) {
+            const int i = wave + j * NW;
+            if (TOTAL % NW == 0 || i < TOTAL)
+                __builtin_amdgcn_global_load_lds(
+                    (const __attribute__((address_space(1))) void *)(tile + (off[j] - dma_half_back<ROWS, BK, KC>(i * 64 + lane, ld))),
+                    (lds_void_ptr)(lds + i * 1024), 16, 0, 0);
+        }
+    }
 };
 
 // vmcnt(n) with the other counters left alone (gfx9 encoding: vmcnt in bits 3:0 and 15:14)
@@ -64,7 +94,7 @@ __device__ __forceinline__ void wait_vmcnt() {
 }
 
 template <int F, int BM, int BN, int BK, int WM, int WN, int STAGES, bool SPLIT, bool AKC, bool BKC,
-          bool F16 = false>
+          bool F16 = false, bool CUT = false>
 __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) void gemm_bf16_dma_kernel(const GemmParams p) {
     constexpr int NW = (BM / WM) * (BN / WN);
     constexpr int FM = WM / F, FN = WN / F;
@@ -87,7 +117,9 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) void gemm_bf16_dma_kern
     const int row0 = tc.tm * BM, col0 = tc.tn * BN;
     const int kBegin = tc.split * p.kChunk;
     const int kEnd = min(p.K, kBegin + p.kChunk);
-    const int nk = (kEnd - kBegin) / BK;
+    const int whole = (kEnd - kBegin) / BK;                   // K-steps, and half a one where K ends in one
+    const bool half = CUT && kEnd > kBegin && (kEnd - kBegin) % BK != 0;
+    const int nk = whole + (half ? 1 : 0);
     const uint16_t *Ab = static_cast<const uint16_t *>(p.A) + (long long)tc.batch * p.strideA;
     const uint16_t *Bb = static_cast<const uint16_t *>(p.B) + (long long)tc.batch * p.strideB;
     float *Cb = p.C + (long long)tc.batch * p.strideC;
@@ -132,14 +164,15 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) void gemm_bf16_dma_kern
     constexpr int NSUB = BK / KSTEP;
     constexpr int NREAD = (AKC ? FM : 2 * FM) + (BKC ? FN : 2 * FN);   // LDS reads per substep
     constexpr int NMFMA = FM * FN;
-    auto compute = [&](const char *as, const char *bs) {
+    auto compute = [&](const char *as, const char *bs, auto subs) {
+        constexpr int SUBS = decltype(subs)::value;
         bf16x8 a[2][FM], b[2][FN];
         load_frags(as, bs, 0, a[0], b[0]);
         __builtin_amdgcn_sched_group_barrier(0x100, NREAD, 0);
 #pragma unroll
-        for (int sub = 0; sub < NSUB; ++sub) {
+        for (int sub = 0; sub < SUBS; ++sub) {
             const int cur = sub & 1;
-            if (sub + 1 < NSUB) load_frags(as, bs, (sub + 1) * KSTEP, a[cur ^ 1], b[cur ^ 1]);
+            if (sub + 1 < SUBS) load_frags(as, bs, (sub + 1) * KSTEP, a[cur ^ 1], b[cur ^ 1]);
 #pragma unroll
             for (int i = 0; i < FM; ++i)
 #pragma unroll
@@ -149,7 +182,7 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) void gemm_bf16_dma_kern
                     else
                         acc32[i][j] = mfma_32x32x16<F16>(a[cur][i], b[cur][j], acc32[i][j]);
                 }
-            if (sub + 1 < NSUB) InterleaveHint<0, NMFMA, NREAD>::emit();
+            if (sub + 1 < SUBS) InterleaveHint<0, NMFMA, NREAD>::emit();
             else InterleaveHint<0, NMFMA, 0>::emit();
         }
     };
@@ -165,8 +198,13 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) void gemm_bf16_dma_kern
         constexpr int S = decltype(stage)::value;
         char *as = S == 0 ? As0 : S == 1 ? As1 : S == 2 ? As2 : As3;
         char *bs = S == 0 ? Bs0 : S == 1 ? Bs1 : S == 2 ? Bs2 : Bs3;
-        pa.issue(aTile + t * aStep, as, wave);
-        pb.issue(bTile + t * bStep, bs, wave);
+        if (CUT && t == whole) {
+            pa.issue_half(aTile + t * aStep, as, wave, lane, p.lda);
+            pb.issue_half(bTile + t * bStep, bs, wave, lane, p.ldb);
+        } else {
+            pa.issue(aTile + t * aStep, as, wave);
+            pb.issue(bTile + t * bStep, bs, wave);
+        }
     };
     auto step = [&](int t, auto stage) {
         constexpr int S = decltype(stage)::value;
@@ -181,7 +219,7 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) void gemm_bf16_dma_kern
         const char *bs = S == 0 ? Bs0 : S == 1 ? Bs1 : S == 2 ? Bs2 : Bs3;
         // waves that are issuing MFMAs go ahead of waves that are still issuing loads or waiting
         __builtin_amdgcn_s_setprio(3);
-        compute(as, bs);
+        compute(as, bs, std::integral_constant<int, NSUB>{});
         __builtin_amdgcn_s_setprio(0);
     };
 
@@ -189,15 +227,24 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) void gemm_bf16_dma_kern
     if (STAGES > 2 && nk > 1) issue(1, std::integral_constant<int, 1>{});
     if (STAGES > 3 && nk > 2) issue(2, std::integral_constant<int, 2>{});
     int t = 0;
-    for (; t + STAGES <= nk; t += STAGES) {
+    for (; t + STAGES <= whole; t += STAGES) {
         step(t, std::integral_constant<int, 0>{});
         step(t + 1, std::integral_constant<int, 1>{});
         if constexpr (STAGES > 2) step(t + 2, std::integral_constant<int, 2>{});
         if constexpr (STAGES > 3) step(t + 3, std::integral_constant<int, 3>{});
     }
-    if (t < nk) step(t, std::integral_constant<int, 0>{});
-    if (t + 1 < nk) step(t + 1, std::integral_constant<int, 1>{});
-    if constexpr (STAGES > 2) { if (t + 2 < nk) step(t + 2, std::integral_constant<int, 2>{}); }
+    if (t < whole) step(t, std::integral_constant<int, 0>{});
+    if (t + 1 < whole) step(t + 1, std::integral_constant<int, 1>{});
+    if constexpr (STAGES > 2) { if (t + 2 < whole) step(t + 2, std::integral_constant<int, 2>{}); }
+    if (CUT && half) {
+        const int s = whole - t;                             // its stage
+        wait_vmcnt<0>();
+        __syncthreads();
+        const char *as = s == 0 ? As0 : As1, *bs = s == 0 ? Bs0 : Bs1;
+        if constexpr (STAGES > 2) { if (s == 2) { as = As2; bs = Bs2; } }
+        if constexpr (STAGES > 3) { if (s == 3) { as = As3; bs = Bs3; } }
+        compute(as, bs, std::integral_constant<int, (NSUB + 1) / 2>{});
+    }
 
     if constexpr (F == 16)
         write_tile_mfma16<SPLIT, FM, FN>(p, tc, Cb, row0 + subM, col0 + subN, lane, acc16);

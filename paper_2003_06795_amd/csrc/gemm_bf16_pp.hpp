@@ -29,7 +29,9 @@
 // [A0 B0 B1](u), A1(u), [A0 B0 B1](u+1), ... so each wait leaves exactly the eight youngest loads
 // in flight.  Past the end of the K range the same loads are issued on the last K-step's
 // addresses into halves nobody reads any more: every step is the same straight-line code.
-// Preconditions are those of gemm_bf16_dma.hpp.
+// Preconditions are those of gemm_bf16_dma.hpp.  CUT (BK = 128): K is an odd multiple of 64, and the second
+// half of the last K-step is fetched from the first half and multiplied as zeros.  A form of its own: the
+// branches around the loads cost 10 % where K is whole (2048^3 23.2 -> 25.6 us).
 #pragma once
 #include "gemm_bf16_dma.hpp"
 
@@ -68,13 +70,20 @@ struct PpPlan {
     // written here and read by nothing else in this kernel.
     __device__ __forceinline__ void issue(const char *tile, char *lds, int wave) const {
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const unsigned dst = (unsigned)(uintptr_t)(lds_void_ptr)(lds + (wave + j * 8) * 1024);
-            asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-                         :
-                         : "v"(off[j]), "s"(tile), "s"(dst)
-                         : "memory");
-        }
+        for (int j = 0; j < 2; ++j) issue_one(off[j], tile, lds, wave + j * 8);
+    }
+    // the same for half a K-step: chunks of the second half repeat the first (and count as zero)
+    __device__ __forceinline__ void issue_half(const char *tile, char *lds, int wave, int lane, long long ld) const {
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+            issue_one(off[j] - dma_half_back<HALF, BK, KC>((wave + j * 8) * 64 + lane, ld), tile, lds, wave + j * 8);
+    }
+    __device__ __forceinline__ static void issue_one(unsigned from, const char *tile, char *lds, int i) {
+        const unsigned dst = (unsigned)(uintptr_t)(lds_void_ptr)(lds + i * 1024);
+        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+                     :
+                     : "v"(from), "s"(tile), "s"(dst)
+                     : "memory");
     }
 };
 
@@ -87,7 +96,8 @@ struct PpPlan {
 // pp_probe_clocks, which gives the clock the device holds while this kernel runs.
 static __device__ unsigned long long pp_probe_clocks[2];
 
-template <int F, bool SPLIT, bool AKC, bool BKC, bool F16 = false, int ABLATE = 0, int TILE = 256, int BK = 64>
+template <int F, bool SPLIT, bool AKC, bool BKC, bool F16 = false, int ABLATE = 0, int TILE = 256, int BK = 64,
+          bool CUT = false>
 __global__ __launch_bounds__(512) void gemm_bf16_pp_kernel(const GemmParams p) {
     static_assert((TILE == 256 && BK == 64) || (TILE == 128 && BK == 128 && F == 16), "tiles of this form");
     constexpr int BM = TILE, BN = TILE, HALF = TILE / 2;
@@ -111,7 +121,9 @@ __global__ __launch_bounds__(512) void gemm_bf16_pp_kernel(const GemmParams p) {
     const int row0 = tc.tm * BM, col0 = tc.tn * BN;
     const int kBegin = tc.split * p.kChunk;
     const int kEnd = min(p.K, kBegin + p.kChunk);
-    const int nk = (kEnd - kBegin) / BK;
+    // K-steps; in the CUT form the last one may be half a step
+    const bool half = CUT && max(kEnd - kBegin, 0) % BK != 0;
+    const int nk = max(kEnd - kBegin, 0) / BK + (half ? 1 : 0);
     const uint16_t *Ab = static_cast<const uint16_t *>(p.A) + (long long)tc.batch * p.strideA;
     const uint16_t *Bb = static_cast<const uint16_t *>(p.B) + (long long)tc.batch * p.strideB;
     float *Cb = p.C + (long long)tc.batch * p.strideC;
@@ -201,6 +213,17 @@ __global__ __launch_bounds__(512) void gemm_bf16_pp_kernel(const GemmParams p) {
         slot_end();
     };
 
+    auto issue = [&](const auto &plan, const char *tile, long long ld, int t, char *lds) {
+        if (CUT && half && t == nk - 1) plan.issue_half(tile, lds, wave, lane, ld);
+        else plan.issue(tile, lds, wave);
+    };
+    // fragments of the second half of a K-step that ends K are zeros
+    auto drop_half = [&](int t, bf16x8 (&f)[NSUB]) {
+        if (CUT && half && t == nk - 1) {
+#pragma unroll
+            for (int ks = NSUB / 2; ks < NSUB; ++ks) f[ks] = bf16x8{};
+        }
+    };
     auto step = [&](int t, auto s) {
         constexpr int S = decltype(s)::value;
         using SC = std::integral_constant<int, S>;
@@ -213,7 +236,11 @@ __global__ __launch_bounds__(512) void gemm_bf16_pp_kernel(const GemmParams p) {
             read_b(lds_b(SC{}, I0{}), b0);
             read_b(lds_b(SC{}, I1{}), b1);
         }
-        if constexpr ((ABLATE & 1) == 0) pa1.issue(aTile + t1 * aStep, lds_a(SN{}, I1{}), wave);
+        if constexpr ((ABLATE & 1) == 0) issue(pa1, aTile + t1 * aStep, p.lda, t1, lds_a(SN{}, I1{}));
+#pragma unroll
+        for (int m = 0; m < FM; ++m) drop_half(t, a[m]);
+#pragma unroll
+        for (int n = 0; n < FN; ++n) { drop_half(t, b0[n]); drop_half(t, b1[n]); }
         memory_slot_end();
         // C0: the wave that is issuing MFMAs goes ahead of the one issuing memory instructions
         __builtin_amdgcn_s_setprio(1);
@@ -224,10 +251,12 @@ __global__ __launch_bounds__(512) void gemm_bf16_pp_kernel(const GemmParams p) {
         // M1
         if (reads) read_a(lds_a(SC{}, I1{}));
         if constexpr ((ABLATE & 1) == 0) {
-            pa0.issue(aTile + t2 * aStep, lds_a(SC{}, I0{}), wave);
-            pb0.issue(bTile + t2 * bStep, lds_b(SC{}, I0{}), wave);
-            pb1.issue(bTile + t2 * bStep, lds_b(SC{}, I1{}), wave);
+            issue(pa0, aTile + t2 * aStep, p.lda, t2, lds_a(SC{}, I0{}));
+            issue(pb0, bTile + t2 * bStep, p.ldb, t2, lds_b(SC{}, I0{}));
+            issue(pb1, bTile + t2 * bStep, p.ldb, t2, lds_b(SC{}, I1{}));
         }
+#pragma unroll
+        for (int m = 0; m < FM; ++m) drop_half(t, a[m]);
         memory_slot_end();
         // C1
         __builtin_amdgcn_s_setprio(1);
@@ -246,13 +275,13 @@ __global__ __launch_bounds__(512) void gemm_bf16_pp_kernel(const GemmParams p) {
     if (nk > 0) {
         // prologue: K-steps 0 and 1 except A1(1), in the order the waits count on
         const int s1 = min(1, nk - 1);
-        pa0.issue(aTile, lds_a(I0{}, I0{}), wave);
-        pb0.issue(bTile, lds_b(I0{}, I0{}), wave);
-        pb1.issue(bTile, lds_b(I0{}, I1{}), wave);
-        pa1.issue(aTile, lds_a(I0{}, I1{}), wave);
-        pa0.issue(aTile + s1 * aStep, lds_a(I1{}, I0{}), wave);
-        pb0.issue(bTile + s1 * bStep, lds_b(I1{}, I0{}), wave);
-        pb1.issue(bTile + s1 * bStep, lds_b(I1{}, I1{}), wave);
+        issue(pa0, aTile, p.lda, 0, lds_a(I0{}, I0{}));
+        issue(pb0, bTile, p.ldb, 0, lds_b(I0{}, I0{}));
+        issue(pb1, bTile, p.ldb, 0, lds_b(I0{}, I1{}));
+        issue(pa1, aTile, p.lda, 0, lds_a(I0{}, I1{}));
+        issue(pa0, aTile + s1 * aStep, p.lda, s1, lds_a(I1{}, I0{}));
+        issue(pb0, bTile + s1 * bStep, p.ldb, s1, lds_b(I1{}, I0{}));
+        issue(pb1, bTile + s1 * bStep, p.ldb, s1, lds_b(I1{}, I1{}));
         wait_vmcnt<8>();
         slot_end();
         if (wr == 1) slot_end();                             // the second group starts one slot later

@@ -25,12 +25,22 @@ static void launch_bf16_dma_fixed(const GemmParams &p, int grid, int variant, hi
 #define KS_V(A, B)                                                                                                  \
     do {                                                                                                            \
         if constexpr (kTwoGroups<F, BM, BN, BK, WM, WN, STAGES>) {                                                  \
-            if (variant & 16) hipLaunchKernelGGL((gemm_bf16_pp_kernel<F, SPLIT, A, B, true, 0, BM, BK>), g, b, 0, s, p);  \
+            constexpr bool MAY_CUT = BK == 128;                                                                     \
+            if (MAY_CUT && p.K % BK != 0) {                                                                         \
+                if (variant & 16) hipLaunchKernelGGL((gemm_bf16_pp_kernel<F, SPLIT, A, B, true, 0, BM, BK, MAY_CUT>), g, b, 0, s, p); \
+                else hipLaunchKernelGGL((gemm_bf16_pp_kernel<F, SPLIT, A, B, false, 0, BM, BK, MAY_CUT>), g, b, 0, s, p); \
+            } else if (variant & 16)                                                                                \
+                hipLaunchKernelGGL((gemm_bf16_pp_kernel<F, SPLIT, A, B, true, 0, BM, BK>), g, b, 0, s, p);          \
             else hipLaunchKernelGGL((gemm_bf16_pp_kernel<F, SPLIT, A, B, false, 0, BM, BK>), g, b, 0, s, p);        \
-        } else if (variant & 16)                                                                                    \
-            hipLaunchKernelGGL((gemm_bf16_dma_kernel<F, BM, BN, BK, WM, WN, STAGES, SPLIT, A, B, true>), g, b, 0, s, p);  \
-        else                                                                                                        \
-            hipLaunchKernelGGL((gemm_bf16_dma_kernel<F, BM, BN, BK, WM, WN, STAGES, SPLIT, A, B, false>), g, b, 0, s, p); \
+        } else {                                                                                                    \
+            constexpr bool MAY_CUT = BK == 128;                                                                     \
+            if (MAY_CUT && p.K % BK != 0) {                                                                         \
+                if (variant & 16) hipLaunchKernelGGL((gemm_bf16_dma_kernel<F, BM, BN, BK, WM, WN, STAGES, SPLIT, A, B, true, MAY_CUT>), g, b, 0, s, p); \
+                else hipLaunchKernelGGL((gemm_bf16_dma_kernel<F, BM, BN, BK, WM, WN, STAGES, SPLIT, A, B, false, MAY_CUT>), g, b, 0, s, p); \
+            } else if (variant & 16)                                                                                \
+                hipLaunchKernelGGL((gemm_bf16_dma_kernel<F, BM, BN, BK, WM, WN, STAGES, SPLIT, A, B, true>), g, b, 0, s, p);  \
+            else hipLaunchKernelGGL((gemm_bf16_dma_kernel<F, BM, BN, BK, WM, WN, STAGES, SPLIT, A, B, false>), g, b, 0, s, p); \
+        }                                                                                                           \
     } while (0)
     switch (variant & 3) {
         case 0: KS_V(false, false); break;
