@@ -156,6 +156,15 @@ struct TileLoader {
         }
     }
 
+    // clear() goes before the load_edge() of both operands: zeros that the compiler writes between the
+    // loads make it wait for those in flight.
+    __device__ __forceinline__ void clear() {
+#pragma unroll
+        for (int it = 0; it < ITERS; ++it) {
+            reg[it] = floatx4{0.f, 0.f, 0.f, 0.f};
+            asm volatile("" : "+v"(reg[it]));
+        }
+    }
     __device__ __forceinline__ void load_edge(const float *base, long long ld, int row0, int limit, int k0, int kEnd,
                                               int tid) {
         // (the addresses are recomputed here: the compiler would otherwise keep them in registers
@@ -168,15 +177,13 @@ struct TileLoader {
             const int k = KC ? k0 + inner * W : k0 + outer;
             const int n = !has(tid, it) ? 0 : KC ? kEnd - k : k < kEnd ? limit - row : 0;   // elements that exist
             const float *src = KC ? base + (long long)row * ld + k : base + (long long)k * ld + row;
-            floatx4 v = {0.f, 0.f, 0.f, 0.f};
             if (n >= W) {
-                v = load_float4_any(src);
+                reg[it] = load_float4_any(src);
             } else {
 #pragma unroll
                 for (int e = 0; e < W - 1; ++e)
-                    if (e < n) v[e] = src[e];
+                    if (e < n) reg[it][e] = src[e];
             }
-            reg[it] = v;
         }
     }
 
@@ -271,6 +278,8 @@ __global__ __launch_bounds__((F32Shape<CORE, BM, BN, P1, P2>::threads * KW), (SK
             a.load(pa, AKC ? A + (long long)r * p.lda + k0 : A + (long long)k0 * p.lda + r, p.lda, tid);
             b.load(pb, BKC ? B + (long long)c * p.ldb + k0 : B + (long long)k0 * p.ldb + c, p.ldb, tid);
         } else {
+            a.clear();
+            b.clear();
             a.load_edge(A, p.lda, r, p.M, k0, kE, tid);
             b.load_edge(B, p.ldb, c, p.N, k0, kE, tid);
         }
