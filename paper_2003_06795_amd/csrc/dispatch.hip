@@ -386,6 +386,20 @@ int validate(int transA, int transB, int64_t M, int64_t N, int64_t K, const void
 
 bool aligned(const void *p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
 
+// 16-byte accesses: aligned operands, leading dimensions, contiguous extents and batch strides (w elements each)
+bool vector_operands(int w, bool akc, bool bkc, int64_t M, int64_t N, int64_t K, const void *A, int64_t lda, const void *B,
+                     int64_t ldb, int64_t batch, int64_t strideA, int64_t strideB) {
+    return aligned(A, 16) && aligned(B, 16) && lda % w == 0 && ldb % w == 0 && (akc ? K : M) % w == 0 && (bkc ? K : N) % w == 0 &&
+           (batch == 1 || (strideA % w == 0 && strideB % w == 0));
+}
+// what the direct-to-LDS path of the 16-bit members asks of them beside whole K-steps: 16-byte accesses and
+// tile-relative byte offsets that fit 32 bits
+bool dma_operands(bool akc, bool bkc, int64_t M, int64_t N, int64_t K, const void *A, int64_t lda, const void *B, int64_t ldb,
+                  int64_t batch, int64_t strideA, int64_t strideB) {
+    return vector_operands(8, akc, bkc, M, N, K, A, lda, B, ldb, batch, strideA, strideB) && g_forceGeneric == 0 &&
+           lda <= (1LL << 22) && ldb <= (1LL << 22);
+}
+
 // Scratch for split-K partial sums: the registered workspace, or the library's static array.
 struct Workspace {
     void *ptr;
@@ -542,19 +556,14 @@ int run_ws(Workspace wsp, int dtype, int id, int transA, int transB, int64_t M, 
 
     // contiguous direction: A is K-contiguous when not transposed, B when transposed
     const bool akc = transA == 0, bkc = transB == 1;
-    const int w = dtype == KS_F32 ? 4 : 8;            // elements per 16-byte access
-    const int64_t extA = akc ? K : M, extB = bkc ? K : N;
-    const bool vec = aligned(A, 16) && aligned(B, 16) && lda % w == 0 && ldb % w == 0 &&
-                     extA % w == 0 && extB % w == 0 &&
-                     (batch == 1 || (strideA % w == 0 && strideB % w == 0));
+    const bool vec = vector_operands(dtype == KS_F32 ? 4 : 8, akc, bkc, M, N, K, A, lda, B, ldb, batch, strideA, strideB);
     const int splitBit = p.splitK > 1 ? 8 : 0;       // read by instances whose split is chosen per call
     const int variant = (akc ? 4 : 0) + (bkc ? 2 : 0) + (vec ? 1 : 0) + splitBit;
 
-    // bf16 fast path: operand tiles go global -> LDS directly.  Needs 16-byte accesses, whole
-    // K-steps, and tile-relative byte offsets that fit 32 bits.
+    // bf16 fast path: operand tiles go global -> LDS directly.
     const int f16Bit = dtype == KS_F16 ? 16 : 0;     // same 16-bit members, binary16 MFMA
-    const bool dma = dtype != KS_F32 && vec && g_forceGeneric == 0 && K % dma_k_step(*d) == 0 &&
-                     lda <= (1LL << 22) && ldb <= (1LL << 22);
+    const bool dma = dtype != KS_F32 && K % dma_k_step(*d) == 0 &&
+                     dma_operands(akc, bkc, M, N, K, A, lda, B, ldb, batch, strideA, strideB);
     // Hybrid launch of a 16-bit member whose split is chosen per call: whole rounds of work-groups
     // compute their tiles over all of K, the tiles of the last, partly filled round are cut along
     // K (tail_split), and a third kernel adds their partial tiles up.
@@ -771,6 +780,45 @@ static int select_checked(int dtype, int64_t M, int64_t N, int64_t K, int64_t ba
 
 namespace ks {
 namespace {
+// Members of the built-in trees that a launch count decides between: the trees split on sizes, and what a
+// call costs here steps with its tiles per compute unit, which no threshold of theirs can follow.  Only
+// these exchanges are made, each where both sides were timed (operands rotated through three buffers):
+//
+// 16-bit 23 (128 x 64 tiles) -> 47 (two groups of waves on 128 x 128) for one round of 128 x 128 tiles that
+//   fills over half the device, whole K-steps and K >= 2048: 2048^3 NT 26.1 -> 23.2 us, 1024 x 4096 x 4096 TN
+//   46.1 -> 40.4, 1408 x 2944 x 2560 NT 30.4 -> 25.3; level at K = 1664, behind below 1024.  Off the direct-to-LDS
+//   path 23 stays (1063 x 5269 x 2193 NT 68 us against 80).
+// 16-bit 47 -> 9 (same tile, one group) where K ends in half a K-step and neither is split: the two-group form
+//   of that pays branches in every memory slot (2560 x 1280 x 1728 NT 20.5 -> 19.2 us, 1216 x 2880 x 3520 NN 35.7 ->
+//   34.8, 1024 x 3712 x 5056 TN 52.6 -> 51.1).
+// fp32 47 (128 x 128 tiles, balanced where that pays) -> 28 (64 x 64) by the time both take, to 5 % of the
+//   measured ones: 28 finishes a tile every 18.1 ns of K on a compute unit and the fullest unit decides; 47
+//   does a K-step of 32 on two tiles of a unit in 4.14 us, or shares all K-steps evenly at 4.3 us and 20 us
+//   for the divided tiles.  6272 x 704 x 576 80 -> 58.5 us, 25088 x 288 x 1152 193 -> 176, 12544 x 576 x 1152 170 -> 150.
+constexpr int kF32Large = 47, kF32Small = 28, k16Narrow = 23, k16TwoGroups = 47, k16OneGroup = 9;
+
+int exchanged(int dtype, int id, int64_t M, int64_t N, int64_t K, int64_t batch, int tA, int tB, const void *A, int64_t lda,
+              const void *B, int64_t ldb, Workspace w) {
+    if (batch != 1 || M <= 0 || N <= 0 || K <= 0 || M > (1 << 28) || N > (1 << 28) || !builtin_tree(dtype)) return id;
+    std::call_once(g_once, init_tables);
+    auto tiles = [&](int64_t e) { return ((M + e - 1) / e) * ((N + e - 1) / e); };
+    const int64_t t128 = tiles(128);
+    if (dtype == KS_F32) {
+        if (id != kF32Large || g_f32[kF32Small] == nullptr) return id;
+        const double steps = (double)((K + 31) / 32);
+        const bool balanced = t128 % 512 != 0 && t128 < 2048 && K >= 1024 && w.ptr &&
+                              w.bytes >= sk_workspace_bytes(&kF32[kF32Large]) && aligned(w.ptr, 16);
+        const double large = balanced ? (double)t128 * steps / 512 * 4.3 + 20 : (double)((t128 + 511) / 512) * steps * 4.14 + 8;
+        const double small = (double)((tiles(64) + 255) / 256) * (double)K * 0.0181 + 8;
+        return 1.03 * small < large ? kF32Small : id;
+    }
+    if (K % 64 != 0 || !dma_operands(tA == 0, tB == 1, M, N, K, A, lda, B, ldb, 1, 0, 0)) return id;
+    if (id == k16Narrow && K % 128 == 0 && K >= 2048 && t128 > 128 && t128 <= 256 && g_bf16[k16TwoGroups] != nullptr)
+        return k16TwoGroups;
+    if (id == k16TwoGroups && K % 128 != 0 && t128 > 128 && t128 <= 256 && g_bf16[k16OneGroup] != nullptr) return k16OneGroup;
+    return id;
+}
+
 // member that runs the remainder of a K range that is not a whole number of K-steps (run_ws)
 int remainder_member(int dtype, int64_t M, int64_t N, int64_t K, int64_t batch, int tA, int tB, Workspace w) {
     const int id = select_checked(dtype, M, N, K, batch, tA, tB, w);
@@ -780,6 +828,11 @@ int remainder_member(int dtype, int64_t M, int64_t N, int64_t K, int64_t batch, 
 }
 }  // namespace
 }  // namespace ks
+
+// member of a selecting entry point: the tree's choice, as exchanged() has it
+#define KS_SELECT(dtype, w)                                                                                       \
+    ks::exchanged(dtype, select_checked(dtype, M, N, K, batch, transA, transB, w), M, N, K, batch, transA, transB, A, lda, \
+                  B, ldb, w)
 
 extern "C" int ks_gemm_f32_with_kernel(int kernel_id, int transA, int transB, int64_t M, int64_t N,
                                        int64_t K, float alpha, const float *A, int64_t lda,
@@ -801,7 +854,7 @@ extern "C" int ks_gemm_f32(int transA, int transB, int64_t M, int64_t N, int64_t
                            const float *A, int64_t lda, const float *B, int64_t ldb, float beta,
                            float *C, int64_t ldc, int64_t batch, int64_t strideA, int64_t strideB,
                            int64_t strideC, void *stream) {
-    const int id = select_checked(KS_F32, M, N, K, batch, transA, transB);
+    const int id = KS_SELECT(KS_F32, registered_ws());
     if (id < 0) return id;
     return run(KS_F32, id, KS_GEMM_PASS);
 }
@@ -810,7 +863,7 @@ extern "C" int ks_gemm_bf16(int transA, int transB, int64_t M, int64_t N, int64_
                             const uint16_t *A, int64_t lda, const uint16_t *B, int64_t ldb, float beta,
                             float *C, int64_t ldc, int64_t batch, int64_t strideA, int64_t strideB,
                             int64_t strideC, void *stream) {
-    const int id = select_checked(KS_BF16, M, N, K, batch, transA, transB);
+    const int id = KS_SELECT(KS_BF16, registered_ws());
     if (id < 0) return id;
     return run(KS_BF16, id, KS_GEMM_PASS);
 }
@@ -819,7 +872,7 @@ extern "C" int ks_gemm_f16(int transA, int transB, int64_t M, int64_t N, int64_t
                            const uint16_t *A, int64_t lda, const uint16_t *B, int64_t ldb, float beta,
                            float *C, int64_t ldc, int64_t batch, int64_t strideA, int64_t strideB,
                            int64_t strideC, void *stream) {
-    const int id = select_checked(KS_F16, M, N, K, batch, transA, transB);
+    const int id = KS_SELECT(KS_F16, registered_ws());
     if (id < 0) return id;
     return run(KS_F16, id, KS_GEMM_PASS);
 }
@@ -839,7 +892,7 @@ extern "C" int ks_gemm_bias(int dtype, int kernel_id, int transA, int transB, in
                             void *stream) {
     if (dtype != KS_F32 && dtype != KS_BF16 && dtype != KS_F16) return KS_ERR_INVALID_ARG;
     if (kernel_id < 0) {
-        kernel_id = select_checked(dtype, M, N, K, batch, transA, transB);
+        kernel_id = KS_SELECT(dtype, registered_ws());
         if (kernel_id < 0) return kernel_id;
     }
     return run(dtype, kernel_id, KS_GEMM_PASS, bias);
@@ -852,7 +905,7 @@ extern "C" int ks_gemm_out_bf16(int dtype, int kernel_id, int transA, int transB
                                 void *stream) {
     if (dtype != KS_F32 && dtype != KS_BF16 && dtype != KS_F16) return KS_ERR_INVALID_ARG;
     if (kernel_id < 0) {
-        kernel_id = select_checked(dtype, M, N, K, batch, transA, transB);
+        kernel_id = KS_SELECT(dtype, registered_ws());
         if (kernel_id < 0) return kernel_id;
     }
     float *C = reinterpret_cast<float *>(C16);        // element size is carried by the out16 flag
@@ -899,7 +952,7 @@ extern "C" int ks_gemm_static_scratch(int dtype, int kernel_id, int transA, int 
     const int rc = static_scratch(&w);
     if (rc != KS_OK) return rc;
     if (kernel_id < 0) {
-        kernel_id = select_checked(dtype, M, N, K, batch, transA, transB, w);
+        kernel_id = KS_SELECT(dtype, w);
         if (kernel_id < 0) return kernel_id;
     }
     return run_ws(w, dtype, kernel_id, KS_GEMM_PASS);
@@ -915,7 +968,7 @@ extern "C" int ks_gemm_with_workspace(int dtype, int kernel_id, int transA, int 
     if (reinterpret_cast<uintptr_t>(workspace_device) % sizeof(float)) return KS_ERR_INVALID_ARG;
     const Workspace w{workspace_device, workspace_bytes};
     if (kernel_id < 0) {
-        kernel_id = select_checked(dtype, M, N, K, batch, transA, transB, w);
+        kernel_id = KS_SELECT(dtype, w);
         if (kernel_id < 0) return kernel_id;
     }
     return run_ws(w, dtype, kernel_id, KS_GEMM_PASS);
@@ -928,7 +981,7 @@ extern "C" int ks_gemm_plan(int dtype, int kernel_id, int transA, int transB, in
     if (dtype != KS_F32 && dtype != KS_BF16 && dtype != KS_F16) return KS_ERR_INVALID_ARG;
     if (!out) return KS_ERR_INVALID_ARG;
     if (kernel_id < 0) {
-        kernel_id = select_checked(dtype, M, N, K, batch, transA, transB);
+        kernel_id = KS_SELECT(dtype, registered_ws());
         if (kernel_id < 0) return kernel_id;
     }
     void *stream = nullptr;
@@ -943,7 +996,7 @@ extern "C" int ks_time_gemm(int dtype, int kernel_id, int transA, int transB, in
     if (dtype != KS_F32 && dtype != KS_BF16 && dtype != KS_F16) return KS_ERR_INVALID_ARG;
     if (iters < 1 || iters > 1024 || reps < 1 || warmup < 0 || !ms_out) return KS_ERR_INVALID_ARG;
     if (kernel_id < 0) {
-        kernel_id = select_checked(dtype, M, N, K, batch, transA, transB);
+        kernel_id = KS_SELECT(dtype, registered_ws());
         if (kernel_id < 0) return kernel_id;
     }
     hipStream_t s = static_cast<hipStream_t>(stream);

@@ -41,6 +41,12 @@ int64_t sat_mul(int64_t a, int64_t b) {
 
 }  // namespace
 
+namespace ks {
+bool builtin_tree(int dtype) {
+    return !g_tree[dtype == KS_F16 ? KS_BF16 : dtype].custom;
+}
+}  // namespace ks
+
 extern "C" int ks_features(int64_t M, int64_t N, int64_t K, int64_t batch, int transA, int transB,
                            int64_t *out) {
     if (!out) return KS_ERR_INVALID_ARG;
