@@ -45,7 +45,7 @@ def attainable_tflops(dtype, M, N, K, batch=1, beta=0.0):
     return min(PEAK[dtype], 2.0 * M * N * K * batch / by * HBM_TBS)
 
 
-def kernel_symbol(ks, dt, plan, tA, tB, K):
+def kernel_symbol(ks, dt, plan, tA, tB, M, N, K):
     """Name of the device function a call resolves to (as rocprofv3 prints it), from what the
     library says it would launch (ks_gemm_plan): member, split actually taken, code path."""
     ki = ks.kernel_info(dt, plan["kernel_id"])
@@ -60,8 +60,12 @@ def kernel_symbol(ks, dt, plan, tA, tB, K):
             ki["bm"], ki["bn"], ki["bk"], ki["k_waves"], ki["wm"], b(split), b(akc), b(bkc))
     if dt == ks.F32:
         p1, p2 = (ki["tm"], ki["tn"]) if ki["core_name"] == "fma" else (ki["wm"], ki["wn"])
-        return "gemm_f32_kernel<%d, %d, %d, %d, %d, %d, %s, %s, %s, %d, %s, %s>" % (
-            ki["core"], ki["bm"], ki["bn"], ki["bk"], p1, p2, b(split), b(akc), b(bkc), ki["k_waves"],
+        chunk = -(-(-(-K // ki["bk"])) // plan["split_k"]) * ki["bk"]
+        units = (K if akc else M) % 4 == 0 and (K if bkc else N) % 4 == 0 and plan["balanced_groups"] == 0 and \
+            plan["tiles_per_workgroup"] == 1 and \
+            min(K, chunk) <= 8 * ki["bk"] * ki["k_waves"]
+        return "gemm_f32_kernel<%d, %d, %d, %d, %d, %d, %s, %s, %s, %s, %d, %s, %s>" % (
+            ki["core"], ki["bm"], ki["bn"], ki["bk"], p1, p2, b(split), b(akc), b(bkc), b(units), ki["k_waves"],
             b(plan["tiles_per_workgroup"] > 1), b(plan["balanced_groups"] > 0))
     f = 16 if ki["core_name"] == "mfma16" else 32
     if plan["path"] == 2:
@@ -538,7 +542,7 @@ def main():
                 f.write("%d,%d,%d,%d,%d,%d,%d,%d,%d,%.6g,%.6g\n" % (i, r["tA"], r["tB"], r["M"], r["N"], r["K"],
                                                                   chosen[i], plans[i]["split_k"], reps[i], med[i],
                                                                   tflops[i]))
-    sym = [kernel_symbol(ks, dt, p, r["tA"], r["tB"], r["K"]) for p, r in zip(plans, rows)]
+    sym = [kernel_symbol(ks, dt, p, r["tA"], r["tB"], r["M"], r["N"], r["K"]) for p, r in zip(plans, rows)]
     # Per kernel symbol: `pass_*` counts every row once (one pass of the workload = one GEMM per
     # row); `all_*` counts every timed launch (rows of few flops are repeated up to 64 times per
     # sample, a measurement device), which is what a profiler's per-symbol average sees.

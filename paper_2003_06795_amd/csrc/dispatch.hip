@@ -558,7 +558,12 @@ int run_ws(Workspace wsp, int dtype, int id, int transA, int transB, int64_t M, 
     const bool akc = transA == 0, bkc = transB == 1;
     const bool vec = vector_operands(dtype == KS_F32 ? 4 : 8, akc, bkc, M, N, K, A, lda, B, ldb, batch, strideA, strideB);
     const int splitBit = p.splitK > 1 ? 8 : 0;       // read by instances whose split is chosen per call
-    const int variant = (akc ? 4 : 0) + (bkc ? 2 : 0) + (vec ? 1 : 0) + splitBit;
+    // Form of the fp32 LDS-staged members for a short K (gemm_f32.hpp): no unit of four straddles an edge, lane
+    // offsets fit 32 bits, and a wave runs at most eight K-steps (it gains up to four of them and loses
+    // from ten on; the multi-tile form loses 3 % with it).
+    const bool units = (akc ? K : M) % 4 == 0 && (bkc ? K : N) % 4 == 0 && lda <= (1LL << 22) && ldb <= (1LL << 22) &&
+                       p.skGroups == 0 && p.tilesPerWG == 1 && (K < p.kChunk ? K : p.kChunk) <= 8LL * d->bk * d->kw;
+    const int variant = (akc ? 4 : 0) + (bkc ? 2 : 0) + (units ? 1 : 0) + splitBit;
 
     // bf16 fast path: operand tiles go global -> LDS directly.
     const int f16Bit = dtype == KS_F16 ? 16 : 0;     // same 16-bit members, binary16 MFMA

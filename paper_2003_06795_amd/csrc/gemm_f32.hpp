@@ -12,7 +12,8 @@
 //   SPLIT     the instantiation is a split-K member: partial sums go to the workspace
 //   AKC/BKC   whether op(A)/op(B) is K-contiguous in memory (A: transA == 0, B: transB == 1);
 //             decides the coalescing direction of the global loads
-// Operands are fetched sixteen bytes per lane at any element address (see TileLoader).
+//   SHORTK    extents are multiples of 4 and K is short: one kind of K-step, see TileLoader
+// Operands are fetched sixteen bytes per lane at any element address.
 //
 // LDS layout (both operands): tile[k][m or n] with the row padded by 4 floats.  All cores read
 // "one k, many m/n", so rows of consecutive m/n are conflict-free for them.
@@ -92,6 +93,11 @@ struct F32Shape {
 // offset that stays the same for the whole tile on a scalar address that advances with K.
 // load_edge() is for the steps that are left, as a rule the one that holds the end of K: it reads
 // inside the matrix only, and k beyond the end read as zero.
+// Where extents are multiples of four a unit lies inside the matrix or outside, and load_units() serves any
+// step with one predicate per unit.  A short K runs the form that knows this kind of step only: the code
+// of both other kinds, up to four K-steps deep, costs it more than the predicates (944 x 40x52x52 17.2 against
+// 14.5 us, 4096 x 64x64x64 62.5 against 53.8, 3056 x 704 x 16 NT 8.4 against 7.4), while from about ten K-steps
+// on it is the slower one (1024^3 NN 26.1 against 24.6 us, 25088 x 256 x 1152 151 against 146).
 //
 // What it is there for: the large members wait for the issue of their loads, not for memory (a matrix
 // pipe kept busy by other waves holds up vector-memory issue), and four-byte loads took four times as
@@ -153,6 +159,18 @@ struct TileLoader {
         for (int it = 0; it < ITERS; ++it) {
             const char *t = reinterpret_cast<const char *>(tile + (KC ? 0 : it * STRIDE * ld));
             if (has(tid, it)) reg[it] = load_float4_any(t + plan.off[KC ? it : 0]);
+        }
+    }
+
+    // kLeft: k of the step that exist
+    __device__ __forceinline__ void load_units(const Plan &plan, const float *tile, long long ld, int kLeft, int tid) {
+#pragma unroll
+        for (int it = 0; it < ITERS; ++it) {
+            const int k = KC ? tid % INNER * W : tid / INNER + it * STRIDE;
+            const char *t = reinterpret_cast<const char *>(tile + (KC ? 0 : it * STRIDE * ld));
+            floatx4 v = {0.f, 0.f, 0.f, 0.f};
+            if (has(tid, it) && k < kLeft) v = load_float4_any(t + plan.off[KC ? it : 0]);
+            reg[it] = v;
         }
     }
 
@@ -230,7 +248,7 @@ struct TileLoader {
 // share), and gemm_f32_sk_fixup_kernel adds the parts of every divided tile in K order and applies
 // the epilogue.  No work-group waits for another, so there is nothing to deadlock on.
 template <int CORE, int BM, int BN, int BK, int P1, int P2, bool SPLIT, bool AKC, bool BKC,
-          int KW = 1, bool MULTI = false, bool SK = false>
+          bool SHORTK, int KW = 1, bool MULTI = false, bool SK = false>
 __global__ __launch_bounds__((F32Shape<CORE, BM, BN, P1, P2>::threads * KW), (SK ? KS_F32_SK_MIN_WAVES(BM, BN, P1, P2) : KS_F32_MIN_WAVES(MULTI, CORE, BM, BN, BK, P1, P2, KW))) void gemm_f32_kernel(
     const GemmParams p) {
     static_assert(!MULTI || (f32_multi_tile(CORE, BM, BN, P1, P2, KW) && !SPLIT), "multi-tile form");
@@ -274,9 +292,14 @@ __global__ __launch_bounds__((F32Shape<CORE, BM, BN, P1, P2>::threads * KW), (SK
     typename LoaderB::Plan pb;
     // one K-step, from k0 on, of the tile at (r, c) that pa and pb describe
     auto load_step = [&](LoaderA &a, LoaderB &b, const float *A, const float *B, int r, int c, int k0, int kE, bool whole) {
-        if (whole) {
-            a.load(pa, AKC ? A + (long long)r * p.lda + k0 : A + (long long)k0 * p.lda + r, p.lda, tid);
-            b.load(pb, BKC ? B + (long long)c * p.ldb + k0 : B + (long long)k0 * p.ldb + c, p.ldb, tid);
+        const float *at = AKC ? A + (long long)r * p.lda + k0 : A + (long long)k0 * p.lda + r;
+        const float *bt = BKC ? B + (long long)c * p.ldb + k0 : B + (long long)k0 * p.ldb + c;
+        if constexpr (SHORTK) {
+            a.load_units(pa, at, p.lda, kE - k0, tid);
+            b.load_units(pb, bt, p.ldb, kE - k0, tid);
+        } else if (whole) {
+            a.load(pa, at, p.lda, tid);
+            b.load(pb, bt, p.ldb, tid);
         } else {
             a.clear();
             b.clear();

@@ -19,7 +19,7 @@ static void launch_f32_fixed(const GemmParams &p, int grid, int variant, hipStre
     // the multi-tile form exists beside the single-tile one and runs when the host asks for it
     constexpr bool MULTI_OK = !SPLIT && f32_multi_tile(CORE, BM, BN, P1, P2, KW);
     const dim3 g = launch_grid(p, grid), b(NT);
-#define KS_V(A, B)                                                                                   \
+#define KS_V(A, B, U)                                                                                   \
     do {                                                                                                \
         if constexpr (CORE == CORE_KSLICE)                                                              \
             hipLaunchKernelGGL((gemm_f32_kslice_kernel<BM, BN, BK, P1, P2, SPLIT, A, B>), g, b, 0, s, p); \
@@ -27,17 +27,21 @@ static void launch_f32_fixed(const GemmParams &p, int grid, int variant, hipStre
             hipLaunchKernelGGL((gemm_f32_direct_kernel<BM, BN, BK, P1, P2, SPLIT, A, B>), g, b, 0, s, p); \
         else if constexpr (MULTI_OK) {                                                                  \
             if (p.tilesPerWG > 1)                                                                       \
-                hipLaunchKernelGGL((gemm_f32_kernel<CORE, BM, BN, BK, P1, P2, SPLIT, A, B, KW, true>), g, b, 0, s, p); \
+                hipLaunchKernelGGL((gemm_f32_kernel<CORE, BM, BN, BK, P1, P2, SPLIT, A, B, U, KW, true>), g, b, 0, s, p); \
             else                                                                                        \
-                hipLaunchKernelGGL((gemm_f32_kernel<CORE, BM, BN, BK, P1, P2, SPLIT, A, B, KW>), g, b, 0, s, p); \
+                hipLaunchKernelGGL((gemm_f32_kernel<CORE, BM, BN, BK, P1, P2, SPLIT, A, B, U, KW>), g, b, 0, s, p); \
         } else                                                                                          \
-            hipLaunchKernelGGL((gemm_f32_kernel<CORE, BM, BN, BK, P1, P2, SPLIT, A, B, KW>), g, b, 0, s, p);  \
+            hipLaunchKernelGGL((gemm_f32_kernel<CORE, BM, BN, BK, P1, P2, SPLIT, A, B, U, KW>), g, b, 0, s, p);  \
     } while (0)
-    switch ((variant >> 1) & 3) {
-        case 0: KS_V(false, false); break;
-        case 1: KS_V(false, true); break;
-        case 2: KS_V(true, false); break;
-        default: KS_V(true, true); break;
+    switch (variant & 7) {                            // bit 0: units of four, short K
+        case 0: KS_V(false, false, false); break;
+        case 1: KS_V(false, false, true); break;
+        case 2: KS_V(false, true, false); break;
+        case 3: KS_V(false, true, true); break;
+        case 4: KS_V(true, false, false); break;
+        case 5: KS_V(true, false, true); break;
+        case 6: KS_V(true, true, false); break;
+        default: KS_V(true, true, true); break;
     }
 #undef KS_V
 }
@@ -64,7 +68,7 @@ static void launch_f32_sk(const GemmParams &p, int grid, int variant, hipStream_
     constexpr int NT = F32Shape<CORE, BM, BN, P1, P2>::threads;
     const dim3 g((unsigned)p.skGroups), b(NT);
 #define KS_V(A, B) \
-    hipLaunchKernelGGL((gemm_f32_kernel<CORE, BM, BN, BK, P1, P2, false, A, B, 1, false, true>), g, b, 0, s, p)
+    hipLaunchKernelGGL((gemm_f32_kernel<CORE, BM, BN, BK, P1, P2, false, A, B, false, 1, false, true>), g, b, 0, s, p)
     switch ((variant >> 1) & 3) {
         case 0: KS_V(false, false); break;
         case 1: KS_V(false, true); break;

@@ -14,7 +14,9 @@ pytestmark = pytest.mark.gpu
 # multi-tile, split per call, balanced
 MEMBERS = (0, 6, 7, 16, 21, 25, 28, 30, 32, 37, 43, 44, 47, 56, 60, 63)
 SHAPES = [(1, 1, 1), (7, 5, 9), (2, 130, 131), (130, 3, 131), (65, 129, 34), (257, 255, 193), (127, 40, 260),
-          (16, 16, 128), (129, 263, 1030)]
+          (16, 16, 128), (129, 263, 1030),
+          # extents of whole units and a short K: the form with one kind of K-step
+          (4, 4, 4), (40, 56, 24), (68, 132, 20), (260, 64, 100)]
 
 
 @pytest.fixture(scope="module")
