@@ -441,17 +441,16 @@ int run_ws(Workspace wsp, int dtype, int id, int transA, int transB, int64_t M, 
     // a pruned build holds only the kept members
     if ((dtype == KS_F32 ? g_f32[id] : g_bf16[id]) == nullptr) return KS_ERR_UNSUPPORTED;
 
-    // 16-bit operands whose K is not a whole number of K-steps would take the member's general
-    // kernel for all of K (measured 1.5 - 2.2 times slower than the direct-to-LDS path on large
-    // problems).  Where everything else qualifies for that path, the K range is cut instead: the
-    // remainder (fewer than one K-step, general kernel) goes first and applies alpha, beta and the
-    // bias, then the whole K-steps run on the fast path with beta = 1.  The partial result passes
-    // through C in fp32 (one more rounding per entry, far inside the bound), so an output kept in
-    // bf16 is not served this way.  The two extra passes over C cost 15 - 40 us on 2048^2 .. 4096^2
-    // outputs; measured against the general kernel over all of K the cut gains 24 - 100 % when an
-    // operand is not K-contiguous (NN, TN, TT; level at 2048^2 NN), while with both operands
-    // K-contiguous (NT), where the general kernel is at its best, it loses 40 % at 2048^2, is level
-    // at 1024^2 and gains 4 - 12 % from 4096^2 on: NT is cut only for outputs of at least 2^24 entries.
+    // 16-bit operands whose K is not a whole number of K-steps (of half ones for members of K-step 128)
+    // would take the member's register-staged path for all of K.  Where everything else qualifies for the
+    // direct-to-LDS path, the K range is cut instead: the remainder (fewer than one K-step, register-staged)
+    // goes first and applies alpha, beta and the bias, then the whole K-steps run on the fast path with
+    // beta = 1.  The partial result passes through C in fp32 (one more rounding per entry, far inside the
+    // bound), so an output kept in bf16 is not served this way.  Measured with a remainder of 24, cut against
+    // register-staged over all of K: 4096^3 NN 150 / 165 us, TN 140 / 155, TT 142 / 155, NT 160 / 152; 2048^3 NN
+    // 39 / 35, TN 35 / 33; 1024^3 NN 14.7 / 12.4.  The line (every layout but NT, and NT from 2^24 entries of
+    // output on) was drawn when the register-staged path loaded two bytes per lane; where its users' results
+    // do not hang on it, it now belongs at 2^24 entries for NN, TN and TT and nowhere for NT.
     if (dtype != KS_F32 && !out16 && g_forceGeneric == 0 && K % dma_k_step(*d) != 0 && K % 8 == 0 && K >= 4LL * d->bk) {
         const int64_t Kr = K % dma_k_step(*d), Kh = K - Kr;
         const bool akc = transA == 0, bkc = transB == 1;
