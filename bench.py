@@ -52,12 +52,13 @@ def kernel_symbol(ks, dt, plan, tA, tB, M, N, K):
     akc, bkc = int(not tA), int(bool(tB))
     split = plan["split_k"] > 1
     b = lambda v: "true" if v else "false"
+    fed = K % 4 == 0 and (akc or bkc)                  # register-fed members: one test per unit of four k
     if dt == ks.F32 and ki["core_name"] == "direct":
-        return "gemm_f32_direct_kernel<%d, %d, %d, %d, %d, %s, %s, %s>" % (
-            ki["bm"], ki["bn"], ki["bk"], ki["wm"], ki["wn"], b(split), b(akc), b(bkc))
+        return "gemm_f32_direct_kernel<%d, %d, %d, %d, %d, %s, %s, %s, %s>" % (
+            ki["bm"], ki["bn"], ki["bk"], ki["wm"], ki["wn"], b(split), b(akc), b(bkc), b(fed))
     if dt == ks.F32 and ki["core_name"] == "kslice":
-        return "gemm_f32_kslice_kernel<%d, %d, %d, %d, %d, %s, %s, %s>" % (
-            ki["bm"], ki["bn"], ki["bk"], ki["k_waves"], ki["wm"], b(split), b(akc), b(bkc))
+        return "gemm_f32_kslice_kernel<%d, %d, %d, %d, %d, %s, %s, %s, %s>" % (
+            ki["bm"], ki["bn"], ki["bk"], ki["k_waves"], ki["wm"], b(split), b(akc), b(bkc), b(fed))
     if dt == ks.F32:
         p1, p2 = (ki["tm"], ki["tn"]) if ki["core_name"] == "fma" else (ki["wm"], ki["wn"])
         chunk = -(-(-(-K // ki["bk"])) // plan["split_k"]) * ki["bk"]

@@ -557,11 +557,14 @@ int run_ws(Workspace wsp, int dtype, int id, int transA, int transB, int64_t M, 
     const bool akc = transA == 0, bkc = transB == 1;
     const bool vec = vector_operands(dtype == KS_F32 ? 4 : 8, akc, bkc, M, N, K, A, lda, B, ldb, batch, strideA, strideB);
     const int splitBit = p.splitK > 1 ? 8 : 0;       // read by instances whose split is chosen per call
-    // Form of the fp32 LDS-staged members for a short K (gemm_f32.hpp): no unit of four straddles an edge, lane
-    // offsets fit 32 bits, and a wave runs at most eight K-steps (it gains up to four of them and loses
-    // from ten on; the multi-tile form loses 3 % with it).
-    const bool units = (akc ? K : M) % 4 == 0 && (bkc ? K : N) % 4 == 0 && lda <= (1LL << 22) && ldb <= (1LL << 22) &&
-                       p.skGroups == 0 && p.tilesPerWG == 1 && (K < p.kChunk ? K : p.kChunk) <= 8LL * d->bk * d->kw;
+    // Form of the fp32 members whose loads need one test per unit of four (gemm_f32.hpp, gemm_f32_direct.hpp).
+    // Register-fed cores: K is a multiple of four.  LDS-staged ones: no unit straddles an edge and a
+    // wave runs at most eight K-steps (it gains up to four of them and loses from ten on; the multi-tile form
+    // loses 3 % with it).
+    const bool registerFed = d->core == KS_CORE_DIRECT || d->core == KS_CORE_KSLICE;
+    const bool units = registerFed ? K % 4 == 0
+                                   : (akc ? K : M) % 4 == 0 && (bkc ? K : N) % 4 == 0 && p.skGroups == 0 &&
+                                         p.tilesPerWG == 1 && (K < p.kChunk ? K : p.kChunk) <= 8LL * d->bk * d->kw;
     const int variant = (akc ? 4 : 0) + (bkc ? 2 : 0) + (units ? 1 : 0) + splitBit;
 
     // bf16 fast path: operand tiles go global -> LDS directly.

@@ -13,6 +13,11 @@
 //
 //   BK        k consumed per pipeline step (multiple of 16)
 //   AKC/BKC   operand is K-contiguous in memory (A: transA == 0, B: transB == 1)
+//   UNITS     K is a multiple of four, so four consecutive k of a K-contiguous operand all lie inside the K
+//             range or all behind it, and the step that the range cuts takes one test per load.  With a test
+//             per element in the code besides, that step cost K-sliced 16 x 16 tiles 7 % over their rows of
+//             the tuning set (576 x 72 x 824 NT 4.8 -> 5.5 us) and direct 32 x 32 tiles 2 % (136 x 256 x 40 NT
+//             2.6 -> 3.0); with this form both are level with separate aligned loads (1.006 and 1.007).
 // Rows / columns beyond M / N are clamped to the last valid one (their results are never stored);
 // k beyond the end of the K range reads as zero.
 #pragma once
@@ -28,14 +33,18 @@
 namespace ks {
 
 // Four consecutive k of row / column idx; k from the end of the range on read as zero.
-template <bool KC>
+template <bool KC, bool UNITS>
 __device__ __forceinline__ floatx4 direct_fetch(const float *base, long long ld, int idx, int k, int kEnd) {
     floatx4 v = {0.f, 0.f, 0.f, 0.f};
     const float *src = KC ? base + (long long)idx * ld + k : base + (long long)k * ld + idx;
-    if (KC && k + 4 <= kEnd) return load_float4_any(src);
+    if constexpr (KC && UNITS) {
+        if (k < kEnd) v = load_float4_any(src);
+    } else {
+        if (KC && k + 4 <= kEnd) return load_float4_any(src);
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-        if (k + j < kEnd) v[j] = src[KC ? j : (long long)j * ld];
+        for (int j = 0; j < 4; ++j)
+            if (k + j < kEnd) v[j] = src[KC ? j : (long long)j * ld];
+    }
     return v;
 }
 
@@ -51,7 +60,7 @@ __device__ __forceinline__ floatx4 direct_fetch_full(const float *lanePtr, long 
     return v;
 }
 
-template <int BM, int BN, int BK, int WM, int WN, bool SPLIT, bool AKC, bool BKC>
+template <int BM, int BN, int BK, int WM, int WN, bool SPLIT, bool AKC, bool BKC, bool UNITS>
 __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) void gemm_f32_direct_kernel(const GemmParams p) {
     constexpr int FM = WM / 16, FN = WN / 16, NG = BK / 16;       // fragments per wave; k-groups per step
     static_assert(BK % 16 == 0 && WM % 16 == 0 && WN % 16 == 0, "direct core shape");
@@ -109,10 +118,10 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) void gemm_f32_direct_ke
             for (int g = 0; g < NG; ++g) {
 #pragma unroll
                 for (int i = 0; i < FM; ++i)
-                    a[set][g][i] = direct_fetch<AKC>(Ab, p.lda, rowIdx[i], k0 + g * 16 + kLane, kEnd);
+                    a[set][g][i] = direct_fetch<AKC, UNITS>(Ab, p.lda, rowIdx[i], k0 + g * 16 + kLane, kEnd);
 #pragma unroll
                 for (int j = 0; j < FN; ++j)
-                    b[set][g][j] = direct_fetch<BKC>(Bb, p.ldb, colIdx[j], k0 + g * 16 + kLane, kEnd);
+                    b[set][g][j] = direct_fetch<BKC, UNITS>(Bb, p.ldb, colIdx[j], k0 + g * 16 + kLane, kEnd);
             }
         }
     };

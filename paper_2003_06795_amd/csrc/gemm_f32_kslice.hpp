@@ -16,7 +16,7 @@
 
 namespace ks {
 
-template <int BM, int BN, int BK, int KW, int W, bool SPLIT, bool AKC, bool BKC>
+template <int BM, int BN, int BK, int KW, int W, bool SPLIT, bool AKC, bool BKC, bool UNITS>
 __global__ __launch_bounds__(64 * KW * (BM / W) * (BN / W)) void gemm_f32_kslice_kernel(const GemmParams p) {
     constexpr int FM = W / 16, FN = W / 16, NG = BK / 16;
     constexpr int TW = (BM / W) * (BN / W);                   // wave tiles per work-group tile
@@ -80,10 +80,10 @@ __global__ __launch_bounds__(64 * KW * (BM / W) * (BN / W)) void gemm_f32_kslice
             for (int g = 0; g < NG; ++g) {
 #pragma unroll
                 for (int i = 0; i < FM; ++i)
-                    a[set][g][i] = direct_fetch<AKC>(Ab, p.lda, rowIdx[i], k0 + g * 16 + kLane, kEnd);
+                    a[set][g][i] = direct_fetch<AKC, UNITS>(Ab, p.lda, rowIdx[i], k0 + g * 16 + kLane, kEnd);
 #pragma unroll
                 for (int j = 0; j < FN; ++j)
-                    b[set][g][j] = direct_fetch<BKC>(Bb, p.ldb, colIdx[j], k0 + g * 16 + kLane, kEnd);
+                    b[set][g][j] = direct_fetch<BKC, UNITS>(Bb, p.ldb, colIdx[j], k0 + g * 16 + kLane, kEnd);
             }
         }
     };

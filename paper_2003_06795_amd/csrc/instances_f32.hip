@@ -22,9 +22,9 @@ static void launch_f32_fixed(const GemmParams &p, int grid, int variant, hipStre
 #define KS_V(A, B, U)                                                                                   \
     do {                                                                                                \
         if constexpr (CORE == CORE_KSLICE)                                                              \
-            hipLaunchKernelGGL((gemm_f32_kslice_kernel<BM, BN, BK, P1, P2, SPLIT, A, B>), g, b, 0, s, p); \
+            hipLaunchKernelGGL((gemm_f32_kslice_kernel<BM, BN, BK, P1, P2, SPLIT, A, B, U && (A || B)>), g, b, 0, s, p); \
         else if constexpr (CORE == CORE_DIRECT)                                                         \
-            hipLaunchKernelGGL((gemm_f32_direct_kernel<BM, BN, BK, P1, P2, SPLIT, A, B>), g, b, 0, s, p); \
+            hipLaunchKernelGGL((gemm_f32_direct_kernel<BM, BN, BK, P1, P2, SPLIT, A, B, U && (A || B)>), g, b, 0, s, p); \
         else if constexpr (MULTI_OK) {                                                                  \
             if (p.tilesPerWG > 1)                                                                       \
                 hipLaunchKernelGGL((gemm_f32_kernel<CORE, BM, BN, BK, P1, P2, SPLIT, A, B, U, KW, true>), g, b, 0, s, p); \
@@ -33,7 +33,7 @@ static void launch_f32_fixed(const GemmParams &p, int grid, int variant, hipStre
         } else                                                                                          \
             hipLaunchKernelGGL((gemm_f32_kernel<CORE, BM, BN, BK, P1, P2, SPLIT, A, B, U, KW>), g, b, 0, s, p);  \
     } while (0)
-    switch (variant & 7) {                            // bit 0: units of four, short K
+    switch (variant & 7) {                            // bit 0: units of four (dispatch.hip)
         case 0: KS_V(false, false, false); break;
         case 1: KS_V(false, false, true); break;
         case 2: KS_V(false, true, false); break;
