@@ -45,6 +45,24 @@ def attainable_tflops(dtype, M, N, K, batch=1, beta=0.0):
     return min(PEAK[dtype], 2.0 * M * N * K * batch / by * HBM_TBS)
 
 
+def f32_load_form(ki, plan, akc, bkc, M, N, K):
+    """Load form of an LDS-staged fp32 member (ks_common.hpp): 0 whole steps, 1 units of four, 2 elements."""
+    if plan["balanced_groups"] > 0 or plan["tiles_per_workgroup"] > 1:
+        return 0
+    kw, bk, nt, mfma16 = ki["k_waves"], ki["bk"], ki["threads"] // ki["k_waves"], ki["core_name"] == "mfma16"
+    chunk = -(-(-(-K // bk)) // plan["split_k"]) * bk
+    steps = min(K, chunk) / (bk * kw)
+    units = [r * bk // 4 for r in (ki["bm"], ki["bn"])]
+    idle = [u % nt != 0 for u in units]
+    if (K if akc else M) % 4 == 0 and (K if bkc else N) % 4 == 0:
+        one_unit = units == [nt, nt] and (mfma16 if kw > 1 else nt >= 512)
+        return 1 if steps <= 8 or ki["core_name"] == "fma" or any(idle) or one_unit else 0
+    if all(idle) and bk <= 16:
+        return 2
+    most = 0 if kw > 1 and bk >= 64 else 2 if any(idle) or (mfma16 and kw > 1) else 1
+    return 2 if steps <= most else 0
+
+
 def kernel_symbol(ks, dt, plan, tA, tB, M, N, K):
     """Name of the device function a call resolves to (as rocprofv3 prints it), from what the
     library says it would launch (ks_gemm_plan): member, split actually taken, code path."""
@@ -61,12 +79,9 @@ def kernel_symbol(ks, dt, plan, tA, tB, M, N, K):
             ki["bm"], ki["bn"], ki["bk"], ki["k_waves"], ki["wm"], b(split), b(akc), b(bkc), b(fed))
     if dt == ks.F32:
         p1, p2 = (ki["tm"], ki["tn"]) if ki["core_name"] == "fma" else (ki["wm"], ki["wn"])
-        chunk = -(-(-(-K // ki["bk"])) // plan["split_k"]) * ki["bk"]
-        units = (K if akc else M) % 4 == 0 and (K if bkc else N) % 4 == 0 and plan["balanced_groups"] == 0 and \
-            plan["tiles_per_workgroup"] == 1 and \
-            min(K, chunk) <= 8 * ki["bk"] * ki["k_waves"]
-        return "gemm_f32_kernel<%d, %d, %d, %d, %d, %d, %s, %s, %s, %s, %d, %s, %s>" % (
-            ki["core"], ki["bm"], ki["bn"], ki["bk"], p1, p2, b(split), b(akc), b(bkc), b(units), ki["k_waves"],
+        return "gemm_f32_kernel<%d, %d, %d, %d, %d, %d, %s, %s, %s, %d, %d, %s, %s>" % (
+            ki["core"], ki["bm"], ki["bn"], ki["bk"], p1, p2, b(split), b(akc), b(bkc),
+            f32_load_form(ki, plan, akc, bkc, M, N, K), ki["k_waves"],
             b(plan["tiles_per_workgroup"] > 1), b(plan["balanced_groups"] > 0))
     f = 16 if ki["core_name"] == "mfma16" else 32
     if plan["path"] == 2:

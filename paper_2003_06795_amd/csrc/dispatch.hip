@@ -557,15 +557,17 @@ int run_ws(Workspace wsp, int dtype, int id, int transA, int transB, int64_t M, 
     const bool akc = transA == 0, bkc = transB == 1;
     const bool vec = vector_operands(dtype == KS_F32 ? 4 : 8, akc, bkc, M, N, K, A, lda, B, ldb, batch, strideA, strideB);
     const int splitBit = p.splitK > 1 ? 8 : 0;       // read by instances whose split is chosen per call
-    // Form of the fp32 members whose loads need one test per unit of four (gemm_f32.hpp, gemm_f32_direct.hpp).
-    // Register-fed cores: K is a multiple of four.  LDS-staged ones: no unit straddles an edge and a
-    // wave runs at most eight K-steps (it gains up to four of them and loses from ten on; the multi-tile form
-    // loses 3 % with it).
+    // Load form of the fp32 members: of the LDS-staged ones as described in ks_common.hpp, UNITS up to eight K-steps
+    // of a wave in any member (it gains up to four of them); of the register-fed ones (gemm_f32_direct.hpp) by K alone.
     const bool registerFed = d->core == KS_CORE_DIRECT || d->core == KS_CORE_KSLICE;
+    const int64_t waveK = K < p.kChunk ? K : p.kChunk, stepK = (int64_t)d->bk * d->kw;
+    const bool oneTile = p.skGroups == 0 && p.tilesPerWG == 1;
+    const int group = d->threads / d->kw;
     const bool units = registerFed ? K % 4 == 0
-                                   : (akc ? K : M) % 4 == 0 && (bkc ? K : N) % 4 == 0 && p.skGroups == 0 &&
-                                         p.tilesPerWG == 1 && (K < p.kChunk ? K : p.kChunk) <= 8LL * d->bk * d->kw;
-    const int variant = (akc ? 4 : 0) + (bkc ? 2 : 0) + (units ? 1 : 0) + splitBit;
+                                   : oneTile && (akc ? K : M) % 4 == 0 && (bkc ? K : N) % 4 == 0 &&
+                                         (waveK <= 8 * stepK || f32_units_at_any_k(d->core, d->bm, d->bn, d->bk, group, d->kw));
+    const bool elements = oneTile && waveK <= f32_element_steps(d->core, d->bm, d->bn, d->bk, group, d->kw) * stepK;
+    const int variant = (akc ? 4 : 0) + (bkc ? 2 : 0) + (units ? 1 : 0) + (elements ? 32 : 0) + splitBit;
 
     // bf16 fast path: operand tiles go global -> LDS directly.
     const int f16Bit = dtype == KS_F16 ? 16 : 0;     // same 16-bit members, binary16 MFMA

@@ -12,8 +12,7 @@
 //   SPLIT     the instantiation is a split-K member: partial sums go to the workspace
 //   AKC/BKC   whether op(A)/op(B) is K-contiguous in memory (A: transA == 0, B: transB == 1);
 //             decides the coalescing direction of the global loads
-//   SHORTK    extents are multiples of 4 and K is short: one kind of K-step, see TileLoader
-// Operands are fetched sixteen bytes per lane at any element address.
+//   LOADS     how a K-step is fetched (ks_common.hpp, TileLoader)
 //
 // LDS layout (both operands): tile[k][m or n] with the row padded by 4 floats.  All cores read
 // "one k, many m/n", so rows of consecutive m/n are conflict-free for them.
@@ -36,13 +35,14 @@ namespace ks {
 // forms keep the next tile's staging registers alive across the epilogue; the four-wave members
 // with 64 x 32 wave tiles then drift a few registers past the budget of three waves per SIMD (168
 // with the accumulators) that they met before, and lose a resident work-group; the eight-wave members
-// need four.  The sixteen-wave 16x16 members hold two work-groups per compute unit with 64 registers
-// and would take 65 - 67 with both kinds of K-step in their loop.
+// need four.  The sixteen-wave 16x16 members without K groups hold two work-groups per compute unit with 64
+// registers and would take 65 - 67 with both kinds of K-step in their loop.
 #ifndef KS_F32_MIN_WAVES
-#define KS_F32_MIN_WAVES(multi, core, bm, bn, bk, p1, p2, kw)                                        \
-    ((core) == CORE_MFMA16 && ((bm) / (p1)) * ((bn) / (p2)) * (kw) == 16                  ? 8 \
-     : !(multi)                                                                            ? 0 \
-     : ((bm) / (p1)) * ((bn) / (p2)) <= 4 ? 3 : 4)
+#define KS_F32_MIN_WAVES(multi, core, bm, bn, bk, p1, p2, kw, loads)                                             \
+    ((core) == CORE_MFMA16 && ((bm) / (p1)) * ((bn) / (p2)) == 16 && (kw) == 1 && (loads) == LOAD_STEPS ? 8 \
+     : !(multi)                                                                                          ? 0 \
+     : ((bm) / (p1)) * ((bn) / (p2)) <= 4                                                                ? 3 \
+                                                                                                         : 4)
 #endif
 // The balanced persistent form counts on a fixed number of resident work-groups per compute unit:
 // two of eight waves (four waves per SIMD, 128 registers) or three of four waves (three per SIMD),
@@ -51,8 +51,8 @@ namespace ks {
 #define KS_F32_SK_MIN_WAVES(bm, bn, p1, p2) (((bm) / (p1)) * ((bn) / (p2)) >= 8 ? 4 : 3)
 #endif
 
-// Row padding of the row-contiguous operand's LDS tile when the other operand is K-contiguous
-// (NN and TT layouts): the padding of its partner instead of its own 4
+// Row padding of the row-contiguous operand's LDS tile when the other operand is K-contiguous and
+// both are fetched sixteen bytes per lane (NN and TT layouts): the padding of its partner instead of its own 4
 // for the members named below.  With unequal row lengths (130 and 132 floats at BK = 32) the
 // compiler keeps separate sets of fragment addresses for the two tiles, 23 - 28 registers.  The
 // balanced persistent form of the 128 x 128 x 32 member does not have them inside its budget of 128,
@@ -64,10 +64,12 @@ namespace ks {
 // loses 1 - 9 % (among them the four-wave 64 x 64 x 32 balanced member), so only those get it.
 // -1 = no override.
 constexpr int f32_pad_of_partner(bool persistent, int core, int bm, int bn, int p1, int p2, int kw, bool kc, bool partnerKc,
-                                 int bk, int threads) {
+                                 int bk, int threads, int loads) {
     const bool persistentLarge = persistent && threads >= 512;
     const bool squareOn16 = core == 1 && bm == bn && p1 == 16 && p2 == 16 && bk == 32 && threads * kw >= 512;
-    return (persistentLarge || squareOn16) && !kc && partnerKc && bk <= 32 && (64 / bk) % 2 == 0 ? 64 / bk : -1;
+    return loads != LOAD_ELEMENTS && (persistentLarge || squareOn16) && !kc && partnerKc && bk <= 32 && (64 / bk) % 2 == 0
+               ? 64 / bk
+               : -1;
 }
 
 enum { CORE_FMA = 0, CORE_MFMA16 = 1, CORE_MFMA32 = 2, CORE_DIRECT = 3, CORE_KSLICE = 4 };
@@ -81,8 +83,8 @@ struct F32Shape {
 
 // ---- global -> registers -> LDS staging of one ROWS x BK operand tile ------------------------
 // KC:  memory is [row][k] (k contiguous);  !KC: memory is [k][row] (row contiguous).
-// Units are four floats walked so that consecutive lanes touch consecutive addresses.  INNER = units
-// along the contiguous direction, OUTER = the other direction.
+// Units are W floats (four, or one in the ELEMENTS form) walked so that consecutive lanes touch consecutive
+// addresses.  INNER = units along the contiguous direction, OUTER = the other direction.
 // PAD >= 0 overrides the row padding chosen below (see f32_pad_of_partner).
 //
 // load() is for K-steps in which every unit may be read whole (whole_steps() of them): the rows of a
@@ -93,20 +95,20 @@ struct F32Shape {
 // offset that stays the same for the whole tile on a scalar address that advances with K.
 // load_edge() is for the steps that are left, as a rule the one that holds the end of K: it reads
 // inside the matrix only, and k beyond the end read as zero.
-// Where extents are multiples of four a unit lies inside the matrix or outside, and load_units() serves any
-// step with one predicate per unit.  A short K runs the form that knows this kind of step only: the code
-// of both other kinds, up to four K-steps deep, costs it more than the predicates (944 x 40x52x52 17.2 against
-// 14.5 us, 4096 x 64x64x64 62.5 against 53.8, 3056 x 704 x 16 NT 8.4 against 7.4), while from about ten K-steps
-// on it is the slower one (1024^3 NN 26.1 against 24.6 us, 25088 x 256 x 1152 151 against 146).
+// load_units() serves any step of the UNITS and ELEMENTS forms with one predicate per unit, none of which
+// straddles an edge there.  A short K runs these: the code of both other kinds, up to four K-steps deep, costs
+// it more than the predicates (944 x 40x52x52 17.2 against 14.5 us, 4096 x 64x64x64 62.5 against 53.8, 3056 x 704 x 16
+// NT 8.4 against 7.4), while from about ten K-steps on the predicates are the slower ones (1024^3 NN 26.1 against
+// 24.6 us, 25088 x 256 x 1152 151 against 146), but for the members named in ks_common.hpp.
 //
-// What it is there for: the large members wait for the issue of their loads, not for memory (a matrix
+// What load() is there for: the large members wait for the issue of their loads, not for memory (a matrix
 // pipe kept busy by other waves holds up vector-memory issue), and four-byte loads took four times as
 // many of them.  Against scalar loads of unaligned operands and predicated ones of aligned operands:
 // 4095 x 3000 x 4089 NT 950 -> 805 us (TN 1020 -> 797), 1000^3 with padded rows NN 33.3 -> 26.2 us;
 // aligned 4096^3 TN 1058 -> 1006 us, 1024^3 NN 26.0 -> 24.5 us, im2col 25088 x 256 x 1152 149 -> 144 us.
-template <int ROWS, int BK, int NT, bool KC, int PAD = -1>
+template <int ROWS, int BK, int NT, bool KC, int W, int PAD = -1>
 struct TileLoader {
-    static constexpr int W = 4;
+    typedef float Unit __attribute__((ext_vector_type(W)));
     static constexpr int INNER = (KC ? BK : ROWS) / W;
     static constexpr int OUTER = KC ? ROWS : BK;
     static constexpr int UNITS = INNER * OUTER;
@@ -115,12 +117,12 @@ struct TileLoader {
     // Row padding of the LDS tile.  A K-contiguous operand is written as four scalars to rows
     // k .. k+3; a wave's lanes then differ in k by multiples of 4 (BK/4 lanes) and in the row, and
     // land in 64 different banks when 4 * LDS_LD = 256/BK (mod 64), i.e. a padding of 64/BK floats.
-    // A row-contiguous one is written along a row and takes the padding of 4 that keeps its 16-byte
-    // writes aligned.  (Measured: bank-conflict cycles of the 128 x 128 x 32 member fell to a third
-    // and the BK = 32 / 64 members gained 2 - 20 % on long K; giving the lane groups of an MFMA read
-    // rows 4 or 8 apart instead of adjacent ones changed nothing.)
-    static constexpr int LDS_LD = ROWS + (PAD >= 0 ? PAD : KC ? (BK >= 64 ? 1 : 64 / BK) : 4);
-    static_assert(KC || LDS_LD % 2 == 0, "row-contiguous vector writes need 8-byte alignment");
+    // One written along a row takes the padding of 4 that keeps its 16-byte writes aligned.  (Measured:
+    // bank-conflict cycles of the 128 x 128 x 32 member fell to a third and the BK = 32 / 64 members gained
+    // 2 - 20 % on long K; giving the lane groups of an MFMA read rows 4 or 8 apart instead of adjacent ones
+    // changed nothing.)
+    static constexpr int LDS_LD = ROWS + (PAD >= 0 ? PAD : KC && W == 4 ? (BK >= 64 ? 1 : 64 / BK) : 4);
+    static_assert(KC || W == 1 || LDS_LD % 2 == 0, "row-contiguous vector writes need 8-byte alignment");
     static_assert(INNER <= NT && NT % INNER == 0, "walk");
 
     // byte offsets of a thread's units from the tile origin (row0, first k of the step); the units of a
@@ -139,7 +141,7 @@ struct TileLoader {
         }
     };
 
-    floatx4 reg[ITERS];
+    Unit reg[ITERS];
 
     __device__ __forceinline__ static bool has(int tid, int it) {
         return UNITS % NT == 0 || tid / INNER + it * STRIDE < OUTER;
@@ -162,14 +164,19 @@ struct TileLoader {
         }
     }
 
-    // kLeft: k of the step that exist
-    __device__ __forceinline__ void load_units(const Plan &plan, const float *tile, long long ld, int kLeft, int tid) {
+    // any step where no unit straddles an edge of the matrix: rows and k beyond it read as zero
+    __device__ __forceinline__ void load_units(const float *base, long long ld, int row0, int limit, int k0, int kEnd,
+                                               int tid) {
 #pragma unroll
         for (int it = 0; it < ITERS; ++it) {
-            const int k = KC ? tid % INNER * W : tid / INNER + it * STRIDE;
-            const char *t = reinterpret_cast<const char *>(tile + (KC ? 0 : it * STRIDE * ld));
-            floatx4 v = {0.f, 0.f, 0.f, 0.f};
-            if (has(tid, it) && k < kLeft) v = load_float4_any(t + plan.off[KC ? it : 0]);
+            const int inner = tid % INNER, outer = tid / INNER + it * STRIDE;
+            const int row = row0 + (KC ? outer : inner * W), k = k0 + (KC ? inner * W : outer);
+            const float *src = KC ? base + (long long)row * ld + k : base + (long long)k * ld + row;
+            Unit v = 0.f;
+            if (has(tid, it) && row < limit && k < kEnd) {
+                if constexpr (W == 4) v = load_float4_any(src);
+                else v[0] = *src;
+            }
             reg[it] = v;
         }
     }
@@ -212,7 +219,7 @@ struct TileLoader {
             const int inner = tid % INNER, outer = tid / INNER + it * STRIDE;
             const int r = KC ? outer : inner * W;
             const int k = KC ? inner * W : outer;
-            if constexpr (KC) {
+            if constexpr (KC || W == 1) {
 #pragma unroll
                 for (int j = 0; j < W; ++j) lds[(k + j) * LDS_LD + r] = reg[it][j];
             } else if constexpr (LDS_LD % 4 == 0) {
@@ -248,17 +255,19 @@ struct TileLoader {
 // share), and gemm_f32_sk_fixup_kernel adds the parts of every divided tile in K order and applies
 // the epilogue.  No work-group waits for another, so there is nothing to deadlock on.
 template <int CORE, int BM, int BN, int BK, int P1, int P2, bool SPLIT, bool AKC, bool BKC,
-          bool SHORTK, int KW = 1, bool MULTI = false, bool SK = false>
-__global__ __launch_bounds__((F32Shape<CORE, BM, BN, P1, P2>::threads * KW), (SK ? KS_F32_SK_MIN_WAVES(BM, BN, P1, P2) : KS_F32_MIN_WAVES(MULTI, CORE, BM, BN, BK, P1, P2, KW))) void gemm_f32_kernel(
+          int LOADS, int KW = 1, bool MULTI = false, bool SK = false>
+__global__ __launch_bounds__((F32Shape<CORE, BM, BN, P1, P2>::threads * KW), (SK ? KS_F32_SK_MIN_WAVES(BM, BN, P1, P2) : KS_F32_MIN_WAVES(MULTI, CORE, BM, BN, BK, P1, P2, KW, LOADS))) void gemm_f32_kernel(
     const GemmParams p) {
+    static_assert(LOADS == LOAD_STEPS || !(MULTI || SK), "persistent forms");
     static_assert(!MULTI || (f32_multi_tile(CORE, BM, BN, P1, P2, KW) && !SPLIT), "multi-tile form");
     static_assert(!SK || (CORE == CORE_MFMA32 && KW == 1 && !SPLIT && !MULTI), "balanced persistent form");
     using Shape = F32Shape<CORE, BM, BN, P1, P2>;
     constexpr int NT = Shape::threads;                        // threads of one group
     static_assert(KW == 1 || CORE != CORE_FMA, "K groups need an MFMA core");
-    constexpr int PADA = f32_pad_of_partner(SK || MULTI, CORE, BM, BN, P1, P2, KW, AKC, BKC, BK, NT);
-    constexpr int PADB = f32_pad_of_partner(SK || MULTI, CORE, BM, BN, P1, P2, KW, BKC, AKC, BK, NT);
-    constexpr int LDA = TileLoader<BM, BK, NT, AKC, PADA>::LDS_LD, LDB = TileLoader<BN, BK, NT, BKC, PADB>::LDS_LD;
+    constexpr int PADA = f32_pad_of_partner(SK || MULTI, CORE, BM, BN, P1, P2, KW, AKC, BKC, BK, NT, LOADS);
+    constexpr int PADB = f32_pad_of_partner(SK || MULTI, CORE, BM, BN, P1, P2, KW, BKC, AKC, BK, NT, LOADS);
+    constexpr int W = LOADS == LOAD_ELEMENTS ? 1 : 4;
+    constexpr int LDA = TileLoader<BM, BK, NT, AKC, W, PADA>::LDS_LD, LDB = TileLoader<BN, BK, NT, BKC, W, PADB>::LDS_LD;
     __shared__ __attribute__((aligned(16))) float AsAll[KW][2][BK * LDA];
     __shared__ __attribute__((aligned(16))) float BsAll[KW][2][BK * LDB];
 
@@ -282,9 +291,9 @@ __global__ __launch_bounds__((F32Shape<CORE, BM, BN, P1, P2>::threads * KW), (SK
     // K-steps in flight between global memory and LDS (each in its own set of staging registers):
     // small tiles are latency-bound - few waves per compute unit, short MFMA runs per K-step - and
     // afford several; large tiles hide the latency behind their MFMAs and keep the registers.
-    using LoaderA = TileLoader<BM, BK, NT, AKC, PADA>;
-    using LoaderB = TileLoader<BN, BK, NT, BKC, PADB>;
-    constexpr int STAGE_REGS = (LoaderA::ITERS + LoaderB::ITERS) * LoaderA::W;
+    using LoaderA = TileLoader<BM, BK, NT, AKC, W, PADA>;
+    using LoaderB = TileLoader<BN, BK, NT, BKC, W, PADB>;
+    constexpr int STAGE_REGS = (LoaderA::ITERS + LoaderB::ITERS) * W;
     constexpr int PF = KS_F32_PREFETCH(STAGE_REGS, NT);
     LoaderA la[PF];
     LoaderB lb[PF];
@@ -294,9 +303,9 @@ __global__ __launch_bounds__((F32Shape<CORE, BM, BN, P1, P2>::threads * KW), (SK
     auto load_step = [&](LoaderA &a, LoaderB &b, const float *A, const float *B, int r, int c, int k0, int kE, bool whole) {
         const float *at = AKC ? A + (long long)r * p.lda + k0 : A + (long long)k0 * p.lda + r;
         const float *bt = BKC ? B + (long long)c * p.ldb + k0 : B + (long long)k0 * p.ldb + c;
-        if constexpr (SHORTK) {
-            a.load_units(pa, at, p.lda, kE - k0, tid);
-            b.load_units(pb, bt, p.ldb, kE - k0, tid);
+        if constexpr (LOADS != LOAD_STEPS) {
+            a.load_units(A, p.lda, r, p.M, k0, kE, tid);
+            b.load_units(B, p.ldb, c, p.N, k0, kE, tid);
         } else if (whole) {
             a.load(pa, at, p.lda, tid);
             b.load(pb, bt, p.ldb, tid);

@@ -19,30 +19,36 @@ static void launch_f32_fixed(const GemmParams &p, int grid, int variant, hipStre
     // the multi-tile form exists beside the single-tile one and runs when the host asks for it
     constexpr bool MULTI_OK = !SPLIT && f32_multi_tile(CORE, BM, BN, P1, P2, KW);
     const dim3 g = launch_grid(p, grid), b(NT);
-#define KS_V(A, B, U)                                                                                   \
+#define KS_V(A, B, L)                                                                                   \
     do {                                                                                                \
         if constexpr (CORE == CORE_KSLICE)                                                              \
-            hipLaunchKernelGGL((gemm_f32_kslice_kernel<BM, BN, BK, P1, P2, SPLIT, A, B, U && (A || B)>), g, b, 0, s, p); \
+            hipLaunchKernelGGL((gemm_f32_kslice_kernel<BM, BN, BK, P1, P2, SPLIT, A, B, L == LOAD_UNITS && (A || B)>), g, b, 0, s, p); \
         else if constexpr (CORE == CORE_DIRECT)                                                         \
-            hipLaunchKernelGGL((gemm_f32_direct_kernel<BM, BN, BK, P1, P2, SPLIT, A, B, U && (A || B)>), g, b, 0, s, p); \
+            hipLaunchKernelGGL((gemm_f32_direct_kernel<BM, BN, BK, P1, P2, SPLIT, A, B, L == LOAD_UNITS && (A || B)>), g, b, 0, s, p); \
         else if constexpr (MULTI_OK) {                                                                  \
             if (p.tilesPerWG > 1)                                                                       \
-                hipLaunchKernelGGL((gemm_f32_kernel<CORE, BM, BN, BK, P1, P2, SPLIT, A, B, U, KW, true>), g, b, 0, s, p); \
+                hipLaunchKernelGGL((gemm_f32_kernel<CORE, BM, BN, BK, P1, P2, SPLIT, A, B, LOAD_STEPS, KW, true>), g, b, 0, s, p); \
             else                                                                                        \
-                hipLaunchKernelGGL((gemm_f32_kernel<CORE, BM, BN, BK, P1, P2, SPLIT, A, B, U, KW>), g, b, 0, s, p); \
+                hipLaunchKernelGGL((gemm_f32_kernel<CORE, BM, BN, BK, P1, P2, SPLIT, A, B, L, KW>), g, b, 0, s, p); \
         } else                                                                                          \
-            hipLaunchKernelGGL((gemm_f32_kernel<CORE, BM, BN, BK, P1, P2, SPLIT, A, B, U, KW>), g, b, 0, s, p);  \
+            hipLaunchKernelGGL((gemm_f32_kernel<CORE, BM, BN, BK, P1, P2, SPLIT, A, B, L, KW>), g, b, 0, s, p);  \
     } while (0)
-    switch (variant & 7) {                            // bit 0: units of four (dispatch.hip)
-        case 0: KS_V(false, false, false); break;
-        case 1: KS_V(false, false, true); break;
-        case 2: KS_V(false, true, false); break;
-        case 3: KS_V(false, true, true); break;
-        case 4: KS_V(true, false, false); break;
-        case 5: KS_V(true, false, true); break;
-        case 6: KS_V(true, true, false); break;
-        default: KS_V(true, true, true); break;
+    // variant bit 0: units of four; bit 5: elements.  The register-fed members have one form more for the former.
+    constexpr bool STAGED = CORE != CORE_KSLICE && CORE != CORE_DIRECT;
+#define KS_FORMS(A, B)                                                                                  \
+    do {                                                                                                \
+        if (variant & 1) KS_V(A, B, LOAD_UNITS);                                                        \
+        else if constexpr (STAGED && f32_never_steps(BM, BN, BK, NT / KW)) KS_V(A, B, LOAD_ELEMENTS);   \
+        else if (STAGED && (variant & 32)) KS_V(A, B, STAGED ? LOAD_ELEMENTS : LOAD_STEPS);             \
+        else KS_V(A, B, LOAD_STEPS);                                                                    \
+    } while (0)
+    switch ((variant >> 1) & 3) {
+        case 0: KS_FORMS(false, false); break;
+        case 1: KS_FORMS(false, true); break;
+        case 2: KS_FORMS(true, false); break;
+        default: KS_FORMS(true, true); break;
     }
+#undef KS_FORMS
 #undef KS_V
 }
 
@@ -50,10 +56,10 @@ static void launch_f32_fixed(const GemmParams &p, int grid, int variant, hipStre
 template <int CORE, int BM, int BN, int BK, int P1, int P2, int SPLITMODE, int KW>
 static void launch_f32(const GemmParams &p, int grid, int variant, hipStream_t s) {
     if constexpr (SPLITMODE == 2) {
-        if (variant & 8) launch_f32_fixed<CORE, BM, BN, BK, P1, P2, true, KW>(p, grid, variant & 7, s);
-        else launch_f32_fixed<CORE, BM, BN, BK, P1, P2, false, KW>(p, grid, variant & 7, s);
+        if (variant & 8) launch_f32_fixed<CORE, BM, BN, BK, P1, P2, true, KW>(p, grid, variant, s);
+        else launch_f32_fixed<CORE, BM, BN, BK, P1, P2, false, KW>(p, grid, variant, s);
     } else {
-        launch_f32_fixed<CORE, BM, BN, BK, P1, P2, SPLITMODE == 1, KW>(p, grid, variant & 7, s);
+        launch_f32_fixed<CORE, BM, BN, BK, P1, P2, SPLITMODE == 1, KW>(p, grid, variant, s);
     }
 }
 
@@ -62,13 +68,13 @@ static void launch_f32(const GemmParams &p, int grid, int variant, hipStream_t s
 template <int CORE, int BM, int BN, int BK, int P1, int P2>
 static void launch_f32_sk(const GemmParams &p, int grid, int variant, hipStream_t s) {
     if (p.skGroups <= 0) {
-        launch_f32_fixed<CORE, BM, BN, BK, P1, P2, false, 1>(p, grid, variant & 7, s);
+        launch_f32_fixed<CORE, BM, BN, BK, P1, P2, false, 1>(p, grid, variant, s);
         return;
     }
     constexpr int NT = F32Shape<CORE, BM, BN, P1, P2>::threads;
     const dim3 g((unsigned)p.skGroups), b(NT);
 #define KS_V(A, B) \
-    hipLaunchKernelGGL((gemm_f32_kernel<CORE, BM, BN, BK, P1, P2, false, A, B, false, 1, false, true>), g, b, 0, s, p)
+    hipLaunchKernelGGL((gemm_f32_kernel<CORE, BM, BN, BK, P1, P2, false, A, B, LOAD_STEPS, 1, false, true>), g, b, 0, s, p)
     switch ((variant >> 1) & 3) {
         case 0: KS_V(false, false); break;
         case 1: KS_V(false, true); break;

@@ -74,6 +74,39 @@ __device__ __forceinline__ void store_bf16_out(float *Cb, long long idx, float a
     *c = float_to_bf16_bits(x + biasv);
 }
 
+// How the LDS-staged fp32 members (nt threads to a group of waves) fetch a K-step: one of three forms of the
+// kernel.  STEPS reads whole K-steps without a test, sixteen bytes per lane at any element, and the step that
+// holds the end of K in a second way; UNITS knows one way, a test per sixteen bytes, for extents that are
+// multiples of four; ELEMENTS reads four bytes per lane and test.
+enum { LOAD_STEPS = 0, LOAD_UNITS = 1, LOAD_ELEMENTS = 2 };
+// threads that find nothing to fetch in a K-step of sixteen-byte units
+constexpr bool f32_idle_threads(int rows, int bk, int nt) { return (rows * bk / 4) % nt != 0; }
+// UNITS at any K.  The second way of STEPS is code that a short K-step does not amortise, and threads without a
+// unit branch around every load: UNITS / STEPS over ten to forty K-steps, geometric means over the layouts, for
+// idle threads 64 x 32 x 32 0.91, 32 x 64 x 32 0.90, 16 x 16 x 8 0.86, 32 x 32 x 16 0.85, 64 x 64 x 8 0.89, 16 x 128 x 16 0.88,
+// 64 x 64 x 16 and x 32 with sixteen waves 0.93; one unit each: 32 x 32 x 32 with two K groups 0.97 (3928 x 24 x 1568 NN
+// 13.4 -> 12.5 us), eight-wave 128 x 128 x 16 0.95; FMA 64 x 64 x 8 0.95.  Elsewhere 0.99 (64 x 64 x 16) to 1.11 (16 x 16 x 32).
+constexpr bool f32_units_at_any_k(int core, int bm, int bn, int bk, int nt, int kw) {
+    return core == 0 || f32_idle_threads(bm, bk, nt) || f32_idle_threads(bn, bk, nt) ||
+           (bm * bk == 4 * nt && bn * bk == 4 * nt && (kw > 1 ? core == 1 : nt >= 512));
+}
+// No STEPS form: neither operand keeps the threads busy and the K-step is short.  ELEMENTS / STEPS on ragged
+// operands over three to forty K-steps: 16 x 16 x 8 0.90, 32 x 32 x 16 0.92, 64 x 64 x 8 0.92, 64 x 64 x 16 0.91, FMA 32 x 32 x 8 0.88;
+// the other members 1.0 to 1.5.
+constexpr bool f32_never_steps(int bm, int bn, int bk, int nt) {
+    return f32_idle_threads(bm, bk, nt) && f32_idle_threads(bn, bk, nt) && bk <= 16;
+}
+// K-steps up to which ragged operands take ELEMENTS in the members that have STEPS: where the step that holds
+// the end of K is all there is (3136 x 256 x 3 NN on 64 x 64 x 16 3.8 -> 3.6 us, 196 x 512 x 27 on 32 x 32 x 32 3.05 -> 2.9), and
+// where it is every second one for the members above that branch most (512 x 35x30x58 NT on 32 x 64 x 32 6.1 -> 5.7,
+// 784 x 256 x 75 NN with two K groups 4.0 -> 3.7); behind by 5 - 20 % beyond, and by 8 - 13 % from the first with K groups
+// of 64, whose steps are nearly all whole.
+constexpr int f32_element_steps(int core, int bm, int bn, int bk, int nt, int kw) {
+    return kw > 1 && bk >= 64                                                                        ? 0
+           : f32_idle_threads(bm, bk, nt) || f32_idle_threads(bn, bk, nt) || (core == 1 && kw > 1) ? 2
+                                                                                                     : 1;
+}
+
 // fp32 LDS-staged members that also exist in a form whose work-groups walk several tiles
 // (GemmParams::tilesPerWG): 32x32 MFMA members (core 2) with large tiles of at least 128 columns
 // (the 128 x 64 member measured slower in that form), wave tiles of at most 2048 entries (the form
