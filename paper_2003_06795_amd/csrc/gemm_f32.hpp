@@ -147,12 +147,13 @@ struct TileLoader {
         return UNITS % NT == 0 || tid / INNER + it * STRIDE < OUTER;
     }
 
-    // leading K-steps of [kBegin, kEnd) that load() may take (lane offsets fit 32 bits below 2^22; a row
-    // of one or two elements could reach beyond the row after next)
+    // leading K-steps of [kBegin, kEnd) that load() may take (lane offsets fit 32 bits below 2^22).  A unit that
+    // hangs over the edge of row k reaches three elements beyond it, which lie inside the matrix while
+    // (K - 1 - k) ld >= 3: all but the last row, or the last two or three where rows are that short.
     __device__ __forceinline__ static int whole_steps(long long ld, int limit, int K, int kBegin, int kEnd) {
         if (ld > (1LL << 22)) return 0;
         if (KC || (limit & 3) == 0) return max((kEnd - kBegin) / BK, 0);
-        return ld < 3 ? 0 : max((min(kEnd, K - 1) - kBegin) / BK, 0);
+        return max((min(kEnd, K - (ld >= 3 ? 1 : ld == 2 ? 2 : 3)) - kBegin) / BK, 0);
     }
 
     // tile: address of the tile origin at this K-step (the same for all lanes)

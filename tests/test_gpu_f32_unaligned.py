@@ -63,3 +63,17 @@ def test_rows_longer_than_lane_offsets_reach(gpu):
         C = torch.full((M, N), float("nan"), device="cuda")
         ks.gemm_f32_with_kernel(kid, 0, 0, M, N, K, 1.0, A, ld, B, N, 0.0, C, N)
         assert float((C.double() - ref).abs().max()) <= 1e-5 * K, kid
+
+
+@pytest.mark.parametrize("few", [1, 2, 3])
+def test_rows_shorter_than_a_unit(gpu, few):
+    """Row-contiguous operands whose rows of one to three elements lie side by side: a unit of four reaches up to
+    three rows ahead, which the last rows do not have."""
+    for K in (32, 33, 34, 35, 64, 257, 1030):
+        for M, N, layout in ((few, 130, (1, 0)), (few, 130, (1, 1)), (130, few, (0, 0)), (130, few, (1, 0)), (few, few, (1, 0))):
+            p = wl.make_problem("f32", *layout, M, N, K, alpha=1.5, beta=-0.5, seed=94, key=K, dist="uniform")
+            ref, tol = gpu.oracle_full(p), tolerance(p)
+            dp = gpu.DeviceProblem(p)
+            for kid in MEMBERS:
+                err = float(np.max(np.abs(dp.run(kid).astype(np.float64) - ref)))
+                assert err <= tol, "kernel %d %s: %.3e > %.3e" % (kid, (M, N, K), err, tol)
