@@ -800,26 +800,29 @@ namespace {
 // 16-bit 47 -> 9 (same tile, one group) where K ends in half a K-step and neither is split: the two-group form
 //   of that pays branches in every memory slot (2560 x 1280 x 1728 NT 20.5 -> 19.2 us, 1216 x 2880 x 3520 NN 35.7 ->
 //   34.8, 1024 x 3712 x 5056 TN 52.6 -> 51.1).
-// fp32 47 (128 x 128 tiles, balanced where that pays) -> 28 (64 x 64) by the time both take, to 5 % of the
-//   measured ones: 28 finishes a tile every 18.1 ns of K on a compute unit and the fullest unit decides; 47
-//   does a K-step of 32 on two tiles of a unit in 4.14 us, or shares all K-steps evenly at 4.3 us and 20 us
-//   for the divided tiles.  6272 x 704 x 576 80 -> 58.5 us, 25088 x 288 x 1152 193 -> 176, 12544 x 576 x 1152 170 -> 150.
+// fp32 47 (128 x 128 tiles) -> 28 (64 x 64).  A unit works through its tiles one after the other, so what counts
+//   is the fullest unit: r128 quarters of large tiles against r64 small ones.
+//   K < 1024, r64 <= 6/7 r128: 52 problems at 0.82 of the time (6272 x 704 x 576 79 -> 57 us, 3312 x 888 x 320 30 -> 24),
+//     one of them slower (1.006); from 7/8 on also 1.10.
+//   K <= 128 and a ragged last column of large tiles, which the pass over C decides: 60 more at 0.87 (17956 x 1067 x 15
+//     29 -> 22 us, 14400 x 1147 x 45 38 -> 29), four of them slower by up to 1.056; with whole columns 1.10.
+//   K >= 1024, where the large tiles may be shared out evenly among all units: only if padding to them costs a
+//     fifth as well.  25 problems at 0.78, 0.73 without scratch (25088 x 288 x 1152 217 -> 180, 204800 x 33 x 1287 569 -> 358);
+//     at less padding up to 1.34.
 constexpr int kF32Large = 47, kF32Small = 28, k16Narrow = 23, k16TwoGroups = 47, k16OneGroup = 9;
 
 int exchanged(int dtype, int id, int64_t M, int64_t N, int64_t K, int64_t batch, int tA, int tB, const void *A, int64_t lda,
-              const void *B, int64_t ldb, Workspace w) {
+              const void *B, int64_t ldb) {
     if (batch != 1 || M <= 0 || N <= 0 || K <= 0 || M > (1 << 28) || N > (1 << 28) || !builtin_tree(dtype)) return id;
     std::call_once(g_once, init_tables);
     auto tiles = [&](int64_t e) { return ((M + e - 1) / e) * ((N + e - 1) / e); };
     const int64_t t128 = tiles(128);
     if (dtype == KS_F32) {
         if (id != kF32Large || g_f32[kF32Small] == nullptr) return id;
-        const double steps = (double)((K + 31) / 32);
-        const bool balanced = t128 % 512 != 0 && t128 < 2048 && K >= 1024 && w.ptr &&
-                              w.bytes >= sk_workspace_bytes(&kF32[kF32Large]) && aligned(w.ptr, 16);
-        const double large = balanced ? (double)t128 * steps / 512 * 4.3 + 20 : (double)((t128 + 511) / 512) * steps * 4.14 + 8;
-        const double small = (double)((tiles(64) + 255) / 256) * (double)K * 0.0181 + 8;
-        return 1.03 * small < large ? kF32Small : id;
+        const int64_t t64 = tiles(64), r64 = (t64 + 255) / 256, r128 = 4 * ((t128 + 255) / 256);
+        const bool small = K < 1024 ? 7 * r64 <= 6 * r128 || (K <= 128 && N % 128 != 0)
+                                    : 4 * r64 <= 3 * r128 && 6 * t64 <= 20 * t128;
+        return small ? kF32Small : id;
     }
     if (K % 64 != 0 || !dma_operands(tA == 0, tB == 1, M, N, K, A, lda, B, ldb, 1, 0, 0)) return id;
     if (id == k16Narrow && K % 128 == 0 && K >= 2048 && t128 > 128 && t128 <= 256 && g_bf16[k16TwoGroups] != nullptr)
@@ -841,7 +844,7 @@ int remainder_member(int dtype, int64_t M, int64_t N, int64_t K, int64_t batch, 
 // member of a selecting entry point: the tree's choice, as exchanged() has it
 #define KS_SELECT(dtype, w)                                                                                       \
     ks::exchanged(dtype, select_checked(dtype, M, N, K, batch, transA, transB, w), M, N, K, batch, transA, transB, A, lda, \
-                  B, ldb, w)
+                  B, ldb)
 
 extern "C" int ks_gemm_f32_with_kernel(int kernel_id, int transA, int transB, int64_t M, int64_t N,
                                        int64_t K, float alpha, const float *A, int64_t lda,
