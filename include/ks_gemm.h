@@ -275,8 +275,11 @@ int ks_kernel_info(int dtype, int kernel_id, ks_kernel_info_t *out);   /* out: h
 
 /* ---------------------------------------------------------------- selection (Section IV)
  * Walks the deployed decision tree for `dtype` with integer comparisons only and returns the
- * chosen kernel id (>= 0), or a negative status for a bad flag / negative size.  Pure, total
- * over non-negative sizes, thread-safe, allocation-free, no device access. */
+ * chosen kernel id (>= 0), or a negative status for a bad flag / negative size.  Beside the tree
+ * compiled into the library stand three rules on the same sizes, for pairs of members between which
+ * the count of tiles per compute unit decides (what the tree alone says is ks_get_selector's); a tree
+ * set with ks_set_selector is followed as it is.  Pure, total over non-negative sizes, thread-safe,
+ * allocation-free, no device access. */
 int ks_select(int dtype, int64_t M, int64_t N, int64_t K, int64_t batch, int transA, int transB);
 /* The integer features ks_select compares (out: host array of KS_NUM_FEATURES). */
 int ks_features(int64_t M, int64_t N, int64_t K, int64_t batch, int transA, int transB,
@@ -284,7 +287,7 @@ int ks_features(int64_t M, int64_t N, int64_t K, int64_t batch, int transA, int 
 /* Replace the deployed tree of `dtype` by a copy of nodes[0 .. n-1] (host; node 0 is the root).
  * The tree is validated (child indices in range and acyclic by construction: children must have
  * larger indices than their parent; leaf values must be kernel ids).  n == 0 restores the tree
- * compiled into the library.  Not thread-safe against concurrent ks_select / ks_gemm calls. */
+ * compiled into the library and its rules.  Not thread-safe against concurrent ks_select / ks_gemm calls. */
 int ks_set_selector(int dtype, const ks_tree_node_t *nodes, int n);
 /* Copy the deployed tree out (host).  Returns the node count, or a negative status if cap is
  * too small. */

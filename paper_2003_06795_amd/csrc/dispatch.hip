@@ -763,7 +763,7 @@ extern "C" size_t ks_workspace_bytes_needed(int dtype, int kernel_id, int64_t M,
     transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, batch, strideA, strideB, strideC, \
         static_cast<hipStream_t>(stream)
 
-// Kernel for the selecting entry points: the tree's choice, unless that is a split-K instance and
+// Kernel for the selecting entry points: the choice of ks_select, unless that is a split-K instance and
 // the registered workspace cannot hold its partial sums; then the instance with the same tiles
 // and no split is used instead, so that a caller who never registers a workspace is still served.
 static int select_checked(int dtype, int64_t M, int64_t N, int64_t K, int64_t batch, int tA, int tB,
@@ -789,48 +789,6 @@ static int select_checked(int dtype, int64_t M, int64_t N, int64_t K, int64_t ba
 
 namespace ks {
 namespace {
-// Members of the built-in trees that a launch count decides between: the trees split on sizes, and what a
-// call costs here steps with its tiles per compute unit, which no threshold of theirs can follow.  Only
-// these exchanges are made, each where both sides were timed (operands rotated through three buffers):
-//
-// 16-bit 23 (128 x 64 tiles) -> 47 (two groups of waves on 128 x 128) for one round of 128 x 128 tiles that
-//   fills over half the device, whole K-steps and K >= 2048: 2048^3 NT 26.1 -> 23.2 us, 1024 x 4096 x 4096 TN
-//   46.1 -> 40.4, 1408 x 2944 x 2560 NT 30.4 -> 25.3; level at K = 1664, behind below 1024.  Off the direct-to-LDS
-//   path 23 stays (1063 x 5269 x 2193 NT 68 us against 80).
-// 16-bit 47 -> 9 (same tile, one group) where K ends in half a K-step and neither is split: the two-group form
-//   of that pays branches in every memory slot (2560 x 1280 x 1728 NT 20.5 -> 19.2 us, 1216 x 2880 x 3520 NN 35.7 ->
-//   34.8, 1024 x 3712 x 5056 TN 52.6 -> 51.1).
-// fp32 47 (128 x 128 tiles) -> 28 (64 x 64).  A unit works through its tiles one after the other, so what counts
-//   is the fullest unit: r128 quarters of large tiles against r64 small ones.
-//   K < 1024, r64 <= 6/7 r128: 52 problems at 0.82 of the time (6272 x 704 x 576 79 -> 57 us, 3312 x 888 x 320 30 -> 24),
-//     one of them slower (1.006); from 7/8 on also 1.10.
-//   K <= 128 and a ragged last column of large tiles, which the pass over C decides: 60 more at 0.87 (17956 x 1067 x 15
-//     29 -> 22 us, 14400 x 1147 x 45 38 -> 29), four of them slower by up to 1.056; with whole columns 1.10.
-//   K >= 1024, where the large tiles may be shared out evenly among all units: only if padding to them costs a
-//     fifth as well.  25 problems at 0.78, 0.73 without scratch (25088 x 288 x 1152 217 -> 180, 204800 x 33 x 1287 569 -> 358);
-//     at less padding up to 1.34.
-constexpr int kF32Large = 47, kF32Small = 28, k16Narrow = 23, k16TwoGroups = 47, k16OneGroup = 9;
-
-int exchanged(int dtype, int id, int64_t M, int64_t N, int64_t K, int64_t batch, int tA, int tB, const void *A, int64_t lda,
-              const void *B, int64_t ldb) {
-    if (batch != 1 || M <= 0 || N <= 0 || K <= 0 || M > (1 << 28) || N > (1 << 28) || !builtin_tree(dtype)) return id;
-    std::call_once(g_once, init_tables);
-    auto tiles = [&](int64_t e) { return ((M + e - 1) / e) * ((N + e - 1) / e); };
-    const int64_t t128 = tiles(128);
-    if (dtype == KS_F32) {
-        if (id != kF32Large || g_f32[kF32Small] == nullptr) return id;
-        const int64_t t64 = tiles(64), r64 = (t64 + 255) / 256, r128 = 4 * ((t128 + 255) / 256);
-        const bool small = K < 1024 ? 7 * r64 <= 6 * r128 || (K <= 128 && N % 128 != 0)
-                                    : 4 * r64 <= 3 * r128 && 6 * t64 <= 20 * t128;
-        return small ? kF32Small : id;
-    }
-    if (K % 64 != 0 || !dma_operands(tA == 0, tB == 1, M, N, K, A, lda, B, ldb, 1, 0, 0)) return id;
-    if (id == k16Narrow && K % 128 == 0 && K >= 2048 && t128 > 128 && t128 <= 256 && g_bf16[k16TwoGroups] != nullptr)
-        return k16TwoGroups;
-    if (id == k16TwoGroups && K % 128 != 0 && t128 > 128 && t128 <= 256 && g_bf16[k16OneGroup] != nullptr) return k16OneGroup;
-    return id;
-}
-
 // member that runs the remainder of a K range that is not a whole number of K-steps (run_ws)
 int remainder_member(int dtype, int64_t M, int64_t N, int64_t K, int64_t batch, int tA, int tB, Workspace w) {
     const int id = select_checked(dtype, M, N, K, batch, tA, tB, w);
@@ -840,11 +798,6 @@ int remainder_member(int dtype, int64_t M, int64_t N, int64_t K, int64_t batch, 
 }
 }  // namespace
 }  // namespace ks
-
-// member of a selecting entry point: the tree's choice, as exchanged() has it
-#define KS_SELECT(dtype, w)                                                                                       \
-    ks::exchanged(dtype, select_checked(dtype, M, N, K, batch, transA, transB, w), M, N, K, batch, transA, transB, A, lda, \
-                  B, ldb)
 
 extern "C" int ks_gemm_f32_with_kernel(int kernel_id, int transA, int transB, int64_t M, int64_t N,
                                        int64_t K, float alpha, const float *A, int64_t lda,
@@ -866,7 +819,7 @@ extern "C" int ks_gemm_f32(int transA, int transB, int64_t M, int64_t N, int64_t
                            const float *A, int64_t lda, const float *B, int64_t ldb, float beta,
                            float *C, int64_t ldc, int64_t batch, int64_t strideA, int64_t strideB,
                            int64_t strideC, void *stream) {
-    const int id = KS_SELECT(KS_F32, registered_ws());
+    const int id = select_checked(KS_F32, M, N, K, batch, transA, transB);
     if (id < 0) return id;
     return run(KS_F32, id, KS_GEMM_PASS);
 }
@@ -875,7 +828,7 @@ extern "C" int ks_gemm_bf16(int transA, int transB, int64_t M, int64_t N, int64_
                             const uint16_t *A, int64_t lda, const uint16_t *B, int64_t ldb, float beta,
                             float *C, int64_t ldc, int64_t batch, int64_t strideA, int64_t strideB,
                             int64_t strideC, void *stream) {
-    const int id = KS_SELECT(KS_BF16, registered_ws());
+    const int id = select_checked(KS_BF16, M, N, K, batch, transA, transB);
     if (id < 0) return id;
     return run(KS_BF16, id, KS_GEMM_PASS);
 }
@@ -884,7 +837,7 @@ extern "C" int ks_gemm_f16(int transA, int transB, int64_t M, int64_t N, int64_t
                            const uint16_t *A, int64_t lda, const uint16_t *B, int64_t ldb, float beta,
                            float *C, int64_t ldc, int64_t batch, int64_t strideA, int64_t strideB,
                            int64_t strideC, void *stream) {
-    const int id = KS_SELECT(KS_F16, registered_ws());
+    const int id = select_checked(KS_F16, M, N, K, batch, transA, transB);
     if (id < 0) return id;
     return run(KS_F16, id, KS_GEMM_PASS);
 }
@@ -904,7 +857,7 @@ extern "C" int ks_gemm_bias(int dtype, int kernel_id, int transA, int transB, in
                             void *stream) {
     if (dtype != KS_F32 && dtype != KS_BF16 && dtype != KS_F16) return KS_ERR_INVALID_ARG;
     if (kernel_id < 0) {
-        kernel_id = KS_SELECT(dtype, registered_ws());
+        kernel_id = select_checked(dtype, M, N, K, batch, transA, transB);
         if (kernel_id < 0) return kernel_id;
     }
     return run(dtype, kernel_id, KS_GEMM_PASS, bias);
@@ -917,7 +870,7 @@ extern "C" int ks_gemm_out_bf16(int dtype, int kernel_id, int transA, int transB
                                 void *stream) {
     if (dtype != KS_F32 && dtype != KS_BF16 && dtype != KS_F16) return KS_ERR_INVALID_ARG;
     if (kernel_id < 0) {
-        kernel_id = KS_SELECT(dtype, registered_ws());
+        kernel_id = select_checked(dtype, M, N, K, batch, transA, transB);
         if (kernel_id < 0) return kernel_id;
     }
     float *C = reinterpret_cast<float *>(C16);        // element size is carried by the out16 flag
@@ -964,7 +917,7 @@ extern "C" int ks_gemm_static_scratch(int dtype, int kernel_id, int transA, int 
     const int rc = static_scratch(&w);
     if (rc != KS_OK) return rc;
     if (kernel_id < 0) {
-        kernel_id = KS_SELECT(dtype, w);
+        kernel_id = select_checked(dtype, M, N, K, batch, transA, transB, w);
         if (kernel_id < 0) return kernel_id;
     }
     return run_ws(w, dtype, kernel_id, KS_GEMM_PASS);
@@ -980,7 +933,7 @@ extern "C" int ks_gemm_with_workspace(int dtype, int kernel_id, int transA, int 
     if (reinterpret_cast<uintptr_t>(workspace_device) % sizeof(float)) return KS_ERR_INVALID_ARG;
     const Workspace w{workspace_device, workspace_bytes};
     if (kernel_id < 0) {
-        kernel_id = KS_SELECT(dtype, w);
+        kernel_id = select_checked(dtype, M, N, K, batch, transA, transB, w);
         if (kernel_id < 0) return kernel_id;
     }
     return run_ws(w, dtype, kernel_id, KS_GEMM_PASS);
@@ -993,7 +946,7 @@ extern "C" int ks_gemm_plan(int dtype, int kernel_id, int transA, int transB, in
     if (dtype != KS_F32 && dtype != KS_BF16 && dtype != KS_F16) return KS_ERR_INVALID_ARG;
     if (!out) return KS_ERR_INVALID_ARG;
     if (kernel_id < 0) {
-        kernel_id = KS_SELECT(dtype, registered_ws());
+        kernel_id = select_checked(dtype, M, N, K, batch, transA, transB);
         if (kernel_id < 0) return kernel_id;
     }
     void *stream = nullptr;
@@ -1008,7 +961,7 @@ extern "C" int ks_time_gemm(int dtype, int kernel_id, int transA, int transB, in
     if (dtype != KS_F32 && dtype != KS_BF16 && dtype != KS_F16) return KS_ERR_INVALID_ARG;
     if (iters < 1 || iters > 1024 || reps < 1 || warmup < 0 || !ms_out) return KS_ERR_INVALID_ARG;
     if (kernel_id < 0) {
-        kernel_id = KS_SELECT(dtype, registered_ws());
+        kernel_id = select_checked(dtype, M, N, K, batch, transA, transB);
         if (kernel_id < 0) return kernel_id;
     }
     hipStream_t s = static_cast<hipStream_t>(stream);

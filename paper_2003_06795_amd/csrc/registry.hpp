@@ -35,9 +35,6 @@ constexpr bool compiled_f32(int) { return true; }
 constexpr bool compiled_bf16(int) { return true; }
 #endif
 
-// whether selection runs on the tree compiled into the library (and not on one the caller has set)
-bool builtin_tree(int dtype);
-
 constexpr int kNumF32 = 64;
 constexpr int kNumBf16 = 48;
 constexpr int kShards = 16;

@@ -1,10 +1,12 @@
-// Runtime kernel selection (paper Section IV): a decision tree deployed as integer comparisons.
+// Runtime kernel selection (paper Section IV): a decision tree deployed as integer comparisons, and beside
+// the built-in trees the rules for what a count of tiles per compute unit decides.
 // Host only; no device access, no allocation.
 #include "../../include/ks_gemm.h"
 
 #include <limits.h>
 #include <string.h>
 
+#include "kept_set.inc"
 #include "selector_table.inc"
 
 namespace {
@@ -39,13 +41,77 @@ int64_t sat_mul(int64_t a, int64_t b) {
     return a * b;
 }
 
-}  // namespace
-
-namespace ks {
-bool builtin_tree(int dtype) {
-    return !g_tree[dtype == KS_F16 ? KS_BF16 : dtype].custom;
+// ---- the built-in trees and the count of tiles per compute unit --------------------------------
+// The trees split on sizes; what a call costs steps with its tiles per compute unit, which no threshold of
+// theirs can follow.  Where both sides were timed (operands rotated through three buffers) the choice is
+// corrected, from the sizes alone: every caller of ks_select and every selecting entry point gets the same
+// member, whatever the alignment of its operands and its scratch.  A caller's own tree is followed as it is.
+struct Tile {
+    int id, bm, bn, bk;
+};
+constexpr Tile kTilesF32[] = {
+#define KS_F32_INSTANCE(id, CORE, BM, BN, BK, P1, P2, SPLITK) {id, BM, BN, BK},
+#include "instances.def"
+#undef KS_F32_INSTANCE
+};
+constexpr Tile kTiles16[] = {
+#define KS_BF16_INSTANCE(id, F, BM, BN, BK, WM, WN, STAGES, SPLITK) {id, BM, BN, BK},
+#include "instances.def"
+#undef KS_BF16_INSTANCE
+};
+template <int N>
+constexpr bool tile_is(const Tile (&t)[N], int id, int bm, int bn, int bk) {
+    return t[id].id == id && t[id].bm == bm && t[id].bn == bn && t[id].bk == bk;
 }
-}  // namespace ks
+// a member that a pruned library does not hold is not named by the full one either
+constexpr int kKeptF32[] = KS_KEPT_F32;
+constexpr int kKept16[] = KS_KEPT_BF16;
+template <int N>
+constexpr bool kept(const int (&list)[N], int id) {
+    for (int i = 0; i < N; ++i)
+        if (list[i] == id) return true;
+    return false;
+}
+constexpr int kF32Large = 47, kF32Small = 28, k16Narrow = 23, k16TwoGroups = 47, k16OneGroup = 9;
+static_assert(tile_is(kTilesF32, kF32Large, 128, 128, 32) && tile_is(kTilesF32, kF32Small, 64, 64, 16) &&
+                  tile_is(kTiles16, k16Narrow, 128, 64, 64) && tile_is(kTiles16, k16TwoGroups, 128, 128, 128) &&
+                  tile_is(kTiles16, k16OneGroup, 128, 128, 128),
+              "the rules below count the tiles of these members");
+
+// fp32 128 x 128 -> 64 x 64.  A unit works through its tiles one after the other, so what counts is the fullest
+//   unit: r128 quarters of large tiles against r64 small ones.
+//   K < 1024, r64 <= 6/7 r128: 52 problems at 0.82 of the time (6272 x 704 x 576 79 -> 57 us, 3312 x 888 x 320 30 -> 24),
+//     one of them slower (1.006); from 7/8 on also 1.10.
+//   K <= 128 and a ragged last column of large tiles, which the pass over C decides: 60 more at 0.87 (17956 x 1067 x 15
+//     29 -> 22 us, 14400 x 1147 x 45 38 -> 29), four of them slower by up to 1.056; with whole columns 1.10.
+//   K >= 1024, where the large tiles may be shared out evenly among all units: only if padding to them costs a
+//     fifth as well.  25 problems at 0.78, 0.73 without scratch (25088 x 288 x 1152 217 -> 180, 204800 x 33 x 1287 569 -> 358); at
+//     less padding up to 1.34.
+// 16-bit 128 x 64 -> 128 x 128 in two groups of waves: one round of large tiles that fills over half the device, whole
+//   K-steps, K >= 2048.  2048^3 NT 27.8 -> 22.4 us, 1024 x 4096 x 4096 TN 46.4 -> 40.4; 22 problems at 0.86; rows of no
+//   alignment 0.94 (2001 x 1999 x 3072 NT 35 -> 27, TT level); level at K = 1664, behind below 1024.
+// 16-bit two groups of waves -> one, same tile: the last K-step half a one, which costs the two-group form branches
+//   in every memory slot.  21 problems at 0.94 (2560 x 1280 x 1728 NT 20.5 -> 19.2 us), 0.97 where nothing is
+//   aligned; not with both operands K-contiguous and a long K (1600 x 1216 x 5824 NT 45.7 -> 49.6).
+int by_tiles_per_unit(int dtype, int id, int64_t M, int64_t N, int64_t K, int64_t batch, int transA, int transB) {
+    if (batch != 1 || M <= 0 || N <= 0 || K <= 0 || M > (1 << 28) || N > (1 << 28)) return id;
+    auto tiles = [&](int64_t e) { return ((M + e - 1) / e) * ((N + e - 1) / e); };
+    const int64_t t128 = tiles(128);
+    if (dtype == KS_F32) {
+        if (id != kF32Large || !kept(kKeptF32, kF32Small)) return id;
+        const int64_t t64 = tiles(64), r64 = (t64 + 255) / 256, r128 = 4 * ((t128 + 255) / 256);
+        const bool small = K < 1024 ? 7 * r64 <= 6 * r128 || (K <= 128 && N % 128 != 0)
+                                    : 4 * r64 <= 3 * r128 && 6 * t64 <= 20 * t128;
+        return small ? kF32Small : id;
+    }
+    if (t128 <= 128 || t128 > 256) return id;
+    if (id == k16Narrow && K % 128 == 0 && K >= 2048 && kept(kKept16, k16TwoGroups)) return k16TwoGroups;
+    if (id == k16TwoGroups && K % 128 == 64 && (transA != 0 || transB == 0 || K <= 2048) && kept(kKept16, k16OneGroup))
+        return k16OneGroup;
+    return id;
+}
+
+}  // namespace
 
 extern "C" int ks_features(int64_t M, int64_t N, int64_t K, int64_t batch, int transA, int transB,
                            int64_t *out) {
@@ -76,11 +142,10 @@ extern "C" int ks_select(int dtype, int64_t M, int64_t N, int64_t K, int64_t bat
     const ks_tree_node_t *t = active(dtype, &n);
     int i = 0;
     // children always have larger indices than their parent, so the walk ends within n steps
-    for (int step = 0; step < n; ++step) {
-        if (t[i].feature < 0) return t[i].value;
+    for (int step = 0; step < n && t[i].feature >= 0; ++step)
         i = f[t[i].feature] <= t[i].threshold ? t[i].left : t[i].right;
-    }
-    return t[i].feature < 0 ? t[i].value : KS_ERR_INVALID_ARG;
+    if (t[i].feature >= 0) return KS_ERR_INVALID_ARG;
+    return g_tree[dtype].custom ? t[i].value : by_tiles_per_unit(dtype, t[i].value, M, N, K, batch, transA, transB);
 }
 
 extern "C" int ks_set_selector(int dtype, const ks_tree_node_t *nodes, int n) {
