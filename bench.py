@@ -91,8 +91,10 @@ def kernel_symbol(ks, dt, plan, tA, tB, M, N, K):
         stages = ki["lds_bytes"] // (ki["bk"] * (ki["bm"] + ki["bn"]) * 2)
         return "gemm_bf16_dma_kernel<%d, %d, %d, %d, %d, %d, %d, %s, %s, %s, false, %s>" % (
             f, ki["bm"], ki["bn"], ki["bk"], ki["wm"], ki["wn"], stages, b(split), b(akc), b(bkc), b(K % ki["bk"] != 0))
-    return "gemm_bf16_kernel<%d, %d, %d, %d, %d, %d, %s, %s, %s, false>" % (
-        f, ki["bm"], ki["bn"], ki["bk"], ki["wm"], ki["wn"], b(split), b(akc), b(bkc))
+    wave_k = min(K, -(-(-(-K // ki["bk"])) // plan["split_k"]) * ki["bk"])
+    return "gemm_bf16_kernel<%d, %d, %d, %d, %d, %d, %s, %s, %s, false, %s>" % (
+        f, ki["bm"], ki["bn"], ki["bk"], ki["wm"], ki["wn"], b(split), b(akc), b(bkc),
+        b(akc and bkc and ki["bk"] == 128 and K % 8 == 0 and K % 128 and 128 < wave_k < 512))
 
 
 def build_rows(workload):

@@ -567,7 +567,9 @@ int run_ws(Workspace wsp, int dtype, int id, int transA, int transB, int64_t M, 
                                    : oneTile && (akc ? K : M) % 4 == 0 && (bkc ? K : N) % 4 == 0 &&
                                          (waveK <= 8 * stepK || f32_units_at_any_k(d->core, d->bm, d->bn, d->bk, group, d->kw));
     const bool elements = oneTile && waveK <= f32_element_steps(d->core, d->bm, d->bn, d->bk, group, d->kw) * stepK;
-    const int variant = (akc ? 4 : 0) + (bkc ? 2 : 0) + (units ? 1 : 0) + (elements ? 32 : 0) + splitBit;
+    // and of the register-staged path of the 16-bit ones (gemm_bf16.hpp)
+    const bool chunks = akc && bkc && d->bk == 128 && K % 8 == 0 && K % 128 != 0 && waveK > 128 && waveK < 512;
+    const int variant = (akc ? 4 : 0) + (bkc ? 2 : 0) + ((dtype == KS_F32 ? units : chunks) ? 1 : 0) + (elements ? 32 : 0) + splitBit;
 
     // bf16 fast path: operand tiles go global -> LDS directly.
     const int f16Bit = dtype == KS_F16 ? 16 : 0;     // same 16-bit members, binary16 MFMA

@@ -140,6 +140,8 @@ __device__ __forceinline__ uintx4 load16_any(const uint16_t *src) {
 // rows of C that do not exist).  Rows beyond `limit` are clamped to valid ones for the same reason.
 // load_edge() is for the steps that are left, at most one for all but very narrow operands: it
 // reads inside the matrix only, and k beyond the end read as zero.
+// load_units() serves any step of a K-contiguous operand whose K is a multiple of eight, with a test per chunk
+// (the UNITS form of the kernel).
 template <int ROWS, int BK, int NT, bool KC, int F>
 struct Bf16Staging {
     static constexpr int CPR = (KC ? BK : ROWS) / 8;         // chunks along the contiguous direction
@@ -167,6 +169,17 @@ struct Bf16Staging {
 #pragma unroll
         for (int j = 0; j < PER; ++j)
             if (has(tid, j)) reg[j] = load16_any(src[j] + advance);
+    }
+
+    // kLeft: k of the step that exist
+    __device__ __forceinline__ void load_units(uintx4 (&reg)[PER], long long advance, int kLeft, int tid) const {
+        static_assert(KC, "rows of a row-contiguous operand end anywhere");
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            uintx4 v = {0u, 0u, 0u, 0u};
+            if (has(tid, j) && (tid + j * NT) % CPR * 8 < kLeft) v = load16_any(src[j] + advance);
+            reg[j] = v;
+        }
     }
 
     __device__ __forceinline__ static void load_edge(uintx4 (&reg)[PER], const uint16_t *base, long long ld, int row0,
@@ -213,14 +226,21 @@ struct Bf16Staging {
 // element-wise loads (two bytes per lane, transposed in registers where row-contiguous) that this form
 // replaced: fp16 1000 x 777 x 1509 NN 116 -> 19.6 us, bf16 5120 x 6528 x 2560 NT with odd rows 1312 ->
 // 303 us (0.57 PFLOP/s), 4959 x 2007 x 1325 TN 713 -> 70 us.
-template <int F, int BM, int BN, int BK, int WM, int WN, bool SPLIT, bool AKC, bool BKC, bool F16 = false>
+//
+// UNITS (both operands K-contiguous, K a multiple of eight): one loop of one kind of step, the next one in
+// flight.  With one to three whole K-steps of 128 before a partial one the other form pays for the code of
+// its unrolled loop and for a last step whose loads nothing hides: against the predicated sixteen-byte loads that
+// aligned NT operands had before 64 x 16 tiles 1.08, with this form 1.03; 64 x 64 1.07 and 1.015; 128 x 128 on eight
+// waves 1.05 and 1.02.  From four steps on, and with steps of 64 (1.02 at one whole step), the other one stays.
+template <int F, int BM, int BN, int BK, int WM, int WN, bool SPLIT, bool AKC, bool BKC, bool F16 = false,
+          bool UNITS = false>
 __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) void gemm_bf16_kernel(const GemmParams p) {
     constexpr int NT = 64 * (BM / WM) * (BN / WN);
     constexpr int FM = WM / F, FN = WN / F;
     constexpr int KSTEP = F == 32 ? 16 : 32;          // k consumed by one MFMA
     using LoadA = Bf16Staging<BM, BK, NT, AKC, F>;
     using LoadB = Bf16Staging<BN, BK, NT, BKC, F>;
-    constexpr int PF = 4 * (LoadA::PER + LoadB::PER) <= 32 && WM * WN <= 4096 ? 2 : 1;
+    constexpr int PF = !UNITS && 4 * (LoadA::PER + LoadB::PER) <= 32 && WM * WN <= 4096 ? 2 : 1;
     __shared__ __attribute__((aligned(1024))) char As0[BM * BK * 2];
     __shared__ __attribute__((aligned(1024))) char As1[BM * BK * 2];
     __shared__ __attribute__((aligned(1024))) char Bs0[BN * BK * 2];
@@ -241,7 +261,7 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) void gemm_bf16_kernel(c
     // of fewer than seven elements could reach beyond the row after next: it has none.
     const int fullA = AKC ? (kEnd - kBegin) / BK : p.lda < 7 ? 0 : (min(kEnd, p.K - 1) - kBegin) / BK;
     const int fullB = BKC ? (kEnd - kBegin) / BK : p.ldb < 7 ? 0 : (min(kEnd, p.K - 1) - kBegin) / BK;
-    const int full = max(min(fullA, fullB), 0);
+    const int full = UNITS ? nk : max(min(fullA, fullB), 0);
     const long long aStep = AKC ? (long long)BK : BK * p.lda, bStep = BKC ? (long long)BK : BK * p.ldb;
 
     LoadA la;
@@ -263,8 +283,13 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) void gemm_bf16_kernel(c
         }
 
     auto load = [&](int t, uintx4 (&a)[LoadA::PER], uintx4 (&b)[LoadB::PER]) {
-        la.load(a, t * aStep, tid);
-        lb.load(b, t * bStep, tid);
+        if constexpr (UNITS) {
+            la.load_units(a, t * aStep, kEnd - kBegin - t * BK, tid);
+            lb.load_units(b, t * bStep, kEnd - kBegin - t * BK, tid);
+        } else {
+            la.load(a, t * aStep, tid);
+            lb.load(b, t * bStep, tid);
+        }
     };
     auto load_edge = [&](int t, uintx4 (&a)[LoadA::PER], uintx4 (&b)[LoadB::PER]) {
         LoadA::load_edge(a, Ab, p.lda, row0, p.M, kBegin + t * BK, kEnd, tid);
@@ -305,7 +330,22 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) void gemm_bf16_kernel(c
         __syncthreads();
     };
 
-    if (full > 0) {
+    if constexpr (UNITS) {
+        load(0, ra[0], rb[0]);
+        LoadA::store(ra[0], As0, tid);
+        LoadB::store(rb[0], Bs0, tid);
+        __syncthreads();
+        for (int t = 0; t < nk; ++t) {
+            const bool odd = t & 1, more = t + 1 < nk;
+            if (more) load(t + 1, ra[0], rb[0]);
+            compute(odd ? As1 : As0, odd ? Bs1 : Bs0);
+            if (more) {
+                LoadA::store(ra[0], odd ? As0 : As1, tid);
+                LoadB::store(rb[0], odd ? Bs0 : Bs1, tid);
+            }
+            __syncthreads();
+        }
+    } else if (full > 0) {
         load(0, ra[0], rb[0]);
         if (PF > 1 && full > 1) load(1, ra[PF - 1], rb[PF - 1]);
         LoadA::store(ra[0], As0, tid);
@@ -318,7 +358,7 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) void gemm_bf16_kernel(c
     }
     // what is left: as a rule the one K-step that holds the end of K.  Every step above ended with a
     // barrier, so the first stage is free.
-    for (int t = full; t < nk; ++t) {
+    for (int t = full; !UNITS && t < nk; ++t) {
         load_edge(t, ra[0], rb[0]);
         LoadA::store(ra[0], As0, tid);
         LoadB::store(rb[0], Bs0, tid);

@@ -15,18 +15,24 @@ static void launch_bf16_fixed(const GemmParams &p, int grid, int variant, hipStr
     constexpr int NT = 64 * (BM / WM) * (BN / WN);
     const dim3 g = launch_grid(p, grid), b(NT);
     // variant bit 4: the operands are IEEE binary16 instead of bf16
-#define KS_V(A, B)                                                                                        \
-    do {                                                                                                  \
-        if (variant & 16)                                                                                 \
-            hipLaunchKernelGGL((gemm_bf16_kernel<F, BM, BN, BK, WM, WN, SPLIT, A, B, true>), g, b, 0, s, p);  \
-        else                                                                                              \
-            hipLaunchKernelGGL((gemm_bf16_kernel<F, BM, BN, BK, WM, WN, SPLIT, A, B, false>), g, b, 0, s, p); \
+#define KS_V(A, B, U)                                                                                        \
+    do {                                                                                                     \
+        if (variant & 16)                                                                                    \
+            hipLaunchKernelGGL((gemm_bf16_kernel<F, BM, BN, BK, WM, WN, SPLIT, A, B, true, U>), g, b, 0, s, p);  \
+        else                                                                                                 \
+            hipLaunchKernelGGL((gemm_bf16_kernel<F, BM, BN, BK, WM, WN, SPLIT, A, B, false, U>), g, b, 0, s, p); \
     } while (0)
     switch ((variant >> 1) & 3) {
-        case 0: KS_V(false, false); break;
-        case 1: KS_V(false, true); break;
-        case 2: KS_V(true, false); break;
-        default: KS_V(true, true); break;
+        case 0: KS_V(false, false, false); break;
+        case 1: KS_V(false, true, false); break;
+        case 2: KS_V(true, false, false); break;
+        default:                                      // bit 0: K a multiple of eight and few K-steps (dispatch.hip)
+            if constexpr (BK == 128) {
+                if (variant & 1) KS_V(true, true, true);
+                else KS_V(true, true, false);
+            } else
+                KS_V(true, true, false);
+            break;
     }
 #undef KS_V
 }

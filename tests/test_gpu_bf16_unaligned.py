@@ -48,3 +48,21 @@ def test_unaligned_operands_match_the_oracle(gpu, dtype, layout):
             for kid in MEMBERS:
                 err = np.abs(dp.run(kid).astype(np.float64) - ref)
                 assert float(np.max(err)) <= tol, "kernel %d %s: %.3e > %.3e" % (kid, (M, N, K), np.max(err), tol)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+def test_few_k_steps_of_k_contiguous_operands(gpu, dtype):
+    """K a multiple of eight with one to four K-steps of 128, the last one partial: the one-loop form of the members of
+    that K-step and, on both sides of its limits, the other one."""
+    nan = 0x7FC0 if dtype == "bf16" else 0x7E00
+    for s, (M, N, K) in enumerate([(65, 129, 120), (7, 5, 136), (130, 17, 248), (257, 255, 264), (16, 16, 392), (129, 263, 504),
+                                   (66, 130, 520)]):
+        p = wl.make_problem(dtype, 0, 1, M, N, K, batch=1 + s % 2, alpha=1.5, beta=-0.5, seed=96, key=s, dist="normal",
+                            pad=(s % 3, (s + 1) % 4, s % 3))
+        ref, tol = gpu.oracle_full(p), tolerance(p)
+        for buf, ld in ((p.A, p.lda), (p.B, p.ldb)):
+            buf.reshape(-1, ld)[:, K:] = nan
+        dp = gpu.DeviceProblem(p)
+        for kid in (6, 9, 11, 13, 16, 19, 27, 28, 36, 38, 39, 46, 47):
+            err = float(np.max(np.abs(dp.run(kid).astype(np.float64) - ref)))
+            assert err <= tol, "kernel %d %s: %.3e > %.3e" % (kid, (M, N, K), err, tol)
