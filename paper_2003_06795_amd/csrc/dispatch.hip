@@ -555,7 +555,6 @@ int run_ws(Workspace wsp, int dtype, int id, int transA, int transB, int64_t M, 
 
     // contiguous direction: A is K-contiguous when not transposed, B when transposed
     const bool akc = transA == 0, bkc = transB == 1;
-    const bool vec = vector_operands(dtype == KS_F32 ? 4 : 8, akc, bkc, M, N, K, A, lda, B, ldb, batch, strideA, strideB);
     const int splitBit = p.splitK > 1 ? 8 : 0;       // read by instances whose split is chosen per call
     // Load form of the fp32 members: of the LDS-staged ones as described in ks_common.hpp, UNITS up to eight K-steps
     // of a wave in any member (it gains up to four of them); of the register-fed ones (gemm_f32_direct.hpp) by K alone.
@@ -592,7 +591,8 @@ int run_ws(Workspace wsp, int dtype, int id, int transA, int transB, int64_t M, 
     if (planOnly) {
         planOnly->tail_split = (int32_t)tailS;
         planOnly->split_k = p.splitK;
-        planOnly->vector_loads = vec ? 1 : 0;
+        planOnly->vector_loads =
+            vector_operands(dtype == KS_F32 ? 4 : 8, akc, bkc, M, N, K, A, lda, B, ldb, batch, strideA, strideB) ? 1 : 0;
         planOnly->grid_3d = p.grid3d;
         planOnly->tiles_per_workgroup = p.tilesPerWG;
         planOnly->workgroups = tailS ? mainGrid + tailTiles * tailS : grid64;
