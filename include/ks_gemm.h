@@ -243,8 +243,9 @@ typedef struct {
     int32_t tail_split;           /* > 0: hybrid launch of a 16-bit member (ks_set_tail_split): the tiles of the
                                      last, partly filled round of work-groups run in this many K partitions
                                      (three kernels: whole tiles, partitioned tiles, their reduction) */
-    int32_t k_remainder;          /* > 0 (16-bit operands only): K is not a whole number of the member's K-steps;
-                                     the last k_remainder of K run first through the member's general kernel
+    int32_t k_remainder;          /* > 0 (16-bit operands only): K is not a whole number of the member's K-steps
+                                     (of half ones for a K-step of 128: a half at the end needs no cut); the
+                                     last k_remainder of K run first through the member's general kernel
                                      (applying alpha, beta and the bias), then the whole K-steps run on the
                                      direct-to-LDS path with beta = 1, which the other fields describe */
 } ks_launch_plan_t;
@@ -295,8 +296,8 @@ int ks_get_selector(int dtype, ks_tree_node_t *nodes, int cap);
 
 /* The bf16 instantiations have two code paths with the same tiles: a generic one (any alignment,
  * any K) and a direct-to-LDS one used when operands are 16-byte aligned, leading dimensions and
- * contiguous extents are multiples of 8 and K is a multiple of the K-step.  When only the last
- * condition fails (K a multiple of 8 and at least four K-steps, output in fp32; with both operands
+ * contiguous extents are multiples of 8 and K is a multiple of the K-step, or of 64 where that is 128
+ * (the last K-step is then half a one).  When only the last condition fails (K a multiple of 8 and at least four K-steps, output in fp32; with both operands
  * K-contiguous, where the generic path is at its best, only for outputs of 2^24 entries or more), the call runs as
  * two launches: the remainder of K beyond the whole K-steps through the generic path first, with
  * alpha, beta and the bias, then the whole K-steps through the direct-to-LDS path with beta = 1
