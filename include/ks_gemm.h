@@ -34,7 +34,8 @@
  *     stream, or ordered by the caller); ks_gemm_with_workspace takes the
  *     scratch per call and has no such limit.  ks_set_workspace,
  *     ks_set_fast_path, ks_set_tiles_per_workgroup, ks_set_balanced_groups,
- *     ks_set_tail_split, ks_set_split_partitions and ks_set_selector are not thread-safe: they change process-wide settings
+ *     ks_set_tail_split, ks_set_split_partitions, ks_set_operand_copies
+ *     and ks_set_selector are not thread-safe: they change process-wide settings
  *     that the compute entry points read.  ks_time_gemm keeps its events per
  *     host thread.  The library acts on the calling thread's current HIP device
  *     and never changes it.
@@ -213,8 +214,8 @@ int ks_gemm_static_scratch(int dtype, int kernel_id, int transA, int transB, int
 /* The same GEMM with the scratch passed per call instead of registered: ks_gemm_*_with_kernel
  * (kernel_id >= 0) or ks_gemm_* (kernel_id < 0, with the same fallback to the split_k == 1 twin when
  * the scratch is too small) using `workspace_device` (device pointer, at least 4-byte aligned; may
- * be NULL with workspace_bytes == 0) for split-K partial sums and for the divided tiles of the
- * balanced persistent form.  The registered workspace is neither read nor needed, so GEMMs on
+ * be NULL with workspace_bytes == 0) for split-K partial sums, for the divided tiles of the
+ * balanced persistent form and for copies of 16-bit operands (ks_set_operand_copies).  The registered workspace is neither read nor needed, so GEMMs on
  * different streams or host threads that each bring their own scratch may be in flight together
  * (Section II-A's tuner times one cell at a time; a serving process does not).  Needs what
  * ks_workspace_bytes_needed reports for the member; errors as for ks_gemm_*. */
@@ -232,8 +233,9 @@ int ks_gemm_with_workspace(int dtype, int kernel_id, int transA, int transB, int
 typedef struct {
     int32_t kernel_id;            /* the member that runs (after selection and the no-workspace fallback) */
     int32_t split_k;              /* K partitions taken; > 1 means partial-sum kernel + reduction pass */
-    int32_t path;                 /* 0: the member's general kernel; 1: direct-to-LDS 16-bit kernel;
-                                     2: direct-to-LDS kernel in its two-groups-of-waves form */
+    int32_t path;                 /* 0: the member's general kernel, or aligned copies of the operands
+                                     (ks_set_operand_copies); 1: direct-to-LDS 16-bit kernel on the operands as they
+                                     are; 2: the same in its two-groups-of-waves form */
     int32_t vector_loads;         /* 16-byte global accesses are legal for these operands */
     int32_t grid_3d;              /* launched (tilesN, tilesM, batch * split_k) instead of one-dimensional */
     int32_t tiles_per_workgroup;  /* > 1: the multi-tile form of the large fp32 members */
@@ -348,6 +350,15 @@ int ks_set_tail_split(int partitions);
  * thread-safe. */
 int ks_set_split_partitions(int partitions);
 
+/* 16-bit operands that the direct-to-LDS path cannot read as they are (ks_set_fast_path), batch 1: one more kernel
+ * copies them to the end of the scratch, rows padded to sixteen bytes and K to whole K-steps (half ones for a K-step
+ * of 128) with zeros, and the member runs on the copies, with the same order along K as on the operands.  Scratch is what
+ * the call brings (ks_gemm_with_workspace: any member) or shares (the registered workspace and the static array: members
+ * with split_k != 1 only; the others never touch them).  mode == -1 (the default) does so where a cost estimate by
+ * flops and bytes says it pays and the scratch holds the copies beside the partial sums of a fixed split; 0 never; 1
+ * wherever it can be done (for testing and tuning).  Not thread-safe. */
+int ks_set_operand_copies(int mode);
+
 /* Measurement aid: copies `bytes` (a multiple of 16; both device pointers 16-byte aligned) with a
  * plain one-read-one-write kernel (ks::copy_kernel).  Hardware traffic counters collected over a
  * profile that contains this launch are scaled by what they report for it. */
@@ -391,7 +402,8 @@ int ks_bf16_ablation(int mode, const uint16_t *A_device, const uint16_t *B_devic
  * Split-K kernels (K partitioned over work-groups, partial sums reduced in a fixed order, no
  * atomics) need split_k * batch * M * N floats of scratch.  The caller registers one device
  * buffer per process (at least 4-byte aligned; 16-byte alignment lets the reduction pass use
- * 16-byte accesses); NULL / 0 unregisters.  Kernels with split_k == 1 never touch it. */
+ * 16-byte accesses); NULL / 0 unregisters.  Kernels with split_k == 1 never touch it; 16-bit ones with
+ * another split_k keep aligned copies of large operands in what is left of it (ks_set_operand_copies). */
 int ks_set_workspace(void *device_ptr, size_t bytes);
 /* Bytes the kernel would like for this output size (for split_k == 0 the most it can use: the
  * partial sums of the largest partition count it may choose, or, for a 16-bit member that launches

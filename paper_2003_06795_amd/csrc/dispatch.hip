@@ -100,6 +100,7 @@ int g_forceGeneric = 0;
 int g_tilesPerWG = 0;        // 0: chosen per call (multi_tiles); n >= 1: forced
 int g_skPerCU = 0;           // 0: the member's own count of work-groups per compute unit; n >= 1: forced
 int g_tailSplit = -1;        // -1: chosen per call (tail_split); 0: never; n >= 2: forced where it can run
+int g_operandCopies = -1;    // -1: chosen per call (copies_pay); 0: never; 1: wherever they can be made
 int g_splitForced = 0;       // 0: per-call split members take auto_split's count; n >= 1: forced (at least two K-steps each)
 void *g_ws = nullptr;
 size_t g_wsBytes = 0;
@@ -357,6 +358,54 @@ __global__ void tail_reduce_kernel(const GemmParams p) {
     }
 }
 
+// One 16-bit operand copied to where the direct-to-LDS path can read it: rows of `cols` elements, `ld` apart, to
+// outRows rows of outChunks x 8 elements without a gap; what the operand does not have reads as zero.
+struct OperandCopy {
+    const uint16_t *src;
+    uint16_t *dst;
+    long long ld;
+    int rows, cols;
+    unsigned outChunks, units;       // units: sixteen-byte chunks of the whole copy
+};
+#define KS_COPY_CHUNKS 4             // chunks per thread, loads of all in flight
+// Bound by memory: every operand byte is read and written once, 27.5 MB of copies in 10.1 us (5.4 TB/s).  Loads are
+// sixteen bytes at any element, which the memory pipe takes at a quarter of its rate where the address is no multiple of
+// four (15 against 59 bytes per clock and compute unit from L2): still above what memory delivers.  A chunk over the
+// end of a row is read whole as well, up to the last ones of the operand; element loads for all of them took 6.7 us
+// instead of 5.3 over 1000 x 777 x 1509.
+__global__ __launch_bounds__(256) void copy_operands_kernel(const OperandCopy a, const OperandCopy b, unsigned groupsA) {
+    const bool second = blockIdx.x >= groupsA;
+    const OperandCopy o = second ? b : a;
+    const unsigned first = (blockIdx.x - (second ? groupsA : 0u)) * (256u * KS_COPY_CHUNKS) + threadIdx.x;
+    const long long lastWhole = (o.rows - 1) * o.ld + o.cols - 8;       // last element from which eight may be read
+    uintx4 v[KS_COPY_CHUNKS];
+#pragma unroll
+    for (int j = 0; j < KS_COPY_CHUNKS; ++j) {
+        const unsigned n = first + j * 256u, row = n / o.outChunks, col = (n - row * o.outChunks) * 8u;
+        const int left = (int)row < o.rows ? o.cols - (int)col : 0;
+        const long long at = (long long)row * o.ld + col;
+        v[j] = uintx4{0u, 0u, 0u, 0u};
+        if (n < o.units && left > 0) {
+            if (at <= lastWhole) {
+                v[j] = load16_any(o.src + at);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    if (e < left) v[j][e >> 1] |= (unsigned)o.src[at + e] << (16 * (e & 1));
+            }
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < KS_COPY_CHUNKS; ++j) {
+        const unsigned n = first + j * 256u, row = n / o.outChunks, col = (n - row * o.outChunks) * 8u;
+        const int left = o.cols - (int)col;
+        // what was read beyond the end of the row is taken out again
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[j][e] &= 2 * e + 2 <= left ? ~0u : 2 * e + 1 == left ? 0xFFFFu : 0u;
+        if (n < o.units) reinterpret_cast<uintx4 *>(o.dst)[n] = v[j];
+    }
+}
+
 int validate(int transA, int transB, int64_t M, int64_t N, int64_t K, const void *A, int64_t lda,
              const void *B, int64_t ldb, const float *C, int64_t ldc, int64_t batch,
              int64_t strideC) {
@@ -400,6 +449,15 @@ bool dma_operands(bool akc, bool bkc, int64_t M, int64_t N, int64_t K, const voi
            lda <= (1LL << 22) && ldb <= (1LL << 22);
 }
 
+// Whether aligned copies of 16-bit operands (`bytes` of them) pay: what the direct-to-LDS path saves grows with the
+// flops, what the copies cost (a launch, then each byte written and read once more, 5.4 TB/s) with the bytes.
+// Of 176 problems of at least 1.5 GFLOP on operands that nothing aligns, 65 lie on this side of the line at 0.775 of the
+// time of the register-staged path (6208 x 1472 x 5312 NN 216 -> 137 us, 1152 x 2624 x 4096 NN 61 -> 47), one of them
+// slower (1.04); with the line at 4 GFLOP it would be 80 at 0.806, eight slower by up to 1.19 (1472 x 1280 x 1088 TT).
+bool copies_pay(int64_t M, int64_t N, int64_t K, size_t bytes) {
+    return 2.0 * (double)M * (double)N * (double)K >= 1e10 + 250.0 * (double)bytes;
+}
+
 // Scratch for split-K partial sums: the registered workspace, or the library's static array.
 struct Workspace {
     void *ptr;
@@ -412,7 +470,8 @@ int remainder_member(int dtype, int64_t M, int64_t N, int64_t K, int64_t batch, 
 int run_ws(Workspace wsp, int dtype, int id, int transA, int transB, int64_t M, int64_t N, int64_t K, float alpha,
            const void *A, int64_t lda, const void *B, int64_t ldb, float beta, float *C, int64_t ldc,
            int64_t batch, int64_t strideA, int64_t strideB, int64_t strideC, hipStream_t stream,
-           const float *bias = nullptr, int out16 = 0, ks_launch_plan_t *planOnly = nullptr) {
+           const float *bias = nullptr, int out16 = 0, ks_launch_plan_t *planOnly = nullptr, bool own = false,
+           bool copied = false) {
     const InstanceDesc *d = desc_of(dtype, id);
     if (!d) return KS_ERR_INVALID_ARG;
     const int rc = validate(transA, transB, M, N, K, A, lda, B, ldb, C, ldc, batch, strideC);
@@ -477,6 +536,49 @@ int run_ws(Workspace wsp, int dtype, int id, int transA, int transB, int64_t M, 
             if (r1 != KS_OK) return r1;
             return run_ws(wsp, dtype, id, transA, transB, M, N, Kh, alpha, A, lda, B, ldb, 1.0f, C, ldc, batch, strideA,
                           strideB, strideC, stream, nullptr, 0, nullptr);
+        }
+    }
+
+    // 16-bit operands that the direct-to-LDS path cannot read as they are: copies that it can (OperandCopy), where the
+    // scratch holds them and they pay.  The member, its order along K and so its bits stay the same.  The
+    // registered workspace is for members that may use it (those with split_k == 1 never do).
+    if (dtype != KS_F32 && !copied && batch == 1 && g_forceGeneric == 0 && g_operandCopies != 0 && wsp.ptr &&
+        (own || d->splitK != 1)) {
+        const bool akc = transA == 0, bkc = transB == 1;
+        const int64_t Kc = (K + dma_k_step(*d) - 1) / dma_k_step(*d) * dma_k_step(*d);
+        auto misfit = [&](const void *x, int64_t ld, bool kc, int64_t extent) {
+            return Kc != K || !aligned(x, 16) || ld % 8 != 0 || ld > (1LL << 22) || (!kc && extent % 8 != 0);
+        };
+        const bool copyA = misfit(A, lda, akc, M), copyB = misfit(B, ldb, bkc, N);
+        auto rows_of = [&](bool kc, int64_t extent) { return kc ? extent : Kc; };
+        auto length_of = [&](bool kc, int64_t extent) { return kc ? Kc : (extent + 7) / 8 * 8; };
+        const int64_t chunksA = copyA ? rows_of(akc, M) * length_of(akc, M) / 8 : 0;
+        const int64_t chunksB = copyB ? rows_of(bkc, N) * length_of(bkc, N) / 8 : 0;
+        const size_t bytes = (size_t)(chunksA + chunksB) * 16;
+        const size_t split = d->splitK > 1 ? (size_t)d->splitK * (size_t)M * (size_t)N * sizeof(float) : 0;
+        const bool reach = length_of(akc, M) <= (1LL << 22) && length_of(bkc, N) <= (1LL << 22);
+        if ((copyA || copyB) && reach && chunksA + chunksB < (1LL << 31) && wsp.bytes >= bytes + split + 16 &&
+            (g_operandCopies > 0 || copies_pay(M, N, K, bytes))) {
+            // at the end of the scratch: partial sums stay at its beginning
+            char *const end = static_cast<char *>(wsp.ptr) + wsp.bytes;
+            char *const at = end - bytes - reinterpret_cast<uintptr_t>(end - bytes) % 16;
+            const Workspace rest{wsp.ptr, (size_t)(at - static_cast<char *>(wsp.ptr))};
+            uint16_t *const toA = reinterpret_cast<uint16_t *>(at), *const toB = toA + chunksA * 8;
+            if (!planOnly) {
+                const OperandCopy a{static_cast<const uint16_t *>(A), toA, lda, (int)(akc ? M : K), (int)(akc ? K : M),
+                                    (unsigned)(length_of(akc, M) / 8), (unsigned)chunksA};
+                const OperandCopy b{static_cast<const uint16_t *>(B), toB, ldb, (int)(bkc ? N : K), (int)(bkc ? K : N),
+                                    (unsigned)(length_of(bkc, N) / 8), (unsigned)chunksB};
+                const int64_t per = 256 * KS_COPY_CHUNKS, groupsA = (chunksA + per - 1) / per, groupsB = (chunksB + per - 1) / per;
+                hipLaunchKernelGGL(copy_operands_kernel, dim3((unsigned)(groupsA + groupsB)), dim3(256), 0, stream, a, b,
+                                   (unsigned)groupsA);
+                if (hipGetLastError() != hipSuccess) return KS_ERR_LAUNCH;
+            }
+            const int rc = run_ws(rest, dtype, id, transA, transB, M, N, Kc, alpha, copyA ? toA : A,
+                                  copyA ? length_of(akc, M) : lda, copyB ? toB : B, copyB ? length_of(bkc, N) : ldb, beta, C,
+                                  ldc, 1, 0, 0, 0, stream, bias, out16, planOnly, own, true);
+            if (rc == KS_OK && planOnly) planOnly->path = planOnly->vector_loads = 0;
+            return rc;
         }
     }
 
@@ -573,8 +675,7 @@ int run_ws(Workspace wsp, int dtype, int id, int transA, int transB, int64_t M, 
 
     // bf16 fast path: operand tiles go global -> LDS directly.
     const int f16Bit = dtype == KS_F16 ? 16 : 0;     // same 16-bit members, binary16 MFMA
-    const bool dma = dtype != KS_F32 && K % dma_k_step(*d) == 0 &&
-                     dma_operands(akc, bkc, M, N, K, A, lda, B, ldb, batch, strideA, strideB);
+    const bool dma = copied || (dtype != KS_F32 && K % dma_k_step(*d) == 0 && dma_operands(akc, bkc, M, N, K, A, lda, B, ldb, batch, strideA, strideB));
     // Hybrid launch of a 16-bit member whose split is chosen per call: whole rounds of work-groups
     // compute their tiles over all of K, the tiles of the last, partly filled round are cut along
     // K (tail_split), and a third kernel adds their partial tiles up.
@@ -726,6 +827,12 @@ extern "C" int ks_set_balanced_groups(int per_cu) {
 extern "C" int ks_set_tail_split(int partitions) {
     if (partitions != -1 && partitions != 0 && (partitions < 2 || partitions > 16)) return KS_ERR_INVALID_ARG;
     g_tailSplit = partitions;
+    return KS_OK;
+}
+
+extern "C" int ks_set_operand_copies(int mode) {
+    if (mode < -1 || mode > 1) return KS_ERR_INVALID_ARG;
+    g_operandCopies = mode;
     return KS_OK;
 }
 
@@ -939,7 +1046,7 @@ extern "C" int ks_gemm_with_workspace(int dtype, int kernel_id, int transA, int 
         kernel_id = select_checked(dtype, M, N, K, batch, transA, transB, w);
         if (kernel_id < 0) return kernel_id;
     }
-    return run_ws(w, dtype, kernel_id, KS_GEMM_PASS);
+    return run_ws(w, dtype, kernel_id, KS_GEMM_PASS, nullptr, 0, nullptr, true);
 }
 
 extern "C" int ks_gemm_plan(int dtype, int kernel_id, int transA, int transB, int64_t M, int64_t N, int64_t K,

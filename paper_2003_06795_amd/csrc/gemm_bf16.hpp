@@ -25,7 +25,6 @@ namespace ks {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
-typedef unsigned int uintx4 __attribute__((ext_vector_type(4)));
 typedef short shortx4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) void *lds_void_ptr;
 
@@ -121,15 +120,6 @@ struct InterleaveHint {
         }
     }
 };
-
-// Sixteen bytes at an address that only the element type aligns.  Global memory takes such accesses at
-// any byte (the target's unaligned access mode), so this is one global_load_dwordx4 like the aligned form.
-struct __attribute__((packed, aligned(2))) AnyUintx4 {
-    uintx4 v;
-};
-__device__ __forceinline__ uintx4 load16_any(const uint16_t *src) {
-    return reinterpret_cast<const AnyUintx4 *>(src)->v;
-}
 
 // Global memory -> registers -> LDS for one operand tile of a K-step, ROWS x BK in the layout above.
 // A thread moves the 16-byte chunks tid, tid + NT, ... of the LDS tile.

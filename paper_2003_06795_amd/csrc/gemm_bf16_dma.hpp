@@ -33,6 +33,9 @@ __device__ __forceinline__ unsigned dma_half_back(int L, long long ld) {
     }
 }
 
+// Extent of a row-contiguous operand: a multiple of eight, or a copy whose rows are padded to one (dispatch.hip).
+__device__ __forceinline__ int dma_extent(int n) { return (n + 7) & ~7; }
+
 // Per-lane source offsets of the direct-to-LDS loads of one operand tile.
 template <int ROWS, int BK, int NW, bool KC, int F = 32>
 struct DmaPlan {
@@ -133,8 +136,8 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) void gemm_bf16_dma_kern
 
     DmaPlan<BM, BK, NW, AKC, F> pa;
     DmaPlan<BN, BK, NW, BKC, F> pb;
-    pa.init(wave, lane, p.lda, row0, p.M);
-    pb.init(wave, lane, p.ldb, col0, p.N);
+    pa.init(wave, lane, p.lda, row0, AKC ? p.M : dma_extent(p.M));
+    pb.init(wave, lane, p.ldb, col0, BKC ? p.N : dma_extent(p.N));
 
     const int subM = (wave / (BN / WN)) * WM, subN = (wave % (BN / WN)) * WN;
 

@@ -139,10 +139,11 @@ __global__ __launch_bounds__(512) void gemm_bf16_pp_kernel(const GemmParams p) {
 
     PpPlan<AKC, HALF, BK, F> pa0, pa1;
     PpPlan<BKC, HALF, BK, F> pb0, pb1;
-    pa0.init(wave, lane, p.lda, lrow0, 0, p.M);
-    pa1.init(wave, lane, p.lda, lrow0, 1, p.M);
-    pb0.init(wave, lane, p.ldb, lcol0, 0, p.N);
-    pb1.init(wave, lane, p.ldb, lcol0, 1, p.N);
+    const int endA = AKC ? p.M : dma_extent(p.M), endB = BKC ? p.N : dma_extent(p.N);
+    pa0.init(wave, lane, p.lda, lrow0, 0, endA);
+    pa1.init(wave, lane, p.lda, lrow0, 1, endA);
+    pb0.init(wave, lane, p.ldb, lcol0, 0, endB);
+    pb1.init(wave, lane, p.ldb, lcol0, 1, endB);
 
     // acc[i][j]: the wave's block of quadrant (i, j)
     floatx4 acc16[2][2][F == 16 ? FM : 1][F == 16 ? FN : 1];

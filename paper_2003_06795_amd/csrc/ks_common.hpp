@@ -15,7 +15,14 @@ struct __attribute__((packed, aligned(4))) AnyFloatx4 {
     floatx4 v;
 };
 __device__ __forceinline__ floatx4 load_float4_any(const void *src) { return static_cast<const AnyFloatx4 *>(src)->v; }
-
+// and eight 16-bit elements
+typedef unsigned int uintx4 __attribute__((ext_vector_type(4)));
+struct __attribute__((packed, aligned(2))) AnyUintx4 {
+    uintx4 v;
+};
+__device__ __forceinline__ uintx4 load16_any(const uint16_t *src) {
+    return reinterpret_cast<const AnyUintx4 *>(src)->v;
+}
 
 struct GemmParams {
     const void *A;
