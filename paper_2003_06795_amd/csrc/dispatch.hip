@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <mutex>
+#include <type_traits>
 
 #include "../../include/ks_gemm.h"
 #include "registry.hpp"
@@ -245,69 +246,104 @@ __global__ void copy_kernel(const floatx4 *src, floatx4 *dst, long long n16) {
         dst[i] = src[i];
 }
 
-// Split-K second pass, four consecutive entries of a row per lane (N, ldc, strideC multiples of 4;
-// ws and C 16-byte aligned).  Each entry is summed in the same order as in the scalar form.
-__global__ void splitk_reduce4_kernel(const float *ws, float *C, long long ldc, long long strideC, int M,
-                                      int N, int batch, int splitK, float alpha, float beta,
-                                      const float *bias) {
-    const long long per = (long long)batch * M * N, per4 = per >> 2;
-    for (long long q = blockIdx.x * (long long)blockDim.x + threadIdx.x; q < per4;
-         q += (long long)gridDim.x * blockDim.x) {
-        const long long i = q << 2;
-        floatx4 acc = *reinterpret_cast<const floatx4 *>(ws + i);
-        // partial sums are fetched eight at a time (independent loads) and added in partition order
-        int s = 1;
-        for (; s + 8 <= splitK; s += 8) {
-            floatx4 v[8];
+// Split-K second pass: C = alpha * (ws[0] + ws[1] + ...) + beta * C (+ bias), V consecutive entries of a row per lane.
+// A work-group takes 2^logCols units of V columns by 2^logRows rows (rows of all batch items in one sequence), and
+// 2^logParts groups of its lanes share the partitions between them: a group adds its partitions in order, the sums of the
+// groups meet in LDS and are added in order too, so the result does not depend on timing.
+// Bound by one or two memory latencies behind the launch.  Places come from shifts (three 64-bit divisions per lane were
+// most of the instructions) and all partitions of a group are in flight together: whole calls 16-bit 256 x 256 x 65536
+// (32 partitions) 21.4 -> 19.8 us, 128 x 64 x 25536 (50) 9.7 -> 8.4, fp32 24 x 112 x 3904 (8) 8.0 -> 6.9; 480 x 1184 x 2592
+// (3, bound by the bytes) 40.7 -> 39.9.
+struct ReduceParams {
+    const float *ws;
+    float *C;
+    const float *bias;
+    long long ldc, strideC;
+    long long per;                   // entries of one partition
+    int M, N;
+    unsigned rows, blocks, colBlocks;    // rows: of all batch items
+    int splitK, perGroup;            // perGroup: partitions of a group of lanes
+    int logCols, logRows;
+    float alpha, beta;
+    int out16, vecC;                 // vecC: C takes 16-byte accesses
+};
+template <int V>
+__global__ __launch_bounds__(256) void splitk_reduce_kernel(const ReduceParams p) {
+    typedef float Unit __attribute__((ext_vector_type(V)));
+    __shared__ Unit sums[256];
+    const int tid = threadIdx.x, col0 = tid & ((1 << p.logCols) - 1);
+    const int row0 = (tid >> p.logCols) & ((1 << p.logRows) - 1), g = tid >> (p.logCols + p.logRows);
+    const int first = g * p.perGroup, last = min(p.splitK, first + p.perGroup);
+    for (unsigned block = blockIdx.x; block < p.blocks; block += gridDim.x) {
+        const unsigned rb = block / p.colBlocks;
+        const unsigned row = (rb << p.logRows) + row0;
+        const long long col = ((long long)((block - rb * p.colBlocks) << p.logCols) + col0) * V;
+        const bool inside = row < p.rows && col < p.N;
+        Unit acc = 0.f;
+        if (inside) {
+            const float *w = p.ws + (long long)row * p.N + col;
+            int s = first;
+            for (; s + 8 <= last; s += 8) {               // eight independent loads, added in partition order
+                Unit v[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const floatx4 *>(ws + (long long)(s + u) * per + i);
+                for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const Unit *>(w + (s + u) * p.per);
 #pragma unroll
-            for (int u = 0; u < 8; ++u) acc += v[u];
+                for (int u = 0; u < 8; ++u) acc += v[u];
+            }
+            // and what is left in one go, the last one read again where there is less
+            auto rest = [&](auto n) {
+                Unit v[decltype(n)::value];
+#pragma unroll
+                for (int u = 0; u < decltype(n)::value; ++u)
+                    v[u] = *reinterpret_cast<const Unit *>(w + min(s + u, last - 1) * p.per);
+#pragma unroll
+                for (int u = 0; u < decltype(n)::value; ++u)
+                    if (s + u < last) acc += v[u];
+            };
+            if (s + 3 < last) rest(std::integral_constant<int, 7>{});
+            else if (s < last) rest(std::integral_constant<int, 3>{});
         }
-        for (; s < splitK; ++s) acc += *reinterpret_cast<const floatx4 *>(ws + (long long)s * per + i);
-        const long long b = i / ((long long)M * N), r = i - b * (long long)M * N;
-        floatx4 *c = reinterpret_cast<floatx4 *>(C + b * strideC + (r / N) * ldc + (r % N));
-        floatx4 v = alpha * acc;
-        if (beta != 0.0f) {
-            const floatx4 c0 = *c;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = fmaf(beta, c0[e], alpha * acc[e]);
+        if (p.perGroup < p.splitK) {
+            sums[tid] = acc;
+            __syncthreads();
+            if (g == 0)
+                for (int t = tid + (1 << (p.logCols + p.logRows)); t < 256; t += 1 << (p.logCols + p.logRows)) acc += sums[t];
+            __syncthreads();
         }
-        if (bias) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] += bias[r % N + e];
+        if (g != 0 || !inside) continue;
+        unsigned r = row;
+        long long at = 0;
+        if (p.rows != (unsigned)p.M) {
+            const unsigned b = row / (unsigned)p.M;
+            r = row - b * (unsigned)p.M;
+            at = b * p.strideC;
         }
-        *c = v;
-    }
-}
-
-// Split-K second pass: C = alpha * (ws[0] + ws[1] + ... in this fixed order) + beta * C (+ bias)
-__global__ void splitk_reduce_kernel(const float *ws, float *C, long long ldc, long long strideC, int M,
-                                     int N, int batch, int splitK, float alpha, float beta,
-                                     const float *bias, int out16) {
-    const long long per = (long long)batch * M * N;
-    for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < per;
-         i += (long long)gridDim.x * blockDim.x) {
-        float acc = ws[i];
-        int s = 1;
-        for (; s + 8 <= splitK; s += 8) {                 // eight independent loads, added in partition order
-            float v[8];
+        at += r * p.ldc + col;
+        if (p.out16) {
 #pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = ws[(long long)(s + u) * per + i];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) acc += v[u];
-        }
-        for (; s < splitK; ++s) acc += ws[(long long)s * per + i];
-        const long long b = i / ((long long)M * N), r = i - b * (long long)M * N;
-        if (out16) {
-            store_bf16_out(C, b * strideC + (r / N) * ldc + (r % N), acc, alpha, beta, bias ? bias[r % N] : 0.0f);
+            for (int e = 0; e < V; ++e)
+                store_bf16_out(p.C, at + e, acc[e], p.alpha, p.beta, p.bias ? p.bias[col + e] : 0.0f);
             continue;
         }
-        float *c = C + b * strideC + (r / N) * ldc + (r % N);
-        float v = alpha * acc;
-        if (beta != 0.0f) v = fmaf(beta, *c, v);
-        if (bias) v += bias[r % N];
-        *c = v;
+        float *c = p.C + at;
+        Unit v = p.alpha * acc;
+        if (p.beta != 0.0f) {
+            Unit old;
+            if (V == 4 && p.vecC) old = *reinterpret_cast<const Unit *>(c);
+            else
+#pragma unroll
+                for (int e = 0; e < V; ++e) old[e] = c[e];
+#pragma unroll
+            for (int e = 0; e < V; ++e) v[e] = fmaf(p.beta, old[e], p.alpha * acc[e]);
+        }
+        if (p.bias) {
+#pragma unroll
+            for (int e = 0; e < V; ++e) v[e] += p.bias[col + e];
+        }
+        if (V == 4 && p.vecC) *reinterpret_cast<Unit *>(c) = v;
+        else
+#pragma unroll
+            for (int e = 0; e < V; ++e) c[e] = v[e];
     }
 }
 
@@ -456,6 +492,44 @@ bool dma_operands(bool akc, bool bkc, int64_t M, int64_t N, int64_t K, const voi
 // slower (1.04); with the line at 4 GFLOP it would be 80 at 0.806, eight slower by up to 1.19 (1472 x 1280 x 1088 TT).
 bool copies_pay(int64_t M, int64_t N, int64_t K, size_t bytes) {
     return 2.0 * (double)M * (double)N * (double)K >= 1e10 + 250.0 * (double)bytes;
+}
+
+// The reduction pass of a split-K launch.  Lanes share the partitions of an entry, two or more to a group, while that
+// leaves fewer than 2^17 of them, eight waves a compute unit: with more the reads fill the memory pipe by themselves.
+int launch_reduce(const GemmParams &p, bool vecC, hipStream_t stream) {
+    // the kernel counts rows in 32 bits: all batch items in one launch, or one each
+    const bool each = (int64_t)p.batch * p.M >= (1LL << 31);
+    const int64_t rows = each ? p.M : (int64_t)p.batch * p.M;
+    ReduceParams r;
+    r.bias = p.bias;
+    r.ldc = p.ldc; r.strideC = p.out16 ? p.strideC16 : p.strideC;
+    r.M = p.M; r.N = p.N;
+    r.rows = (unsigned)rows;
+    r.per = (long long)p.batch * p.M * p.N;
+    r.splitK = p.splitK;
+    r.alpha = p.alpha; r.beta = p.beta;
+    r.out16 = p.out16; r.vecC = vecC ? 1 : 0;
+    const bool vec = p.N % 4 == 0 && aligned(p.ws, 16);
+    const int64_t units = vec ? p.N / 4 : p.N;
+    int logParts = 0;
+    while (logParts < 3 && (units * rows << logParts) < (1 << 17) && p.splitK >= 4 << logParts) ++logParts;
+    r.perGroup = (p.splitK + (1 << logParts) - 1) >> logParts;
+    r.logCols = 0;
+    while (r.logCols < 8 - logParts && (1 << r.logCols) < units) ++r.logCols;
+    r.logRows = 8 - logParts - r.logCols;
+    const int64_t colBlocks = (units + (1 << r.logCols) - 1) >> r.logCols;
+    const int64_t blocks = colBlocks * ((rows + (1 << r.logRows) - 1) >> r.logRows);   // < 2^31 for any scratch a device holds
+    r.colBlocks = (unsigned)colBlocks;
+    r.blocks = (unsigned)blocks;
+    const dim3 grid((unsigned)(blocks < 1048576 ? blocks : 1048576));
+    for (int64_t item = 0; item < (each ? p.batch : 1); ++item) {
+        r.ws = p.ws + item * p.M * p.N;
+        r.C = p.out16 ? reinterpret_cast<float *>(reinterpret_cast<uint16_t *>(p.C) + item * r.strideC) : p.C + item * r.strideC;
+        if (vec) hipLaunchKernelGGL(splitk_reduce_kernel<4>, grid, dim3(256), 0, stream, r);
+        else hipLaunchKernelGGL(splitk_reduce_kernel<1>, grid, dim3(256), 0, stream, r);
+        if (hipGetLastError() != hipSuccess) return KS_ERR_LAUNCH;
+    }
+    return KS_OK;
 }
 
 // Scratch for split-K partial sums: the registered workspace, or the library's static array.
@@ -731,21 +805,8 @@ int run_ws(Workspace wsp, int dtype, int id, int transA, int transB, int64_t M, 
     if (hipGetLastError() != hipSuccess) return KS_ERR_LAUNCH;
 
     if (p.splitK > 1) {
-        const long long total = (long long)batch * M * N;
-        // four entries per lane once there are enough entries to fill the device that way; small
-        // outputs with many partitions run one entry per lane (same sums either way)
-        const bool vec4 = !out16 && N % 4 == 0 && ldc % 4 == 0 && aligned(C, 16) && aligned(p.ws, 16) &&
-                          (batch == 1 || strideC % 4 == 0) && total >= 4LL * 256 * 256;
-        const long long units = vec4 ? total / 4 : total;
-        const int grid = (int)((units + 255) / 256 < 1048576 ? (units + 255) / 256 : 1048576);
-        if (vec4)
-            hipLaunchKernelGGL(splitk_reduce4_kernel, dim3(grid), dim3(256), 0, stream, p.ws, C, (long long)ldc,
-                               (long long)strideC, (int)M, (int)N, (int)batch, p.splitK, alpha, beta, bias);
-        else
-            hipLaunchKernelGGL(splitk_reduce_kernel, dim3(grid), dim3(256), 0, stream, p.ws, C, (long long)ldc,
-                               (long long)strideC, (int)M, (int)N, (int)batch, p.splitK, alpha, beta, bias,
-                               out16);
-        if (hipGetLastError() != hipSuccess) return KS_ERR_LAUNCH;
+        const int rc = launch_reduce(p, aligned(C, 16) && ldc % 4 == 0 && (batch == 1 || strideC % 4 == 0), stream);
+        if (rc != KS_OK) return rc;
     }
     return KS_OK;
 }
