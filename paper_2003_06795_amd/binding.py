@@ -10,6 +10,11 @@ import os
 
 import numpy as np
 
+try:
+    from . import _pycall                 # the same marshalling in C (csrc/pycall.cpp), built beside the library
+except ImportError:
+    _pycall = None
+
 _HERE = os.path.dirname(os.path.abspath(__file__))
 # KS_GEMM_LIBRARY=libks_gemm_kept.so loads the pruned build (kept members only) instead
 LIB_PATH = os.path.join(_HERE, os.environ.get("KS_GEMM_LIBRARY", "libks_gemm.so"))
@@ -126,6 +131,8 @@ def lib():
     L.ks_tune_pca_variance.argtypes = [_p, _i, _i, _p]
     L.ks_status_string.argtypes = [_i]
     L.ks_status_string.restype = ctypes.c_char_p
+    L.entries = {n: ctypes.cast(getattr(L, n), _p).value for n in EXPORTS if n.startswith("ks_gemm_")}
+    _bind_call()
     _lib = L
     return L
 
@@ -180,81 +187,141 @@ def _gemm_args(transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, bat
             batch, strideA, strideB, strideC, _stream(stream))
 
 
+# What the calls below hand to _pycall comes back as NotImplemented where an argument is of an unusual type
+# (and always where the module is not built): ctypes converts it then.
+def _call(*args):
+    return NotImplemented
+
+
+def _bind_call():
+    """The marshalling in C takes over, with torch's own functions for the current stream (see _stream)."""
+    global _call
+    if _pycall is None:
+        return
+    try:
+        import torch
+        _pycall.streams(torch.cuda.is_initialized, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+    except (ImportError, AttributeError):         # no torch, or one without devices: only calls that name their stream
+        pass
+    _call = _pycall.gemm
+
+
 def gemm_f32(transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, batch=1, strideA=0,
-             strideB=0, strideC=0, stream=None):
-    _check(lib().ks_gemm_f32(*_gemm_args(transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc,
-                                         batch, strideA, strideB, strideC, stream)), "ks_gemm_f32")
+            strideB=0, strideC=0, stream=None):
+    L = _lib or lib()
+    rc = _call(L.entries["ks_gemm_f32"], 0, 0, 0, transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, batch,
+               strideA, strideB, strideC, stream, None, 0)
+    if rc is NotImplemented:
+        rc = L.ks_gemm_f32(*_gemm_args(transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, batch, strideA,
+                                 strideB, strideC, stream))
+    _check(rc, "ks_gemm_f32")
 
 
 def gemm_bf16(transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, batch=1, strideA=0,
-              strideB=0, strideC=0, stream=None):
-    _check(lib().ks_gemm_bf16(*_gemm_args(transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc,
-                                          batch, strideA, strideB, strideC, stream)), "ks_gemm_bf16")
+             strideB=0, strideC=0, stream=None):
+    L = _lib or lib()
+    rc = _call(L.entries["ks_gemm_bf16"], 0, 0, 0, transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, batch,
+               strideA, strideB, strideC, stream, None, 0)
+    if rc is NotImplemented:
+        rc = L.ks_gemm_bf16(*_gemm_args(transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, batch, strideA,
+                                  strideB, strideC, stream))
+    _check(rc, "ks_gemm_bf16")
 
 
 def gemm_f16(transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, batch=1, strideA=0,
-             strideB=0, strideC=0, stream=None):
-    _check(lib().ks_gemm_f16(*_gemm_args(transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc,
-                                         batch, strideA, strideB, strideC, stream)), "ks_gemm_f16")
+            strideB=0, strideC=0, stream=None):
+    L = _lib or lib()
+    rc = _call(L.entries["ks_gemm_f16"], 0, 0, 0, transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, batch,
+               strideA, strideB, strideC, stream, None, 0)
+    if rc is NotImplemented:
+        rc = L.ks_gemm_f16(*_gemm_args(transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, batch, strideA,
+                                 strideB, strideC, stream))
+    _check(rc, "ks_gemm_f16")
 
 
 def gemm_f16_with_kernel(kernel_id, transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc,
-                         batch=1, strideA=0, strideB=0, strideC=0, stream=None):
-    _check(lib().ks_gemm_f16_with_kernel(
-        int(kernel_id), *_gemm_args(transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc,
-                                    batch, strideA, strideB, strideC, stream)), "ks_gemm_f16_with_kernel")
+                        batch=1, strideA=0, strideB=0, strideC=0, stream=None):
+    L = _lib or lib()
+    rc = _call(L.entries["ks_gemm_f16_with_kernel"], 1, 0, kernel_id, transA, transB, M, N, K, alpha, A, lda, B, ldb, beta,
+               C, ldc, batch, strideA, strideB, strideC, stream, None, 0)
+    if rc is NotImplemented:
+        rc = L.ks_gemm_f16_with_kernel(int(kernel_id), *_gemm_args(transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C,
+                                             ldc, batch, strideA, strideB, strideC, stream))
+    _check(rc, "ks_gemm_f16_with_kernel")
 
 
 def gemm_f32_with_kernel(kernel_id, transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc,
-                         batch=1, strideA=0, strideB=0, strideC=0, stream=None):
-    _check(lib().ks_gemm_f32_with_kernel(
-        int(kernel_id), *_gemm_args(transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc,
-                                    batch, strideA, strideB, strideC, stream)), "ks_gemm_f32_with_kernel")
+                        batch=1, strideA=0, strideB=0, strideC=0, stream=None):
+    L = _lib or lib()
+    rc = _call(L.entries["ks_gemm_f32_with_kernel"], 1, 0, kernel_id, transA, transB, M, N, K, alpha, A, lda, B, ldb, beta,
+               C, ldc, batch, strideA, strideB, strideC, stream, None, 0)
+    if rc is NotImplemented:
+        rc = L.ks_gemm_f32_with_kernel(int(kernel_id), *_gemm_args(transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C,
+                                             ldc, batch, strideA, strideB, strideC, stream))
+    _check(rc, "ks_gemm_f32_with_kernel")
 
 
 def gemm_bf16_with_kernel(kernel_id, transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc,
-                          batch=1, strideA=0, strideB=0, strideC=0, stream=None):
-    _check(lib().ks_gemm_bf16_with_kernel(
-        int(kernel_id), *_gemm_args(transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc,
-                                    batch, strideA, strideB, strideC, stream)), "ks_gemm_bf16_with_kernel")
+                         batch=1, strideA=0, strideB=0, strideC=0, stream=None):
+    L = _lib or lib()
+    rc = _call(L.entries["ks_gemm_bf16_with_kernel"], 1, 0, kernel_id, transA, transB, M, N, K, alpha, A, lda, B, ldb, beta,
+               C, ldc, batch, strideA, strideB, strideC, stream, None, 0)
+    if rc is NotImplemented:
+        rc = L.ks_gemm_bf16_with_kernel(int(kernel_id), *_gemm_args(transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C,
+                                              ldc, batch, strideA, strideB, strideC, stream))
+    _check(rc, "ks_gemm_bf16_with_kernel")
 
 
-def gemm_bias(dtype, kernel_id, transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, bias,
-              batch=1, strideA=0, strideB=0, strideC=0, stream=None):
+def gemm_bias(dtype, kernel_id, transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc,
+              bias, batch=1, strideA=0, strideB=0, strideC=0, stream=None):
     """C = alpha*op(A)*op(B) + beta*C + bias[j] per column; kernel_id < 0 lets the deployed tree choose."""
-    a = _gemm_args(transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, batch, strideA,
-                   strideB, strideC, stream)
-    _check(lib().ks_gemm_bias(int(dtype), int(kernel_id), *a[:13], _dev(bias) if bias is not None else None,
-                              *a[13:]), "ks_gemm_bias")
+    L = _lib or lib()
+    rc = _call(L.entries["ks_gemm_bias"], 3, dtype, kernel_id, transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, batch,
+               strideA, strideB, strideC, stream, bias, 0)
+    if rc is NotImplemented:
+        a = _gemm_args(transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, batch, strideA, strideB, strideC, stream)
+        rc = L.ks_gemm_bias(int(dtype), int(kernel_id), *a[:13], _dev(bias) if bias is not None else None, *a[13:])
+    _check(rc, "ks_gemm_bias")
 
 
 def gemm_out_bf16(dtype, kernel_id, transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C16, ldc,
                   bias=None, batch=1, strideA=0, strideB=0, strideC=0, stream=None):
     """C16 (bf16 bit patterns) = bf16(alpha*op(A)*op(B) + beta*C16 + bias[j]); kernel_id < 0 selects."""
-    a = _gemm_args(transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C16, ldc, batch, strideA,
-                   strideB, strideC, stream)
-    _check(lib().ks_gemm_out_bf16(int(dtype), int(kernel_id), *a[:13],
-                                  _dev(bias) if bias is not None else None, *a[13:]), "ks_gemm_out_bf16")
+    L = _lib or lib()
+    rc = _call(L.entries["ks_gemm_out_bf16"], 3, dtype, kernel_id, transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C16, ldc, batch,
+               strideA, strideB, strideC, stream, bias, 0)
+    if rc is NotImplemented:
+        a = _gemm_args(transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C16, ldc, batch, strideA, strideB, strideC, stream)
+        rc = L.ks_gemm_out_bf16(int(dtype), int(kernel_id), *a[:13], _dev(bias) if bias is not None else None, *a[13:])
+    _check(rc, "ks_gemm_out_bf16")
 
 
 def gemm_static_scratch(dtype, kernel_id, transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc,
                         batch=1, strideA=0, strideB=0, strideC=0, stream=None):
     """GEMM whose split-K scratch is the library's static device array; allocates nothing."""
-    _check(lib().ks_gemm_static_scratch(
-        int(dtype), int(kernel_id), *_gemm_args(transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc,
-                                                batch, strideA, strideB, strideC, stream)), "ks_gemm_static_scratch")
+    L = _lib or lib()
+    rc = _call(L.entries["ks_gemm_static_scratch"], 2, dtype, kernel_id, transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C,
+               ldc, batch, strideA, strideB, strideC, stream, None, 0)
+    if rc is NotImplemented:
+        rc = L.ks_gemm_static_scratch(int(dtype), int(kernel_id), *_gemm_args(transA, transB, M, N, K, alpha, A, lda, B, ldb,
+                                                                             beta, C, ldc, batch, strideA, strideB, strideC,
+                                                                             stream))
+    _check(rc, "ks_gemm_static_scratch")
 
 
 def gemm_with_workspace(dtype, kernel_id, transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc,
                         workspace, batch=1, strideA=0, strideB=0, strideC=0, stream=None):
-    """GEMM whose scratch (split-K partial sums, divided tiles) is `workspace` (torch tensor or None),
-    not the registered one."""
-    a = _gemm_args(transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, batch, strideA, strideB,
-                   strideC, stream)
+    """GEMM whose scratch (split-K partial sums, divided tiles, copies of operands) is `workspace` (torch
+    tensor or None), not the registered one."""
     nbytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(lib().ks_gemm_with_workspace(int(dtype), int(kernel_id), *a[:-1],
-                                        _dev(workspace) if workspace is not None else None, nbytes, a[-1]),
-           "ks_gemm_with_workspace")
+    L = _lib or lib()
+    rc = _call(L.entries["ks_gemm_with_workspace"], 4, dtype, kernel_id, transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C,
+               ldc, batch, strideA, strideB, strideC, stream, workspace, nbytes)
+    if rc is NotImplemented:
+        a = _gemm_args(transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, batch, strideA, strideB, strideC, stream)
+        rc = L.ks_gemm_with_workspace(int(dtype), int(kernel_id), *a[:-1],
+                                      _dev(workspace) if workspace is not None else None, nbytes, a[-1])
+    _check(rc, "ks_gemm_with_workspace")
 
 
 def gemm_plan(dtype, kernel_id, transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc,

@@ -16,6 +16,7 @@ import glob
 import os
 import subprocess
 import sys
+import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -36,6 +37,7 @@ def _deps():
 
 
 LIB_KEPT = os.path.join(PKG, "libks_gemm_kept.so")
+PYCALL = os.path.join(PKG, "_pycall" + sysconfig.get_config_var("EXT_SUFFIX"))    # argument marshalling of binding.py
 
 
 def _jobs(kept_only=False):
@@ -61,6 +63,15 @@ def _compile(job):
     r = subprocess.run(cmd + ["-o", obj], capture_output=True, text=True)
     err = "\n".join(l for l in r.stderr.splitlines() if "packed-fp32-ops" not in l)
     return obj, r.returncode, err
+
+
+def build_pycall(force=False):
+    src = os.path.join(CSRC, "pycall.cpp")
+    if force or not os.path.exists(PYCALL) or os.path.getmtime(PYCALL) < os.path.getmtime(src):
+        tmp = PYCALL + ".tmp.%d" % os.getpid()
+        subprocess.run(["g++"] + CXX_FLAGS + ["-I", sysconfig.get_paths()["include"], "-shared", src, "-o", tmp], check=True)
+        os.replace(tmp, PYCALL)
+    return PYCALL
 
 
 def build(force=False, jobs=None, verbose=True, kept_only=False):
@@ -91,6 +102,7 @@ def build(force=False, jobs=None, verbose=True, kept_only=False):
         os.replace(tmp, lib)
         if verbose:
             print("[build] linked %s (%.1f MB)" % (lib, os.path.getsize(lib) / 1e6), flush=True)
+    build_pycall(force)
     return lib
 
 
