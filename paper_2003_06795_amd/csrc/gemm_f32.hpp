@@ -14,8 +14,16 @@
 //             decides the coalescing direction of the global loads
 //   LOADS     how a K-step is fetched (ks_common.hpp, TileLoader)
 //
-// LDS layout (both operands): tile[k][m or n] with the row padded by 4 floats.  All cores read
-// "one k, many m/n", so rows of consecutive m/n are conflict-free for them.
+// LDS layout.  A row-contiguous operand: tile[k][m or n] with the row padded by 4 floats; all cores read "one k, many
+// m/n", so rows of consecutive m/n are conflict-free for them.  A K-contiguous operand of the MFMA cores (K-steps of
+// at least eight k with 32-wide and sixteen with 16-wide fragments): tile[m or n][k] as it comes from memory, in
+// chunks of four k whose place in the row is XOR-swizzled by the row (F32Chunks).  A lane reads a chunk, four
+// consecutive k of its row, and MFMA j of a group of four takes element j of both operands, so the sum over the
+// group runs in another order than k's.  With [k][row] tiles for both, a K-contiguous operand took four times as many
+// LDS instructions either way, which the matrix pipe's neighbours wait to issue: over the members in layouts NN / NT / TT
+// and one to forty K-steps 0.97 of the time in the mean, 0.945 in NT (1024^3 NT 31.2 -> 28.8 us on 64 x 64 x 16, 4096^3 1051 -> 994
+// on 128 x 128 x 32, 26.5 -> 23.4 on sixteen waves of 64 x 64 x 32).  The balanced persistent form keeps [k][row] where both
+// operands are K-contiguous (4095 x 3000 x 4089 801 us against 843).
 #pragma once
 #include "ks_common.hpp"
 
@@ -51,27 +59,6 @@ namespace ks {
 #define KS_F32_SK_MIN_WAVES(bm, bn, p1, p2) (((bm) / (p1)) * ((bn) / (p2)) >= 8 ? 4 : 3)
 #endif
 
-// Row padding of the row-contiguous operand's LDS tile when the other operand is K-contiguous and
-// both are fetched sixteen bytes per lane (NN and TT layouts): the padding of its partner instead of its own 4
-// for the members named below.  With unequal row lengths (130 and 132 floats at BK = 32) the
-// compiler keeps separate sets of fragment addresses for the two tiles, 23 - 28 registers.  The
-// balanced persistent form of the 128 x 128 x 32 member does not have them inside its budget of 128,
-// nor does its multi-tile form (the balanced one spilled 13 - 14 and ran 16 % slower in NN than in NT / TN; with equal rows it needs 110), and
-// the sixteen-wave 64 x 64 x 32 member on 16 x 16 wave tiles loses its second resident work-group
-// (75 registers against 52).  The tile is then written with 8-byte stores, which costs elsewhere:
-// measured on the NN and TT rows of the tuning set, the three members on 16 x 16 wave tiles with
-// square tiles, K-step 32 and at least 512 threads gain 2.5 - 9 %, every other member is level or
-// loses 1 - 9 % (among them the four-wave 64 x 64 x 32 balanced member), so only those get it.
-// -1 = no override.
-constexpr int f32_pad_of_partner(bool persistent, int core, int bm, int bn, int p1, int p2, int kw, bool kc, bool partnerKc,
-                                 int bk, int threads, int loads) {
-    const bool persistentLarge = persistent && threads >= 512;
-    const bool squareOn16 = core == 1 && bm == bn && p1 == 16 && p2 == 16 && bk == 32 && threads * kw >= 512;
-    return loads != LOAD_ELEMENTS && (persistentLarge || squareOn16) && !kc && partnerKc && bk <= 32 && (64 / bk) % 2 == 0
-               ? 64 / bk
-               : -1;
-}
-
 enum { CORE_FMA = 0, CORE_MFMA16 = 1, CORE_MFMA32 = 2, CORE_DIRECT = 3, CORE_KSLICE = 4 };
 
 template <int CORE, int BM, int BN, int P1, int P2>
@@ -81,11 +68,18 @@ struct F32Shape {
     static constexpr int frag = CORE == CORE_MFMA16 ? 16 : 32;
 };
 
+// LDS place (in floats) of the four k of chunk c of tile row r: rows of BK floats, chunks XOR-swizzled by the row
+template <int BK>
+struct F32Chunks {
+    static constexpr int CPR = BK / 4, RP = CPR >= 16 ? 1 : 16 / CPR;      // chunks per row; rows per 256 bytes
+    __device__ __forceinline__ static int at(int r, int c) { return r * BK + 4 * (c ^ ((r / RP) & (CPR - 1))); }
+};
+
 // ---- global -> registers -> LDS staging of one ROWS x BK operand tile ------------------------
 // KC:  memory is [row][k] (k contiguous);  !KC: memory is [k][row] (row contiguous).
 // Units are W floats (four, or one in the ELEMENTS form) walked so that consecutive lanes touch consecutive
 // addresses.  INNER = units along the contiguous direction, OUTER = the other direction.
-// PAD >= 0 overrides the row padding chosen below (see f32_pad_of_partner).
+// CHUNKS: the tile is [row][k] in swizzled chunks of four k.
 //
 // load() is for K-steps in which every unit may be read whole (whole_steps() of them): the rows of a
 // K-contiguous operand end at or behind the step, or the step of a row-contiguous one ends before the
@@ -106,7 +100,7 @@ struct F32Shape {
 // many of them.  Against scalar loads of unaligned operands and predicated ones of aligned operands:
 // 4095 x 3000 x 4089 NT 950 -> 805 us (TN 1020 -> 797), 1000^3 with padded rows NN 33.3 -> 26.2 us;
 // aligned 4096^3 TN 1058 -> 1006 us, 1024^3 NN 26.0 -> 24.5 us, im2col 25088 x 256 x 1152 149 -> 144 us.
-template <int ROWS, int BK, int NT, bool KC, int W, int PAD = -1>
+template <int ROWS, int BK, int NT, bool KC, int W, bool CHUNKS = false>
 struct TileLoader {
     typedef float Unit __attribute__((ext_vector_type(W)));
     static constexpr int INNER = (KC ? BK : ROWS) / W;
@@ -121,8 +115,9 @@ struct TileLoader {
     // bank-conflict cycles of the 128 x 128 x 32 member fell to a third and the BK = 32 / 64 members gained
     // 2 - 20 % on long K; giving the lane groups of an MFMA read rows 4 or 8 apart instead of adjacent ones
     // changed nothing.)
-    static constexpr int LDS_LD = ROWS + (PAD >= 0 ? PAD : KC && W == 4 ? (BK >= 64 ? 1 : 64 / BK) : 4);
-    static_assert(KC || W == 1 || LDS_LD % 2 == 0, "row-contiguous vector writes need 8-byte alignment");
+    static constexpr int LDS_LD = ROWS + (KC && W == 4 ? (BK >= 64 ? 1 : 64 / BK) : 4);
+    static constexpr int LDS_SIZE = CHUNKS ? ROWS * BK : BK * LDS_LD;
+    static_assert(KC || W == 1 || LDS_LD % 4 == 0, "row-contiguous vector writes need 16-byte alignment");
     static_assert(INNER <= NT && NT % INNER == 0, "walk");
 
     // byte offsets of a thread's units from the tile origin (row0, first k of the step); the units of a
@@ -213,6 +208,15 @@ struct TileLoader {
         }
     }
 
+    // four consecutive k, from k on, of tile row `row`
+    __device__ __forceinline__ static floatx4 read(const float *lds, int row, int k) {
+        if constexpr (CHUNKS) return *reinterpret_cast<const floatx4 *>(lds + F32Chunks<BK>::at(row, k / 4));
+        floatx4 v;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[j] = lds[(k + j) * LDS_LD + row];
+        return v;
+    }
+
     __device__ __forceinline__ void store(float *lds, int tid) const {
 #pragma unroll
         for (int it = 0; it < ITERS; ++it) {
@@ -220,16 +224,13 @@ struct TileLoader {
             const int inner = tid % INNER, outer = tid / INNER + it * STRIDE;
             const int r = KC ? outer : inner * W;
             const int k = KC ? inner * W : outer;
-            if constexpr (KC || W == 1) {
+            if constexpr (CHUNKS) {
+                *reinterpret_cast<floatx4 *>(lds + F32Chunks<BK>::at(r, inner)) = reg[it];
+            } else if constexpr (KC || W == 1) {
 #pragma unroll
                 for (int j = 0; j < W; ++j) lds[(k + j) * LDS_LD + r] = reg[it][j];
-            } else if constexpr (LDS_LD % 4 == 0) {
-                *reinterpret_cast<floatx4 *>(lds + k * LDS_LD + r) = reg[it];
             } else {
-                typedef float floatx2 __attribute__((ext_vector_type(2)));
-                floatx2 *dst = reinterpret_cast<floatx2 *>(lds + k * LDS_LD + r);
-                dst[0] = floatx2{reg[it][0], reg[it][1]};
-                dst[1] = floatx2{reg[it][2], reg[it][3]};
+                *reinterpret_cast<floatx4 *>(lds + k * LDS_LD + r) = reg[it];
             }
         }
     }
@@ -265,17 +266,21 @@ __global__ __launch_bounds__((F32Shape<CORE, BM, BN, P1, P2>::threads * KW), (SK
     using Shape = F32Shape<CORE, BM, BN, P1, P2>;
     constexpr int NT = Shape::threads;                        // threads of one group
     static_assert(KW == 1 || CORE != CORE_FMA, "K groups need an MFMA core");
-    constexpr int PADA = f32_pad_of_partner(SK || MULTI, CORE, BM, BN, P1, P2, KW, AKC, BKC, BK, NT, LOADS);
-    constexpr int PADB = f32_pad_of_partner(SK || MULTI, CORE, BM, BN, P1, P2, KW, BKC, AKC, BK, NT, LOADS);
     constexpr int W = LOADS == LOAD_ELEMENTS ? 1 : 4;
-    constexpr int LDA = TileLoader<BM, BK, NT, AKC, W, PADA>::LDS_LD, LDB = TileLoader<BN, BK, NT, BKC, W, PADB>::LDS_LD;
-    __shared__ __attribute__((aligned(16))) float AsAll[KW][2][BK * LDA];
-    __shared__ __attribute__((aligned(16))) float BsAll[KW][2][BK * LDB];
+    constexpr int FR = Shape::frag, KV = 4 * (64 / FR);       // KV: k of a substep of whole chunks
+    // groups of four k to a lane: the order of the sums, the same in every load form
+    constexpr bool BY_FOUR = CORE != CORE_FMA && BK % KV == 0 && (AKC || BKC) && !(SK && AKC && BKC);
+    constexpr bool CHA = BY_FOUR && W == 4 && AKC, CHB = BY_FOUR && W == 4 && BKC;
+    using LoaderA = TileLoader<BM, BK, NT, AKC, W, CHA>;
+    using LoaderB = TileLoader<BN, BK, NT, BKC, W, CHB>;
+    constexpr int LDA = LoaderA::LDS_LD, LDB = LoaderB::LDS_LD;
+    __shared__ __attribute__((aligned(1024))) float AsAll[KW][2][LoaderA::LDS_SIZE];
+    __shared__ __attribute__((aligned(1024))) float BsAll[KW][2][LoaderB::LDS_SIZE];
 
     const int grp = KW == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x / NT);
     const int tid = KW == 1 ? (int)threadIdx.x : (int)threadIdx.x % NT;
-    float (*As)[BK * LDA] = AsAll[grp];
-    float (*Bs)[BK * LDB] = BsAll[grp];
+    float (*As)[LoaderA::LDS_SIZE] = AsAll[grp];
+    float (*Bs)[LoaderB::LDS_SIZE] = BsAll[grp];
     // the (first) tile of this work-group
     const TileCoord tc = MULTI && !p.grid3d ? tile_of_logical(p, logical_of_block() * (unsigned)p.tilesPerWG)
                                             : tile_of_block(p);
@@ -292,10 +297,10 @@ __global__ __launch_bounds__((F32Shape<CORE, BM, BN, P1, P2>::threads * KW), (SK
     // K-steps in flight between global memory and LDS (each in its own set of staging registers):
     // small tiles are latency-bound - few waves per compute unit, short MFMA runs per K-step - and
     // afford several; large tiles hide the latency behind their MFMAs and keep the registers.
-    using LoaderA = TileLoader<BM, BK, NT, AKC, W, PADA>;
-    using LoaderB = TileLoader<BN, BK, NT, BKC, W, PADB>;
     constexpr int STAGE_REGS = (LoaderA::ITERS + LoaderB::ITERS) * W;
-    constexpr int PF = KS_F32_PREFETCH(STAGE_REGS, NT);
+    // (sixteen waves that must fit 64 registers: four sets beside fragments of four k spilled 4 - 16)
+    constexpr bool TIGHT = KS_F32_MIN_WAVES(MULTI, CORE, BM, BN, BK, P1, P2, KW, LOADS) == 8 && (CHA || CHB) && BK >= 32;
+    constexpr int PF = TIGHT ? 2 : KS_F32_PREFETCH(STAGE_REGS, NT);
     LoaderA la[PF];
     LoaderB lb[PF];
     typename LoaderA::Plan pa;
@@ -322,7 +327,6 @@ __global__ __launch_bounds__((F32Shape<CORE, BM, BN, P1, P2>::threads * KW), (SK
     };
 
     // accumulators
-    constexpr int FR = Shape::frag;
     constexpr int FM = CORE == CORE_FMA ? 1 : P1 / FR, FN = CORE == CORE_FMA ? 1 : P2 / FR;
     float accF[CORE == CORE_FMA ? P1 : 1][CORE == CORE_FMA ? P2 : 1];
     floatx4 acc16[CORE == CORE_MFMA16 ? FM : 1][CORE == CORE_MFMA16 ? FN : 1];
@@ -371,6 +375,28 @@ __global__ __launch_bounds__((F32Shape<CORE, BM, BN, P1, P2>::threads * KW), (SK
                 for (int i = 0; i < P1; ++i)
 #pragma unroll
                     for (int j = 0; j < P2; ++j) accF[i][j] = fmaf(a[i], b[j], accF[i][j]);
+            }
+        } else if constexpr (BY_FOUR) {
+            // a lane holds four consecutive k of its row, MFMA j of a group of four consumes element j
+#pragma unroll
+            for (int kk = 0; kk < BK; kk += KV) {
+                const int g = lane / FR, r = lane % FR;
+                floatx4 a[FM], b[FN];
+#pragma unroll
+                for (int i = 0; i < FM; ++i) a[i] = LoaderA::read(as, subM + i * FR + r, kk + 4 * g);
+#pragma unroll
+                for (int j = 0; j < FN; ++j) b[j] = LoaderB::read(bs, subN + j * FR + r, kk + 4 * g);
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int i = 0; i < FM; ++i)
+#pragma unroll
+                        for (int j = 0; j < FN; ++j) {
+                            if constexpr (CORE == CORE_MFMA16)
+                                acc16[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][e], b[j][e], acc16[i][j], 0, 0, 0);
+                            else
+                                acc32[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][e], b[j][e], acc32[i][j], 0, 0, 0);
+                        }
             }
         } else if constexpr (CORE == CORE_MFMA16) {
             // 16x16x4: lane l feeds A[l%16][l/16] and B[l/16][l%16]
