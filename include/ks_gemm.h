@@ -279,8 +279,8 @@ int ks_kernel_info(int dtype, int kernel_id, ks_kernel_info_t *out);   /* out: h
 /* ---------------------------------------------------------------- selection (Section IV)
  * Walks the deployed decision tree for `dtype` with integer comparisons only and returns the
  * chosen kernel id (>= 0), or a negative status for a bad flag / negative size.  Beside the tree
- * compiled into the library stand three rules on the same sizes, for pairs of members between which
- * the count of tiles per compute unit decides (what the tree alone says is ks_get_selector's); a tree
+ * compiled into the library stand rules on the same sizes, for pairs of members between which the
+ * count of tiles per compute unit or a few rows or columns decide (what the tree alone says is ks_get_selector's); a tree
  * set with ks_set_selector is followed as it is.  Pure, total over non-negative sizes, thread-safe,
  * allocation-free, no device access. */
 int ks_select(int dtype, int64_t M, int64_t N, int64_t K, int64_t batch, int transA, int transB);

@@ -1,5 +1,5 @@
 // Runtime kernel selection (paper Section IV): a decision tree deployed as integer comparisons, and beside
-// the built-in trees the rules for what a count of tiles per compute unit decides.
+// the built-in trees the rules for what a count of tiles per compute unit or a few rows or columns decide.
 // Host only; no device access, no allocation.
 #include "../../include/ks_gemm.h"
 
@@ -41,7 +41,7 @@ int64_t sat_mul(int64_t a, int64_t b) {
     return a * b;
 }
 
-// ---- the built-in trees and the count of tiles per compute unit --------------------------------
+// ---- the built-in trees and what they cannot follow --------------------------------------------
 // The trees split on sizes; what a call costs steps with its tiles per compute unit, which no threshold of
 // theirs can follow.  Where both sides were timed (operands rotated through three buffers) the choice is
 // corrected, from the sizes alone: every caller of ks_select and every selecting entry point gets the same
@@ -73,9 +73,12 @@ constexpr bool kept(const int (&list)[N], int id) {
     return false;
 }
 constexpr int kF32Large = 47, kF32Small = 28, k16Narrow = 23, k16TwoGroups = 47, k16OneGroup = 9;
+constexpr int k16Columns = 13, k16ColumnsDeep = 38, k16Square = 27, k16SquareDeep = 39;
 static_assert(tile_is(kTilesF32, kF32Large, 128, 128, 32) && tile_is(kTilesF32, kF32Small, 64, 64, 16) &&
                   tile_is(kTiles16, k16Narrow, 128, 64, 64) && tile_is(kTiles16, k16TwoGroups, 128, 128, 128) &&
-                  tile_is(kTiles16, k16OneGroup, 128, 128, 128),
+                  tile_is(kTiles16, k16OneGroup, 128, 128, 128) && tile_is(kTiles16, k16Columns, 64, 16, 128) &&
+                  tile_is(kTiles16, k16ColumnsDeep, 64, 16, 128) && tile_is(kTiles16, k16Square, 64, 64, 128) &&
+                  tile_is(kTiles16, k16SquareDeep, 64, 64, 128),
               "the rules below count the tiles of these members");
 
 // fp32 128 x 128 -> 64 x 64.  A unit works through its tiles one after the other, so what counts is the fullest
@@ -108,6 +111,32 @@ int by_tiles_per_unit(int dtype, int id, int64_t M, int64_t N, int64_t K, int64_
     if (id == k16Narrow && K % 128 == 0 && K >= 2048 && kept(kKept16, k16TwoGroups)) return k16TwoGroups;
     if (id == k16TwoGroups && K % 128 == 64 && (transA != 0 || transB == 0 || K <= 2048) && kept(kKept16, k16OneGroup))
         return k16OneGroup;
+    return id;
+}
+
+// 16-bit products of a wide operand with a few columns or rows, one pass over the wide one.  The tables the tree was
+//   trained on hold two such sizes, timed on operands that stay in the last-level cache.  With operands from memory
+//   (three sets in turn; 7856 problems, the wide side and K in 1024 .. 16384, 1 to 128 on the other, whole and ragged sizes):
+//   up to 16 columns: 64 x 16 tiles with three K-steps in flight for 64 x 64 ones, which load and multiply what does not
+//     exist (1304 at 0.79: 8192 x 1 x 8192 NN 48 -> 35 us, 2048 x 4 x 16384 35 -> 19; behind by 3 - 9 % where both operands
+//     are row-contiguous and whole, which keep the square tiles), and for the same tile with no K split from K = 1792 on
+//     (322 at 0.65; below, 1.03 and more on every tenth).  The tree's other square member up to 32 columns (208 at 0.71).
+//   up to 32 rows: 64 x 64 tiles for 64 x 16 ones, four times the work-groups over the same rows, and for three K-steps
+//     in flight, which cost a resident work-group (1354 at 0.58: 6 x 6163 x 5041 NT 57 -> 28 us, 13 x 3909 x 12757 NN 39 ->
+//     29; from 1536 columns on, below some at 1.15); for 64 x 16 without a split up to 16 rows and 8192 columns, K >= 2048 (160 at 0.59).
+int by_few_rows_or_columns(int dtype, int id, int64_t M, int64_t N, int64_t K, int64_t batch, int transA, int transB) {
+    if (dtype == KS_F32 || batch != 1 || K < 1024) return id;
+    if (M >= 1024 && N <= 32 && kept(kKept16, k16ColumnsDeep)) {
+        const bool wholeTT = transA != 0 && transB != 0 && M % 8 == 0 && K % 8 == 0;
+        if (N <= 16 && id == k16Square && !wholeTT) return k16ColumnsDeep;
+        if (N <= 16 && id == k16Columns && K >= 1792) return k16ColumnsDeep;
+        if (id == k16SquareDeep && (N <= 16 || !wholeTT)) return k16ColumnsDeep;
+        return id;
+    }
+    if (M <= 32 && N >= 1024 && K >= 2048 && kept(kKept16, k16Square)) {
+        if ((id == k16ColumnsDeep || id == k16SquareDeep) && N >= 1536) return k16Square;
+        if (id == k16Columns && M <= 16 && N < 8192) return k16Square;
+    }
     return id;
 }
 
@@ -145,7 +174,9 @@ extern "C" int ks_select(int dtype, int64_t M, int64_t N, int64_t K, int64_t bat
     for (int step = 0; step < n && t[i].feature >= 0; ++step)
         i = f[t[i].feature] <= t[i].threshold ? t[i].left : t[i].right;
     if (t[i].feature >= 0) return KS_ERR_INVALID_ARG;
-    return g_tree[dtype].custom ? t[i].value : by_tiles_per_unit(dtype, t[i].value, M, N, K, batch, transA, transB);
+    if (g_tree[dtype].custom) return t[i].value;
+    const int id = by_tiles_per_unit(dtype, t[i].value, M, N, K, batch, transA, transB);
+    return by_few_rows_or_columns(dtype, id, M, N, K, batch, transA, transB);
 }
 
 extern "C" int ks_set_selector(int dtype, const ks_tree_node_t *nodes, int n) {
