@@ -300,8 +300,10 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const ReduceParams p
                 for (int u = 0; u < decltype(n)::value; ++u)
                     if (s + u < last) acc += v[u];
             };
-            if (s + 3 < last) rest(std::integral_constant<int, 7>{});
-            else if (s < last) rest(std::integral_constant<int, 3>{});
+            if (s + 4 < last) rest(std::integral_constant<int, 7>{});
+            else if (s + 2 < last) rest(std::integral_constant<int, 4>{});
+            else if (s + 1 < last) rest(std::integral_constant<int, 2>{});
+            else if (s < last) rest(std::integral_constant<int, 1>{});
         }
         if (p.perGroup < p.splitK) {
             sums[tid] = acc;
@@ -515,7 +517,7 @@ int launch_reduce(const GemmParams &p, bool vecC, hipStream_t stream) {
     while (logParts < 3 && (units * rows << logParts) < (1 << 17) && p.splitK >= 4 << logParts) ++logParts;
     r.perGroup = (p.splitK + (1 << logParts) - 1) >> logParts;
     r.logCols = 0;
-    while (r.logCols < 8 - logParts && (1 << r.logCols) < units) ++r.logCols;
+    while (r.logCols < 6 && r.logCols < 8 - logParts && (1 << r.logCols) < units) ++r.logCols;   // a wave's row
     r.logRows = 8 - logParts - r.logCols;
     const int64_t colBlocks = (units + (1 << r.logCols) - 1) >> r.logCols;
     const int64_t blocks = colBlocks * ((rows + (1 << r.logRows) - 1) >> r.logRows);   // < 2^31 for any scratch a device holds
