@@ -124,7 +124,8 @@ typedef struct {
  * ks_gemm_* picks the kernel with ks_select (Section IV) and is bit-identical to
  * ks_gemm_*_with_kernel(ks_select(...), ...) whenever the registered workspace can hold the
  * chosen kernel's split-K partial sums; if it cannot (or none is registered) the instance with
- * the same tiles and split_k == 1 runs instead.  A, B, C: device pointers.
+ * the same tiles and split_k == 1 runs instead, and for 16-bit products of up to 32 rows or 16 columns without any scratch the
+ * member that gains without a K split.  A, B, C: device pointers.
  * bf16 operands are raw bfloat16 bit patterns; accumulation and C are fp32.
  * Degenerate sizes: M, N or batch == 0 -> success, nothing launched; K == 0 -> C = beta*C.
  * Errors: KS_ERR_INVALID_ARG (see ks_status), KS_ERR_UNSUPPORTED when M, N or K >= 2^31 - 512 or a leading dimension >= 2^31,
@@ -280,7 +281,7 @@ int ks_kernel_info(int dtype, int kernel_id, ks_kernel_info_t *out);   /* out: h
  * Walks the deployed decision tree for `dtype` with integer comparisons only and returns the
  * chosen kernel id (>= 0), or a negative status for a bad flag / negative size.  Beside the tree
  * compiled into the library stand rules on the same sizes, for pairs of members between which the
- * count of tiles per compute unit or a few rows or columns decide (what the tree alone says is ks_get_selector's); a tree
+ * count of tiles per compute unit, a few rows or columns or ragged sizes decide (what the tree alone says is ks_get_selector's); a tree
  * set with ks_set_selector is followed as it is.  Pure, total over non-negative sizes, thread-safe,
  * allocation-free, no device access. */
 int ks_select(int dtype, int64_t M, int64_t N, int64_t K, int64_t batch, int transA, int transB);

@@ -17,6 +17,8 @@
 
 namespace ks {
 
+int select_member(int dtype, int64_t M, int64_t N, int64_t K, int64_t batch, int transA, int transB, bool scratch);   // selector.cpp
+
 #define KS_DECL(n)                              \
     void register_f32_shard_##n(LaunchFn *);    \
     void register_bf16_shard_##n(LaunchFn *);   \
@@ -936,12 +938,12 @@ extern "C" size_t ks_workspace_bytes_needed(int dtype, int kernel_id, int64_t M,
     transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, batch, strideA, strideB, strideC, \
         static_cast<hipStream_t>(stream)
 
-// Kernel for the selecting entry points: the choice of ks_select, unless that is a split-K instance and
-// the registered workspace cannot hold its partial sums; then the instance with the same tiles
+// Kernel for the selecting entry points: the choice of ks_select (without scratch: without the rules that count on a K
+// split, selector.cpp), unless that is a split-K instance and the registered workspace cannot hold its partial sums; then the instance with the same tiles
 // and no split is used instead, so that a caller who never registers a workspace is still served.
 static int select_checked(int dtype, int64_t M, int64_t N, int64_t K, int64_t batch, int tA, int tB,
                           Workspace w = registered_ws()) {
-    const int id = ks_select(dtype, M, N, K, batch, tA, tB);
+    const int id = ks::select_member(dtype, M, N, K, batch, tA, tB, w.ptr != nullptr);
     if (id < 0) return id;
     const InstanceDesc *d = desc_of(dtype, id);
     if (!d || d->splitK <= 1 || M <= 0 || N <= 0 || batch <= 0) return id;

@@ -1,5 +1,5 @@
 // Runtime kernel selection (paper Section IV): a decision tree deployed as integer comparisons, and beside
-// the built-in trees the rules for what a count of tiles per compute unit or a few rows or columns decide.
+// the built-in trees the rules for what a count of tiles per compute unit, a few rows or columns or ragged sizes decide.
 // Host only; no device access, no allocation.
 #include "../../include/ks_gemm.h"
 
@@ -74,11 +74,17 @@ constexpr bool kept(const int (&list)[N], int id) {
 }
 constexpr int kF32Large = 47, kF32Small = 28, k16Narrow = 23, k16TwoGroups = 47, k16OneGroup = 9;
 constexpr int k16Columns = 13, k16ColumnsDeep = 38, k16Square = 27, k16SquareDeep = 39;
+constexpr int k16Wide = 7, k16Large = 45;
+constexpr int kF32ShortK = 23, kF32Halves = 41, kF32Tall = 15, kF32Sixteen = 38, kF32Half = 21, kF32GroupsLarge = 32, kF32Groups = 30;
 static_assert(tile_is(kTilesF32, kF32Large, 128, 128, 32) && tile_is(kTilesF32, kF32Small, 64, 64, 16) &&
                   tile_is(kTiles16, k16Narrow, 128, 64, 64) && tile_is(kTiles16, k16TwoGroups, 128, 128, 128) &&
                   tile_is(kTiles16, k16OneGroup, 128, 128, 128) && tile_is(kTiles16, k16Columns, 64, 16, 128) &&
                   tile_is(kTiles16, k16ColumnsDeep, 64, 16, 128) && tile_is(kTiles16, k16Square, 64, 64, 128) &&
-                  tile_is(kTiles16, k16SquareDeep, 64, 64, 128),
+                  tile_is(kTiles16, k16SquareDeep, 64, 64, 128) && tile_is(kTiles16, k16Wide, 128, 128, 64) &&
+                  tile_is(kTiles16, k16Large, 256, 256, 64) && tile_is(kTilesF32, kF32ShortK, 64, 64, 8) &&
+                  tile_is(kTilesF32, kF32Halves, 32, 32, 32) && tile_is(kTilesF32, kF32Tall, 32, 64, 32) &&
+                  tile_is(kTilesF32, kF32Sixteen, 16, 16, 32) && tile_is(kTilesF32, kF32Half, 32, 32, 16) &&
+                  tile_is(kTilesF32, kF32GroupsLarge, 64, 64, 16) && tile_is(kTilesF32, kF32Groups, 32, 32, 32),
               "the rules below count the tiles of these members");
 
 // fp32 128 x 128 -> 64 x 64.  A unit works through its tiles one after the other, so what counts is the fullest
@@ -124,19 +130,73 @@ int by_tiles_per_unit(int dtype, int id, int64_t M, int64_t N, int64_t K, int64_
 //   up to 32 rows: 64 x 64 tiles for 64 x 16 ones, four times the work-groups over the same rows, and for three K-steps
 //     in flight, which cost a resident work-group (1354 at 0.58: 6 x 6163 x 5041 NT 57 -> 28 us, 13 x 3909 x 12757 NN 39 ->
 //     29; from 1536 columns on, below some at 1.15); for 64 x 16 without a split up to 16 rows and 8192 columns, K >= 2048 (160 at 0.59).
-int by_few_rows_or_columns(int dtype, int id, int64_t M, int64_t N, int64_t K, int64_t batch, int transA, int transB) {
+//   Those that gain by a K split stay with the tree's member in a call without scratch: unsplit, 27 is 1.07 - 1.32 times
+//   as slow there as 38 and 13.
+int by_few_rows_or_columns(int dtype, int id, int64_t M, int64_t N, int64_t K, int64_t batch, int transA, int transB,
+                           bool scratch) {
     if (dtype == KS_F32 || batch != 1 || K < 1024) return id;
     if (M >= 1024 && N <= 32 && kept(kKept16, k16ColumnsDeep)) {
         const bool wholeTT = transA != 0 && transB != 0 && M % 8 == 0 && K % 8 == 0;
         if (N <= 16 && id == k16Square && !wholeTT) return k16ColumnsDeep;
-        if (N <= 16 && id == k16Columns && K >= 1792) return k16ColumnsDeep;
+        if (N <= 16 && id == k16Columns && K >= 1792 && scratch) return k16ColumnsDeep;
         if (id == k16SquareDeep && (N <= 16 || !wholeTT)) return k16ColumnsDeep;
         return id;
     }
     if (M <= 32 && N >= 1024 && K >= 2048 && kept(kKept16, k16Square)) {
-        if ((id == k16ColumnsDeep || id == k16SquareDeep) && N >= 1536) return k16Square;
-        if (id == k16Columns && M <= 16 && N < 8192) return k16Square;
+        if (N >= 1536 && (id == k16SquareDeep || (id == k16ColumnsDeep && scratch))) return k16Square;
+        if (id == k16Columns && M <= 16 && N < 8192 && scratch) return k16Square;
     }
+    return id;
+}
+
+// Sizes that the tables hold few of or none (they are multiples of eight and were timed on cached operands): members
+//   compared on 11491 drawn problems, whole and ragged, operands rotated through three sets.
+// 16-bit, `ragged`: no leading dimension puts these sizes on the direct-to-LDS path as they are.
+//   128 x 64 -> 256 x 256 in two groups of waves, whose ragged operands are copied where there is scratch, once half the
+//     device has such a tile: from 1.5e10 products on, ragged from 1.0e10: aligned 59 at 0.85 (worst 1.02), ragged 74 at 0.73,
+//     0.94 without scratch (1.10).  With fewer tiles only a K split pays (0.84 with scratch, 1.16 without).  128 x 128 x 64 only
+//     ragged, from 3e10 on and up to two rounds: 17 at 0.63, 0.89 without scratch (1.25); aligned 1.02.
+//   64 x 64 -> 128 x 128 in two groups of waves, from 2.1e6 entries on, where half the device has a tile: 45 at 0.79 with
+//     and without scratch (one at 1.3).
+// fp32, `odd`: an operand whose rows are no multiple of four.
+//   64 x 64 x 16 -> 64 x 64 x 8 up to K = 24, and 32 x 32 x 32 -> 64 x 64 x 8 up to K = 71, on large outputs: what a K-step holds
+//     beyond K is loaded element by element and multiplied all the same (181 at 0.88, six over 1.03; 28 at 0.83).
+//   members with two K groups -> 32 x 32 x 32: 41 at 0.88 where K is short, 40 at 0.89 where it is long.
+//   batches: 32 columns or fewer on 32 x 64 tiles -> 32 x 32 (31 at 0.83, none slower); items that fill less than nine
+//     tenths of their 16 x 16 tiles -> 32 x 32 (118 at 0.89, twelve over 1.03: 1.12); 32 x 32 x 16 -> 64 x 64 from 9036 of the
+//     former on (24 at 0.88).
+// leaf: what the tree says
+int by_tile_fit(int dtype, int leaf, int id, int64_t M, int64_t N, int64_t K, int64_t batch, int transA, int transB) {
+    if (M <= 0 || N <= 0 || K <= 0 || batch <= 0 || M > (1 << 28) || N > (1 << 28) || batch > (1 << 28)) return id;
+    const double entries = (double)M * (double)N, products = entries * (double)K;
+    auto tiles = [&](int64_t e) { return (double)((M + e - 1) / e) * (double)((N + e - 1) / e); };
+    if (dtype != KS_F32) {
+        if (batch != 1) return id;
+        const bool ragged = K % 64 != 0 || (transA != 0 && M % 8 != 0) || (transB == 0 && N % 8 != 0);
+        const double large = tiles(256);
+        if (kept(kKept16, k16Large) && large >= 128 &&
+            ((id == k16Narrow && (products >= 1.5e10 || (ragged && products >= 1e10))) ||
+             (id == k16Wide && ragged && products >= 3e10 && large < 512)))
+            return k16Large;
+        if (id == k16Square && kept(kKept16, k16TwoGroups) && tiles(128) >= 128 && entries >= 2.1e6) return k16TwoGroups;
+        return id;
+    }
+    if (batch == 1) {
+        const bool odd = (transA != 0 ? M : K) % 4 != 0 || (transB != 0 ? K : N) % 4 != 0;
+        if (!odd) return id;
+        if (kept(kKeptF32, kF32ShortK) && ((leaf == kF32Small && K <= 24 && entries >= 1 << 20) ||
+                                           (id == kF32Halves && K <= 71 && entries >= 2.1e6)))
+            return kF32ShortK;
+        if (kept(kKeptF32, kF32Halves) && ((id == kF32GroupsLarge && K < 576 && tiles(16) < 6038) ||
+                                           (id == kF32Groups && K >= 1226 && (double)(M + N) * (double)K >= 1.65e6)))
+            return kF32Halves;
+        return id;
+    }
+    if (kept(kKeptF32, kF32Halves) &&
+        ((id == kF32Tall && N <= 32) || (id == kF32Sixteen && M >= 17 && N >= 17 && entries < 0.9 * 256.0 * tiles(16) &&
+                                         (M % 8 != 0 || N % 8 != 0 || K % 8 != 0))))
+        return kF32Halves;
+    if (id == kF32Half && tiles(32) * (double)batch >= 9036 && kept(kKeptF32, kF32Small)) return kF32Small;
     return id;
 }
 
@@ -160,8 +220,9 @@ extern "C" int ks_features(int64_t M, int64_t N, int64_t K, int64_t batch, int t
     return KS_OK;
 }
 
-extern "C" int ks_select(int dtype, int64_t M, int64_t N, int64_t K, int64_t batch, int transA,
-                         int transB) {
+namespace ks {
+// The member for these sizes; without scratch the rules that count on a K split are left out.
+int select_member(int dtype, int64_t M, int64_t N, int64_t K, int64_t batch, int transA, int transB, bool scratch) {
     if (dtype == KS_F16) dtype = KS_BF16;          // the fp16 form runs the 16-bit family with its tree
     if (dtype != KS_F32 && dtype != KS_BF16) return KS_ERR_INVALID_ARG;
     int64_t f[KS_NUM_FEATURES];
@@ -176,7 +237,13 @@ extern "C" int ks_select(int dtype, int64_t M, int64_t N, int64_t K, int64_t bat
     if (t[i].feature >= 0) return KS_ERR_INVALID_ARG;
     if (g_tree[dtype].custom) return t[i].value;
     const int id = by_tiles_per_unit(dtype, t[i].value, M, N, K, batch, transA, transB);
-    return by_few_rows_or_columns(dtype, id, M, N, K, batch, transA, transB);
+    const int few = by_few_rows_or_columns(dtype, id, M, N, K, batch, transA, transB, scratch);
+    return by_tile_fit(dtype, t[i].value, few, M, N, K, batch, transA, transB);
+}
+}  // namespace ks
+
+extern "C" int ks_select(int dtype, int64_t M, int64_t N, int64_t K, int64_t batch, int transA, int transB) {
+    return ks::select_member(dtype, M, N, K, batch, transA, transB, true);
 }
 
 extern "C" int ks_set_selector(int dtype, const ks_tree_node_t *nodes, int n) {

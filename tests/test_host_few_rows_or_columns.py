@@ -1,9 +1,54 @@
-"""The members of 16-bit products with a few rows or columns: where the rule beside the built-in tree takes over, both sides
-of each of its limits, and that everything else is the tree's."""
+"""The members of 16-bit products with a few rows or columns and of ragged sizes: where the rules beside the built-in tree
+take over, both sides of their limits, and that everything else is the tree's."""
 import numpy as np
 import pytest
 
 import paper_2003_06795_amd.binding as ks
+
+
+# (type, M, N, K, batch, transA, transB, the tree's member, the member): a size of each rule and one beside it
+CASES = [
+    (ks.F32, 131072, 285, 9, 1, 0, 0, 28, 23),
+    (ks.F32, 118336, 79, 36, 1, 0, 0, 28, 28),
+    (ks.F32, 138384, 109, 7, 1, 0, 0, 28, 23),
+    (ks.F32, 3496, 1888, 16, 1, 0, 1, 28, 28),
+    (ks.F32, 63368, 35, 57, 1, 0, 0, 41, 23),
+    (ks.F32, 928, 448, 304, 1, 1, 0, 41, 41),
+    (ks.F32, 23716, 108, 27, 1, 0, 0, 41, 23),
+    (ks.F32, 10816, 89, 72, 1, 0, 0, 41, 41),
+    (ks.F32, 784, 1572, 198, 1, 0, 0, 32, 41),
+    (ks.F32, 360, 1768, 384, 1, 1, 0, 32, 32),
+    (ks.F32, 315, 2963, 249, 1, 0, 0, 32, 41),
+    (ks.F32, 3032, 272, 280, 1, 0, 1, 32, 32),
+    (ks.F32, 33, 2180, 2769, 1, 1, 1, 30, 41),
+    (ks.F32, 274, 1748, 418, 1, 0, 1, 30, 30),
+    (ks.F32, 70, 1401, 1860, 1, 1, 1, 30, 41),
+    (ks.F32, 477, 591, 648, 1, 0, 0, 30, 30),
+    (ks.F32, 36, 29, 48, 265, 0, 1, 15, 41),
+    (ks.F32, 28, 50, 36, 678, 1, 0, 15, 15),
+    (ks.F32, 32, 30, 17, 364, 1, 0, 15, 41),
+    (ks.F32, 34, 48, 10, 302, 0, 1, 15, 15),
+    (ks.F32, 44, 60, 64, 300, 1, 1, 38, 41),
+    (ks.F32, 60, 48, 64, 206, 0, 1, 38, 38),
+    (ks.F32, 20, 36, 44, 765, 0, 1, 38, 41),
+    (ks.F32, 16, 36, 55, 575, 0, 0, 38, 38),
+    (ks.F32, 44, 64, 64, 2830, 0, 1, 21, 28),
+    (ks.F32, 64, 64, 44, 1175, 0, 1, 21, 21),
+    (ks.F32, 52, 52, 55, 3274, 1, 1, 21, 28),
+    (ks.F32, 61, 40, 61, 1120, 1, 0, 21, 21),
+    (ks.BF16, 2319, 4402, 1025, 1, 1, 0, 23, 45),
+    (ks.BF16, 3072, 2048, 1664, 1, 0, 0, 23, 23),
+    (ks.BF16, 1434, 7807, 1343, 1, 1, 1, 23, 45),
+    (ks.BF16, 1856, 2944, 2752, 1, 0, 0, 23, 23),
+    (ks.BF16, 5113, 5712, 1304, 1, 0, 1, 7, 45),
+    (ks.BF16, 6720, 3712, 1536, 1, 1, 1, 7, 7),
+    (ks.BF16, 8135, 3481, 1199, 1, 0, 1, 7, 45),
+    (ks.BF16, 6080, 5440, 1024, 1, 1, 0, 7, 7),
+    (ks.BF16, 1024, 2368, 2432, 1, 0, 0, 27, 47),
+    (ks.BF16, 320, 320, 58112, 1, 1, 0, 27, 27),
+    (ks.BF16, 1919, 1530, 2450, 1, 1, 1, 27, 47),
+    (ks.BF16, 1088, 1536, 4288, 1, 0, 1, 27, 27),
+]
 
 
 def tree(M, N, K, tA, tB):
@@ -29,7 +74,7 @@ def rule(M, N, K, tA, tB):
 @pytest.mark.parametrize("dtype", [ks.BF16, ks.F16])
 def test_rule_and_its_limits(dtype):
     r, seen = np.random.default_rng(3), {}
-    few = (1, 2, 7, 8, 15, 16, 17, 31, 32, 33, 64)
+    few = (1, 2, 7, 8, 15, 16, 17, 31, 32, 33)
     wide = (512, 1023, 1024, 1535, 1536, 2048, 4095, 8191, 8192, 16384)
     deep = (512, 1023, 1024, 1791, 1792, 2047, 2048, 4096, 5041, 8192, 16384, 65536)
     for f in few:
@@ -43,6 +88,27 @@ def test_rule_and_its_limits(dtype):
                     assert ks.select(dtype, M, N, K, 2, tA, tB) == int(ks.tune_predict(
                         ks.get_selector(ks.BF16), ks.features(M, N, K, 2, tA, tB)[None])[0])
     assert {(27, 38), (13, 38), (39, 38), (38, 27), (13, 27)} <= set(seen)
+
+
+def test_calls_without_scratch_keep_what_gains_unsplit():
+    ptr = 1 << 20                                                        # never dereferenced
+
+    def plan(M, N, K):
+        return ks.gemm_plan(ks.BF16, -1, 0, 1, M, N, K, 1.0, ptr, K, ptr, K, 0.0, ptr, N)["kernel_id"]
+    try:
+        for (M, N, K), without in (((6, 6163, 5041), 38), ((12, 3000, 2100), 13), ((5000, 7, 2100), 13), ((8192, 1, 8192), 38)):
+            ks.set_workspace(None)
+            assert plan(M, N, K) == without, (M, N, K)
+            ks.set_workspace(ptr, 256 << 20)
+            assert plan(M, N, K) == ks.select(ks.BF16, M, N, K, 1, 0, 1) == (38 if N < M else 27), (M, N, K)
+    finally:
+        ks.set_workspace(None)
+
+
+def test_tiles_that_sizes_fit():
+    for dtype, M, N, K, batch, tA, tB, was, now in CASES:
+        got = int(ks.tune_predict(ks.get_selector(dtype), ks.features(M, N, K, batch, tA, tB)[None])[0])
+        assert (got, ks.select(dtype, M, N, K, batch, tA, tB)) == (was, now), (dtype, M, N, K, batch, tA, tB)
 
 
 def test_a_callers_tree_is_followed():
