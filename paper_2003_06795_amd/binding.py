@@ -207,7 +207,7 @@ def _bind_call():
 
 
 def gemm_f32(transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, batch=1, strideA=0,
-            strideB=0, strideC=0, stream=None):
+             strideB=0, strideC=0, stream=None):
     L = _lib or lib()
     rc = _call(L.entries["ks_gemm_f32"], 0, 0, 0, transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, batch,
                strideA, strideB, strideC, stream, None, 0)
@@ -218,7 +218,7 @@ def gemm_f32(transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, batch
 
 
 def gemm_bf16(transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, batch=1, strideA=0,
-             strideB=0, strideC=0, stream=None):
+              strideB=0, strideC=0, stream=None):
     L = _lib or lib()
     rc = _call(L.entries["ks_gemm_bf16"], 0, 0, 0, transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, batch,
                strideA, strideB, strideC, stream, None, 0)
@@ -229,7 +229,7 @@ def gemm_bf16(transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, batc
 
 
 def gemm_f16(transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, batch=1, strideA=0,
-            strideB=0, strideC=0, stream=None):
+             strideB=0, strideC=0, stream=None):
     L = _lib or lib()
     rc = _call(L.entries["ks_gemm_f16"], 0, 0, 0, transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, batch,
                strideA, strideB, strideC, stream, None, 0)
@@ -240,7 +240,7 @@ def gemm_f16(transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, batch
 
 
 def gemm_f16_with_kernel(kernel_id, transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc,
-                        batch=1, strideA=0, strideB=0, strideC=0, stream=None):
+                         batch=1, strideA=0, strideB=0, strideC=0, stream=None):
     L = _lib or lib()
     rc = _call(L.entries["ks_gemm_f16_with_kernel"], 1, 0, kernel_id, transA, transB, M, N, K, alpha, A, lda, B, ldb, beta,
                C, ldc, batch, strideA, strideB, strideC, stream, None, 0)
@@ -251,7 +251,7 @@ def gemm_f16_with_kernel(kernel_id, transA, transB, M, N, K, alpha, A, lda, B, l
 
 
 def gemm_f32_with_kernel(kernel_id, transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc,
-                        batch=1, strideA=0, strideB=0, strideC=0, stream=None):
+                         batch=1, strideA=0, strideB=0, strideC=0, stream=None):
     L = _lib or lib()
     rc = _call(L.entries["ks_gemm_f32_with_kernel"], 1, 0, kernel_id, transA, transB, M, N, K, alpha, A, lda, B, ldb, beta,
                C, ldc, batch, strideA, strideB, strideC, stream, None, 0)
@@ -262,7 +262,7 @@ def gemm_f32_with_kernel(kernel_id, transA, transB, M, N, K, alpha, A, lda, B, l
 
 
 def gemm_bf16_with_kernel(kernel_id, transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc,
-                         batch=1, strideA=0, strideB=0, strideC=0, stream=None):
+                          batch=1, strideA=0, strideB=0, strideC=0, stream=None):
     L = _lib or lib()
     rc = _call(L.entries["ks_gemm_bf16_with_kernel"], 1, 0, kernel_id, transA, transB, M, N, K, alpha, A, lda, B, ldb, beta,
                C, ldc, batch, strideA, strideB, strideC, stream, None, 0)
