@@ -128,8 +128,8 @@ struct InterleaveHint {
 // at or behind the step, or the step of a row-contiguous one ends before the last k (a chunk that
 // hangs over the right edge of row k then reads the beginning of row k + 1, and what it gets belongs to
 // rows of C that do not exist).  Rows beyond `limit` are clamped to valid ones for the same reason.
-// load_edge() is for the steps that are left, at most one for all but very narrow operands: it
-// reads inside the matrix only, and k beyond the end read as zero.
+// load_edge_back() / load_edge() are for the steps that are left, at most one for all but very narrow operands: they
+// read inside the matrix only, and k beyond the end read as zero.
 // load_units() serves any step of a K-contiguous operand whose K is a multiple of eight, with a test per chunk
 // (the UNITS form of the kernel).
 template <int ROWS, int BK, int NT, bool KC, int F>
@@ -169,6 +169,43 @@ struct Bf16Staging {
             uintx4 v = {0u, 0u, 0u, 0u};
             if (has(tid, j) && (tid + j * NT) % CPR * 8 < kLeft) v = load16_any(src[j] + advance);
             reg[j] = v;
+        }
+    }
+
+    // load_edge() of an operand with at least eight elements along the contiguous direction: a chunk over the end is read
+    // from further back, whole, and fit_edge() moves what exists of it to the front.  No branch, so the loads of a step wait
+    // for memory once and not, chunk by chunk, for the elements of those over the end (every wave has some where the
+    // operand is K-contiguous).  261 drawn calls on this path 0.92 of the time with the lighter binding, 0.90 in NN and NT, 0.94 in TN and
+    // TT: 1000 x 777 x 1509 NN 19.6 -> 17.9 us, 108 x 79 x 6085 NT in 39 partitions 10.5 -> 7.4; where few chunks are over the end the moving
+    // shows (517 x 2936 x 152 TN 7.25 -> 7.5, kernel 7.8 -> 8.0).
+    __device__ __forceinline__ static void load_edge_back(uintx4 (&reg)[PER], const uint16_t *base, long long ld, int row0,
+                                                          int limit, int k0, int kEnd, int tid) {
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            const int L = tid + j * NT, outer = L / CPR, c = L % CPR;
+            const int line = KC ? min(row0 + outer, limit - 1) : min(k0 + outer, kEnd - 1);
+            const int at = KC ? min(k0 + c * 8, kEnd - 8) : min(row0 + c * 8, limit - 8);
+            if (has(tid, j)) reg[j] = load16_any(base + (long long)line * ld + at);
+        }
+    }
+    __device__ __forceinline__ static void fit_edge(uintx4 (&reg)[PER], int row0, int limit, int k0, int kEnd, int tid) {
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            const int L = tid + j * NT, outer = L / CPR, c = L % CPR;
+            if constexpr (!KC)
+                if (row0 + ROWS <= limit) {               // no chunk of the tile hangs over
+                    reg[j] = k0 + outer < kEnd ? reg[j] : uintx4{0u, 0u, 0u, 0u};
+                    continue;
+                }
+            const int left = KC ? kEnd - (k0 + c * 8) : k0 + outer < kEnd ? limit - (row0 + c * 8) : 0;
+            const int drop = 8 - max(0, min(left, 8)), b = 16 * (drop & 3);     // elements in front that are not the chunk's
+            unsigned long long lo = reg[j][0] | (unsigned long long)reg[j][1] << 32;
+            unsigned long long hi = reg[j][2] | (unsigned long long)reg[j][3] << 32;
+            if (drop & 4) { lo = hi; hi = 0; }
+            lo = lo >> b | (hi << 1) << (63 - b);
+            hi >>= b;
+            if (drop & 8) lo = hi = 0;
+            reg[j] = uintx4{(unsigned)lo, (unsigned)(lo >> 32), (unsigned)hi, (unsigned)(hi >> 32)};
         }
     }
 
@@ -214,7 +251,7 @@ struct Bf16Staging {
 // MFMAs against 1 - 2 us from memory.  Two K-steps are therefore in flight where two sets of staging
 // registers of at most 32 fit beside at most 64 accumulators, one otherwise.  Measured against the
 // element-wise loads (two bytes per lane, transposed in registers where row-contiguous) that this form
-// replaced: fp16 1000 x 777 x 1509 NN 116 -> 19.6 us, bf16 5120 x 6528 x 2560 NT with odd rows 1312 ->
+// replaced: fp16 1000 x 777 x 1509 NN 116 -> 19.6 us (17.9 since the last step reads back), bf16 5120 x 6528 x 2560 NT with odd rows 1312 ->
 // 303 us (0.57 PFLOP/s), 4959 x 2007 x 1325 TN 713 -> 70 us.
 //
 // UNITS (both operands K-contiguous, K a multiple of eight): one loop of one kind of step, the next one in
@@ -281,9 +318,18 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) void gemm_bf16_kernel(c
             lb.load(b, t * bStep, tid);
         }
     };
+    const bool backA = (AKC ? p.K : p.M) >= 8, backB = (BKC ? p.K : p.N) >= 8;
     auto load_edge = [&](int t, uintx4 (&a)[LoadA::PER], uintx4 (&b)[LoadB::PER]) {
-        LoadA::load_edge(a, Ab, p.lda, row0, p.M, kBegin + t * BK, kEnd, tid);
-        LoadB::load_edge(b, Bb, p.ldb, col0, p.N, kBegin + t * BK, kEnd, tid);
+        const int k0 = kBegin + t * BK;
+        if (backA && backB) {
+            LoadA::load_edge_back(a, Ab, p.lda, row0, p.M, k0, kEnd, tid);
+            LoadB::load_edge_back(b, Bb, p.ldb, col0, p.N, k0, kEnd, tid);
+            LoadA::fit_edge(a, row0, p.M, k0, kEnd, tid);
+            LoadB::fit_edge(b, col0, p.N, k0, kEnd, tid);
+        } else {
+            LoadA::load_edge(a, Ab, p.lda, row0, p.M, k0, kEnd, tid);
+            LoadB::load_edge(b, Bb, p.ldb, col0, p.N, k0, kEnd, tid);
+        }
     };
     auto compute = [&](const char *as, const char *bs) {
 #pragma unroll
