@@ -499,7 +499,10 @@ bool copies_pay(int64_t M, int64_t N, int64_t K, size_t bytes) {
 }
 
 // The reduction pass of a split-K launch.  Lanes share the partitions of an entry, two or more to a group, while that
-// leaves fewer than 2^17 of them, eight waves a compute unit: with more the reads fill the memory pipe by themselves.
+// leaves fewer than 2^17 of them, eight waves a compute unit, or 2^16 where a lane reads one float: with more the reads fill the
+// memory pipe by themselves.  240 split calls against 2^17 for both: 0.997 in the mean, 23 faster by more than 1.5 %, nearly all
+// of single floats (86 x 199 x 8704 in 17 partitions 0.93), three slower (158 x 257 x 18688 1.03); sixteen bytes a lane were level or
+// slower with 2^16 (256 x 256 x 65536 19.6 -> 20.2 us).
 int launch_reduce(const GemmParams &p, bool vecC, hipStream_t stream) {
     // the kernel counts rows in 32 bits: all batch items in one launch, or one each
     const bool each = (int64_t)p.batch * p.M >= (1LL << 31);
@@ -516,7 +519,7 @@ int launch_reduce(const GemmParams &p, bool vecC, hipStream_t stream) {
     const bool vec = p.N % 4 == 0 && aligned(p.ws, 16);
     const int64_t units = vec ? p.N / 4 : p.N;
     int logParts = 0;
-    while (logParts < 3 && (units * rows << logParts) < (1 << 17) && p.splitK >= 4 << logParts) ++logParts;
+    while (logParts < 3 && (units * rows << logParts) < (vec ? 1 << 17 : 1 << 16) && p.splitK >= 4 << logParts) ++logParts;
     r.perGroup = (p.splitK + (1 << logParts) - 1) >> logParts;
     r.logCols = 0;
     while (r.logCols < 6 && r.logCols < 8 - logParts && (1 << r.logCols) < units) ++r.logCols;   // a wave's row
