@@ -356,8 +356,8 @@ int ks_set_split_partitions(int partitions);
  * of 128) with zeros, and the member runs on the copies, with the same order along K as on the operands.  Scratch is what
  * the call brings (ks_gemm_with_workspace: any member) or shares (the registered workspace and the static array: members
  * with split_k != 1 only; the others never touch them).  mode == -1 (the default) does so where a cost estimate by
- * flops and bytes says it pays and the scratch holds the copies beside the partial sums of a fixed split; 0 never; 1
- * wherever it can be done (for testing and tuning).  Not thread-safe. */
+ * flops and bytes says it pays and the scratch holds the copies beside the partial sums of the K partitions that the
+ * call takes without them; 0 never; 1 wherever the scratch allows (for testing and tuning).  Not thread-safe. */
 int ks_set_operand_copies(int mode);
 
 /* Measurement aid: copies `bytes` (a multiple of 16; both device pointers 16-byte aligned) with a

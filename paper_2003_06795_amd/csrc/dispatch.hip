@@ -546,6 +546,19 @@ struct Workspace {
 };
 Workspace registered_ws() { return Workspace{g_ws, g_wsBytes}; }
 
+// K partitions of a member whose count is chosen per call: as many as fill the device, at least two K-steps
+// each, and no more than the scratch can hold (1 = the plain single-kernel form)
+int64_t partitions(const InstanceDesc *d, bool f32, int64_t M, int64_t N, int64_t K, int64_t batch, Workspace w) {
+    const int64_t tiles = ((M + d->bm - 1) / d->bm) * ((N + d->bn - 1) / d->bn) * batch;
+    const int64_t steps = ((K + d->bk - 1) / d->bk + d->kw - 1) / d->kw;
+    if (!w.ptr) return 1;
+    int64_t s = auto_split(d, tiles, steps, f32);
+    if (g_splitForced > 0) s = g_splitForced > 1 && 2 * (int64_t)g_splitForced > steps ? (steps / 2 > 1 ? steps / 2 : 1) : g_splitForced;
+    const size_t per = (size_t)batch * (size_t)M * (size_t)N * sizeof(float);
+    if ((size_t)s * per > w.bytes) s = (int64_t)(w.bytes / per);
+    return s < 1 ? 1 : s;
+}
+
 int remainder_member(int dtype, int64_t M, int64_t N, int64_t K, int64_t batch, int tA, int tB, Workspace w);
 
 int run_ws(Workspace wsp, int dtype, int id, int transA, int transB, int64_t M, int64_t N, int64_t K, float alpha,
@@ -623,6 +636,8 @@ int run_ws(Workspace wsp, int dtype, int id, int transA, int transB, int64_t M, 
     // 16-bit operands that the direct-to-LDS path cannot read as they are: copies that it can (OperandCopy), where the
     // scratch holds them and they pay.  The member, its order along K and so its bits stay the same.  The
     // registered workspace is for members that may use it (those with split_k == 1 never do).
+    // Partial sums come first: without their partitions a few tiles leave the device idle (1024 x 1024 x 64001 NT in
+    // 256 MiB would run 16 work-groups instead of 256), which no alignment makes up for.
     if (dtype != KS_F32 && !copied && batch == 1 && g_forceGeneric == 0 && g_operandCopies != 0 && wsp.ptr &&
         (own || d->splitK != 1)) {
         const bool akc = transA == 0, bkc = transB == 1;
@@ -636,10 +651,13 @@ int run_ws(Workspace wsp, int dtype, int id, int transA, int transB, int64_t M, 
         const int64_t chunksA = copyA ? rows_of(akc, M) * length_of(akc, M) / 8 : 0;
         const int64_t chunksB = copyB ? rows_of(bkc, N) * length_of(bkc, N) / 8 : 0;
         const size_t bytes = (size_t)(chunksA + chunksB) * 16;
-        const size_t split = d->splitK > 1 ? (size_t)d->splitK * (size_t)M * (size_t)N * sizeof(float) : 0;
+        auto holds = [&] {
+            const int64_t s = d->splitK > 0 ? d->splitK : partitions(d, false, M, N, K, 1, wsp);
+            return wsp.bytes >= bytes + (s > 1 ? (size_t)s * (size_t)M * (size_t)N * sizeof(float) : 0) + 16;
+        };
         const bool reach = length_of(akc, M) <= (1LL << 22) && length_of(bkc, N) <= (1LL << 22);
-        if ((copyA || copyB) && reach && chunksA + chunksB < (1LL << 31) && wsp.bytes >= bytes + split + 16 &&
-            (g_operandCopies > 0 || copies_pay(M, N, K, bytes))) {
+        if ((copyA || copyB) && reach && chunksA + chunksB < (1LL << 31) &&
+            (g_operandCopies > 0 || copies_pay(M, N, K, bytes)) && holds()) {
             // at the end of the scratch: partial sums stay at its beginning
             char *const end = static_cast<char *>(wsp.ptr) + wsp.bytes;
             char *const at = end - bytes - reinterpret_cast<uintptr_t>(end - bytes) % 16;
@@ -673,17 +691,7 @@ int run_ws(Workspace wsp, int dtype, int id, int transA, int transB, int64_t M, 
     p.tilesN = (int)((N + d->bn - 1) / d->bn);
     const int64_t kTiles = (K + d->bk - 1) / d->bk;
     p.splitK = d->splitK;
-    if (d->splitK == 0) {
-        // automatic split: as many K partitions as fill the device, at least two K-steps each,
-        // and no more than the registered workspace can hold (1 = the plain single-kernel form)
-        const int64_t steps = (kTiles + d->kw - 1) / d->kw;
-        int64_t s = auto_split(d, (int64_t)p.tilesM * p.tilesN * batch, steps, dtype == KS_F32);
-        if (g_splitForced > 0) s = g_splitForced > 1 && 2 * (int64_t)g_splitForced > steps ? (steps / 2 > 1 ? steps / 2 : 1) : g_splitForced;
-        const size_t per = (size_t)batch * (size_t)M * (size_t)N * sizeof(float);
-        if (!wsp.ptr) s = 1;
-        else if ((size_t)s * per > wsp.bytes) s = (int64_t)(wsp.bytes / per);
-        p.splitK = s < 1 ? 1 : (int)s;
-    }
+    if (d->splitK == 0) p.splitK = (int)partitions(d, dtype == KS_F32, M, N, K, batch, wsp);
     p.kChunk = (int)(((kTiles + p.splitK - 1) / p.splitK) * d->bk);
     p.alpha = alpha; p.beta = beta;
 
