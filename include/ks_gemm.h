@@ -30,8 +30,11 @@
  *   - Threads: the compute entry points keep no per-call host state and may be
  *     called from several host threads (each on its own stream) at once, with
  *     one exception: the registered workspace is a single buffer, so two GEMMs
- *     that both run a split-K member must not be in flight together (same
- *     stream, or ordered by the caller); ks_gemm_with_workspace takes the
+ *     that both write it must not be in flight together (same stream, or
+ *     ordered by the caller).  Those are the launches for which ks_gemm_plan
+ *     reports split_k > 1, tail_split, divided_tiles or operand_copies; any call
+ *     on a 16-bit member with split_k != 1 may be one, also when it takes one
+ *     partition.  ks_gemm_with_workspace takes the
  *     scratch per call and has no such limit.  ks_set_workspace,
  *     ks_set_fast_path, ks_set_tiles_per_workgroup, ks_set_balanced_groups,
  *     ks_set_tail_split, ks_set_split_partitions, ks_set_operand_copies
@@ -234,9 +237,9 @@ int ks_gemm_with_workspace(int dtype, int kernel_id, int transA, int transB, int
 typedef struct {
     int32_t kernel_id;            /* the member that runs (after selection and the no-workspace fallback) */
     int32_t split_k;              /* K partitions taken; > 1 means partial-sum kernel + reduction pass */
-    int32_t path;                 /* 0: the member's general kernel, or aligned copies of the operands
-                                     (ks_set_operand_copies); 1: direct-to-LDS 16-bit kernel on the operands as they
-                                     are; 2: the same in its two-groups-of-waves form */
+    int32_t path;                 /* how the operands are read as they are.  0: by the member's general kernel, or not
+                                     at all (operand_copies); 1: direct-to-LDS 16-bit kernel; 2: the same in its
+                                     two-groups-of-waves form */
     int32_t vector_loads;         /* 16-byte global accesses are legal for these operands */
     int32_t grid_3d;              /* launched (tilesN, tilesM, batch * split_k) instead of one-dimensional */
     int32_t tiles_per_workgroup;  /* > 1: the multi-tile form of the large fp32 members */
@@ -251,6 +254,9 @@ typedef struct {
                                      last k_remainder of K run first through the member's general kernel
                                      (applying alpha, beta and the bias), then the whole K-steps run on the
                                      direct-to-LDS path with beta = 1, which the other fields describe */
+    int32_t operand_copies;       /* 1: A, 2: B, 3: both are first copied to the end of the scratch, which the call so
+                                     writes whatever split_k says; the member's direct-to-LDS kernel (two groups of
+                                     waves where it has that form) runs on the copies (ks_set_operand_copies) */
 } ks_launch_plan_t;
 int ks_gemm_plan(int dtype, int kernel_id, int transA, int transB, int64_t M, int64_t N, int64_t K,
                  float alpha, const void *A, int64_t lda, const void *B, int64_t ldb,
@@ -403,8 +409,9 @@ int ks_bf16_ablation(int mode, const uint16_t *A_device, const uint16_t *B_devic
  * Split-K kernels (K partitioned over work-groups, partial sums reduced in a fixed order, no
  * atomics) need split_k * batch * M * N floats of scratch.  The caller registers one device
  * buffer per process (at least 4-byte aligned; 16-byte alignment lets the reduction pass use
- * 16-byte accesses); NULL / 0 unregisters.  Kernels with split_k == 1 never touch it; 16-bit ones with
- * another split_k keep aligned copies of large operands in what is left of it (ks_set_operand_copies). */
+ * 16-byte accesses); NULL / 0 unregisters.  Kernels with split_k == 1 touch it in their balanced form
+ * only (fp32); 16-bit ones with another split_k keep aligned copies of large operands in what is left of it
+ * (ks_set_operand_copies). */
 int ks_set_workspace(void *device_ptr, size_t bytes);
 /* Bytes the kernel would like for this output size (for split_k == 0 the most it can use: the
  * partial sums of the largest partition count it may choose, or, for a 16-bit member that launches

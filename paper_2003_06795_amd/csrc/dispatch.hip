@@ -676,7 +676,11 @@ int run_ws(Workspace wsp, int dtype, int id, int transA, int transB, int64_t M, 
             const int rc = run_ws(rest, dtype, id, transA, transB, M, N, Kc, alpha, copyA ? toA : A,
                                   copyA ? length_of(akc, M) : lda, copyB ? toB : B, copyB ? length_of(bkc, N) : ldb, beta, C,
                                   ldc, 1, 0, 0, 0, stream, bias, out16, planOnly, own, true);
-            if (rc == KS_OK && planOnly) planOnly->path = planOnly->vector_loads = 0;
+            if (rc == KS_OK && planOnly) {               // the operands as they are, and that they are copied
+                planOnly->path = 0;
+                planOnly->vector_loads = vector_operands(8, akc, bkc, M, N, K, A, lda, B, ldb, 1, 0, 0) ? 1 : 0;
+                planOnly->operand_copies = (copyA ? 1 : 0) + (copyB ? 2 : 0);
+            }
             return rc;
         }
     }

@@ -37,3 +37,24 @@ def test_copies_leave_the_partitions_their_scratch(plan):
             assert has["split_k"] == without["split_k"], (M, N, K, tA, tB, size, without, has)
             split += without["split_k"] > 1
     assert split > 300
+
+
+def test_the_plan_reports_copies(plan):
+    """A call that writes the scratch says so, also in one partition: beside split_k, tail_split stands operand_copies."""
+    size = (0, 0, 4096, 4000, 4100)
+    both = plan(-1, 256 << 20, *size, kid=45)
+    assert (both["operand_copies"], both["split_k"], both["path"], both["vector_loads"]) == (3, 1, 0, 0)
+    assert plan(0, 256 << 20, *size, kid=45)["operand_copies"] == 0
+    assert plan(-1, 0, *size, kid=45)["operand_copies"] == 0                       # no scratch
+    assert plan(-1, 32 << 20, *size, kid=45)["operand_copies"] == 0                # too little
+    assert plan(1, 256 << 20, *size, kid=13)["operand_copies"] == 0                # split_k == 1: never the registered scratch
+    assert plan(-1, 256 << 20, *size, kid=-1, dtype=ks.F32)["operand_copies"] == 0
+    # one operand: whole K-steps, and only the rows of one are no multiple of eight
+    def rows(lda, ldb):
+        return ks.gemm_plan(ks.BF16, 45, 0, 1, 4096, 4000, 4096, 1.0, PTR, lda, PTR, ldb, 0.0, PTR, 4000)
+    ks.set_operand_copies(-1)
+    ks.set_workspace(PTR, 256 << 20)
+    assert [rows(4096 + a, 4096 + b)["operand_copies"] for a, b in ((0, 0), (3, 0), (0, 3), (8, 8))] == [0, 1, 2, 0]
+    # sixteen-byte accesses are legal, K is no whole number of half K-steps: what the operands admit is still reported
+    got = ks.gemm_plan(ks.BF16, 45, 0, 1, 2048, 2048, 8168, 1.0, PTR, 8168, PTR, 8168, 0.0, PTR, 2048)
+    assert (got["operand_copies"], got["vector_loads"], got["k_remainder"]) == (3, 1, 0)
