@@ -127,8 +127,8 @@ typedef struct {
  * ks_gemm_* picks the kernel with ks_select (Section IV) and is bit-identical to
  * ks_gemm_*_with_kernel(ks_select(...), ...) whenever the registered workspace can hold the
  * chosen kernel's split-K partial sums; if it cannot (or none is registered) the instance with
- * the same tiles and split_k == 1 runs instead, and for 16-bit products of up to 32 rows or 16 columns without any scratch the
- * member that gains without a K split.  A, B, C: device pointers.
+ * the same tiles and split_k == 1 runs instead, and for 16-bit products of up to 32 rows or 16 columns without scratch for the
+ * K partitions that the chosen member would take, the member that gains without them.  A, B, C: device pointers.
  * bf16 operands are raw bfloat16 bit patterns; accumulation and C are fp32.
  * Degenerate sizes: M, N or batch == 0 -> success, nothing launched; K == 0 -> C = beta*C.
  * Errors: KS_ERR_INVALID_ARG (see ks_status), KS_ERR_UNSUPPORTED when M, N or K >= 2^31 - 512 or a leading dimension >= 2^31,

@@ -953,14 +953,22 @@ extern "C" size_t ks_workspace_bytes_needed(int dtype, int kernel_id, int64_t M,
     transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, batch, strideA, strideB, strideC, \
         static_cast<hipStream_t>(stream)
 
-// Kernel for the selecting entry points: the choice of ks_select (without scratch: without the rules that count on a K
-// split, selector.cpp), unless that is a split-K instance and the registered workspace cannot hold its partial sums; then the instance with the same tiles
-// and no split is used instead, so that a caller who never registers a workspace is still served.
+// Kernel for the selecting entry points: the choice of ks_select, unless the scratch does not hold its partial sums.
+// Where a rule counts on a K split (selector.cpp), it is left out when the scratch holds fewer partitions than the member
+// takes by its estimate, which is what the rule was timed with.  For an instance with a fixed split the one with the
+// same tiles and no split is used instead, so that a caller who never registers a workspace is still served.
 static int select_checked(int dtype, int64_t M, int64_t N, int64_t K, int64_t batch, int tA, int tB,
                           Workspace w = registered_ws()) {
-    const int id = ks::select_member(dtype, M, N, K, batch, tA, tB, w.ptr != nullptr);
+    int id = ks::select_member(dtype, M, N, K, batch, tA, tB, true);
     if (id < 0) return id;
     const InstanceDesc *d = desc_of(dtype, id);
+    const int unsplit = ks::select_member(dtype, M, N, K, batch, tA, tB, false);
+    if (unsplit != id && d && d->splitK == 0 &&
+        (!w.ptr || partitions(d, dtype == KS_F32, M, N, K, batch, w) <
+                       partitions(d, dtype == KS_F32, M, N, K, batch, Workspace{w.ptr, SIZE_MAX}))) {
+        id = unsplit;
+        d = desc_of(dtype, id);
+    }
     if (!d || d->splitK <= 1 || M <= 0 || N <= 0 || batch <= 0) return id;
     const size_t need = (size_t)d->splitK * (size_t)batch * (size_t)M * (size_t)N * sizeof(float);
     if (w.ptr && w.bytes >= need) return id;

@@ -45,7 +45,9 @@ int64_t sat_mul(int64_t a, int64_t b) {
 // The trees split on sizes; what a call costs steps with its tiles per compute unit, which no threshold of
 // theirs can follow.  Where both sides were timed (operands rotated through three buffers) the choice is
 // corrected, from the sizes alone: every caller of ks_select and every selecting entry point gets the same
-// member, whatever the alignment of its operands and its scratch.  A caller's own tree is followed as it is.
+// member, whatever the alignment of its operands, and whatever its scratch but for the rules that count on a K split
+// (by_few_rows_or_columns): a call whose scratch does not hold the partitions gets what it would without them.  A caller's own
+// tree is followed as it is.
 struct Tile {
     int id, bm, bn, bk;
 };
@@ -130,7 +132,7 @@ int by_tiles_per_unit(int dtype, int id, int64_t M, int64_t N, int64_t K, int64_
 //   up to 32 rows: 64 x 64 tiles for 64 x 16 ones, four times the work-groups over the same rows, and for three K-steps
 //     in flight, which cost a resident work-group (1354 at 0.58: 6 x 6163 x 5041 NT 57 -> 28 us, 13 x 3909 x 12757 NN 39 ->
 //     29; from 1536 columns on, below some at 1.15); for 64 x 16 without a split up to 16 rows and 8192 columns, K >= 2048 (160 at 0.59).
-//   Those that gain by a K split stay with the tree's member in a call without scratch: unsplit, 27 is 1.07 - 1.32 times
+//   Those that gain by a K split stay with the tree's member in a call without scratch for it: unsplit, 27 is 1.07 - 1.32 times
 //   as slow there as 38 and 13.
 int by_few_rows_or_columns(int dtype, int id, int64_t M, int64_t N, int64_t K, int64_t batch, int transA, int transB,
                            bool scratch) {
@@ -221,7 +223,7 @@ extern "C" int ks_features(int64_t M, int64_t N, int64_t K, int64_t batch, int t
 }
 
 namespace ks {
-// The member for these sizes; without scratch the rules that count on a K split are left out.
+// The member for these sizes; without scratch (for the partitions it takes) the rules that count on a K split are left out.
 int select_member(int dtype, int64_t M, int64_t N, int64_t K, int64_t batch, int transA, int transB, bool scratch) {
     if (dtype == KS_F16) dtype = KS_BF16;          // the fp16 form runs the 16-bit family with its tree
     if (dtype != KS_F32 && dtype != KS_BF16) return KS_ERR_INVALID_ARG;
