@@ -167,27 +167,40 @@ int by_few_rows_or_columns(int dtype, int id, int64_t M, int64_t N, int64_t K, i
 //   batches: 32 columns or fewer on 32 x 64 tiles -> 32 x 32 (31 at 0.83, none slower); items that fill less than nine
 //     tenths of their 16 x 16 tiles -> 32 x 32 (118 at 0.89, twelve over 1.03: 1.12); 32 x 32 x 16 -> 64 x 64 from 9036 of the
 //     former on (24 at 0.88).
+// A larger tile is taken where it fits: its padded output against that of the tile it replaces is limited.  Drawn again
+//   (1017 problems of other seeds and wider ranges), time of the larger tile by that ratio, beyond the limit and up to it:
+//   128 x 64 and 128 x 128 -> 256 x 256 1.25: 1.08 (74 problems, worst 2.08: 93709 x 62 x 2633), 0.82 (137, 1.18)
+//   64 x 64 -> 128 x 128 1.15: 1.00 (90, worst 1.36: 152 x 18008 x 2640), 0.80 (48, 1.10)
+//   32 x 32 x 32 -> 64 x 64 x 8 1.34: 1.03 (44, worst 1.49: 179963 x 20 x 59), 0.83 (96, 1.09)
+//   batches 32 x 32 x 16 -> 64 x 64 1.25: 1.20 (72, worst 1.93: 82 x 21 x 65, 8910 of them), 0.84 (48, 1.09)
+//   batches 16 x 16 -> 32 x 32 1.34: 1.03 (29, worst 1.25: 37 x 42 x 61), 0.84 (91, 1.10)
 // leaf: what the tree says
 int by_tile_fit(int dtype, int leaf, int id, int64_t M, int64_t N, int64_t K, int64_t batch, int transA, int transB) {
     if (M <= 0 || N <= 0 || K <= 0 || batch <= 0 || M > (1 << 28) || N > (1 << 28) || batch > (1 << 28)) return id;
     const double entries = (double)M * (double)N, products = entries * (double)K;
+    auto padded = [&](int member) {
+        const Tile &t = dtype == KS_F32 ? kTilesF32[member] : kTiles16[member];
+        return (double)((M + t.bm - 1) / t.bm * t.bm) * (double)((N + t.bn - 1) / t.bn * t.bn);
+    };
+    auto fits = [&](int member, double limit) { return padded(member) <= limit * padded(id); };
     auto tiles = [&](int64_t e) { return (double)((M + e - 1) / e) * (double)((N + e - 1) / e); };
     if (dtype != KS_F32) {
         if (batch != 1) return id;
         const bool ragged = K % 64 != 0 || (transA != 0 && M % 8 != 0) || (transB == 0 && N % 8 != 0);
         const double large = tiles(256);
-        if (kept(kKept16, k16Large) && large >= 128 &&
+        if (kept(kKept16, k16Large) && large >= 128 && fits(k16Large, 1.25) &&
             ((id == k16Narrow && (products >= 1.5e10 || (ragged && products >= 1e10))) ||
              (id == k16Wide && ragged && products >= 3e10 && large < 512)))
             return k16Large;
-        if (id == k16Square && kept(kKept16, k16TwoGroups) && tiles(128) >= 128 && entries >= 2.1e6) return k16TwoGroups;
+        if (id == k16Square && kept(kKept16, k16TwoGroups) && tiles(128) >= 128 && entries >= 2.1e6 && fits(k16TwoGroups, 1.15))
+            return k16TwoGroups;
         return id;
     }
     if (batch == 1) {
         const bool odd = (transA != 0 ? M : K) % 4 != 0 || (transB != 0 ? K : N) % 4 != 0;
         if (!odd) return id;
         if (kept(kKeptF32, kF32ShortK) && ((leaf == kF32Small && K <= 24 && entries >= 1 << 20) ||
-                                           (id == kF32Halves && K <= 71 && entries >= 2.1e6)))
+                                           (id == kF32Halves && K <= 71 && entries >= 2.1e6 && fits(kF32ShortK, 1.34))))
             return kF32ShortK;
         if (kept(kKeptF32, kF32Halves) && ((id == kF32GroupsLarge && K < 576 && tiles(16) < 6038) ||
                                            (id == kF32Groups && K >= 1226 && (double)(M + N) * (double)K >= 1.65e6)))
@@ -196,9 +209,9 @@ int by_tile_fit(int dtype, int leaf, int id, int64_t M, int64_t N, int64_t K, in
     }
     if (kept(kKeptF32, kF32Halves) &&
         ((id == kF32Tall && N <= 32) || (id == kF32Sixteen && M >= 17 && N >= 17 && entries < 0.9 * 256.0 * tiles(16) &&
-                                         (M % 8 != 0 || N % 8 != 0 || K % 8 != 0))))
+                                         (M % 8 != 0 || N % 8 != 0 || K % 8 != 0) && fits(kF32Halves, 1.34))))
         return kF32Halves;
-    if (id == kF32Half && tiles(32) * (double)batch >= 9036 && kept(kKeptF32, kF32Small)) return kF32Small;
+    if (id == kF32Half && tiles(32) * (double)batch >= 9036 && kept(kKeptF32, kF32Small) && fits(kF32Small, 1.25)) return kF32Small;
     return id;
 }
 

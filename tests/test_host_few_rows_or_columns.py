@@ -133,6 +133,31 @@ def test_tiles_that_sizes_fit():
         assert (got, ks.select(dtype, M, N, K, batch, tA, tB)) == (was, now), (dtype, M, N, K, batch, tA, tB)
 
 
+# (type, M, N, K, batch, transA, transB, the tree's member): sizes that the larger tile pads to much more
+PADDED = [
+    (ks.F32, 24, 24, 256, 12000, 0, 0, 21),
+    (ks.F32, 29, 112, 49, 7846, 0, 1, 21),
+    (ks.F32, 91, 28, 65, 3761, 1, 0, 21),
+    (ks.F32, 71, 135, 51, 1856, 1, 0, 21),
+    (ks.F32, 37, 42, 61, 327, 0, 0, 38),
+    (ks.F32, 179963, 20, 59, 1, 0, 0, 41),
+    (ks.F32, 154274, 31, 59, 1, 0, 1, 41),
+    (ks.BF16, 65536, 64, 4096, 1, 0, 0, 23),
+    (ks.BF16, 131072, 33, 4096, 1, 0, 0, 23),
+    (ks.BF16, 34831, 338, 1069, 1, 0, 0, 23),
+    (ks.BF16, 33000, 64, 2048, 1, 0, 0, 27),
+    (ks.BF16, 272, 12160, 2376, 1, 1, 1, 27),
+    (ks.BF16, 152, 18008, 2640, 1, 0, 1, 27),
+]
+
+
+@pytest.mark.parametrize("case", PADDED)
+def test_larger_tiles_only_where_they_fit(case):
+    dtype, M, N, K, batch, tA, tB, member = case
+    assert int(ks.tune_predict(ks.get_selector(dtype), ks.features(M, N, K, batch, tA, tB)[None])[0]) == member
+    assert ks.select(dtype, M, N, K, batch, tA, tB) == member
+
+
 def test_a_callers_tree_is_followed():
     leaf = np.zeros(1, dtype=ks.TREE_DTYPE)
     leaf[0] = (-1, 0, 0, 27, 0)
