@@ -153,7 +153,10 @@ int by_few_rows_or_columns(int dtype, int id, int64_t M, int64_t N, int64_t K, i
 
 // Sizes that the tables hold few of or none (they are multiples of eight and were timed on cached operands): members
 //   compared on 11491 drawn problems, whole and ragged, operands rotated through three sets.
-// 16-bit, `ragged`: no leading dimension puts these sizes on the direct-to-LDS path as they are.
+// 16-bit, `ragged`: no leading dimension puts these sizes on the direct-to-LDS path as they are.  Where K alone is no whole
+//   number of K-steps but a multiple of eight, NN, TN and TT run its whole steps there (dispatch.hip) and are not ragged: as
+//   such they took 256 x 256 tiles for 128 x 128 at 1.03 of the time (16 drawn, worst 1.18: 5720 x 3176 x 1656 TN) and for
+//   128 x 64 below 1.5e10 at 1.04 (8, worst 1.14).
 //   128 x 64 -> 256 x 256 in two groups of waves, whose ragged operands are copied where there is scratch, once half the
 //     device has such a tile: from 1.5e10 products on, ragged from 1.0e10: aligned 59 at 0.85 (worst 1.02), ragged 74 at 0.73,
 //     0.94 without scratch (1.10).  With fewer tiles only a K split pays (0.84 with scratch, 1.16 without).  128 x 128 x 64 only
@@ -186,7 +189,8 @@ int by_tile_fit(int dtype, int leaf, int id, int64_t M, int64_t N, int64_t K, in
     auto tiles = [&](int64_t e) { return (double)((M + e - 1) / e) * (double)((N + e - 1) / e); };
     if (dtype != KS_F32) {
         if (batch != 1) return id;
-        const bool ragged = K % 64 != 0 || (transA != 0 && M % 8 != 0) || (transB == 0 && N % 8 != 0);
+        const bool endOfK = K % 64 != 0 && (K % 8 != 0 || (transA == 0 && transB != 0));
+        const bool ragged = endOfK || (transA != 0 && M % 8 != 0) || (transB == 0 && N % 8 != 0);
         const double large = tiles(256);
         if (kept(kKept16, k16Large) && large >= 128 && fits(k16Large, 1.25) &&
             ((id == k16Narrow && (products >= 1.5e10 || (ragged && products >= 1e10))) ||

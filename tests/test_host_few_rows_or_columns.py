@@ -133,7 +133,8 @@ def test_tiles_that_sizes_fit():
         assert (got, ks.select(dtype, M, N, K, batch, tA, tB)) == (was, now), (dtype, M, N, K, batch, tA, tB)
 
 
-# (type, M, N, K, batch, transA, transB, the tree's member): sizes that the larger tile pads to much more
+# (type, M, N, K, batch, transA, transB, the tree's member): sizes that the larger tile pads to much more, and 16-bit
+# ones that are whole multiples of eight with an end of K of their own
 PADDED = [
     (ks.F32, 24, 24, 256, 12000, 0, 0, 21),
     (ks.F32, 29, 112, 49, 7846, 0, 1, 21),
@@ -148,6 +149,9 @@ PADDED = [
     (ks.BF16, 33000, 64, 2048, 1, 0, 0, 27),
     (ks.BF16, 272, 12160, 2376, 1, 1, 1, 27),
     (ks.BF16, 152, 18008, 2640, 1, 0, 1, 27),
+    (ks.BF16, 4592, 4248, 1640, 1, 0, 0, 7),
+    (ks.BF16, 5720, 3176, 1656, 1, 1, 0, 7),
+    (ks.BF16, 7904, 1280, 1032, 1, 1, 1, 23),
 ]
 
 
