@@ -503,6 +503,8 @@ bool copies_pay(int64_t M, int64_t N, int64_t K, size_t bytes) {
 // memory pipe by themselves.  240 split calls against 2^17 for both: 0.997 in the mean, 23 faster by more than 1.5 %, nearly all
 // of single floats (86 x 199 x 8704 in 17 partitions 0.93), three slower (158 x 257 x 18688 1.03); sixteen bytes a lane were level or
 // slower with 2^16 (256 x 256 x 65536 19.6 -> 20.2 us).
+// The groups, and with them the order of the sums, follow from the sizes alone: where N is a multiple of four and only the
+// scratch is not 16-byte aligned, lanes read one float each in the groups of the wide form.
 int launch_reduce(const GemmParams &p, bool vecC, hipStream_t stream) {
     // the kernel counts rows in 32 bits: all batch items in one launch, or one each
     const bool each = (int64_t)p.batch * p.M >= (1LL << 31);
@@ -516,10 +518,10 @@ int launch_reduce(const GemmParams &p, bool vecC, hipStream_t stream) {
     r.splitK = p.splitK;
     r.alpha = p.alpha; r.beta = p.beta;
     r.out16 = p.out16; r.vecC = vecC ? 1 : 0;
-    const bool vec = p.N % 4 == 0 && aligned(p.ws, 16);
-    const int64_t units = vec ? p.N / 4 : p.N;
+    const bool quads = p.N % 4 == 0, vec = quads && aligned(p.ws, 16);
+    const int64_t units = vec ? p.N / 4 : p.N, lanes = (quads ? p.N / 4 : p.N) * rows;
     int logParts = 0;
-    while (logParts < 3 && (units * rows << logParts) < (vec ? 1 << 17 : 1 << 16) && p.splitK >= 4 << logParts) ++logParts;
+    while (logParts < 3 && (lanes << logParts) < (quads ? 1 << 17 : 1 << 16) && p.splitK >= 4 << logParts) ++logParts;
     r.perGroup = (p.splitK + (1 << logParts) - 1) >> logParts;
     r.logCols = 0;
     while (r.logCols < 6 && r.logCols < 8 - logParts && (1 << r.logCols) < units) ++r.logCols;   // a wave's row

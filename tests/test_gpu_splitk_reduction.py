@@ -55,3 +55,22 @@ def test_bias_and_bf16_output(gpu, N, out16):
     err = np.abs(C.float().cpu().numpy().astype(np.float64) - ref)
     # the bound of the product, one fp32 rounding more, and for bf16 one step (2^-7) of the value
     assert np.all(err <= tolerance(p) + 2.0 ** -20 + (np.abs(ref) * 2.0 ** -7 if out16 else 0)), float(err.max())
+
+
+def test_bits_do_not_depend_on_where_the_scratch_lies(gpu):
+    """The scratch may be aligned to four bytes only: the same partitions, added in the same order."""
+    import torch
+    import paper_2003_06795_amd.binding as ks
+    ks.set_split_partitions(31)
+    scratch = torch.empty((8 << 20) + 16, dtype=torch.uint8, device="cuda")
+    for dtype, kid in (("f32", next(i for i in range(64) if ks.kernel_info(ks.F32, i)["split_k"] == 0)), ("bf16", 39)):
+        p = wl.make_problem(dtype, 0, 1, 130, 132, 8192, alpha=1.5, beta=-0.5, seed=99, key=5)
+        dp, got = gpu.DeviceProblem(p), []
+        for at in (0, 4, 8):
+            C = dp.C0.clone()
+            ks.gemm_with_workspace(gpu.DT[dtype], kid, p.transA, p.transB, p.M, p.N, p.K, p.alpha, dp.A, p.lda, dp.B, p.ldb,
+                                   p.beta, C, p.ldc, scratch[at:at + (8 << 20)])
+            got.append(C.cpu().numpy())
+        assert float(np.max(np.abs(got[0].astype(np.float64) - gpu.oracle_full(p)))) <= tolerance(p)
+        assert np.array_equal(got[0], got[1]) and np.array_equal(got[0], got[2]), dtype
+    ks.set_split_partitions(0)
