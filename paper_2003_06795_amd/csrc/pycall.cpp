@@ -1,6 +1,6 @@
 // Argument marshalling of the GEMM entry points for Python, in C: what binding.py does through ctypes, for the arguments
-// that GEMM calls are made of (plain integers and floats, tensors, addresses, None).  Anything else is answered with
-// NotImplemented, before any side effect but the operands' data_ptr(), and binding.py makes the call through ctypes.
+// that GEMM calls are made of (plain integers and floats, tensors, addresses, streams, None).  Anything else is answered
+// with NotImplemented, before any side effect but the operands' data_ptr(), and binding.py makes the call through ctypes.
 // ctypes converts some twenty arguments in 1.2 us, the Python around it takes as long again; a small GEMM's launch takes 2.5
 // and its kernel 3: 128^3 5.5 -> 4.4 us a call among others, 37 x 1001 x 515 with a bias 6.1 -> 5.1.
 // Host only.
@@ -11,7 +11,7 @@
 
 namespace {
 
-PyObject *g_dataPtr = nullptr;                       // "data_ptr"
+PyObject *g_dataPtr = nullptr, *g_cudaStream = nullptr;      // "data_ptr", "cuda_stream"
 PyObject *g_initialized = nullptr, *g_device = nullptr, *g_rawStream = nullptr;
 
 enum Got { OK, OTHER, ERROR };
@@ -29,8 +29,17 @@ Got integer32(PyObject *o, int &v) {
     return OK;
 }
 Got real(PyObject *o, float &v) {
-    if (!PyFloat_CheckExact(o)) return OTHER;
-    v = (float)PyFloat_AS_DOUBLE(o);
+    if (PyFloat_CheckExact(o)) {
+        v = (float)PyFloat_AS_DOUBLE(o);
+        return OK;
+    }
+    if (!PyLong_CheckExact(o)) return OTHER;
+    const double x = PyLong_AsDouble(o);
+    if (x == -1.0 && PyErr_Occurred()) {
+        PyErr_Clear();
+        return OTHER;
+    }
+    v = (float)x;
     return OK;
 }
 Got address(PyObject *o, void *&v) {
@@ -60,9 +69,18 @@ Got address(PyObject *o, void *&v) {
 Got stream_handle(PyObject *o, void *&v) {
     int64_t x = 0;
     if (o != Py_None) {
-        if (!PyLong_CheckExact(o) || integer(o, x) != OK || x < 0) return OTHER;
+        PyObject *handle = o;
+        if (PyLong_CheckExact(o)) {
+            Py_INCREF(handle);
+        } else if (!(handle = PyObject_GetAttr(o, g_cudaStream))) {
+            if (!PyErr_ExceptionMatches(PyExc_AttributeError)) return ERROR;
+            PyErr_Clear();
+            return OTHER;
+        }
+        const bool plain = PyLong_CheckExact(handle) && integer(handle, x) == OK && x >= 0;
+        Py_DECREF(handle);
         v = (void *)(intptr_t)x;
-        return OK;
+        return plain ? OK : OTHER;
     }
     if (!g_initialized) return OTHER;
     PyObject *r = PyObject_CallNoArgs(g_initialized);
@@ -129,11 +147,11 @@ PyObject *gemm(PyObject *, PyObject *const *a, Py_ssize_t n) {
     KS_GET(integer(a[SC], sC));
     KS_GET(integer(a[BYTES], bytes));
     if (!entry || bytes < 0 || form < PLAIN || form > SCRATCH) Py_RETURN_NOTIMPLEMENTED;
+    KS_GET(stream_handle(a[STREAM], stream));            // before the operands: what it does not take costs no more than that
     KS_GET(address(a[A], pa));
     KS_GET(address(a[B], pb));
     KS_GET(address(a[C], pc));
     KS_GET(address(a[EXTRA], extra));
-    KS_GET(stream_handle(a[STREAM], stream));
 #undef KS_GET
     int rc;
 #define KS_ARGS tA, tB, m, nn, k, alpha, pa, lda, pb, ldb, beta, pc, ldc
@@ -169,5 +187,6 @@ PyModuleDef kModule = {PyModuleDef_HEAD_INIT, "_pycall", nullptr, -1, kMethods, 
 
 PyMODINIT_FUNC PyInit__pycall(void) {
     g_dataPtr = PyUnicode_InternFromString("data_ptr");
-    return g_dataPtr ? PyModule_Create(&kModule) : nullptr;
+    g_cudaStream = PyUnicode_InternFromString("cuda_stream");
+    return g_dataPtr && g_cudaStream ? PyModule_Create(&kModule) : nullptr;
 }

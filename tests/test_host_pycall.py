@@ -41,13 +41,46 @@ def test_every_argument_arrives(module, form):
     assert rc == -7 and list(got[0]) == want
 
 
-@pytest.mark.parametrize("at,value", [(0, 1.0), (0, 2 ** 40), (2, np.int64(5)), (2, 2 ** 70), (5, 1), (5, np.float64(1.0)),
+@pytest.mark.parametrize("at,value", [(0, 1.0), (0, 2 ** 40), (2, np.int64(5)), (2, 2 ** 70), (5, True), (5, 2 ** 2000), (5, np.float64(1.0)),
                                       (6, -1), (6, 2 ** 64), (6, object()), (11, np.int64(8)), (12, None), (16, "1")])
 def test_what_is_left_to_ctypes(module, at, value):
     entry = ctypes.CFUNCTYPE(ctypes.c_int, *TYPES[0])(lambda *a: 0)
     args = list(ARGS)
     args[at] = value
     assert module.gemm(ctypes.cast(entry, ctypes.c_void_p).value, 0, 0, 0, *args, 77, None, 0) is NotImplemented
+
+
+class Stream:
+    def __init__(self, handle):
+        self.cuda_stream = handle
+
+
+def test_whole_scalars_and_stream_objects_are_taken(module):
+    """alpha = 1, beta = 0 and a stream object are what many programs pass."""
+    got = []
+    entry = ctypes.CFUNCTYPE(ctypes.c_int, *TYPES[0])(lambda *a: got.append(a) or 0)
+    args = list(ARGS)
+    args[5], args[10] = 2, 0
+    assert module.gemm(ctypes.cast(entry, ctypes.c_void_p).value, 0, 0, 0, *args, Stream(77), None, 0) == 0
+    assert list(got[0]) == args + [77]
+    args[5], args[10] = -(2 ** 53 + 1), 2 ** 24 + 1                       # rounded as ctypes rounds them
+    assert module.gemm(ctypes.cast(entry, ctypes.c_void_p).value, 0, 0, 0, *args, 77, None, 0) == 0
+    assert got[1][5] == ctypes.c_float(args[5]).value and got[1][10] == ctypes.c_float(args[10]).value
+
+
+@pytest.mark.parametrize("stream", [object(), Stream(None), Stream(-1), Stream(np.int64(5)), "1", True])
+def test_an_unusual_stream_is_seen_before_the_operands(module, stream):
+    class Counted(Operand):
+        asked = 0
+
+        def data_ptr(self):
+            Counted.asked += 1
+            return 4096
+    entry = ctypes.CFUNCTYPE(ctypes.c_int, *TYPES[0])(lambda *a: 0)
+    args = list(ARGS)
+    args[6] = Counted()
+    assert module.gemm(ctypes.cast(entry, ctypes.c_void_p).value, 0, 0, 0, *args, stream, None, 0) is NotImplemented
+    assert Counted.asked == 0
 
 
 def test_errors_of_an_operand_and_unusual_calls(module):
