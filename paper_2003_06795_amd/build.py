@@ -66,10 +66,18 @@ def _compile(job):
 
 
 def build_pycall(force=False):
+    """The marshalling module, or None where it cannot be built (binding.py then goes through ctypes)."""
     src = os.path.join(CSRC, "pycall.cpp")
     if force or not os.path.exists(PYCALL) or os.path.getmtime(PYCALL) < os.path.getmtime(src):
         tmp = PYCALL + ".tmp.%d" % os.getpid()
-        subprocess.run(["g++"] + CXX_FLAGS + ["-I", sysconfig.get_paths()["include"], "-shared", src, "-o", tmp], check=True)
+        try:
+            subprocess.run(["g++"] + CXX_FLAGS + ["-I", sysconfig.get_paths()["include"], "-shared", src, "-o", tmp], check=True)
+        except (OSError, subprocess.CalledProcessError) as err:
+            for left in (tmp, PYCALL):            # a module of an older source does not fit binding.py
+                if os.path.exists(left):
+                    os.remove(left)
+            print("[build] without %s, calls are converted by ctypes: %s" % (os.path.basename(PYCALL), err), flush=True)
+            return None
         os.replace(tmp, PYCALL)
     return PYCALL
 

@@ -1,6 +1,8 @@
 """The marshalling of GEMM calls in C (csrc/pycall.cpp): every argument of every form arrives at the entry point as ctypes
 delivers it, and what it does not take is left to ctypes."""
 import ctypes
+import os
+import sysconfig
 
 import numpy as np
 import pytest
@@ -21,7 +23,10 @@ class Operand:
 @pytest.fixture()
 def module():
     ks.lib()
-    return pytest.importorskip("paper_2003_06795_amd._pycall")
+    if not os.path.exists(os.path.join(sysconfig.get_paths()["include"], "Python.h")):
+        pytest.skip("the module is not built without Python's C headers")
+    from paper_2003_06795_amd import _pycall
+    return _pycall
 
 
 @pytest.mark.parametrize("form", sorted(TYPES))
@@ -97,3 +102,18 @@ def test_errors_of_an_operand_and_unusual_calls(module):
         ks.gemm_f32_with_kernel(kid, 0, 0, 0, 4, 4, 1, None, 4, None, 4, 0, None, 4, stream=0)
     with pytest.raises(ks.KsError):
         ks.gemm_bias(ks.F32, -1, 0, 0, 4, 4, 4, 1.0, None, 4, None, 4, 0.0, None, 4, None, stream=0)
+
+
+@pytest.mark.parametrize("missing", ["headers", "compiler"])
+def test_the_library_builds_without_the_module(monkeypatch, tmp_path, capsys, missing):
+    """No Python.h or no g++: the build goes on, and no module of an older source stays behind."""
+    from paper_2003_06795_amd import build as lib_build
+    stale = tmp_path / "_pycall.so"
+    stale.write_bytes(b"older")
+    monkeypatch.setattr(lib_build, "PYCALL", str(stale))
+    if missing == "headers":
+        monkeypatch.setattr(lib_build.sysconfig, "get_paths", lambda: {"include": str(tmp_path)})
+    else:
+        monkeypatch.setenv("PATH", str(tmp_path))
+    assert lib_build.build_pycall(force=True) is None
+    assert os.listdir(tmp_path) == [] and "ctypes" in capsys.readouterr().out
