@@ -359,7 +359,8 @@ int ks_set_split_partitions(int partitions);
 
 /* 16-bit operands that the direct-to-LDS path cannot read as they are (ks_set_fast_path), batch 1: one more kernel
  * copies them to the end of the scratch, rows padded to sixteen bytes and K to whole K-steps (half ones for a K-step
- * of 128) with zeros, and the member runs on the copies, with the same order along K as on the operands.  Scratch is what
+ * of 128) with zeros, and the member runs on the copies in the same partitions of K as on the operands; a hybrid launch, which only
+ * the direct-to-LDS path has, may partition the tiles of its last round (ks_set_tail_split).  Scratch is what
  * the call brings (ks_gemm_with_workspace: any member) or shares (the registered workspace and the static array: members
  * with split_k != 1 only; the others never touch them).  mode == -1 (the default) does so where a cost estimate by
  * flops and bytes says it pays and the scratch holds the copies beside the partial sums of the K partitions that the

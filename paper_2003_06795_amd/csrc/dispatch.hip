@@ -636,10 +636,12 @@ int run_ws(Workspace wsp, int dtype, int id, int transA, int transB, int64_t M, 
     }
 
     // 16-bit operands that the direct-to-LDS path cannot read as they are: copies that it can (OperandCopy), where the
-    // scratch holds them and they pay.  The member, its order along K and so its bits stay the same.  The
+    // scratch holds them and they pay.  The member and its partitions of K stay the same, and with them the order of the
+    // sums, but for the tiles that a hybrid launch partitions (tail_split, direct-to-LDS only).  The
     // registered workspace is for members that may use it (those with split_k == 1 never do).
     // Partial sums come first: without their partitions a few tiles leave the device idle (1024 x 1024 x 64001 NT in
-    // 256 MiB would run 16 work-groups instead of 256), which no alignment makes up for.
+    // 256 MiB ran 16 work-groups instead of 256, 1173 us against 170 on the operands as they are; 2000 x 900 x 20001 TN in 128
+    // MiB two partitions instead of eight, 211 against 121).
     if (dtype != KS_F32 && !copied && batch == 1 && g_forceGeneric == 0 && g_operandCopies != 0 && wsp.ptr &&
         (own || d->splitK != 1)) {
         const bool akc = transA == 0, bkc = transB == 1;

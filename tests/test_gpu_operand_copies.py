@@ -82,3 +82,28 @@ def test_scratch_of_the_copies(gpu):
     for bad in (-2, 2):
         with pytest.raises(ks.KsError):
             ks.set_operand_copies(bad)
+
+
+@pytest.mark.parametrize("layout", [(0, 0), (0, 1), (1, 0), (1, 1)])
+def test_copies_with_a_hybrid_launch(gpu, layout):
+    """272 tiles on 256 units: the copies at the end of the scratch, the partial tiles of the last round at its beginning."""
+    import torch
+    import paper_2003_06795_amd.binding as ks
+    ks.set_operand_copies(1)
+    ks.set_tail_split(4)
+    try:
+        p = wl.make_problem("bf16", *layout, 1085, 1021, 1091, alpha=1.5, beta=-0.5, seed=99, dist="normal", pad=(3, 1, 2))
+        dp, ref = gpu.DeviceProblem(p), gpu.oracle_full(p)
+        args = (p.transA, p.transB, p.M, p.N, p.K, p.alpha, dp.A, p.lda, dp.B, p.ldb, p.beta)
+        copies = 2 * (1088 + 1024) * 1152 + 16
+        for size, tail in ((copies + 4 * 16 * 64 * 64 * 4, 4), (copies, 0)):          # with and without room for the partial tiles
+            ws = torch.full((size,), 0xFF, dtype=torch.uint8, device="cuda")
+            ks.set_workspace(ws)
+            C = dp.C0.clone()
+            plan = ks.gemm_plan(ks.BF16, 39, *args, C, p.ldc)
+            assert (plan["operand_copies"], plan["tail_split"]) == (3, tail), plan
+            ks.gemm_bf16_with_kernel(39, *args, C, p.ldc)
+            err = float(np.max(np.abs(C.cpu().numpy()[:ref.size].astype(np.float64) - ref)))
+            assert err <= tolerance(p), (size, err)
+    finally:
+        ks.set_tail_split(-1)
