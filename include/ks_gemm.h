@@ -206,9 +206,9 @@ int ks_gemm_out_bf16(int dtype, int kernel_id, int transA, int transB, int64_t M
  *     not fit is replaced by its split_k == 1 twin, as in ks_gemm_*.
  *   - Nothing has to start at zero: every partition writes its whole slice before the reduction
  *     pass reads it, so the array may hold the previous call's contents.
- *   - All calls on one device share that device's array: two such GEMMs that both split must not
- *     be in flight together on one device (same stream, or ordered by the caller); overlapping
- *     calls race. */
+ *   - All calls on one device share that device's array: two such GEMMs that both write it (K
+ *     partitions, divided tiles, copies of operands) must not be in flight together on one device
+ *     (same stream, or ordered by the caller); overlapping calls race. */
 #define KS_STATIC_SCRATCH_BYTES (16u << 20)
 int ks_gemm_static_scratch(int dtype, int kernel_id, int transA, int transB, int64_t M, int64_t N, int64_t K,
                            float alpha, const void *A, int64_t lda, const void *B, int64_t ldb,
@@ -417,7 +417,8 @@ int ks_set_workspace(void *device_ptr, size_t bytes);
 /* Bytes the kernel would like for this output size (for split_k == 0 the most it can use: the
  * partial sums of the largest partition count it may choose, or, for a 16-bit member that launches
  * in the hybrid form on this many tiles, the compact partial tiles of at most 16 partitions of its
- * last round; for a member with a balanced persistent form, the raw tiles of its work-groups). */
+ * last round; for a member with a balanced persistent form, the raw tiles of its work-groups).  Copies of
+ * 16-bit operands come on top: with just this much they are not made. */
 size_t ks_workspace_bytes_needed(int dtype, int kernel_id, int64_t M, int64_t N, int64_t batch);
 
 /* ---------------------------------------------------------------- offline tuner (host only)

@@ -175,9 +175,9 @@ struct Bf16Staging {
     // load_edge() of an operand with at least eight elements along the contiguous direction: a chunk over the end is read
     // from further back, whole, and fit_edge() moves what exists of it to the front.  No branch, so the loads of a step wait
     // for memory once and not, chunk by chunk, for the elements of those over the end (every wave has some where the
-    // operand is K-contiguous).  261 drawn calls on this path 0.92 of the time with the lighter binding, 0.90 in NN and NT, 0.94 in TN and
-    // TT: 1000 x 777 x 1509 NN 19.6 -> 17.9 us, 108 x 79 x 6085 NT in 39 partitions 10.5 -> 7.4; where few chunks are over the end the moving
-    // shows (517 x 2936 x 152 TN 7.25 -> 7.5, kernel 7.8 -> 8.0).
+    // operand is K-contiguous).  160 drawn calls on this path 0.94 of the time by this alone, 0.91 in NT, 0.95 in NN and TT, 0.96 in TN
+    // (worst 1.05: 79 x 3010 x 151 TT): 1000 x 777 x 1509 NN 19.5 -> 17.9 us, 108 x 79 x 6085 NT in 39 partitions 8.5 -> 7.3; where few chunks
+    // are over the end the moving shows (517 x 2936 x 152 TN 7.35 -> 7.6).
     __device__ __forceinline__ static void load_edge_back(uintx4 (&reg)[PER], const uint16_t *base, long long ld, int row0,
                                                           int limit, int k0, int kEnd, int tid) {
 #pragma unroll

@@ -177,6 +177,13 @@ int by_few_rows_or_columns(int dtype, int id, int64_t M, int64_t N, int64_t K, i
 //   32 x 32 x 32 -> 64 x 64 x 8 1.34: 1.03 (44, worst 1.49: 179963 x 20 x 59), 0.83 (96, 1.09)
 //   batches 32 x 32 x 16 -> 64 x 64 1.25: 1.20 (72, worst 1.93: 82 x 21 x 65, 8910 of them), 0.84 (48, 1.09)
 //   batches 16 x 16 -> 32 x 32 1.34: 1.03 (29, worst 1.25: 37 x 42 x 61), 0.84 (91, 1.10)
+// Held out: 1860 problems of two later draws on which the rules act as they stand, time against the member replaced (count,
+//   those over 1.03, worst): 256 x 256 for 128 x 64 ragged 0.75 (119, 4, 1.19), whole 0.84 (65, 2, 1.15); for 128 x 128 x 64 0.71 (114,
+//   4, 1.06), level where nothing but K of NT is ragged (31, 8, 1.10); 128 x 128 for 64 x 64 0.79 (128, 3, 1.11); fp32 64 x 64 x 8 for
+//   64 x 64 x 16 0.90 (64, 5, 1.12), for 32 x 32 x 32 0.83 (256, 15, 1.15); 32 x 32 x 32 for two K groups, short K 0.86 (64, 6, 1.13), long
+//   0.92 (64, 7, 1.35: five rows, fewer than any problem the line was drawn from); batches in that order 0.87 (64, none), 0.84
+//   (251, 16, 1.12), 0.83 (128, 1, 1.09).  Few rows or columns (by_few_rows_or_columns): 0.83, 0.71 and 0.72 for columns (64 each, 1.04), 0.61,
+//   0.59 and 0.74 for rows (128, 128, 64; 1.14).
 // leaf: what the tree says
 int by_tile_fit(int dtype, int leaf, int id, int64_t M, int64_t N, int64_t K, int64_t batch, int transA, int transB) {
     if (M <= 0 || N <= 0 || K <= 0 || batch <= 0 || M > (1 << 28) || N > (1 << 28) || batch > (1 << 28)) return id;
