@@ -318,10 +318,15 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) void gemm_bf16_kernel(c
             lb.load(b, t * bStep, tid);
         }
     };
-    const bool backA = (AKC ? p.K : p.M) >= 8, backB = (BKC ? p.K : p.N) >= 8;
+    // Wave tiles of 8192 entries and more read back where B is K-contiguous only: with both forms of the step beside their
+    // accumulators, the unsplit 256 x 256 tile on 16-wide fragments spilled 48 registers instead of 39 in TN, inside its loop:
+    // ragged calls without scratch for copies 1.06 of the time there (17, worst 1.15: 4981 x 1719 x 1551 73 -> 84 us), 1.00 (18, 1.06)
+    // in NN against 0.99 without, 0.99 and 0.98 in NT and TT against 1.00.
+    constexpr bool BACK = WM * WN < 8192 || BKC;
+    const bool back = BACK && (AKC ? p.K : p.M) >= 8 && (BKC ? p.K : p.N) >= 8;
     auto load_edge = [&](int t, uintx4 (&a)[LoadA::PER], uintx4 (&b)[LoadB::PER]) {
         const int k0 = kBegin + t * BK;
-        if (backA && backB) {
+        if (back) {
             LoadA::load_edge_back(a, Ab, p.lda, row0, p.M, k0, kEnd, tid);
             LoadB::load_edge_back(b, Bb, p.ldb, col0, p.N, k0, kEnd, tid);
             LoadA::fit_edge(a, row0, p.M, k0, kEnd, tid);
