@@ -61,6 +61,15 @@ namespace ks {
 
 enum { CORE_FMA = 0, CORE_MFMA16 = 1, CORE_MFMA32 = 2, CORE_DIRECT = 3, CORE_KSLICE = 4 };
 
+// UNITS forms with fragments of four k that are told to leave room for eight waves per SIMD: by itself the sixteen-wave 64 x 64 x 32
+// member takes 70 registers in NN and TT and loses its second work-group (2048 x 2048 x 96 NN 13.7 -> 16.6 us; with two
+// staging sets instead of four, which spilled 16, 13.5), 32 x 32 x 16 66 in NT (2048 x 2048 x 1024 101 -> 110; 102 with 62).  Where they fit
+// unasked the demand costs up to 6 % (32 x 32 x 16 in the other layouts) and 3 % (64 x 64 x 32 in NT).
+constexpr bool f32_units_eight_waves(int core, int bm, int bn, int bk, int p1, int p2, int kw, bool akc, bool bkc, int loads) {
+    return loads == LOAD_UNITS && core == CORE_MFMA16 && kw == 1 &&
+           ((bm / p1) * (bn / p2) == 16 ? bk >= 32 && akc != bkc : bm == 32 && bn == 32 && bk == 16 && akc && bkc);
+}
+
 template <int CORE, int BM, int BN, int P1, int P2>
 struct F32Shape {
     static constexpr int threads =
@@ -258,7 +267,7 @@ struct TileLoader {
 // the epilogue.  No work-group waits for another, so there is nothing to deadlock on.
 template <int CORE, int BM, int BN, int BK, int P1, int P2, bool SPLIT, bool AKC, bool BKC,
           int LOADS, int KW = 1, bool MULTI = false, bool SK = false>
-__global__ __launch_bounds__((F32Shape<CORE, BM, BN, P1, P2>::threads * KW), (SK ? KS_F32_SK_MIN_WAVES(BM, BN, P1, P2) : KS_F32_MIN_WAVES(MULTI, CORE, BM, BN, BK, P1, P2, KW, LOADS))) void gemm_f32_kernel(
+__global__ __launch_bounds__((F32Shape<CORE, BM, BN, P1, P2>::threads * KW), (SK ? KS_F32_SK_MIN_WAVES(BM, BN, P1, P2) : f32_units_eight_waves(CORE, BM, BN, BK, P1, P2, KW, AKC, BKC, LOADS) ? 8 : KS_F32_MIN_WAVES(MULTI, CORE, BM, BN, BK, P1, P2, KW, LOADS))) void gemm_f32_kernel(
     const GemmParams p) {
     static_assert(LOADS == LOAD_STEPS || !(MULTI || SK), "persistent forms");
     static_assert(!MULTI || (f32_multi_tile(CORE, BM, BN, P1, P2, KW) && !SPLIT), "multi-tile form");
@@ -299,7 +308,8 @@ __global__ __launch_bounds__((F32Shape<CORE, BM, BN, P1, P2>::threads * KW), (SK
     // afford several; large tiles hide the latency behind their MFMAs and keep the registers.
     constexpr int STAGE_REGS = (LoaderA::ITERS + LoaderB::ITERS) * W;
     // (sixteen waves that must fit 64 registers: four sets beside fragments of four k spilled 4 - 16)
-    constexpr bool TIGHT = KS_F32_MIN_WAVES(MULTI, CORE, BM, BN, BK, P1, P2, KW, LOADS) == 8 && (CHA || CHB) && BK >= 32;
+    constexpr bool TIGHT = (KS_F32_MIN_WAVES(MULTI, CORE, BM, BN, BK, P1, P2, KW, LOADS) == 8 ||
+                            f32_units_eight_waves(CORE, BM, BN, BK, P1, P2, KW, AKC, BKC, LOADS)) && (CHA || CHB) && BK >= 32;
     constexpr int PF = TIGHT ? 2 : KS_F32_PREFETCH(STAGE_REGS, NT);
     LoaderA la[PF];
     LoaderB lb[PF];
