@@ -323,7 +323,11 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) void gemm_bf16_kernel(c
     // ragged calls without scratch for copies 1.06 of the time there (17, worst 1.15: 4981 x 1719 x 1551 73 -> 84 us), 1.00 (18, 1.06)
     // in NN against 0.99 without, 0.99 and 0.98 in NT and TT against 1.00.
     constexpr bool BACK = WM * WN < 8192 || BKC;
-    const bool back = BACK && (AKC ? p.K : p.M) >= 8 && (BKC ? p.K : p.N) >= 8;
+    // And only where a chunk can hang over an end: without one load_edge() reads each whole or not at all, and needs no moving
+    // (80 calls on sizes of whole chunks with unaligned rows 0.98 of the time that reading back took, worst before 1.07 of the
+    // form without it: 512 x 1656 x 152 TT, now 1.02; the remainders of a cut K 0.996).
+    const int endA = AKC ? p.K : p.M, endB = BKC ? p.K : p.N;
+    const bool back = BACK && (endA | endB) % 8 != 0 && endA >= 8 && endB >= 8;
     auto load_edge = [&](int t, uintx4 (&a)[LoadA::PER], uintx4 (&b)[LoadB::PER]) {
         const int k0 = kBegin + t * BK;
         if (back) {

@@ -37,3 +37,18 @@ def test_every_remainder(gpu, dtype, nan, layout):
         for kid in MEMBERS:
             err = float(np.max(np.abs(dp.run(kid).astype(np.float64) - ref)))
             assert err <= tol, "kernel %d %s: %.3e > %.3e" % (kid, (M, N, K), err, tol)
+
+
+@pytest.mark.parametrize("layout", [(0, 0), (0, 1), (1, 0), (1, 1)])
+def test_whole_chunks_in_unaligned_rows(gpu, layout):
+    """Sizes that are multiples of a chunk, one of them not, and all but one: both forms of the step on either side of the rule."""
+    for s, (M, N, K) in enumerate([(8, 8, 8), (72, 136, 264), (136, 72, 1032), (72, 136, 265), (71, 136, 264), (72, 135, 264),
+                                   (264, 520, 200)]):
+        p = wl.make_problem("bf16", *layout, M, N, K, alpha=1.5, beta=-0.5, seed=96, key=s, dist="normal", pad=(3, 1, 2))
+        ref, tol = gpu.oracle_full(p), tolerance(p)
+        for buf, ld, cols in ((p.A, p.lda, M if p.transA else K), (p.B, p.ldb, K if p.transB else N)):
+            buf.reshape(-1, ld)[:, cols:] = 0x7FC0
+        dp = gpu.DeviceProblem(p)
+        for kid in MEMBERS:
+            err = float(np.max(np.abs(dp.run(kid).astype(np.float64) - ref)))
+            assert err <= tol, "kernel %d %s: %.3e > %.3e" % (kid, (M, N, K), err, tol)
