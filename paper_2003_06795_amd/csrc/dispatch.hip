@@ -742,7 +742,12 @@ int run_ws(Workspace wsp, int dtype, int id, int transA, int transB, int64_t M, 
             grid64 = groups;
         }
     }
-    if (dtype == KS_F32 && !p.grid3d && p.splitK == 1 && p.skGroups == 0 && f32_multi_tile(d->core, d->bm, d->bn, d->p1, d->p2, d->kw)) {
+    // on the bf16 matrix pipe (gemm_f32_parts.hpp), where the K range of a work-group is long enough; that form has no
+    // work-groups that walk several tiles
+    const int64_t waveK = K < p.kChunk ? K : p.kChunk;
+    const bool parts = dtype == KS_F32 && f32_parts_member(d->core, d->bm, d->bn, d->bk, d->kw, p.splitK > 1) &&
+                       waveK >= f32_parts_least_k(d->kw);
+    if (dtype == KS_F32 && !parts && !p.grid3d && p.splitK == 1 && p.skGroups == 0 && f32_multi_tile(d->core, d->bm, d->bn, d->p1, d->p2, d->kw)) {
         p.tilesPerWG = g_tilesPerWG > 0 ? g_tilesPerWG : multi_tiles(d, grid64, K);
         grid64 = (grid64 + p.tilesPerWG - 1) / p.tilesPerWG;
     }
@@ -759,7 +764,7 @@ int run_ws(Workspace wsp, int dtype, int id, int transA, int transB, int64_t M, 
     // Load form of the fp32 members: of the LDS-staged ones as described in ks_common.hpp, UNITS up to eight K-steps
     // of a wave in any member (it gains up to four of them); of the register-fed ones (gemm_f32_direct.hpp) by K alone.
     const bool registerFed = d->core == KS_CORE_DIRECT || d->core == KS_CORE_KSLICE;
-    const int64_t waveK = K < p.kChunk ? K : p.kChunk, stepK = (int64_t)d->bk * d->kw;
+    const int64_t stepK = (int64_t)d->bk * d->kw;
     const bool oneTile = p.skGroups == 0 && p.tilesPerWG == 1;
     const int group = d->threads / d->kw;
     const bool units = registerFed ? K % 4 == 0
@@ -768,7 +773,7 @@ int run_ws(Workspace wsp, int dtype, int id, int transA, int transB, int64_t M, 
     const bool elements = oneTile && waveK <= f32_element_steps(d->core, d->bm, d->bn, d->bk, group, d->kw) * stepK;
     // and of the register-staged path of the 16-bit ones (gemm_bf16.hpp)
     const bool chunks = akc && bkc && d->bk == 128 && K % 8 == 0 && K % 128 != 0 && waveK > 128 && waveK < 512;
-    const int variant = (akc ? 4 : 0) + (bkc ? 2 : 0) + ((dtype == KS_F32 ? units : chunks) ? 1 : 0) + (elements ? 32 : 0) + splitBit;
+    const int variant = (akc ? 4 : 0) + (bkc ? 2 : 0) + ((dtype == KS_F32 ? units : chunks) ? 1 : 0) + (elements ? 32 : 0) + (parts ? 64 : 0) + splitBit;
 
     // bf16 fast path: operand tiles go global -> LDS directly.
     const int f16Bit = dtype == KS_F16 ? 16 : 0;     // same 16-bit members, binary16 MFMA

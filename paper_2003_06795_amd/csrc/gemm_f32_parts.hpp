@@ -1,0 +1,323 @@
+// fp32 members on the bf16 matrix pipe (paper Section II: the inner-product engine is one of the kernel's template axes).
+//
+// The matrix pipe multiplies bf16 sixteen times as fast as fp32.  A float is the sum of three bf16 numbers, x = h + m + l,
+// each the rest of the one before rounded to nearest: 3 x 8 bits hold the 24 of the fraction, so the split is exact for
+// every |x| >= 2^-100 up to the largest bf16.  Of the nine products of two such sums the six with 2^-17 or more of the
+// whole are added, the smallest first, into the fp32 accumulators of the MFMA: h l', l h', m m', h m', m h', h h'.  The three left out
+// come to 2^-26 of a product at most, under half a unit in its last place, and six MFMAs of sixteen k round an accumulator
+// less often than eight of two k do: against fp64 the result is closer than the fp32 MFMA's (U[-1, 1), relative 2-norm, K = 32 /
+// 512 / 8192: 6.8e-8 / 3.4e-7 / 1.44e-6 against 1.0e-7 / 4.0e-7 / 1.62e-6; U[0, 1) 5.5e-8 / 2.4e-7 / 7.5e-7 against 8.3e-8 / 3.1e-7 / 1.18e-6).
+//
+// What the split cannot hold is computed on the fp32 matrix pipe, in the same launch (`again`): a work-group that meets a
+// magnitude below 2^-100 other than zero, or ends with an accumulator that is no finite number (infinities and NaN of the
+// operands, floats that round to an infinite bf16, products that overflow), computes its K range once more from fp32 tiles in the
+// same LDS.
+//
+// One K-step is 32 k whatever the member's: both operands' parts, 48 KB of a 128 x 128 tile, in one LDS stage of the 16-bit
+// members' layouts (gemm_bf16.hpp); the next step's floats are in flight during the MFMAs and are split behind them.  Two
+// work-groups of a compute unit fill each other's barriers.  Bound by power on large problems (4096^3 at 215 TFLOP/s is 1.29 PFLOP/s
+// of bf16) and by the sum of splitting (seven VALU instructions an element), LDS traffic and MFMAs on 64 x 64 tiles.
+// Against the fp32 matrix pipe, us: 4096^3 NT 1080 -> 635, TN 1040 -> 671; 4095 x 3000 x 4089 NT 806 -> 530; 25088 x 256 x 1152 NN 142 -> 99;
+// 2048^3 147 -> 100; on 64 x 64 tiles 1944 x 1264 x 1576 TT 90 -> 67, with two K groups 480 x 1184 x 2592 TN 39.6 -> 32.6.
+// Measured and left: 64 x 64 of output per wave (4096^3 level, 2048^3 +1 %, 480 x 1184 x 2592 +12 %); two K-steps in flight (level to +4 %);
+// splitting in front of the stores (level to +14 %); v_dot2_f32_bf16 for the two steps of a rest (+5 to +12 %, and its inline -1.0 is
+// the fp32 pattern); without s_setprio around the MFMAs +4 %; the check for small magnitudes costs 0 to 2 %.
+#pragma once
+#include "gemm_bf16.hpp"
+#include "gemm_f32.hpp"
+
+namespace ks {
+
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef unsigned uintx2 __attribute__((ext_vector_type(2)));
+
+// 2^-100 with the sign shifted out: a float from there on has its last bit at 2^-123 and three normal parts
+constexpr unsigned kPartsLeast = (127u - 100u) << 24;
+
+// the parts of four floats, two to a register
+struct FourParts {
+    uintx2 part[3];
+};
+// least: smallest magnitude other than zero so far, with the sign shifted out, less one (zero wraps to the largest)
+__device__ __forceinline__ FourParts split_parts(floatx4 x, unsigned &least) {
+    FourParts out;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        floatx2 v = {x[2 * h], x[2 * h + 1]};
+        const unsigned u0 = __builtin_bit_cast(unsigned, v[0]), u1 = __builtin_bit_cast(unsigned, v[1]);
+        least = min(least, min((u0 << 1) - 1u, (u1 << 1) - 1u));
+#pragma unroll
+        for (int s = 0; s < 3; ++s) {
+            const unsigned u = __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf16x2));      // to nearest, ties to even
+            out.part[s][h] = u;
+            if (s < 2) {
+                v[0] -= __builtin_bit_cast(float, u << 16);
+                v[1] -= __builtin_bit_cast(float, u & 0xFFFF0000u);
+            }
+        }
+    }
+    return out;
+}
+
+// The member's work-groups, tiles, waves, K groups, K ranges and accumulator layout (32x32 fragments) are those of
+// gemm_f32_kernel, which describes SPLIT, KW and SK; only how a work-group multiplies a K range differs.
+template <int BM, int BN, int P1, int P2, bool SPLIT, bool AKC, bool BKC, int KW, bool SK>
+__global__ __launch_bounds__(64 * (BM / P1) * (BN / P2) * KW, 4) void gemm_f32_parts_kernel(const GemmParams p) {
+    static_assert(!SK || (KW == 1 && !SPLIT), "balanced persistent form");
+    constexpr int BK = 32, NT = 64 * (BM / P1) * (BN / P2), FM = P1 / 32, FN = P2 / 32;
+    using KCA = std::integral_constant<bool, AKC>;
+    using KCB = std::integral_constant<bool, BKC>;
+    using LoaderA = TileLoader<BM, BK, NT, AKC, 4, AKC>;
+    using LoaderB = TileLoader<BN, BK, NT, BKC, 4, BKC>;
+    constexpr int PLANE_A = BM * BK * 2, PLANE_B = BN * BK * 2;
+    constexpr int BYTES = 3 * (PLANE_A + PLANE_B);
+    static_assert(4 * (LoaderA::LDS_SIZE + LoaderB::LDS_SIZE) <= BYTES, "fp32 tiles of a range computed again");
+    static_assert(KW == 1 || BM * BN * 4 <= BYTES, "accumulators of the K groups");
+    __shared__ __attribute__((aligned(1024))) char ldsAll[KW][BYTES];
+    __shared__ int again;
+
+    const int grp = KW == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x / NT);
+    char *const lds = ldsAll[grp];
+    const int tid = KW == 1 ? (int)threadIdx.x : (int)threadIdx.x % NT, lane = tid & 63, wave = tid >> 6;
+    const int subM = (wave / (BN / P2)) * P1, subN = (wave % (BN / P2)) * P2;
+    floatx16 acc[FM][FN];
+    auto clear = [&]() {
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int j = 0; j < FN; ++j)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+    };
+
+    // acc = the products of k in [kLo, kHi) of the tile at (row, col), this group's slice of them
+    auto range = [&](const float *A, const float *B, int row, int col, int kLo, int kHi) {
+        const int nk = (max(kHi - kLo, 0) + KW * BK - 1) / (KW * BK);        // steps of the longest slice, for all groups
+        const int kB = kLo + grp * nk * BK, kE = min(kHi, kB + nk * BK);     // kE may lie below kB: an empty slice
+        typename LoaderA::Plan pa;
+        typename LoaderB::Plan pb;
+        pa.init(p.lda, row, p.M, tid);
+        pb.init(p.ldb, col, p.N, tid);
+        const int full = min(LoaderA::whole_steps(p.lda, p.M, p.K, kB, kE), LoaderB::whole_steps(p.ldb, p.N, p.K, kB, kE));
+        LoaderA la;
+        LoaderB lb;
+        auto load = [&](int t) {
+            const int k0 = kB + t * BK;
+            if (t < full) {
+                la.load(pa, AKC ? A + (long long)row * p.lda + k0 : A + (long long)k0 * p.lda + row, p.lda, tid);
+                lb.load(pb, BKC ? B + (long long)col * p.ldb + k0 : B + (long long)k0 * p.ldb + col, p.ldb, tid);
+            } else {
+                la.clear();
+                lb.clear();
+                la.load_edge(A, p.lda, row, p.M, k0, kE, tid);
+                lb.load_edge(B, p.ldb, col, p.N, k0, kE, tid);
+            }
+        };
+        unsigned least = ~0u;
+        FourParts ya[LoaderA::ITERS], yb[LoaderB::ITERS];
+        // (what the loads of a row-contiguous operand reach beyond its edge is none of the matrix's, whatever it holds)
+        auto split = [&](auto &l, auto &y, auto kc, int origin, int limit) {
+            using L = std::remove_reference_t<decltype(l)>;
+            if (!decltype(kc)::value && origin + L::INNER * 4 > limit) {
+#pragma unroll
+                for (int it = 0; it < L::ITERS; ++it)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (origin + tid % L::INNER * 4 + e >= limit) l.reg[it][e] = 0.f;
+            }
+#pragma unroll
+            for (int it = 0; it < L::ITERS; ++it) y[it] = split_parts(l.reg[it], least);
+        };
+        auto store = [&](auto rows, auto kc, char *to, const auto &y) {
+            constexpr int ROWS = decltype(rows)::value;
+            constexpr bool KC = decltype(kc)::value;
+            using L = TileLoader<ROWS, BK, NT, KC, 4, KC>;
+#pragma unroll
+            for (int it = 0; it < L::ITERS; ++it) {
+                const int inner = tid % L::INNER, outer = tid / L::INNER + it * L::STRIDE;
+                const int at = KC ? 16 * Bf16Lds<BK>::chunk(outer, inner / 2) + 8 * (inner & 1)
+                                  : Bf16LdsT<ROWS, 32>::byte_of(outer, inner * 4);
+#pragma unroll
+                for (int s = 0; s < 3; ++s) *reinterpret_cast<uintx2 *>(to + s * (ROWS * BK * 2) + at) = y[it].part[s];
+            }
+        };
+        clear();
+        if (threadIdx.x == 0) again = 0;
+        if (nk > 0) {
+            load(0);
+            split(la, ya, KCA{}, row, p.M);
+            split(lb, yb, KCB{}, col, p.N);
+        }
+        bool stop = false;                                   // the same for the whole work-group
+        for (int t = 0; t < nk && !stop; ++t) {
+            store(std::integral_constant<int, BM>{}, KCA{}, lds, ya);
+            store(std::integral_constant<int, BN>{}, KCB{}, lds + 3 * PLANE_A, yb);
+            if (t + 1 < nk) load(t + 1);
+            __syncthreads();
+            __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+            for (int kk = 0; kk < BK; kk += 16) {
+                bf16x8 a[3][FM], b[3][FN];
+#pragma unroll
+                for (int s = 0; s < 3; ++s) {
+#pragma unroll
+                    for (int i = 0; i < FM; ++i)
+                        a[s][i] = read_fragment<32, BM, BK, AKC>(lds + s * PLANE_A, subM + i * 32, kk, lane);
+#pragma unroll
+                    for (int j = 0; j < FN; ++j)
+                        b[s][j] = read_fragment<32, BN, BK, BKC>(lds + 3 * PLANE_A + s * PLANE_B, subN + j * 32, kk, lane);
+                }
+                constexpr int TA[6] = {0, 2, 1, 0, 1, 0}, TB[6] = {2, 0, 1, 1, 0, 0};
+#pragma unroll
+                for (int q = 0; q < 6; ++q)
+#pragma unroll
+                    for (int i = 0; i < FM; ++i)
+#pragma unroll
+                        for (int j = 0; j < FN; ++j)
+                            acc[i][j] = mfma_32x32x16<false>(a[TA[q]][i], b[TB[q]][j], acc[i][j]);
+            }
+            __builtin_amdgcn_s_setprio(0);
+            if (t + 1 < nk) {
+                split(la, ya, KCA{}, row, p.M);
+                split(lb, yb, KCB{}, col, p.N);
+            }
+            // operands with small magnitudes all over go to the fp32 pipe early
+            const bool look = t % 8 == 0;
+            if (look && least < kPartsLeast) again = 1;
+            __syncthreads();
+            if (look) stop = __builtin_amdgcn_readfirstlane(again) != 0;
+        }
+        float zero = 0.f;                                    // stays zero while the accumulators are finite
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int j = 0; j < FN; ++j)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) zero = fmaf(acc[i][j][e], 0.f, zero);
+        if (least < kPartsLeast || !(zero == 0.f)) again = 1;
+        __syncthreads();
+        if (__builtin_amdgcn_readfirstlane(again) != 0 && nk > 0) {
+            float *as = reinterpret_cast<float *>(lds), *bs = as + LoaderA::LDS_SIZE;
+            clear();
+            load(0);
+            for (int t = 0; t < nk; ++t) {
+                la.store(as, tid);
+                lb.store(bs, tid);
+                if (t + 1 < nk) load(t + 1);
+                __syncthreads();
+#pragma unroll 1
+                for (int kk = 0; kk < BK; kk += 8) {
+                    floatx4 a[FM], b[FN];
+#pragma unroll
+                    for (int i = 0; i < FM; ++i) a[i] = LoaderA::read(as, subM + i * 32 + (lane & 31), kk + 4 * (lane >> 5));
+#pragma unroll
+                    for (int j = 0; j < FN; ++j) b[j] = LoaderB::read(bs, subN + j * 32 + (lane & 31), kk + 4 * (lane >> 5));
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+#pragma unroll
+                        for (int i = 0; i < FM; ++i)
+#pragma unroll
+                            for (int j = 0; j < FN; ++j)
+                                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][e], b[j][e], acc[i][j], 0, 0, 0);
+                }
+                __syncthreads();
+            }
+        }
+        __syncthreads();                                     // LDS and `again` are the next range's
+    };
+
+    if constexpr (SK) {
+        // shares as in gemm_f32_kernel
+        auto uni = [](long long v) -> long long {
+            const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(unsigned long long)v);
+            const unsigned hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)((unsigned long long)v >> 32));
+            return (long long)(((unsigned long long)hi << 32) | lo);
+        };
+        const unsigned lw = (unsigned)__builtin_amdgcn_readfirstlane((int)logical_of_block());
+        const long long groups = (long long)gridDim.x;
+        const int nkT = (p.K + BK - 1) / BK;
+        const long long units = (long long)p.skTailTiles * nkT;
+        const long long ub = uni(sk_share_begin(lw, units, groups)), ue = uni(sk_share_begin(lw + 1, units, groups));
+        const long long t0 = uni(ub / nkT);
+        const int r0 = (int)(ub - t0 * nkT);
+        const int tailSegs = ue > ub ? (int)(uni((ue - 1) / nkT) - t0) + 1 : 0;
+        const int nSeg = p.skRounds + tailSegs;
+        for (int sg = 0; sg < nSeg; ++sg) {
+            unsigned logical;
+            int ks0 = 0, ks1 = nkT;
+            if (sg < p.skRounds) {
+                logical = (unsigned)sg * (unsigned)groups + lw;
+            } else {
+                const long long t = t0 + (sg - p.skRounds);
+                logical = (unsigned)p.skRounds * (unsigned)groups + (unsigned)t;
+                ks0 = sg == p.skRounds ? r0 : 0;
+                ks1 = (int)min((long long)nkT, ue - t * nkT);
+            }
+            TileCoord tc = tile_of_logical(p, logical);
+            tc.batch = __builtin_amdgcn_readfirstlane(tc.batch);
+            tc.tm = __builtin_amdgcn_readfirstlane(tc.tm);
+            tc.tn = __builtin_amdgcn_readfirstlane(tc.tn);
+            tc.split = 0;
+            const int row = tc.tm * BM, col = tc.tn * BN;
+            range(static_cast<const float *>(p.A) + (long long)tc.batch * p.strideA,
+                  static_cast<const float *>(p.B) + (long long)tc.batch * p.strideB, row, col, ks0 * BK, min(p.K, ks1 * BK));
+            int laneE = lane;
+            asm volatile("" : "+v"(laneE));
+            if (ks0 == 0 && ks1 == nkT) {
+                write_tile_mfma32<false, FM, FN>(p, tc, p.C + (long long)tc.batch * p.strideC, row + subM, col + subN, laneE, acc);
+            } else {
+                floatx4 *part = reinterpret_cast<floatx4 *>(p.ws) + ((long long)lw * 2 + (sg == p.skRounds ? 0 : 1)) * (BM * BN / 4);
+#pragma unroll
+                for (int i = 0; i < FM; ++i)
+#pragma unroll
+                    for (int j = 0; j < FN; ++j)
+#pragma unroll
+                        for (int c = 0; c < 4; ++c)
+                            part[(((wave * FM + i) * FN + j) * 4 + c) * 64 + laneE] =
+                                floatx4{acc[i][j][4 * c], acc[i][j][4 * c + 1], acc[i][j][4 * c + 2], acc[i][j][4 * c + 3]};
+            }
+        }
+    } else {
+        const TileCoord tc = tile_of_block(p);
+        const int row = __builtin_amdgcn_readfirstlane(tc.tm) * BM, col = __builtin_amdgcn_readfirstlane(tc.tn) * BN;
+        const int kLo = tc.split * p.kChunk;
+        range(static_cast<const float *>(p.A) + (long long)tc.batch * p.strideA,
+              static_cast<const float *>(p.B) + (long long)tc.batch * p.strideB, row, col, kLo, min(p.K, kLo + p.kChunk));
+        float *Cb = p.C + (long long)tc.batch * p.strideC;
+        if constexpr (KW == 1) {
+            write_tile_mfma32<SPLIT, FM, FN>(p, tc, Cb, row + subM, col + subN, lane, acc);
+        } else {
+            // float4 units [group][wave][i][j][chunk][lane], dealt out over all threads and summed in group order
+            constexpr int UNITS = (NT / 64) * FM * FN * 4 * 64;
+            floatx4 *part = reinterpret_cast<floatx4 *>(ldsAll);
+#pragma unroll
+            for (int i = 0; i < FM; ++i)
+#pragma unroll
+                for (int j = 0; j < FN; ++j)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c)
+                        part[grp * UNITS + (((wave * FM + i) * FN + j) * 4 + c) * 64 + lane] =
+                            floatx4{acc[i][j][4 * c], acc[i][j][4 * c + 1], acc[i][j][4 * c + 2], acc[i][j][4 * c + 3]};
+            __syncthreads();
+            const OutTarget o = out_target<SPLIT>(p, tc, Cb);
+            for (int u = (int)threadIdx.x; u < UNITS; u += NT * KW) {
+                floatx4 sum = part[u];
+#pragma unroll
+                for (int g = 1; g < KW; ++g) sum += part[g * UNITS + u];
+                const int ul = u & 63;
+                int q = __builtin_amdgcn_readfirstlane(u >> 6);
+                const int c = q % 4; q /= 4;
+                const int j = q % FN; q /= FN;
+                const int i = q % FM;
+                const int w = q / FM;
+                const int fr0 = row + (w / (BN / P2)) * P1 + i * 32, fc0 = col + (w % (BN / P2)) * P2 + j * 32;
+                const bool full = fr0 + 32 <= o.M && fc0 + 32 <= o.N;
+                const float v[4] = {sum[0], sum[1], sum[2], sum[3]};
+                store_lane_column<SPLIT, 4>(o, fr0 + 8 * c + 4 * (ul >> 5), fc0 + (ul & 31), full, v, [](int e) { return e; });
+            }
+        }
+    }
+}
+
+}  // namespace ks

@@ -3,6 +3,7 @@
 #include "gemm_f32.hpp"
 #include "gemm_f32_direct.hpp"
 #include "gemm_f32_kslice.hpp"
+#include "gemm_f32_parts.hpp"
 #include "registry.hpp"
 
 #ifndef KS_SHARD
@@ -19,6 +20,19 @@ static void launch_f32_fixed(const GemmParams &p, int grid, int variant, hipStre
     // the multi-tile form exists beside the single-tile one and runs when the host asks for it
     constexpr bool MULTI_OK = !SPLIT && f32_multi_tile(CORE, BM, BN, P1, P2, KW);
     const dim3 g = launch_grid(p, grid), b(NT);
+    if constexpr (f32_parts_member(CORE, BM, BN, BK, KW, SPLIT)) {
+        if (variant & 64) {                                   // on the bf16 matrix pipe
+#define KS_V(A, B) hipLaunchKernelGGL((gemm_f32_parts_kernel<BM, BN, P1, P2, SPLIT, A, B, KW, false>), g, b, 0, s, p)
+            switch ((variant >> 1) & 3) {
+                case 0: KS_V(false, false); break;
+                case 1: KS_V(false, true); break;
+                case 2: KS_V(true, false); break;
+                default: KS_V(true, true); break;
+            }
+#undef KS_V
+            return;
+        }
+    }
 #define KS_V(A, B, L)                                                                                   \
     do {                                                                                                \
         if constexpr (CORE == CORE_KSLICE)                                                              \
@@ -73,8 +87,15 @@ static void launch_f32_sk(const GemmParams &p, int grid, int variant, hipStream_
     }
     constexpr int NT = F32Shape<CORE, BM, BN, P1, P2>::threads;
     const dim3 g((unsigned)p.skGroups), b(NT);
-#define KS_V(A, B) \
-    hipLaunchKernelGGL((gemm_f32_kernel<CORE, BM, BN, BK, P1, P2, false, A, B, LOAD_STEPS, 1, false, true>), g, b, 0, s, p)
+#define KS_V(A, B)                                                                                              \
+    do {                                                                                                        \
+        if constexpr (f32_parts_member(CORE, BM, BN, BK, 1, false))                                                    \
+            if (variant & 64) {                                                                                 \
+                hipLaunchKernelGGL((gemm_f32_parts_kernel<BM, BN, P1, P2, false, A, B, 1, true>), g, b, 0, s, p);  \
+                break;                                                                                          \
+            }                                                                                                   \
+        hipLaunchKernelGGL((gemm_f32_kernel<CORE, BM, BN, BK, P1, P2, false, A, B, LOAD_STEPS, 1, false, true>), g, b, 0, s, p); \
+    } while (0)
     switch ((variant >> 1) & 3) {
         case 0: KS_V(false, false); break;
         case 1: KS_V(false, true); break;

@@ -122,6 +122,19 @@ constexpr bool f32_multi_tile(int core, int bm, int bn, int p1, int p2, int kw) 
     return core == 2 && bm * bn >= 8192 && bn >= 128 && p1 * p2 <= 2048 && kw == 1;
 }
 
+// fp32 members with a form on the bf16 matrix pipe (gemm_f32_parts.hpp): the 128 x 128 x 32 tiles, and 64 x 64 x 16 ones unless
+// K partitions of theirs have one group of waves each.
+constexpr bool f32_parts_member(int core, int bm, int bn, int bk, int kw, bool split) {
+    return core == 2 && ((bm == 128 && bn == 128 && bk == 32 && kw == 1) ||
+                         (bm == 64 && bn == 64 && bk == 16 && (kw == 2 || (kw == 1 && !split))));
+}
+// It takes K ranges (of a work-group) from these on.  Time against the fp32 matrix pipe over drawn problems of 16 to 4096 in each
+// dimension and im2col ones, all layouts, with and without scratch: 128 x 128 tiles 0.68 (110 problems; 1.03 once, at K = 31), 64 x 64
+// 0.845 (110; up to K = 48 half of them slower by up to 1.10, from 56 on 0.80 and none over 0.99), two K groups 0.86 (500; of those
+// with ranges below 360 half slower, up to 1.15, 0.95 in all: a few steps to a slice and one work-group to a compute unit wait
+// for memory, which the fp32 form has four steps in flight for; from 360 on 0.84, four over 1.02, 1.05 at most).
+constexpr int f32_parts_least_k(int kw) { return kw == 2 ? 360 : 49; }
+
 // 16-bit members whose direct-to-LDS path runs in the form with two groups of waves alternating
 // between memory and MFMA slots: the eight-wave 256 x 256 x 64 members (128 x 64 of output per wave)
 // with either fragment shape, and the eight-wave 128 x 128 x 128 members on 16x16x32 fragments

@@ -4,7 +4,7 @@
 
 namespace ks {
 
-// variant bits: 0 units of four, 1 bkc, 2 akc, 3 split over K, 4 binary16, 5 elements (direct-to-LDS path of the
+// variant bits: 0 units of four, 1 bkc, 2 akc, 3 split over K, 4 binary16, 5 elements, 6 bf16 matrix pipe (direct-to-LDS path of the
 // 16-bit members: 0 bkc, 1 akc, 3, 4)
 typedef void (*LaunchFn)(const GemmParams &p, int grid, int variant, hipStream_t stream);
 

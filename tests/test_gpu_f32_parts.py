@@ -1,0 +1,90 @@
+"""fp32 members on the bf16 matrix pipe (128 x 128 tiles plain and balanced, 64 x 64 with one and two K groups, with and without
+K partitions): sizes around the edges of tiles and K-steps against an fp64 product, and operands that three bf16 parts cannot
+hold, which come out as from fp32 arithmetic."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+LARGE, PLAIN, SMALL, GROUPS = 47, 59, 28, 32          # (59: the 128 x 128 x 32 member without a balanced form)
+LAYOUTS = [(0, 0), (0, 1), (1, 0), (1, 1)]
+
+
+@pytest.fixture()
+def ks():
+    import torch
+    import paper_2003_06795_amd.binding as ks
+    import gpu_util
+    scratch = torch.empty(68 << 20, dtype=torch.uint8, device="cuda")
+    ks.set_workspace(scratch)
+    yield ks
+    ks.set_workspace(None)
+    gpu_util.ensure_workspace.__defaults__[0].clear()
+
+
+def run(ks, kid, tA, tB, A, B, beta=0.0, C=None, pad=0):
+    """op(A) op(B) with rows `pad` elements apart that hold NaN."""
+    import torch
+
+    def stored(X, t):
+        X = X.t() if t else X
+        buf = torch.full((X.shape[0], X.shape[1] + pad), float("nan"), device="cuda")
+        buf[:, :X.shape[1]] = X
+        return buf
+    (M, K), N = A.shape, B.shape[1]
+    a, b = stored(A, tA), stored(B, tB)
+    C = torch.full((M, N), float("nan"), device="cuda") if C is None else C.clone()
+    ks.gemm_f32_with_kernel(kid, tA, tB, M, N, K, 1.0, a, a.shape[1], b, b.shape[1], beta, C, N)
+    torch.cuda.synchronize()
+    return C
+
+
+def bound(A, B, K):
+    """An accumulator is rounded after each MFMA of sixteen k, six to a product (toward zero at worst: 2^-23 of what it holds), then
+    once per K group, K partition (64 at most) and epilogue step; the products left out are 2^-25 of the whole."""
+    return ((6 * (K // 16 + 2) + 64 + 4) * 2.0 ** -23 + 2.0 ** -25) * (A.double().abs() @ B.double().abs())
+
+
+@pytest.mark.parametrize("tA,tB", LAYOUTS)
+@pytest.mark.parametrize("kid", [LARGE, PLAIN, SMALL, GROUPS])
+def test_edges(ks, kid, tA, tB):
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(3)
+    for n, (M, N, K) in enumerate([(1, 1, 49), (127, 129, 63), (128, 128, 64), (129, 65, 97), (63, 200, 255), (65, 63, 361),
+                                   (192, 131, 1025), (3, 260, 2047), (300, 257, 4001)]):
+        A = torch.rand(M, K, generator=g, device="cuda") * 2 - 1
+        B = torch.rand(K, N, generator=g, device="cuda") * 2 - 1
+        C0 = torch.rand(M, N, generator=g, device="cuda") if n % 2 else None
+        got = run(ks, kid, tA, tB, A, B, 0.5 if n % 2 else 0.0, C0, pad=(0, 3, 8)[n % 3])
+        ref = A.double() @ B.double() + (0.5 * C0.double() if n % 2 else 0.0)
+        assert ((got.double() - ref).abs() <= bound(A, B, K) + 2.0 ** -23).all(), (kid, M, N, K)
+
+
+@pytest.mark.parametrize("tA,tB", LAYOUTS)
+@pytest.mark.parametrize("kid", [LARGE, SMALL, GROUPS])
+def test_what_three_parts_cannot_hold(ks, kid, tA, tB):
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(4)
+    M, N, K = 300, 260, 1100
+    A = torch.rand(M, K, generator=g, device="cuda") * 2 - 1
+    B = torch.rand(K, N, generator=g, device="cuda") * 2 - 1
+    inf, nan, most = float("inf"), float("nan"), torch.finfo(torch.float32).max
+    for row, k, value in ((0, 0, inf), (299, 1099, -inf), (130, 700, nan), (70, 33, most), (200, 555, -most)):
+        X = A.clone()
+        X[row, k] = value
+        for swap in (False, True):                           # in either operand
+            P, Q = (B.t().contiguous(), X.t().contiguous()) if swap else (X, B)
+            got, ref = run(ks, kid, tA, tB, P, Q), P.double() @ Q.double()
+            ref32 = ref.float()
+            ok = (ref32.isnan() & got.isnan()) | (ref32.isinf() & (got == ref32)) | \
+                 (ref32.isfinite() & ((got.double() - ref).abs() <= bound(P.nan_to_num(0, most, -most), Q.nan_to_num(0, most, -most), K)))
+            # a sum beyond the largest float may overflow a step earlier or later in another order
+            assert ok[ref.abs().nan_to_num(0, 0) < 0.9 * most].all(), (kid, value, swap)
+    for scale, other in ((2.0 ** -110, 1.0), (2.0 ** -126, 2.0 ** 100), (2.0 ** -140, 2.0 ** 120)):
+        X, Y = A * scale, B * other
+        ref = X.double() @ Y.double()
+        assert ((run(ks, kid, tA, tB, X, Y).double() - ref).abs() <= bound(X, Y, K)).all(), (kid, scale)
+    X = A.clone()
+    X[17] *= 2.0 ** -120                                     # one small row among ordinary ones, and zeros
+    X[40:90] = 0.0
+    ref = X.double() @ B.double()
+    assert ((run(ks, kid, tA, tB, X, B).double() - ref).abs() <= bound(X, B, K)).all()
