@@ -61,18 +61,15 @@ template <int ROWS, int F = 32>
 struct Bf16LdsT {
     static constexpr int CPR = ROWS / 8;                    // 16-byte chunks per k row
     static constexpr int UPR = ROWS / 16;                   // 32-byte units per k row
-    // XOR applied to the 32-byte unit index of k row `k`.  A transposing read touches, per group of
-    // sixteen lanes, one or two units of four consecutive k rows, and two such groups (k and k + 8
-    // with 16 x 16 fragments, the next sixteen tile rows with 32 x 32 fragments) are served
-    // together: bits 0, 1 and 3 of k pick the unit, so that all eight land in different banks.
+    // XOR applied to the 32-byte unit index of k row `k`.  A transposing read serves 32 lanes a pass, two groups of sixteen that
+    // touch one unit each of four consecutive k rows: with 16 x 16 fragments the same unit of k and k + 8, with 32 x 32 ones
+    // two neighbouring units, an even one and the next.  All eight have to land in different banks.  k rows of 256 bytes
+    // and more start at the same one: two bits of k and bit 3, or the two bits above the one that tells the neighbours
+    // apart.  Of 128 bytes, k and k + 1 differ by themselves and bit 1 of k (and bit 3) is left; of 64 bytes, four do.
     __device__ __forceinline__ static int swz(int k) {
-        if constexpr (UPR >= 8) return (k & 3) | ((k >> 1) & 4);
-        // narrower tiles: 16 x 16 fragments read k and k + 8 in the same pass, and a k row of 128 or
-        // 64 bytes already puts k and k + 1 into different banks: the units tell k from k + 2 and
-        // from k + 8.  32 x 32 fragments read two units of four consecutive k rows per pass and
-        // keep the pairing that measured fastest for them (the other one cost them 5 - 20 %).
-        else if constexpr (UPR == 4) return F == 16 ? ((k & 2) | ((k >> 3) & 1)) : ((k >> 1) & 3);
-        else if constexpr (UPR == 2) return F == 16 ? ((k >> 3) & 1) : ((k >> 2) & 1);
+        if constexpr (UPR >= 8) return F == 16 ? ((k & 3) | ((k >> 1) & 4)) : (k & 3) << 1;
+        else if constexpr (UPR == 4) return F == 16 ? ((k & 2) | ((k >> 3) & 1)) : k & 2;
+        else if constexpr (UPR == 2) return F == 16 ? ((k >> 3) & 1) : 0;
         else return 0;
     }
     // byte offset of element (k, row) for row a multiple of 4
@@ -96,11 +93,22 @@ __device__ __forceinline__ bf16x8 read_fragment(const char *tile, int rowBase, i
         typedef short shortx8 __attribute__((ext_vector_type(8)));
         using LT = Bf16LdsT<ROWS, F>;
         const int trRow = 4 * (lane & 3) + (F == 32 ? 16 * ((lane >> 4) & 1) : 0);
-        const int kb = kk + 8 * lgrp + ((lane & 15) >> 2);
-        const shortx4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-            (__attribute__((address_space(3))) shortx4 *)(lds_void_ptr)(tile + LT::byte_of(kb, rowBase + trRow)));
-        const shortx4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-            (__attribute__((address_space(3))) shortx4 *)(lds_void_ptr)(tile + LT::byte_of(kb + 4, rowBase + trRow)));
+        const int k0 = 8 * lgrp + ((lane & 15) >> 2);
+        int at, at4;
+        if constexpr (F == 32) {
+            // The swizzle looks at bits 0 and 1 of k: k + 4 and the next k of a step are constants away.  One step from the LDS
+            // array to the address: behind a chain of them the compiler no longer knows the array, takes the stage that
+            // is read for the one being filled and waits for the loads in flight (64 x 64 x 64 NN 10.0 -> 11.8 us).
+            at = LT::byte_of(k0, rowBase + trRow);
+            asm("" : "+v"(at));
+            at += kk * (ROWS * 2);
+            at4 = at + 4 * (ROWS * 2);
+        } else {
+            at = LT::byte_of(kk + k0, rowBase + trRow);
+            at4 = LT::byte_of(kk + k0 + 4, rowBase + trRow);
+        }
+        const shortx4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) shortx4 *)(lds_void_ptr)(tile + at));
+        const shortx4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) shortx4 *)(lds_void_ptr)(tile + at4));
         const shortx8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
         return __builtin_bit_cast(bf16x8, v);
     }
