@@ -247,7 +247,7 @@ typedef struct {
                                      two-groups-of-waves form */
     int32_t vector_loads;         /* 16-byte global accesses are legal for these operands */
     int32_t grid_3d;              /* launched (tilesN, tilesM, batch * split_k) instead of one-dimensional */
-    int32_t tiles_per_workgroup;  /* > 1: the multi-tile form of the large fp32 members */
+    int32_t tiles_per_workgroup;  /* > 1: the multi-tile form of the large fp32 members; 4 on a 64 x 64 one: 2 x 2 tiles as one */
     int64_t workgroups;
     int32_t balanced_groups;      /* > 0: the balanced persistent form runs, with this many work-groups */
     int32_t divided_tiles;        /* left-over tiles of that form, handed to its second kernel (0: none launched) */

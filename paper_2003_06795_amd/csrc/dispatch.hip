@@ -747,6 +747,18 @@ int run_ws(Workspace wsp, int dtype, int id, int transA, int transB, int64_t M, 
     const int64_t waveK = K < p.kChunk ? K : p.kChunk;
     const bool parts = dtype == KS_F32 && f32_parts_member(d->core, d->bm, d->bn, d->bk, d->kw, p.splitK > 1) &&
                        waveK >= f32_parts_least_k(d->kw);
+    bool square = false;                             // 2 x 2 tiles of the member per work-group
+    if (parts && d->bm == 64 && d->kw == 1 && d->splitK == 1 && g_tilesPerWG == 0) {
+        const int64_t tilesM = (M + 127) / 128, tilesN = (N + 127) / 128, tiles128 = tilesM * tilesN * batch;
+        square = f32_parts_square(grid64, tiles128, K);
+        if (square) {
+            p.tilesM = (int)tilesM;
+            p.tilesN = (int)tilesN;
+            p.bm = p.bn = 128;
+            p.tilesPerWG = 4;
+            grid64 = tiles128;
+        }
+    }
     if (dtype == KS_F32 && !parts && !p.grid3d && p.splitK == 1 && p.skGroups == 0 && f32_multi_tile(d->core, d->bm, d->bn, d->p1, d->p2, d->kw)) {
         p.tilesPerWG = g_tilesPerWG > 0 ? g_tilesPerWG : multi_tiles(d, grid64, K);
         grid64 = (grid64 + p.tilesPerWG - 1) / p.tilesPerWG;
@@ -773,7 +785,7 @@ int run_ws(Workspace wsp, int dtype, int id, int transA, int transB, int64_t M, 
     const bool elements = oneTile && waveK <= f32_element_steps(d->core, d->bm, d->bn, d->bk, group, d->kw) * stepK;
     // and of the register-staged path of the 16-bit ones (gemm_bf16.hpp)
     const bool chunks = akc && bkc && d->bk == 128 && K % 8 == 0 && K % 128 != 0 && waveK > 128 && waveK < 512;
-    const int variant = (akc ? 4 : 0) + (bkc ? 2 : 0) + ((dtype == KS_F32 ? units : chunks) ? 1 : 0) + (elements ? 32 : 0) + (parts ? 64 : 0) + splitBit;
+    const int variant = (akc ? 4 : 0) + (bkc ? 2 : 0) + ((dtype == KS_F32 ? units : chunks) ? 1 : 0) + (elements ? 32 : 0) + (parts ? 64 : 0) + (square ? 128 : 0) + splitBit;
 
     // bf16 fast path: operand tiles go global -> LDS directly.
     const int f16Bit = dtype == KS_F16 ? 16 : 0;     // same 16-bit members, binary16 MFMA

@@ -21,6 +21,19 @@ static void launch_f32_fixed(const GemmParams &p, int grid, int variant, hipStre
     constexpr bool MULTI_OK = !SPLIT && f32_multi_tile(CORE, BM, BN, P1, P2, KW);
     const dim3 g = launch_grid(p, grid), b(NT);
     if constexpr (f32_parts_member(CORE, BM, BN, BK, KW, SPLIT)) {
+        if constexpr (BM == 64 && KW == 1) {
+            if (variant & 128) {
+#define KS_V(A, B) hipLaunchKernelGGL((gemm_f32_parts_kernel<128, 128, 64, 32, false, A, B, 1, false>), g, dim3(512), 0, s, p)
+                switch ((variant >> 1) & 3) {
+                    case 0: KS_V(false, false); break;
+                    case 1: KS_V(false, true); break;
+                    case 2: KS_V(true, false); break;
+                    default: KS_V(true, true); break;
+                }
+#undef KS_V
+                return;
+            }
+        }
         if (variant & 64) {                                   // on the bf16 matrix pipe
 #define KS_V(A, B) hipLaunchKernelGGL((gemm_f32_parts_kernel<BM, BN, P1, P2, SPLIT, A, B, KW, false>), g, b, 0, s, p)
             switch ((variant >> 1) & 3) {

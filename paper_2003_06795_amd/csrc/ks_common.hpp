@@ -134,6 +134,14 @@ constexpr bool f32_parts_member(int core, int bm, int bn, int bk, int kw, bool s
 // with ranges below 360 half slower, up to 1.15, 0.95 in all: a few steps to a slice and one work-group to a compute unit wait
 // for memory, which the fp32 form has four steps in flight for; from 360 on 0.84, four over 1.02, 1.05 at most).
 constexpr int f32_parts_least_k(int kw) { return kw == 2 ? 360 : 49; }
+// In that form an unsplit 64 x 64 x 16 member computes 2 x 2 tiles per work-group, on the 128 x 128 tile of eight waves, where a
+// work-group's sum of splitting and LDS traffic is half as long per product: the bits are the same.  Two of them fill a unit, so
+// 512 make a round; the line lies where the rounds, in units of products, are not over 1.15 of those of 256 small tiles (an even
+// share to a unit).  112 of 700 drawn problems of the unsplit member, 0.886 of the time, worst 1.05 (K from 128 on 0.85, up to
+// 80 0.94 with one in ten over 1.03): 50176 x 95 x 2757 NN 289 -> 214 us.  With the line at 1.25 155 at 0.90, eight over 1.03.
+constexpr bool f32_parts_square(int64_t tiles64, int64_t tiles128, int64_t K) {
+    return K >= 80 && 160 * ((tiles128 + 511) / 512) <= 23 * ((tiles64 + 255) / 256);
+}
 
 // 16-bit members whose direct-to-LDS path runs in the form with two groups of waves alternating
 // between memory and MFMA slots: the eight-wave 256 x 256 x 64 members (128 x 64 of output per wave)

@@ -4,8 +4,8 @@
 
 namespace ks {
 
-// variant bits: 0 units of four, 1 bkc, 2 akc, 3 split over K, 4 binary16, 5 elements, 6 bf16 matrix pipe (direct-to-LDS path of the
-// 16-bit members: 0 bkc, 1 akc, 3, 4)
+// variant bits: 0 units of four, 1 bkc, 2 akc, 3 split over K, 4 binary16, 5 elements, 6 bf16 matrix pipe, 7 the same with 2 x 2 tiles
+// per work-group (direct-to-LDS path of the 16-bit members: 0 bkc, 1 akc, 3, 4)
 typedef void (*LaunchFn)(const GemmParams &p, int grid, int variant, hipStream_t stream);
 
 struct InstanceDesc {

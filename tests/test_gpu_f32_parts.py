@@ -88,3 +88,25 @@ def test_what_three_parts_cannot_hold(ks, kid, tA, tB):
     X[40:90] = 0.0
     ref = X.double() @ B.double()
     assert ((run(ks, kid, tA, tB, X, B).double() - ref).abs() <= bound(X, B, K)).all()
+
+
+@pytest.mark.parametrize("tA,tB", LAYOUTS)
+def test_four_tiles_as_one(ks, tA, tB):
+    """The unsplit 64 x 64 member on 2 x 2 tiles per work-group: its bits on whole and ragged edges, where the rule takes it, are
+    those of single tiles, which a forced count gives."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(5)
+    try:
+        for M, N, K in ((2816, 2560, 80), (2753, 2497, 129), (57000, 97, 96)):
+            A, B = torch.rand(M, K, generator=g, device="cuda") - 0.5, torch.rand(K, N, generator=g, device="cuda") - 0.5
+            out = {}
+            for forced, per in ((1, 1), (0, 4)):
+                ks.set_tiles_per_workgroup(forced)
+                plan = ks.gemm_plan(ks.F32, SMALL, tA, tB, M, N, K, 1.0, A, M if tA else K, B, K if tB else N, 0.0, A, N)
+                edge = 128 if per == 4 else 64
+                assert plan["tiles_per_workgroup"] == per and plan["workgroups"] == -(-M // edge) * -(-N // edge)
+                out[per] = run(ks, SMALL, tA, tB, A, B, pad=3)
+            assert torch.equal(out[1], out[4]), (M, N, K)
+            assert ((out[4].double() - A.double() @ B.double()).abs() <= bound(A, B, K)).all()
+    finally:
+        ks.set_tiles_per_workgroup(0)
