@@ -32,6 +32,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 PEAK = {"f32": 157.3, "bf16": 2516.6}      # dense matrix-core TFLOP/s of MI355X
+PARTS_PEAK = 2516.6 / 6                     # of fp32 products that are six bf16 ones
 HBM_TBS = 8.0                              # published HBM3E bandwidth, TB/s
 CALIB_BYTES = 256 * 1024 * 1024
 SAMPLES = 3                                 # timed samples per row per step
@@ -39,10 +40,11 @@ SAMPLES = 3                                 # timed samples per row per step
 
 def attainable_tflops(dtype, M, N, K, batch=1, beta=0.0):
     """Roofline bound of one GEMM: min(matrix peak, arithmetic intensity x HBM bandwidth), with the
-    algorithmic bytes (each operand once, C written once and read once if beta != 0)."""
+    algorithmic bytes (each operand once, C written once and read once if beta != 0); fp32 at six bf16
+    products each, which is above the fp32 pipe's peak."""
     esz = 4 if dtype == "f32" else 2
     by = batch * ((M * K + K * N) * esz + M * N * 4 * (2 if beta != 0.0 else 1))
-    return min(PEAK[dtype], 2.0 * M * N * K * batch / by * HBM_TBS)
+    return min(PARTS_PEAK if dtype == "f32" else PEAK[dtype], 2.0 * M * N * K * batch / by * HBM_TBS)
 
 
 def f32_load_form(ki, plan, akc, bkc, M, N, K):
@@ -77,6 +79,10 @@ def kernel_symbol(ks, dt, plan, tA, tB, M, N, K):
     if dt == ks.F32 and ki["core_name"] == "kslice":
         return "gemm_f32_kslice_kernel<%d, %d, %d, %d, %d, %s, %s, %s, %s>" % (
             ki["bm"], ki["bn"], ki["bk"], ki["k_waves"], ki["wm"], b(split), b(akc), b(bkc), b(fed))
+    if dt == ks.F32 and plan["path"] == 3:
+        bm, bn, p1, p2 = (128, 128, 64, 32) if plan["tiles_per_workgroup"] > 1 else (ki["bm"], ki["bn"], ki["wm"], ki["wn"])
+        return "gemm_f32_parts_kernel<%d, %d, %d, %d, %s, %s, %s, %d, %s>" % (
+            bm, bn, p1, p2, b(split), b(akc), b(bkc), ki["k_waves"], b(plan["balanced_groups"] > 0))
     if dt == ks.F32:
         p1, p2 = (ki["tm"], ki["tn"]) if ki["core_name"] == "fma" else (ki["wm"], ki["wn"])
         return "gemm_f32_kernel<%d, %d, %d, %d, %d, %d, %s, %s, %s, %d, %d, %s, %s>" % (
@@ -589,12 +595,13 @@ def main():
     dom = max(single or list(by), key=lambda s_: by[s_]["pass_flops"])
     d = by[dom]
     achieved = d["pass_flops"] / d["pass_time"] / 1e12
+    peak = PARTS_PEAK if "parts" in dom else PEAK[dtype]
     traffic = stored_traffic(a.workload, dom)
     if traffic is not None:
         traffic["algorithmic_bytes"] = d["pass_bytes"] / d["rows"]
     pass_time = float(med.sum() * 1e-3)
-    roofline = dict(bound="mfma", kernel=dom, achieved=achieved, peak=PEAK[dtype], unit="TFLOP/s",
-                    frac=achieved / PEAK[dtype], traffic=traffic, launches_per_pass=d["rows"],
+    roofline = dict(bound="mfma", kernel=dom, achieved=achieved, peak=peak, unit="TFLOP/s",
+                    frac=achieved / peak, traffic=traffic, launches_per_pass=d["rows"],
                     flops_per_launch=d["pass_flops"] / d["rows"],
                     avg_launch_us=d["pass_time"] / d["rows"] * 1e6,
                     avg_launch_us_over_all_timed_launches=d["all_time"] / d["all_launches"] * 1e6,

@@ -814,7 +814,8 @@ int run_ws(Workspace wsp, int dtype, int id, int transA, int transB, int64_t M, 
         planOnly->workgroups = tailS ? mainGrid + tailTiles * tailS : grid64;
         planOnly->balanced_groups = p.skGroups;
         planOnly->divided_tiles = p.skTailTiles;
-        planOnly->path = !dma ? 0
+        planOnly->path = parts ? 3
+                         : !dma ? 0
                          : bf16_two_groups(d->core == KS_CORE_MFMA32 ? 32 : 16, d->bm, d->bn, d->bk, d->p1, d->p2,
                                            d->ldsBytes / (d->bk * (d->bm + d->bn) * 2))
                              ? 2
