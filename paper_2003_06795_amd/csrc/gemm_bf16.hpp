@@ -93,22 +93,25 @@ __device__ __forceinline__ bf16x8 read_fragment(const char *tile, int rowBase, i
         typedef short shortx8 __attribute__((ext_vector_type(8)));
         using LT = Bf16LdsT<ROWS, F>;
         const int trRow = 4 * (lane & 3) + (F == 32 ? 16 * ((lane >> 4) & 1) : 0);
-        const int k0 = 8 * lgrp + ((lane & 15) >> 2);
-        int at, at4;
+        shortx4 lo, hi;
         if constexpr (F == 32) {
             // The swizzle looks at bits 0 and 1 of k: k + 4 and the next k of a step are constants away.  One step from the LDS
             // array to the address: behind a chain of them the compiler no longer knows the array, takes the stage that
             // is read for the one being filled and waits for the loads in flight (64 x 64 x 64 NN 10.0 -> 11.8 us).
-            at = LT::byte_of(k0, rowBase + trRow);
+            int at = LT::byte_of(8 * lgrp + ((lane & 15) >> 2), rowBase + trRow);
             asm("" : "+v"(at));
             at += kk * (ROWS * 2);
-            at4 = at + 4 * (ROWS * 2);
+            lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) shortx4 *)(lds_void_ptr)(tile + at));
+            hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                (__attribute__((address_space(3))) shortx4 *)(lds_void_ptr)(tile + at + 4 * (ROWS * 2)));
         } else {
-            at = LT::byte_of(kk + k0, rowBase + trRow);
-            at4 = LT::byte_of(kk + k0 + 4, rowBase + trRow);
+            // (the opaque offset costs 1024 x 4096 x 4096 TN on two groups of waves 1 %)
+            const int kb = kk + 8 * lgrp + ((lane & 15) >> 2);
+            lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                (__attribute__((address_space(3))) shortx4 *)(lds_void_ptr)(tile + LT::byte_of(kb, rowBase + trRow)));
+            hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                (__attribute__((address_space(3))) shortx4 *)(lds_void_ptr)(tile + LT::byte_of(kb + 4, rowBase + trRow)));
         }
-        const shortx4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) shortx4 *)(lds_void_ptr)(tile + at));
-        const shortx4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) shortx4 *)(lds_void_ptr)(tile + at4));
         const shortx8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
         return __builtin_bit_cast(bf16x8, v);
     }
