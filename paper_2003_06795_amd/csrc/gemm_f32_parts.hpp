@@ -2,8 +2,8 @@
 //
 // The matrix pipe multiplies bf16 sixteen times as fast as fp32.  A float is the sum of three bf16 numbers, x = h + m + l,
 // each the rest of the one before rounded to nearest: 3 x 8 bits hold the 24 of the fraction, so the split is exact for
-// every |x| >= 2^-100 up to the largest bf16.  Of the nine products of two such sums the six with 2^-17 or more of the
-// whole are added, the smallest first, into the fp32 accumulators of the MFMA: h l', l h', m m', h m', m h', h h'.  The three left out
+// every |x| >= 2^-100 up to the largest bf16.  Of the nine products of two such sums six, those of up to 2^-18 of the
+// whole, are added, the smallest first, into the fp32 accumulators of the MFMA: h l', l h', m m', h m', m h', h h'.  The three left out
 // come to 2^-26 of a product at most, under half a unit in its last place, and six MFMAs of sixteen k round an accumulator
 // less often than eight of two k do: against fp64 the result is closer than the fp32 MFMA's (U[-1, 1), relative 2-norm, K = 32 /
 // 512 / 8192: 6.8e-8 / 3.4e-7 / 1.44e-6 against 1.0e-7 / 4.0e-7 / 1.62e-6; U[0, 1) 5.5e-8 / 2.4e-7 / 7.5e-7 against 8.3e-8 / 3.1e-7 / 1.18e-6).
