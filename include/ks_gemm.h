@@ -132,9 +132,9 @@ typedef struct {
  * bf16 operands are raw bfloat16 bit patterns; accumulation and C are fp32.
  * fp32 members of core KS_CORE_MFMA32 with 128 x 128 x 32 tiles, and those with 64 x 64 x 16 ones that have two K groups or no K
  * partitions, multiply a K range of at least 49 (360 with two K groups) on the bf16 matrix pipe, each float as the exact sum of
- * three bf16 numbers, accumulated in fp32: errors are no larger than the fp32 pipe's.  Work-groups that meet what the sum cannot
- * hold (magnitudes below 2^-100 other than zero, infinities, NaN, overflow) compute their range on the fp32 pipe: the results are
- * fp32 arithmetic's, in up to 1.6 times the time of a call without them.
+ * three bf16 numbers, accumulated in fp32: errors are no larger than the fp32 pipe's.  Work-groups that meet what the accumulators
+ * cannot hold (infinities, NaN, magnitudes from 2^104 on, sums from 2^82 on) compute their range on the fp32 pipe: the results are
+ * fp32 arithmetic's, in up to 2.3 times the time of a call without them.
  * Degenerate sizes: M, N or batch == 0 -> success, nothing launched; K == 0 -> C = beta*C.
  * Errors: KS_ERR_INVALID_ARG (see ks_status), KS_ERR_UNSUPPORTED when M, N or K >= 2^31 - 512 or a leading dimension >= 2^31,
  * KS_ERR_WORKSPACE, KS_ERR_LAUNCH. */

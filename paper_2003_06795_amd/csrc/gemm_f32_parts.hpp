@@ -1,17 +1,18 @@
 // fp32 members on the bf16 matrix pipe (paper Section II: the inner-product engine is one of the kernel's template axes).
 //
 // The matrix pipe multiplies bf16 sixteen times as fast as fp32.  A float is the sum of three bf16 numbers, x = h + m + l,
-// each the rest of the one before rounded to nearest: 3 x 8 bits hold the 24 of the fraction, so the split is exact for
-// every |x| >= 2^-100 up to the largest bf16.  Of the nine products of two such sums six, those of up to 2^-18 of the
-// whole, are added, the smallest first, into the fp32 accumulators of the MFMA: h l', l h', m m', h m', m h', h h'.  The three left out
-// come to 2^-26 of a product at most, under half a unit in its last place, and six MFMAs of sixteen k round an accumulator
-// less often than eight of two k do: against fp64 the result is closer than the fp32 MFMA's (U[-1, 1), relative 2-norm, K = 32 /
-// 512 / 8192: 6.8e-8 / 3.4e-7 / 1.44e-6 against 1.0e-7 / 4.0e-7 / 1.62e-6; U[0, 1) 5.5e-8 / 2.4e-7 / 7.5e-7 against 8.3e-8 / 3.1e-7 / 1.18e-6).
+// each the rest of the one before rounded to nearest: 3 x 8 bits hold the 24 of the fraction.  The split is of 2^23 x: the last
+// bit of any float is then 2^-126 or more and no part is a subnormal number (the matrix pipe keeps those, but a product of one
+// loses its last bits), so that it is exact for every |x| up to 2^104, zero and subnormal ones too.  Accumulators hold
+// 2^46 times the sum.
+// Of the nine products of two such sums six are added, the smallest first, into the fp32 accumulators of the MFMA: h l', l h', m m',
+// h m', m h', h h'.  |m| is up to 2^-8 and |l| up to 2^-17 of |x|: the three left out come to 2^-24 of a product at most.  Against
+// fp64 dense sums are closer than the fp32 MFMA's (U[-1, 1), relative 2-norm, K = 32 / 512 / 8192: 6.8e-8 / 3.4e-7 /
+// 1.44e-6 against 1.0e-7 / 4.0e-7 / 1.62e-6; U[0, 1) 5.5e-8 / 2.4e-7 / 7.5e-7 against 8.3e-8 / 3.1e-7 / 1.18e-6).
 //
-// What the split cannot hold is computed on the fp32 matrix pipe, in the same launch (`again`): a work-group that meets a
-// magnitude below 2^-100 other than zero, or ends with an accumulator that is no finite number (infinities and NaN of the
-// operands, floats that round to an infinite bf16, products that overflow), computes its K range once more from fp32 tiles in the
-// same LDS.
+// What the accumulators cannot hold is computed on the fp32 matrix pipe, in the same launch (`again`): a work-group that ends with
+// one that is no finite number (infinities and NaN of the operands, floats from 2^105 on, sums from 2^82 on) computes its K range
+// once more from fp32 tiles in the same LDS.
 //
 // One K-step is 32 k whatever the member's: both operands' parts, 48 KB of a 128 x 128 tile, in one LDS stage of the 16-bit
 // members' layouts (gemm_bf16.hpp); the next step's floats are in flight during the MFMAs and are split behind them.  Two
@@ -21,7 +22,7 @@
 // 2048^3 147 -> 100; on 64 x 64 tiles 1944 x 1264 x 1576 TT 90 -> 67, with two K groups 480 x 1184 x 2592 TN 39.6 -> 32.6.
 // Measured and left: 64 x 64 of output per wave (4096^3 level, 2048^3 +1 %, 480 x 1184 x 2592 +12 %); two K-steps in flight (level to +4 %);
 // splitting in front of the stores (level to +14 %); v_dot2_f32_bf16 for the two steps of a rest (+5 to +12 %, and its inline -1.0 is
-// the fp32 pattern); without s_setprio around the MFMAs +4 %; the check for small magnitudes costs 0 to 2 %.
+// the fp32 pattern); without s_setprio around the MFMAs +4 %.
 #pragma once
 #include "gemm_bf16.hpp"
 #include "gemm_f32.hpp"
@@ -32,21 +33,18 @@ typedef float floatx2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef unsigned uintx2 __attribute__((ext_vector_type(2)));
 
-// 2^-100 with the sign shifted out: a float from there on has its last bit at 2^-123 and three normal parts
-constexpr unsigned kPartsLeast = (127u - 100u) << 24;
+// what the operands are multiplied by: the last bit of the smallest float, 2^-149, becomes 2^-126
+constexpr float kPartsScale = 8388608.f;
 
 // the parts of four floats, two to a register
 struct FourParts {
     uintx2 part[3];
 };
-// least: smallest magnitude other than zero so far, with the sign shifted out, less one (zero wraps to the largest)
-__device__ __forceinline__ FourParts split_parts(floatx4 x, unsigned &least) {
+__device__ __forceinline__ FourParts split_parts(floatx4 x) {
     FourParts out;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-        floatx2 v = {x[2 * h], x[2 * h + 1]};
-        const unsigned u0 = __builtin_bit_cast(unsigned, v[0]), u1 = __builtin_bit_cast(unsigned, v[1]);
-        least = min(least, min((u0 << 1) - 1u, (u1 << 1) - 1u));
+        floatx2 v = {x[2 * h] * kPartsScale, x[2 * h + 1] * kPartsScale};
 #pragma unroll
         for (int s = 0; s < 3; ++s) {
             const unsigned u = __builtin_bit_cast(unsigned, __builtin_convertvector(v, bf16x2));      // to nearest, ties to even
@@ -114,7 +112,6 @@ __global__ __launch_bounds__(64 * (BM / P1) * (BN / P2) * KW, 4) void gemm_f32_p
                 lb.load_edge(B, p.ldb, col, p.N, k0, kE, tid);
             }
         };
-        unsigned least = ~0u;
         FourParts ya[LoaderA::ITERS], yb[LoaderB::ITERS];
         // (what the loads of a row-contiguous operand reach beyond its edge is none of the matrix's, whatever it holds)
         auto split = [&](auto &l, auto &y, auto kc, int origin, int limit) {
@@ -127,7 +124,7 @@ __global__ __launch_bounds__(64 * (BM / P1) * (BN / P2) * KW, 4) void gemm_f32_p
                         if (origin + tid % L::INNER * 4 + e >= limit) l.reg[it][e] = 0.f;
             }
 #pragma unroll
-            for (int it = 0; it < L::ITERS; ++it) y[it] = split_parts(l.reg[it], least);
+            for (int it = 0; it < L::ITERS; ++it) y[it] = split_parts(l.reg[it]);
         };
         auto store = [&](auto rows, auto kc, char *to, const auto &y) {
             constexpr int ROWS = decltype(rows)::value;
@@ -149,8 +146,7 @@ __global__ __launch_bounds__(64 * (BM / P1) * (BN / P2) * KW, 4) void gemm_f32_p
             split(la, ya, KCA{}, row, p.M);
             split(lb, yb, KCB{}, col, p.N);
         }
-        bool stop = false;                                   // the same for the whole work-group
-        for (int t = 0; t < nk && !stop; ++t) {
+        for (int t = 0; t < nk; ++t) {
             store(std::integral_constant<int, BM>{}, KCA{}, lds, ya);
             store(std::integral_constant<int, BN>{}, KCB{}, lds + 3 * PLANE_A, yb);
             if (t + 1 < nk) load(t + 1);
@@ -182,11 +178,7 @@ __global__ __launch_bounds__(64 * (BM / P1) * (BN / P2) * KW, 4) void gemm_f32_p
                 split(la, ya, KCA{}, row, p.M);
                 split(lb, yb, KCB{}, col, p.N);
             }
-            // operands with small magnitudes all over go to the fp32 pipe early
-            const bool look = t % 8 == 0;
-            if (look && least < kPartsLeast) again = 1;
             __syncthreads();
-            if (look) stop = __builtin_amdgcn_readfirstlane(again) != 0;
         }
         float zero = 0.f;                                    // stays zero while the accumulators are finite
 #pragma unroll
@@ -194,8 +186,11 @@ __global__ __launch_bounds__(64 * (BM / P1) * (BN / P2) * KW, 4) void gemm_f32_p
 #pragma unroll
             for (int j = 0; j < FN; ++j)
 #pragma unroll
-                for (int e = 0; e < 16; ++e) zero = fmaf(acc[i][j][e], 0.f, zero);
-        if (least < kPartsLeast || !(zero == 0.f)) again = 1;
+                for (int e = 0; e < 16; ++e) {
+                    zero = fmaf(acc[i][j][e], 0.f, zero);
+                    acc[i][j][e] *= 1.f / (kPartsScale * kPartsScale);
+                }
+        if (!(zero == 0.f)) again = 1;
         __syncthreads();
         if (__builtin_amdgcn_readfirstlane(again) != 0 && nk > 0) {
             float *as = reinterpret_cast<float *>(lds), *bs = as + LoaderA::LDS_SIZE;

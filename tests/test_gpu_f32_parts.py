@@ -6,6 +6,7 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 LARGE, PLAIN, SMALL, GROUPS = 47, 59, 28, 32          # (59: the 128 x 128 x 32 member without a balanced form)
+UNSPLIT_GROUPS = 13                                   # two K groups, never K partitions
 LAYOUTS = [(0, 0), (0, 1), (1, 0), (1, 1)]
 
 
@@ -36,6 +37,15 @@ def run(ks, kid, tA, tB, A, B, beta=0.0, C=None, pad=0):
     ks.gemm_f32_with_kernel(kid, tA, tB, M, N, K, 1.0, a, a.shape[1], b, b.shape[1], beta, C, N)
     torch.cuda.synchronize()
     return C
+
+
+def assert_parts(ks, kid, tA, tB, M, N, K):
+    """That the call runs on the bf16 matrix pipe (whatever the operands' alignment)."""
+    import torch
+    X = torch.empty(16, device="cuda")
+    plan = ks.gemm_plan(ks.F32, kid, tA, tB, M, N, K, 1.0, X, M if tA else K, X, K if tB else N, 0.0, X, N)
+    assert plan["path"] == 3, (kid, M, N, K, plan)
+    return plan
 
 
 def bound(A, B, K):
@@ -110,3 +120,42 @@ def test_four_tiles_as_one(ks, tA, tB):
             assert ((out[4].double() - A.double() @ B.double()).abs() <= bound(A, B, K)).all()
     finally:
         ks.set_tiles_per_workgroup(0)
+
+
+@pytest.mark.parametrize("tA,tB", LAYOUTS)
+@pytest.mark.parametrize("kid,K", [(PLAIN, 64), (SMALL, 64), (UNSPLIT_GROUPS, 400)])
+def test_small_magnitudes_at_every_place(ks, kid, K, tA, tB):
+    """One term to a sum, small or subnormal, in each place of a chunk of four k and of four rows or columns.  2^-22: three bf16
+    parts hold the operands exactly, the products left out are 2^-24 of the whole and each of the roundings that are not of
+    zeros (two where the parts end, one of the scale) half a unit at most; 2^-149: the unit of a subnormal sum."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(6)
+    M, N = 130, 131
+    assert_parts(ks, kid, tA, tB, M, N, K)
+    for value, other in ((1.2345678e-35, 1.0), (1.2345678e-39, 1.0), (3e-45, 2.0 ** 60), (1.2345678e-35, 2.0 ** 100)):
+        for place in range(4):
+            for k in range(4):
+                X = torch.zeros(M, K, device="cuda")
+                X[place::4, k] = value
+                Y = (torch.rand(K, N, generator=g, device="cuda") + 0.5) * other
+                for P, Q, t in ((X, Y, 0), (Y.t().contiguous(), X.t().contiguous(), 1)):
+                    if t:
+                        assert_parts(ks, kid, tA, tB, N, M, K)
+                    got, ref = run(ks, kid, tA, tB, P, Q).double(), P.double() @ Q.double()
+                    assert ((got - ref).abs() <= 2.0 ** -22 * ref.abs() + 2.0 ** -149).all(), (value, other, place, k, t)
+
+
+@pytest.mark.parametrize("tA,tB", LAYOUTS)
+@pytest.mark.parametrize("kid,K", [(PLAIN, 256), (SMALL, 256), (UNSPLIT_GROUPS, 400)])
+def test_products_around_the_smallest_float(ks, kid, K, tA, tB):
+    """Operands of ordinary magnitude whose products, or whose sums, are near 2^-126 and below: no part of a product is lost."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(7)
+    M, N = 130, 131
+    assert_parts(ks, kid, tA, tB, M, N, K)
+    A = torch.rand(M, K, generator=g, device="cuda") + 0.5
+    B = torch.rand(K, N, generator=g, device="cuda") + 0.5
+    for a, b in ((-55, -62), (-64, -64), (-90, -40), (-40, -90), (-75, -74), (-130, 1)):
+        X, Y = A * 2.0 ** a, B * 2.0 ** b
+        ref = X.double() @ Y.double()
+        assert ((run(ks, kid, tA, tB, X, Y).double() - ref).abs() <= bound(X, Y, K) + 2.0 ** -149).all(), (a, b)
