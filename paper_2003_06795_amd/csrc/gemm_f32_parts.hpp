@@ -5,24 +5,36 @@
 // bit of any float is then 2^-126 or more and no part is a subnormal number (the matrix pipe keeps those, but a product of one
 // loses its last bits), so that it is exact for every |x| up to 2^104, zero and subnormal ones too.  Accumulators hold
 // 2^46 times the sum.
-// Of the nine products of two such sums six are added, the smallest first, into the fp32 accumulators of the MFMA: h l', l h', m m',
-// h m', m h', h h'.  |m| is up to 2^-8 and |l| up to 2^-17 of |x|: the three left out come to 2^-24 of a product at most.  Against
-// fp64 dense sums are closer than the fp32 MFMA's (U[-1, 1), relative 2-norm, K = 32 / 512 / 8192: 6.8e-8 / 3.4e-7 /
-// 1.44e-6 against 1.0e-7 / 4.0e-7 / 1.62e-6; U[0, 1) 5.5e-8 / 2.4e-7 / 7.5e-7 against 8.3e-8 / 3.1e-7 / 1.18e-6).
+// Of the nine products of two such sums six are added: h h' into one fp32 accumulator, the small ones, h m', m h', m m', h l' and
+// l h', into a second one, and the two into one another at the end.  |m| is up to 2^-8 and |l| up to 2^-17 of |x|: the three left
+// out come to 2^-24 of a product at most.  An MFMA drops what lies about 24 bits below the largest of its sixteen products and of the
+// accumulator: with the small products in an accumulator of their own that happens to a sum once in sixteen k, not six times.
+// Error against fp64, rms over sum |a b|, fp32 pipe -> here, K = 49 / 128 / 2048 / 8192, 1e-8:
+//   U[-1, 1) 2.4 / 2.4 / 2.4 / 2.4 -> 0.8 / 0.7 / 0.7 / 0.8      exp(2 N(0, 1)) 11 / 18 / 72 / 272 -> 6.3 / 8.0 / 25 / 49
+//   U[0, 1) 10 / 16 / 60 / 119 -> 4.2 / 6.2 / 22 / 42             four terms of N(0, 1) 2.7 / 2.6 / 2.7 / 2.6 -> 1.9 / 1.9 / 1.9 / 1.9
+//   one term 2.53 -> 2.59 at any K (at most 5.9 -> 9.2: the products left out); softmax(32 N(0, 1)) by N(0, 1), a few terms that are
+//   nearly all of the sum, 3.2 / 3.6 / 4.4 / 4.6 -> 3.8 / 4.0 / 5.0 / 5.1.
+// With all six in one accumulator U[-1, 1) comes to 2.0 / 1.9 / 2.0 / 2.2, four terms to 4.1 / 4.6 / 4.9 / 4.8, one term to 3.4.  Eight
+// products bring one term to 2.53, for 1.07 of the time of two K groups, 1.15 on 64 x 64 tiles, 1.25 on 128 x 128 ones.
 //
 // What the accumulators cannot hold is computed on the fp32 matrix pipe, in the same launch (`again`): a work-group that ends with
 // one that is no finite number (infinities and NaN of the operands, floats from 2^105 on, sums from 2^82 on) computes its K range
 // once more from fp32 tiles in the same LDS.
 //
 // One K-step is 32 k whatever the member's: both operands' parts, 48 KB of a 128 x 128 tile, in one LDS stage of the 16-bit
-// members' layouts (gemm_bf16.hpp); the next step's floats are in flight during the MFMAs and are split behind them.  Two
-// work-groups of a compute unit fill each other's barriers.  Bound by power on large problems (4096^3 at 215 TFLOP/s is 1.29 PFLOP/s
-// of bf16) and by the sum of splitting (seven VALU instructions an element), LDS traffic and MFMAs on 64 x 64 tiles.
-// Against the fp32 matrix pipe, us: 4096^3 NT 1080 -> 635, TN 1040 -> 671; 4095 x 3000 x 4089 NT 806 -> 530; 25088 x 256 x 1152 NN 142 -> 99;
-// 2048^3 147 -> 100; on 64 x 64 tiles 1944 x 1264 x 1576 TT 90 -> 67, with two K groups 480 x 1184 x 2592 TN 39.6 -> 32.6.
-// Measured and left: 64 x 64 of output per wave (4096^3 level, 2048^3 +1 %, 480 x 1184 x 2592 +12 %); two K-steps in flight (level to +4 %);
-// splitting in front of the stores (level to +14 %); v_dot2_f32_bf16 for the two steps of a rest (+5 to +12 %, and its inline -1.0 is
-// the fp32 pattern); without s_setprio around the MFMAs +4 %.
+// members' layouts (gemm_bf16.hpp); the next step's floats are in flight during the MFMAs and are split on their way to LDS.
+// Two work-groups of a compute unit fill each other's barriers, which takes eight waves in 128 registers: 64 of them are
+// accumulators, so that parts live for a store only and a fragment of A for the products that it enters.  Bound
+// by power on large problems (4096^3 at 215 TFLOP/s is 1.29 PFLOP/s of bf16) and by the sum of splitting (seven VALU
+// instructions an element), LDS traffic and MFMAs on 64 x 64 tiles.
+// Against the fp32 matrix pipe, us: 4096^3 NT 1000 -> 634, TN 1030 -> 672; 4095 x 3000 x 4089 NT 802 -> 529; 25088 x 256 x 1152 NN 140 -> 99;
+// 2048^3 NN 150 -> 101; on 64 x 64 tiles 1944 x 1264 x 1576 TT 89 -> 67, 1000^3 NT 33.8 -> 28.0, with two K groups 480 x 1184 x 2592 TN
+// 39.5 -> 31.8.
+// Measured and left, with two accumulators: 64 x 64 of output per wave in 256 registers (1.2 to 1.4 of the time); one work-group of
+// eight waves a unit, two LDS stages, one half of the waves splitting while the other multiplies (1.1 to 1.3); splitting behind
+// the MFMAs (128 registers do not hold the parts too: spills, 1.2 to 1.6; 64 x 64 tiles -2 to +12 %); the sum of a K-step in
+// registers of its own, added by VALU (1.5 to 2.3).  With one: two K-steps in flight (level to +4 %); v_dot2_f32_bf16 for the two steps of a rest
+// (+5 to +12 %, and its inline -1.0 is the fp32 pattern); without s_setprio around the MFMAs +4 %.
 #pragma once
 #include "gemm_bf16.hpp"
 #include "gemm_f32.hpp"
@@ -77,20 +89,27 @@ __global__ __launch_bounds__(64 * (BM / P1) * (BN / P2) * KW, 4) void gemm_f32_p
 
     const int grp = KW == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x / NT);
     char *const lds = ldsAll[grp];
-    const int tid = KW == 1 ? (int)threadIdx.x : (int)threadIdx.x % NT, lane = tid & 63, wave = tid >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x % NT >> 6);
+    // (counted where it is needed: the balanced form's loop over tiles would keep it, and what follows from it, in registers)
+    auto this_lane = []() {
+        int zero = 0;
+        asm volatile("" : "+v"(zero));
+        return (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, (unsigned)zero)) & 63;
+    };
     const int subM = (wave / (BN / P2)) * P1, subN = (wave % (BN / P2)) * P2;
-    floatx16 acc[FM][FN];
-    auto clear = [&]() {
+    floatx16 acc[FM][FN], low[FM][FN];                       // sums of h h', of the small products
+    auto each = [&](auto f) {
 #pragma unroll
         for (int i = 0; i < FM; ++i)
 #pragma unroll
             for (int j = 0; j < FN; ++j)
 #pragma unroll
-                for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+                for (int e = 0; e < 16; ++e) f(i, j, e);
     };
 
     // acc = the products of k in [kLo, kHi) of the tile at (row, col), this group's slice of them
     auto range = [&](const float *A, const float *B, int row, int col, int kLo, int kHi) {
+        const int lane = SK ? this_lane() : (int)threadIdx.x & 63, tid = SK ? wave * 64 + lane : (int)threadIdx.x % NT;
         const int nk = (max(kHi - kLo, 0) + KW * BK - 1) / (KW * BK);        // steps of the longest slice, for all groups
         const int kB = kLo + grp * nk * BK, kE = min(kHi, kB + nk * BK);     // kE may lie below kB: an empty slice
         typename LoaderA::Plan pa;
@@ -103,6 +122,11 @@ __global__ __launch_bounds__(64 * (BM / P1) * (BN / P2) * KW, 4) void gemm_f32_p
         auto load = [&](int t) {
             const int k0 = kB + t * BK;
             if (t < full) {
+                // (so that the compiler extends the offsets here and not, to two registers each, outside the K loop)
+#pragma unroll
+                for (unsigned &o : pa.off) asm volatile("" : "+v"(o));
+#pragma unroll
+                for (unsigned &o : pb.off) asm volatile("" : "+v"(o));
                 la.load(pa, AKC ? A + (long long)row * p.lda + k0 : A + (long long)k0 * p.lda + row, p.lda, tid);
                 lb.load(pb, BKC ? B + (long long)col * p.ldb + k0 : B + (long long)k0 * p.ldb + col, p.ldb, tid);
             } else {
@@ -112,89 +136,95 @@ __global__ __launch_bounds__(64 * (BM / P1) * (BN / P2) * KW, 4) void gemm_f32_p
                 lb.load_edge(B, p.ldb, col, p.N, k0, kE, tid);
             }
         };
-        FourParts ya[LoaderA::ITERS], yb[LoaderB::ITERS];
-        // (what the loads of a row-contiguous operand reach beyond its edge is none of the matrix's, whatever it holds)
-        auto split = [&](auto &l, auto &y, auto kc, int origin, int limit) {
-            using L = std::remove_reference_t<decltype(l)>;
-            if (!decltype(kc)::value && origin + L::INNER * 4 > limit) {
-#pragma unroll
-                for (int it = 0; it < L::ITERS; ++it)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        if (origin + tid % L::INNER * 4 + e >= limit) l.reg[it][e] = 0.f;
-            }
-#pragma unroll
-            for (int it = 0; it < L::ITERS; ++it) y[it] = split_parts(l.reg[it]);
-        };
-        auto store = [&](auto rows, auto kc, char *to, const auto &y) {
+        auto store = [&](auto rows, auto kc, char *to, const auto &l) {
             constexpr int ROWS = decltype(rows)::value;
             constexpr bool KC = decltype(kc)::value;
             using L = TileLoader<ROWS, BK, NT, KC, 4, KC>;
+            int from = tid;
+            if constexpr (SK) {                              // (addresses that are made anew take no registers during the MFMAs)
+                asm volatile("" : "+v"(from));
+                from &= NT - 1;
+            }
 #pragma unroll
             for (int it = 0; it < L::ITERS; ++it) {
-                const int inner = tid % L::INNER, outer = tid / L::INNER + it * L::STRIDE;
+                const int inner = from % L::INNER, outer = from / L::INNER + it * L::STRIDE;
                 const int at = KC ? 16 * Bf16Lds<BK>::chunk(outer, inner / 2) + 8 * (inner & 1)
                                   : Bf16LdsT<ROWS, 32>::byte_of(outer, inner * 4);
+                const FourParts y = split_parts(l.reg[it]);
 #pragma unroll
-                for (int s = 0; s < 3; ++s) *reinterpret_cast<uintx2 *>(to + s * (ROWS * BK * 2) + at) = y[it].part[s];
+                for (int s = 0; s < 3; ++s) *reinterpret_cast<uintx2 *>(to + s * (ROWS * BK * 2) + at) = y.part[s];
             }
         };
-        clear();
-        if (threadIdx.x == 0) again = 0;
-        if (nk > 0) {
-            load(0);
-            split(la, ya, KCA{}, row, p.M);
-            split(lb, yb, KCB{}, col, p.N);
-        }
-        for (int t = 0; t < nk; ++t) {
-            store(std::integral_constant<int, BM>{}, KCA{}, lds, ya);
-            store(std::integral_constant<int, BN>{}, KCB{}, lds + 3 * PLANE_A, yb);
-            if (t + 1 < nk) load(t + 1);
-            __syncthreads();
+        auto multiply = [&](const char *from) {
             __builtin_amdgcn_s_setprio(1);
 #pragma unroll
             for (int kk = 0; kk < BK; kk += 16) {
-                bf16x8 a[3][FM], b[3][FN];
+                bf16x8 a[FM], b[FN], b1[FN];                 // one part of A at a time; one of B and its second
+                auto readA = [&](int s) {
 #pragma unroll
-                for (int s = 0; s < 3; ++s) {
-#pragma unroll
-                    for (int i = 0; i < FM; ++i)
-                        a[s][i] = read_fragment<32, BM, BK, AKC>(lds + s * PLANE_A, subM + i * 32, kk, lane);
+                    for (int i = 0; i < FM; ++i) a[i] = read_fragment<32, BM, BK, AKC>(from + s * PLANE_A, subM + i * 32, kk, lane);
+                };
+                auto readB = [&](bf16x8 (&b)[FN], int s) {
 #pragma unroll
                     for (int j = 0; j < FN; ++j)
-                        b[s][j] = read_fragment<32, BN, BK, BKC>(lds + 3 * PLANE_A + s * PLANE_B, subN + j * 32, kk, lane);
-                }
-                constexpr int TA[6] = {0, 2, 1, 0, 1, 0}, TB[6] = {2, 0, 1, 1, 0, 0};
-#pragma unroll
-                for (int q = 0; q < 6; ++q)
+                        b[j] = read_fragment<32, BN, BK, BKC>(from + 3 * PLANE_A + s * PLANE_B, subN + j * 32, kk, lane);
+                };
+                auto mul = [&](floatx16 (&to)[FM][FN], bf16x8 (&b)[FN]) {
 #pragma unroll
                     for (int i = 0; i < FM; ++i)
 #pragma unroll
-                        for (int j = 0; j < FN; ++j)
-                            acc[i][j] = mfma_32x32x16<false>(a[TA[q]][i], b[TB[q]][j], acc[i][j]);
+                        for (int j = 0; j < FN; ++j) to[i][j] = mfma_32x32x16<false>(a[i], b[j], to[i][j]);
+                };
+                readB(b, 0);
+                readA(2);
+                mul(low, b);
+                readB(b1, 1);
+                readA(1);
+                mul(low, b1);
+                mul(low, b);
+                readA(0);
+                mul(acc, b);
+                mul(low, b1);
+                readB(b, 2);
+                mul(low, b);
             }
             __builtin_amdgcn_s_setprio(0);
-            if (t + 1 < nk) {
-                split(la, ya, KCA{}, row, p.M);
-                split(lb, yb, KCB{}, col, p.N);
-            }
+        };
+        each([&](int i, int j, int e) { acc[i][j][e] = low[i][j][e] = 0.f; });
+        if (nk > 0) load(0);
+        if (grp == 0 && tid == 0) again = 0;
+        for (int t = 0; t < nk; ++t) {
+            store(std::integral_constant<int, BM>{}, KCA{}, lds, la);
+            store(std::integral_constant<int, BN>{}, KCB{}, lds + 3 * PLANE_A, lb);
+            if (t + 1 < nk) load(t + 1);
+            __syncthreads();
+            multiply(lds);
             __syncthreads();
         }
         float zero = 0.f;                                    // stays zero while the accumulators are finite
+        each([&](int i, int j, int e) {
+            acc[i][j][e] += low[i][j][e];
+            zero = fmaf(acc[i][j][e], 0.f, zero);
+            acc[i][j][e] *= 1.f / (kPartsScale * kPartsScale);
+        });
+        // (what the loads of a row-contiguous operand reach beyond its edge is none of the matrix's, whatever it holds)
+        if (!(zero == 0.f)) {
 #pragma unroll
-        for (int i = 0; i < FM; ++i)
+            for (int i = 0; i < FM; ++i)
 #pragma unroll
-            for (int j = 0; j < FN; ++j)
+                for (int j = 0; j < FN; ++j) {
+                    const int rows = p.M - (row + subM + i * 32 + 4 * (lane >> 5)), cols = p.N - (col + subN + j * 32 + (lane & 31));
+                    unsigned bits = 0;                       // bit e: accumulator e of the fragment
 #pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    zero = fmaf(acc[i][j][e], 0.f, zero);
-                    acc[i][j][e] *= 1.f / (kPartsScale * kPartsScale);
+                    for (int e = 0; e < 16; ++e)
+                        bits |= !__builtin_isfinite(acc[i][j][e]) && 8 * (e / 4) + e % 4 < rows && cols > 0 ? 1u << e : 0u;
+                    if (bits) again = 1;
                 }
-        if (!(zero == 0.f)) again = 1;
+        }
         __syncthreads();
         if (__builtin_amdgcn_readfirstlane(again) != 0 && nk > 0) {
+            each([&](int i, int j, int e) { acc[i][j][e] = 0.f; });
             float *as = reinterpret_cast<float *>(lds), *bs = as + LoaderA::LDS_SIZE;
-            clear();
             load(0);
             for (int t = 0; t < nk; ++t) {
                 la.store(as, tid);
@@ -257,8 +287,7 @@ __global__ __launch_bounds__(64 * (BM / P1) * (BN / P2) * KW, 4) void gemm_f32_p
             const int row = tc.tm * BM, col = tc.tn * BN;
             range(static_cast<const float *>(p.A) + (long long)tc.batch * p.strideA,
                   static_cast<const float *>(p.B) + (long long)tc.batch * p.strideB, row, col, ks0 * BK, min(p.K, ks1 * BK));
-            int laneE = lane;
-            asm volatile("" : "+v"(laneE));
+            const int laneE = this_lane();
             if (ks0 == 0 && ks1 == nkT) {
                 write_tile_mfma32<false, FM, FN>(p, tc, p.C + (long long)tc.batch * p.strideC, row + subM, col + subN, laneE, acc);
             } else {
@@ -281,7 +310,7 @@ __global__ __launch_bounds__(64 * (BM / P1) * (BN / P2) * KW, 4) void gemm_f32_p
               static_cast<const float *>(p.B) + (long long)tc.batch * p.strideB, row, col, kLo, min(p.K, kLo + p.kChunk));
         float *Cb = p.C + (long long)tc.batch * p.strideC;
         if constexpr (KW == 1) {
-            write_tile_mfma32<SPLIT, FM, FN>(p, tc, Cb, row + subM, col + subN, lane, acc);
+            write_tile_mfma32<SPLIT, FM, FN>(p, tc, Cb, row + subM, col + subN, (int)threadIdx.x & 63, acc);
         } else {
             // float4 units [group][wave][i][j][chunk][lane], dealt out over all threads and summed in group order
             constexpr int UNITS = (NT / 64) * FM * FN * 4 * 64;
@@ -292,7 +321,7 @@ __global__ __launch_bounds__(64 * (BM / P1) * (BN / P2) * KW, 4) void gemm_f32_p
                 for (int j = 0; j < FN; ++j)
 #pragma unroll
                     for (int c = 0; c < 4; ++c)
-                        part[grp * UNITS + (((wave * FM + i) * FN + j) * 4 + c) * 64 + lane] =
+                        part[grp * UNITS + (((wave * FM + i) * FN + j) * 4 + c) * 64 + ((int)threadIdx.x & 63)] =
                             floatx4{acc[i][j][4 * c], acc[i][j][4 * c + 1], acc[i][j][4 * c + 2], acc[i][j][4 * c + 3]};
             __syncthreads();
             const OutTarget o = out_target<SPLIT>(p, tc, Cb);

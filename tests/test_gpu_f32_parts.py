@@ -49,9 +49,11 @@ def assert_parts(ks, kid, tA, tB, M, N, K):
 
 
 def bound(A, B, K):
-    """An accumulator is rounded after each MFMA of sixteen k, six to a product (toward zero at worst: 2^-23 of what it holds), then
-    once per K group, K partition (64 at most) and epilogue step; the products left out are 2^-25 of the whole."""
-    return ((6 * (K // 16 + 2) + 64 + 4) * 2.0 ** -23 + 2.0 ** -25) * (A.double().abs() @ B.double().abs())
+    """An MFMA adds sixteen products, each cut off 24 bits below the largest of them and of the accumulator at worst: 2^-22 of
+    the sum of magnitudes so far in nearly all cases, once per sixteen k in the accumulator of the large products and five times
+    in the one of the small ones, which are 2^-7 of the whole; then one rounding per K group, K partition (64 at
+    most) and epilogue step; the products left out are 2^-24 of the whole."""
+    return ((K // 16 + 2) * (1 + 5 / 128) * 2.0 ** -22 + (64 + 4 + 1) * 2.0 ** -24) * (A.double().abs() @ B.double().abs())
 
 
 @pytest.mark.parametrize("tA,tB", LAYOUTS)
@@ -126,8 +128,8 @@ def test_four_tiles_as_one(ks, tA, tB):
 @pytest.mark.parametrize("kid,K", [(PLAIN, 64), (SMALL, 64), (UNSPLIT_GROUPS, 400)])
 def test_small_magnitudes_at_every_place(ks, kid, K, tA, tB):
     """One term to a sum, small or subnormal, in each place of a chunk of four k and of four rows or columns.  2^-22: three bf16
-    parts hold the operands exactly, the products left out are 2^-24 of the whole and each of the roundings that are not of
-    zeros (two where the parts end, one of the scale) half a unit at most; 2^-149: the unit of a subnormal sum."""
+    parts hold the operands exactly, the products left out are 2^-24 of the whole, the last rounding as much, and the small
+    products' half a unit of 2^-8 of it; 2^-149: the unit of a subnormal sum."""
     import torch
     g = torch.Generator(device="cuda").manual_seed(6)
     M, N = 130, 131
@@ -159,3 +161,56 @@ def test_products_around_the_smallest_float(ks, kid, K, tA, tB):
         X, Y = A * 2.0 ** a, B * 2.0 ** b
         ref = X.double() @ Y.double()
         assert ((run(ks, kid, tA, tB, X, Y).double() - ref).abs() <= bound(X, Y, K) + 2.0 ** -149).all(), (a, b)
+
+
+# rms error over sum |a b| against that of a member on the fp32 matrix pipe (64 x 64 tiles, one K group), at most: measured 0.28 - 0.45,
+# 0.35 - 0.60, 0.69 - 0.90, 1.02 - 1.03 and 1.13 - 1.20 of it.  (All six products in one accumulator give 0.8, 0.8, 1.5 - 1.9, 1.35 and 1.0 - 1.2.)
+FP32_PIPE = 60
+ERRORS = {"dense": 0.55, "positive, uneven": 0.7, "four terms": 1.0, "one term": 1.1, "nearly one term": 1.3}
+
+
+@pytest.mark.parametrize("tA,tB", LAYOUTS)
+@pytest.mark.parametrize("kid,K", [(PLAIN, 64), (PLAIN, 2048), (LARGE, 1100), (SMALL, 64), (SMALL, 512), (UNSPLIT_GROUPS, 400),
+                                   (UNSPLIT_GROUPS, 2048)])
+def test_error_is_the_fp32_pipes(ks, kid, K, tA, tB):
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(8)
+    M = N = 384
+    ks.set_workspace(None)                                   # one K range to a tile in either member
+    assert_parts(ks, kid, tA, tB, M, N, K)
+
+    def normal(*shape):
+        return torch.randn(*shape, generator=g, device="cuda")
+    one = torch.zeros(M, K, device="cuda")
+    one[torch.arange(M), torch.arange(M) % K] = 1.0
+    few = (torch.rand(M, K, generator=g, device="cuda") < 4.0 / K).float()
+    for what, A, B in (("dense", torch.rand(M, K, generator=g, device="cuda") * 2 - 1, torch.rand(K, N, generator=g, device="cuda") * 2 - 1),
+                       ("positive, uneven", (2 * normal(M, K)).exp(), (2 * normal(K, N)).exp()),
+                       ("four terms", few * normal(M, K), normal(K, N)),
+                       ("one term", one * normal(M, 1), normal(K, N)),
+                       ("nearly one term", torch.softmax(32 * normal(M, K), 1), normal(K, N))):
+        ref, whole = A.double() @ B.double(), A.double().abs() @ B.double().abs()
+        rms = {}
+        for k in (kid, FP32_PIPE):
+            error = (run(ks, k, tA, tB, A, B).double() - ref)[whole > 0] / whole[whole > 0]
+            rms[k] = error.square().mean().sqrt().item()
+        assert rms[kid] <= ERRORS[what] * rms[FP32_PIPE], (what, rms)
+
+
+@pytest.mark.parametrize("tA,tB", LAYOUTS)
+@pytest.mark.parametrize("kid,K", [(PLAIN, 192), (SMALL, 192), (UNSPLIT_GROUPS, 400)])
+def test_every_part_arrives(ks, kid, K, tA, tB):
+    """Floats of 24 random bits times one power of two each come out as they are: each entry is one operand's three parts."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(9)
+    M, N = 150, 170
+    assert_parts(ks, kid, tA, tB, M, N, K)
+    A = (torch.rand(M, K, generator=g, device="cuda") + 0.5) * torch.where(torch.rand(M, K, generator=g, device="cuda") < 0.5, -1.0, 1.0)
+    B = torch.zeros(K, N, device="cuda")
+    at = torch.randint(0, K, (N,), generator=g, device="cuda")
+    powers = torch.randint(-20, 20, (N,), generator=g, device="cuda").cpu()
+    B[at, torch.arange(N, device="cuda")] = torch.ldexp(torch.ones(N), powers).cuda()
+    expected = A[:, at] * B.amax(0)
+    assert torch.equal(run(ks, kid, tA, tB, A, B), expected)
+    assert_parts(ks, kid, tA, tB, N, M, K)
+    assert torch.equal(run(ks, kid, tA, tB, B.t().contiguous(), A.t().contiguous()), expected.t())
