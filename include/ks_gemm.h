@@ -133,9 +133,10 @@ typedef struct {
  * fp32 members of core KS_CORE_MFMA32 with 128 x 128 x 32 tiles, and those with 64 x 64 x 16 ones that have two K groups or no K
  * partitions, multiply a K range of at least 49 (360 with two K groups) on the bf16 matrix pipe, each float as the exact sum of
  * three bf16 numbers, accumulated in fp32: rms errors are 0.3 to 0.9 of the fp32 pipe's for dense and sparse sums, 1.03 for one term
- * (2^-23 of it at most), 1.2 for sums that a few terms nearly are.  Work-groups that meet what the accumulators
- * cannot hold (infinities, NaN, magnitudes from 2^104 on, sums from 2^82 on) compute their range on the fp32 pipe: the results are
- * fp32 arithmetic's, in up to 2.3 times the time of a call without them.
+ * (2^-23 of it at most), 1.2 for sums that a few terms nearly are.  Entries that the accumulators cannot hold (infinities, NaN,
+ * magnitudes from 2^104 on, sums from 2^82 on) are computed once more on the fp32 pipe, in the same launch: the results are fp32
+ * arithmetic's, in up to 2.6 times the time of a call without them.  On which pipe an entry is computed depends on its row of
+ * op(A) and its column of op(B) alone.
  * Degenerate sizes: M, N or batch == 0 -> success, nothing launched; K == 0 -> C = beta*C.
  * Errors: KS_ERR_INVALID_ARG (see ks_status), KS_ERR_UNSUPPORTED when M, N or K >= 2^31 - 512 or a leading dimension >= 2^31,
  * KS_ERR_WORKSPACE, KS_ERR_LAUNCH. */

@@ -17,9 +17,12 @@
 // With all six in one accumulator U[-1, 1) comes to 2.0 / 1.9 / 2.0 / 2.2, four terms to 4.1 / 4.6 / 4.9 / 4.8, one term to 3.4.  Eight
 // products bring one term to 2.53, for 1.07 of the time of two K groups, 1.15 on 64 x 64 tiles, 1.25 on 128 x 128 ones.
 //
-// What the accumulators cannot hold is computed on the fp32 matrix pipe, in the same launch (`again`): a work-group that ends with
-// one that is no finite number (infinities and NaN of the operands, floats from 2^105 on, sums from 2^82 on) computes its K range
-// once more from fp32 tiles in the same LDS.
+// What the accumulators cannot hold is computed on the fp32 matrix pipe, in the same launch: a work-group that ends with one that
+// is no finite number (infinities and NaN of the operands, floats from 2^105 on, sums from 2^82 on) goes through its K range
+// once more with fp32 tiles in the same LDS, and takes from it the entries that were not finite.  How an entry is computed depends
+// on its row of A and its column of B alone, whatever the tile holds beside it.  Waves without such entries leave out
+// the MFMAs: us, without -> one infinity / one in each tile: 4096^3 NT 633 -> 1024 / 1608, 2048^3 NN 103 -> 169 / 225,
+// 480 x 1184 x 2592 TN 35.6 -> 53 / 52 (fp32 pipe 997, 165, 43).
 //
 // One K-step is 32 k whatever the member's: both operands' parts, 48 KB of a 128 x 128 tile, in one LDS stage of the 16-bit
 // members' layouts (gemm_bf16.hpp); the next step's floats are in flight during the MFMAs and are split on their way to LDS.
@@ -208,22 +211,30 @@ __global__ __launch_bounds__(64 * (BM / P1) * (BN / P2) * KW, 4) void gemm_f32_p
             acc[i][j][e] *= 1.f / (kPartsScale * kPartsScale);
         });
         // (what the loads of a row-contiguous operand reach beyond its edge is none of the matrix's, whatever it holds)
+        unsigned lost[FM][FN] = {};                          // bit e: accumulator e of the fragment
         if (!(zero == 0.f)) {
 #pragma unroll
             for (int i = 0; i < FM; ++i)
 #pragma unroll
                 for (int j = 0; j < FN; ++j) {
                     const int rows = p.M - (row + subM + i * 32 + 4 * (lane >> 5)), cols = p.N - (col + subN + j * 32 + (lane & 31));
-                    unsigned bits = 0;                       // bit e: accumulator e of the fragment
+                    unsigned bits = 0;
 #pragma unroll
                     for (int e = 0; e < 16; ++e)
                         bits |= !__builtin_isfinite(acc[i][j][e]) && 8 * (e / 4) + e % 4 < rows && cols > 0 ? 1u << e : 0u;
+                    lost[i][j] = bits;
                     if (bits) again = 1;
                 }
         }
         __syncthreads();
-        if (__builtin_amdgcn_readfirstlane(again) != 0 && nk > 0) {
-            each([&](int i, int j, int e) { acc[i][j][e] = 0.f; });
+        if (__builtin_amdgcn_readfirstlane(again) != 0) {
+            unsigned some = 0;
+#pragma unroll
+            for (int i = 0; i < FM; ++i)
+#pragma unroll
+                for (int j = 0; j < FN; ++j) some |= lost[i][j];
+            const bool mine = __any((int)some);
+            each([&](int i, int j, int e) { low[i][j][e] = 0.f; });
             float *as = reinterpret_cast<float *>(lds), *bs = as + LoaderA::LDS_SIZE;
             load(0);
             for (int t = 0; t < nk; ++t) {
@@ -231,23 +242,28 @@ __global__ __launch_bounds__(64 * (BM / P1) * (BN / P2) * KW, 4) void gemm_f32_p
                 lb.store(bs, tid);
                 if (t + 1 < nk) load(t + 1);
                 __syncthreads();
+                if (mine) {
 #pragma unroll 1
-                for (int kk = 0; kk < BK; kk += 8) {
-                    floatx4 a[FM], b[FN];
+                    for (int kk = 0; kk < BK; kk += 8) {
+                        floatx4 a[FM], b[FN];
 #pragma unroll
-                    for (int i = 0; i < FM; ++i) a[i] = LoaderA::read(as, subM + i * 32 + (lane & 31), kk + 4 * (lane >> 5));
+                        for (int i = 0; i < FM; ++i) a[i] = LoaderA::read(as, subM + i * 32 + (lane & 31), kk + 4 * (lane >> 5));
 #pragma unroll
-                    for (int j = 0; j < FN; ++j) b[j] = LoaderB::read(bs, subN + j * 32 + (lane & 31), kk + 4 * (lane >> 5));
+                        for (int j = 0; j < FN; ++j) b[j] = LoaderB::read(bs, subN + j * 32 + (lane & 31), kk + 4 * (lane >> 5));
 #pragma unroll
-                    for (int e = 0; e < 4; ++e)
+                        for (int e = 0; e < 4; ++e)
 #pragma unroll
-                        for (int i = 0; i < FM; ++i)
+                            for (int i = 0; i < FM; ++i)
 #pragma unroll
-                            for (int j = 0; j < FN; ++j)
-                                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][e], b[j][e], acc[i][j], 0, 0, 0);
+                                for (int j = 0; j < FN; ++j)
+                                    low[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i][e], b[j][e], low[i][j], 0, 0, 0);
+                    }
                 }
                 __syncthreads();
             }
+            each([&](int i, int j, int e) {
+                acc[i][j][e] = (lost[i][j] >> e) & 1u ? low[i][j][e] : acc[i][j][e];
+            });
         }
         __syncthreads();                                     // LDS and `again` are the next range's
     };

@@ -119,6 +119,12 @@ def test_four_tiles_as_one(ks, tA, tB):
                 assert plan["tiles_per_workgroup"] == per and plan["workgroups"] == -(-M // edge) * -(-N // edge)
                 out[per] = run(ks, SMALL, tA, tB, A, B, pad=3)
             assert torch.equal(out[1], out[4]), (M, N, K)
+            X = A.clone()
+            X[70, 3], X[M - 1, K - 1] = float("inf"), 2.0 ** 110
+            for forced in (1, 0):
+                ks.set_tiles_per_workgroup(forced)
+                out[forced] = run(ks, SMALL, tA, tB, X, B, pad=3)
+            assert torch.equal(out[1].nan_to_num(7.0), out[0].nan_to_num(7.0)), (M, N, K)
             assert ((out[4].double() - A.double() @ B.double()).abs() <= bound(A, B, K)).all()
     finally:
         ks.set_tiles_per_workgroup(0)
@@ -214,3 +220,34 @@ def test_every_part_arrives(ks, kid, K, tA, tB):
     assert torch.equal(run(ks, kid, tA, tB, A, B), expected)
     assert_parts(ks, kid, tA, tB, N, M, K)
     assert torch.equal(run(ks, kid, tA, tB, B.t().contiguous(), A.t().contiguous()), expected.t())
+
+
+@pytest.mark.parametrize("tA,tB", LAYOUTS)
+@pytest.mark.parametrize("kid,K", [(LARGE, 1100), (PLAIN, 192), (SMALL, 192), (UNSPLIT_GROUPS, 400)])
+def test_other_rows_and_columns_keep_their_bits(ks, kid, K, tA, tB):
+    """What an entry's own row and column hold decides how it is computed, not what stands beside them: an infinity, a NaN or a
+    float that the parts cannot hold changes the bits of its row or column only, and none of them beyond the matrix changes any."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(10)
+    M, N = 300, 270
+    assert_parts(ks, kid, tA, tB, M, N, K)
+    A = torch.rand(M, K, generator=g, device="cuda") - 0.5
+    B = torch.rand(K, N, generator=g, device="cuda") - 0.5
+    whole = run(ks, kid, tA, tB, A, B)
+    assert torch.equal(run(ks, kid, tA, tB, A, B, pad=3), whole)       # (rows that end in NaN)
+    for value in (float("inf"), float("nan"), 2.0 ** 110):
+        for row, k in ((0, 0), (77, K - 1), (299, K // 2)):
+            X = A.clone()
+            X[row, k] = value
+            got = run(ks, kid, tA, tB, X, B)
+            others = torch.arange(M, device="cuda") != row
+            assert torch.equal(got[others], whole[others]), (value, row)
+            ref = X.double() @ B.double()
+            assert torch.equal(got[row].isnan(), ref[row].float().isnan()) and \
+                (not ref[row].isfinite().all() or ((got[row].double() - ref[row]).abs() <= 2.0 ** -18 * (X.double().abs() @ B.double().abs())[row]).all())
+        for col, k in ((0, 0), (200, K - 1), (269, K // 2)):
+            Y = B.clone()
+            Y[k, col] = value
+            got = run(ks, kid, tA, tB, A, Y)
+            others = torch.arange(N, device="cuda") != col
+            assert torch.equal(got[:, others], whole[:, others]), (value, col)
