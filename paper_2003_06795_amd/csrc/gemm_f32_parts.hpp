@@ -25,17 +25,18 @@
 // 480 x 1184 x 2592 TN 35.6 -> 53 / 52 (fp32 pipe 997, 165, 43).
 //
 // One K-step is 32 k whatever the member's: both operands' parts, 48 KB of a 128 x 128 tile, in one LDS stage of the 16-bit
-// members' layouts (gemm_bf16.hpp); the next step's floats are in flight during the MFMAs and are split on their way to LDS.
-// Two work-groups of a compute unit fill each other's barriers, which takes eight waves in 128 registers: 64 of them are
-// accumulators, so that parts live for a store only and a fragment of A for the products that it enters.  Bound
-// by power on large problems (4096^3 at 215 TFLOP/s is 1.29 PFLOP/s of bf16) and by the sum of splitting (seven VALU
-// instructions an element), LDS traffic and MFMAs on 64 x 64 tiles.
+// members' layouts (gemm_bf16.hpp); the next step's floats are in flight during the MFMAs and are split on their way to LDS.  Two
+// work-groups of a compute unit fill each other's barriers, which takes eight waves in 128 registers: 64 of them are accumulators, so
+// that parts live for a store only and a fragment of A for the products that it enters.  With two K groups, one or two
+// work-groups to a unit, the floats are split behind the MFMAs (1600 x 982 x 3870 NN 102 -> 94 us, 480 x 1184 x 2592 TN 32.5 ->
+// 31.6; 64 x 64 tiles with one group lose by it, 1000^3 NT 27.3 -> 29.6).  Bound by power on large problems (4096^3 at 215 TFLOP/s is
+// 1.29 PFLOP/s of bf16) and by the sum of splitting (seven VALU instructions an element), LDS traffic and MFMAs on 64 x 64 tiles.
 // Against the fp32 matrix pipe, us: 4096^3 NT 1000 -> 634, TN 1030 -> 672; 4095 x 3000 x 4089 NT 802 -> 529; 25088 x 256 x 1152 NN 140 -> 99;
 // 2048^3 NN 150 -> 101; on 64 x 64 tiles 1944 x 1264 x 1576 TT 89 -> 67, 1000^3 NT 33.8 -> 28.0, with two K groups 480 x 1184 x 2592 TN
 // 39.5 -> 31.8.
 // Measured and left, with two accumulators: 64 x 64 of output per wave in 256 registers (1.2 to 1.4 of the time); one work-group of
-// eight waves a unit, two LDS stages, one half of the waves splitting while the other multiplies (1.1 to 1.3); splitting behind
-// the MFMAs (128 registers do not hold the parts too: spills, 1.2 to 1.6; 64 x 64 tiles -2 to +12 %); the sum of a K-step in
+// eight waves a unit, two LDS stages, one half of the waves splitting while the other multiplies (1.1 to 1.3); splitting
+// behind the MFMAs on 128 x 128 tiles (128 registers do not hold the parts too: spills, 1.2 to 1.6); the sum of a K-step in
 // registers of its own, added by VALU (1.5 to 2.3).  With one: two K-steps in flight (level to +4 %); v_dot2_f32_bf16 for the two steps of a rest
 // (+5 to +12 %, and its inline -1.0 is the fp32 pattern); without s_setprio around the MFMAs +4 %.
 #pragma once
@@ -139,7 +140,18 @@ __global__ __launch_bounds__(64 * (BM / P1) * (BN / P2) * KW, 4) void gemm_f32_p
                 lb.load_edge(B, p.ldb, col, p.N, k0, kE, tid);
             }
         };
-        auto store = [&](auto rows, auto kc, char *to, const auto &l) {
+        // two K groups have the registers for a step's parts beside the MFMAs and split behind them
+        constexpr bool BEHIND = KW == 2;
+        FourParts ya[LoaderA::ITERS], yb[LoaderB::ITERS];
+        auto split = [&]() {
+            if constexpr (BEHIND) {
+#pragma unroll
+                for (int it = 0; it < LoaderA::ITERS; ++it) ya[it] = split_parts(la.reg[it]);
+#pragma unroll
+                for (int it = 0; it < LoaderB::ITERS; ++it) yb[it] = split_parts(lb.reg[it]);
+            }
+        };
+        auto store = [&](auto rows, auto kc, char *to, const auto &l, const auto &behind) {
             constexpr int ROWS = decltype(rows)::value;
             constexpr bool KC = decltype(kc)::value;
             using L = TileLoader<ROWS, BK, NT, KC, 4, KC>;
@@ -153,7 +165,7 @@ __global__ __launch_bounds__(64 * (BM / P1) * (BN / P2) * KW, 4) void gemm_f32_p
                 const int inner = from % L::INNER, outer = from / L::INNER + it * L::STRIDE;
                 const int at = KC ? 16 * Bf16Lds<BK>::chunk(outer, inner / 2) + 8 * (inner & 1)
                                   : Bf16LdsT<ROWS, 32>::byte_of(outer, inner * 4);
-                const FourParts y = split_parts(l.reg[it]);
+                const FourParts y = BEHIND ? behind[it] : split_parts(l.reg[it]);
 #pragma unroll
                 for (int s = 0; s < 3; ++s) *reinterpret_cast<uintx2 *>(to + s * (ROWS * BK * 2) + at) = y.part[s];
             }
@@ -196,12 +208,14 @@ __global__ __launch_bounds__(64 * (BM / P1) * (BN / P2) * KW, 4) void gemm_f32_p
         each([&](int i, int j, int e) { acc[i][j][e] = low[i][j][e] = 0.f; });
         if (nk > 0) load(0);
         if (grp == 0 && tid == 0) again = 0;
+        if (nk > 0) split();
         for (int t = 0; t < nk; ++t) {
-            store(std::integral_constant<int, BM>{}, KCA{}, lds, la);
-            store(std::integral_constant<int, BN>{}, KCB{}, lds + 3 * PLANE_A, lb);
+            store(std::integral_constant<int, BM>{}, KCA{}, lds, la, ya);
+            store(std::integral_constant<int, BN>{}, KCB{}, lds + 3 * PLANE_A, lb, yb);
             if (t + 1 < nk) load(t + 1);
             __syncthreads();
             multiply(lds);
+            if (t + 1 < nk) split();
             __syncthreads();
         }
         float zero = 0.f;                                    // stays zero while the accumulators are finite
