@@ -327,7 +327,9 @@ int ks_set_fast_path(int enabled);
  * stored; a one-dimensional launch without split-K uses it with a count chosen per call from the
  * tile count and K (only for very large outputs with at most two K-steps per tile).  n == 0
  * restores that default; 1 <= n <= 64 forces the count (1 = every work-group one tile) for testing
- * and tuning.  Results do not depend on it (every tile is computed the same way whoever walks it).
+ * and tuning.  On the bf16 matrix pipe (ks_launch_plan_t::path 3) work-groups walk no tiles: the unsplit 64 x 64 x 16 member
+ * computes 2 x 2 tiles as one with n == 4 and single ones with any other n (0: chosen per call), the others ignore it.
+ * Results do not depend on it (every tile is computed the same way whoever walks it).
  * Not thread-safe. */
 int ks_set_tiles_per_workgroup(int n);
 

@@ -748,9 +748,9 @@ int run_ws(Workspace wsp, int dtype, int id, int transA, int transB, int64_t M, 
     const bool parts = dtype == KS_F32 && f32_parts_member(d->core, d->bm, d->bn, d->bk, d->kw, p.splitK > 1) &&
                        waveK >= f32_parts_least_k(d->kw);
     bool square = false;                             // 2 x 2 tiles of the member per work-group
-    if (parts && d->bm == 64 && d->kw == 1 && d->splitK == 1 && g_tilesPerWG == 0) {
+    if (parts && d->bm == 64 && d->kw == 1 && d->splitK == 1) {
         const int64_t tilesM = (M + 127) / 128, tilesN = (N + 127) / 128, tiles128 = tilesM * tilesN * batch;
-        square = f32_parts_square(grid64, tiles128, K);
+        square = g_tilesPerWG == 0 ? f32_parts_square(grid64, tiles128, K) : g_tilesPerWG == 4;
         if (square) {
             p.tilesM = (int)tilesM;
             p.tilesN = (int)tilesN;

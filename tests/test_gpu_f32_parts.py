@@ -131,6 +131,27 @@ def test_four_tiles_as_one(ks, tA, tB):
 
 
 @pytest.mark.parametrize("tA,tB", LAYOUTS)
+def test_forced_counts_of_the_64_x_64_member(ks, tA, tB):
+    """Four tiles per work-group are 2 x 2 as one wherever the form runs, any other count single tiles; the bits are the same."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(11)
+    try:
+        for M, N, K in ((1, 1, 49), (65, 130, 79), (127, 64, 100), (200, 257, 192)):
+            A, B = torch.rand(M, K, generator=g, device="cuda") - 0.5, torch.rand(K, N, generator=g, device="cuda") - 0.5
+            out = {}
+            for forced in (1, 2, 4, 64):
+                ks.set_tiles_per_workgroup(forced)
+                plan = assert_parts(ks, SMALL, tA, tB, M, N, K)
+                edge = 128 if forced == 4 else 64
+                assert plan["tiles_per_workgroup"] == (4 if forced == 4 else 1)
+                assert plan["workgroups"] == -(-M // edge) * -(-N // edge)
+                out[forced] = run(ks, SMALL, tA, tB, A, B, pad=3)
+            assert all(torch.equal(out[1], out[n]) for n in (2, 4, 64)), (M, N, K)
+    finally:
+        ks.set_tiles_per_workgroup(0)
+
+
+@pytest.mark.parametrize("tA,tB", LAYOUTS)
 @pytest.mark.parametrize("kid,K", [(PLAIN, 64), (SMALL, 64), (UNSPLIT_GROUPS, 400)])
 def test_small_magnitudes_at_every_place(ks, kid, K, tA, tB):
     """One term to a sum, small or subnormal, in each place of a chunk of four k and of four rows or columns.  2^-22: three bf16

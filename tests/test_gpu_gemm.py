@@ -473,6 +473,40 @@ def test_work_groups_walking_several_tiles(gpu):
         gpu.ensure_workspace.__defaults__[0].clear()
 
 
+@pytest.mark.parametrize("tA,tB", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("K", [33, 40, 48])
+def test_work_groups_walking_several_tiles_of_two_k_steps(gpu, K, tA, tB):
+    """The members whose longer products run on the bf16 matrix pipe, which has no such form: two K-steps of 32 are what is
+    left to their work-groups that walk several tiles."""
+    import paper_2003_06795_amd.binding as ks
+    members = [k for k in multi_tile_members(ks) if ks.kernel_info(ks.F32, k)["bk"] == 32 and
+               ks.kernel_info(ks.F32, k)["bm"] == 128 and ks.kernel_info(ks.F32, k)["bn"] == 128]
+    assert len(members) >= 2
+    ks.set_workspace(None)
+    p = wl.make_problem("f32", tA, tB, 15997, 139, K, batch=2, beta=0.5, seed=24, c_fill="uniform", pad=(3, 3, 3))
+    assert (p.M + p.N) * p.K * p.batch * 4 > (4 << 20)         # one-dimensional launch
+    dp = gpu.DeviceProblem(p)
+    bb, ii, jj = gpu.sample_entries(p, 1024, 6, tile=128)
+    ref = gpu.oracle_entries(p, bb, ii, jj)
+    flat = bb * p.strideC + ii * p.ldc + jj
+    try:
+        for kid in members:
+            one = None
+            for t in (1, 2, 5):
+                ks.set_tiles_per_workgroup(t)
+                plan = ks.gemm_plan(ks.F32, kid, tA, tB, p.M, p.N, p.K, p.alpha, dp.A, p.lda, dp.B, p.ldb, p.beta, dp.C0, p.ldc,
+                                    p.batch, p.strideA, p.strideB, p.strideC)
+                assert plan["path"] == 0 and plan["tiles_per_workgroup"] == t
+                got = dp.run(kid)
+                if t == 1:
+                    one = got
+                    assert np.max(np.abs(one[flat].astype(np.float64) - ref)) <= tolerance(p), kid
+                assert np.array_equal(got, one), "kernel %d, %d tiles per work-group" % (kid, t)
+    finally:
+        ks.set_tiles_per_workgroup(0)
+        gpu.ensure_workspace.__defaults__[0].clear()
+
+
 def test_several_tiles_with_a_single_short_k_step(gpu):
     """K shorter than one K-step and thousands of tiles: every step of the flattened loop ends a
     tile.  Automatic and forced counts agree bitwise; sampled entries match the oracle."""
