@@ -338,7 +338,7 @@ int ks_set_tiles_per_workgroup(int n);
  * kernel); a 512-thread member with two per compute unit launches 256 when the problem has at
  * most 96 tiles.  1 <= per_cu <= 8 forces another count per compute unit for testing and tuning, and
  * makes those members take the form on every call whose scratch is there (or that divides no
- * tile); 0 restores the members' own count and the per-call choice.  ks_workspace_bytes_needed
+ * tile; the 128 x 128 x 32 one, which has it on the bf16 matrix pipe, from K = 49 on); 0 restores the members' own count and the per-call choice.  ks_workspace_bytes_needed
  * follows the forced count.  Results stay within the stated bound but the summation order of
  * divided tiles changes with the count.  Not thread-safe. */
 int ks_set_balanced_groups(int per_cu);

@@ -716,7 +716,9 @@ int run_ws(Workspace wsp, int dtype, int id, int transA, int transB, int64_t M, 
     p.bandRows = d->band;
     p.skGroups = 0; p.skRounds = 0; p.skTailTiles = 0;
     p.tileBase = 0; p.tileSpan = 0; p.bm = d->bm; p.bn = d->bn;
-    if (d->sk > 0) {
+    const bool onBf16Pipe = dtype == KS_F32 && f32_parts_member(d->core, d->bm, d->bn, d->bk, d->kw, p.splitK > 1);
+    // (a member with a form on the bf16 matrix pipe has the balanced form there alone)
+    if (d->sk > 0 && (!onBf16Pipe || K >= f32_parts_least_k(d->kw))) {
         // Balanced persistent form where it pays (measured against the plain member of the same
         // tiles on the tuning tables): tiles that do not divide evenly over the work-groups, fewer
         // than four rounds of them (with more, the uneven last round matters less than what the
@@ -745,8 +747,7 @@ int run_ws(Workspace wsp, int dtype, int id, int transA, int transB, int64_t M, 
     // on the bf16 matrix pipe (gemm_f32_parts.hpp), where the K range of a work-group is long enough; that form has no
     // work-groups that walk several tiles
     const int64_t waveK = K < p.kChunk ? K : p.kChunk;
-    const bool parts = dtype == KS_F32 && f32_parts_member(d->core, d->bm, d->bn, d->bk, d->kw, p.splitK > 1) &&
-                       waveK >= f32_parts_least_k(d->kw);
+    const bool parts = onBf16Pipe && waveK >= f32_parts_least_k(d->kw);
     bool square = false;                             // 2 x 2 tiles of the member per work-group
     if (parts && d->bm == 64 && d->kw == 1 && d->splitK == 1) {
         const int64_t tilesM = (M + 127) / 128, tilesN = (N + 127) / 128, tiles128 = tilesM * tilesN * batch;

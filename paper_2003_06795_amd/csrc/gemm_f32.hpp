@@ -22,8 +22,8 @@
 // group runs in another order than k's.  With [k][row] tiles for both, a K-contiguous operand took four times as many
 // LDS instructions either way, which the matrix pipe's neighbours wait to issue: over the members in layouts NN / NT / TT
 // and one to forty K-steps 0.97 of the time in the mean, 0.945 in NT (1024^3 NT 31.2 -> 28.8 us on 64 x 64 x 16, 4096^3 1051 -> 994
-// on 128 x 128 x 32, 26.5 -> 23.4 on sixteen waves of 64 x 64 x 32).  The balanced persistent form keeps [k][row] where both
-// operands are K-contiguous (4095 x 3000 x 4089 801 us against 843).
+// on 128 x 128 x 32, 26.5 -> 23.4 on sixteen waves of 64 x 64 x 32; the balanced form of
+// 64 x 64 x 32, 2000 x 2000 x 2048 162 -> 153, 640 x 640 x 4096 47.7 -> 46.0).
 #pragma once
 #include "ks_common.hpp"
 
@@ -53,10 +53,9 @@ namespace ks {
                                                                                                          : 4)
 #endif
 // The balanced persistent form counts on a fixed number of resident work-groups per compute unit:
-// two of eight waves (four waves per SIMD, 128 registers) or three of four waves (three per SIMD),
-// which is what the plain forms of those members reach.
+// three of four waves (three per SIMD), which is what the plain form of that member reaches.
 #ifndef KS_F32_SK_MIN_WAVES
-#define KS_F32_SK_MIN_WAVES(bm, bn, p1, p2) (((bm) / (p1)) * ((bn) / (p2)) >= 8 ? 4 : 3)
+#define KS_F32_SK_MIN_WAVES 3
 #endif
 
 enum { CORE_FMA = 0, CORE_MFMA16 = 1, CORE_MFMA32 = 2, CORE_DIRECT = 3, CORE_KSLICE = 4 };
@@ -267,7 +266,7 @@ struct TileLoader {
 // the epilogue.  No work-group waits for another, so there is nothing to deadlock on.
 template <int CORE, int BM, int BN, int BK, int P1, int P2, bool SPLIT, bool AKC, bool BKC,
           int LOADS, int KW = 1, bool MULTI = false, bool SK = false>
-__global__ __launch_bounds__((F32Shape<CORE, BM, BN, P1, P2>::threads * KW), (SK ? KS_F32_SK_MIN_WAVES(BM, BN, P1, P2) : f32_units_eight_waves(CORE, BM, BN, BK, P1, P2, KW, AKC, BKC, LOADS) ? 8 : KS_F32_MIN_WAVES(MULTI, CORE, BM, BN, BK, P1, P2, KW, LOADS))) void gemm_f32_kernel(
+__global__ __launch_bounds__((F32Shape<CORE, BM, BN, P1, P2>::threads * KW), (SK ? KS_F32_SK_MIN_WAVES : f32_units_eight_waves(CORE, BM, BN, BK, P1, P2, KW, AKC, BKC, LOADS) ? 8 : KS_F32_MIN_WAVES(MULTI, CORE, BM, BN, BK, P1, P2, KW, LOADS))) void gemm_f32_kernel(
     const GemmParams p) {
     static_assert(LOADS == LOAD_STEPS || !(MULTI || SK), "persistent forms");
     static_assert(!MULTI || (f32_multi_tile(CORE, BM, BN, P1, P2, KW) && !SPLIT), "multi-tile form");
@@ -278,7 +277,7 @@ __global__ __launch_bounds__((F32Shape<CORE, BM, BN, P1, P2>::threads * KW), (SK
     constexpr int W = LOADS == LOAD_ELEMENTS ? 1 : 4;
     constexpr int FR = Shape::frag, KV = 4 * (64 / FR);       // KV: k of a substep of whole chunks
     // groups of four k to a lane: the order of the sums, the same in every load form
-    constexpr bool BY_FOUR = CORE != CORE_FMA && BK % KV == 0 && (AKC || BKC) && !(SK && AKC && BKC);
+    constexpr bool BY_FOUR = CORE != CORE_FMA && BK % KV == 0 && (AKC || BKC);
     constexpr bool CHA = BY_FOUR && W == 4 && AKC, CHB = BY_FOUR && W == 4 && BKC;
     using LoaderA = TileLoader<BM, BK, NT, AKC, W, CHA>;
     using LoaderB = TileLoader<BN, BK, NT, BKC, W, CHB>;

@@ -100,14 +100,12 @@ static void launch_f32_sk(const GemmParams &p, int grid, int variant, hipStream_
     }
     constexpr int NT = F32Shape<CORE, BM, BN, P1, P2>::threads;
     const dim3 g((unsigned)p.skGroups), b(NT);
-#define KS_V(A, B)                                                                                              \
-    do {                                                                                                        \
-        if constexpr (f32_parts_member(CORE, BM, BN, BK, 1, false))                                                    \
-            if (variant & 64) {                                                                                 \
-                hipLaunchKernelGGL((gemm_f32_parts_kernel<BM, BN, P1, P2, false, A, B, 1, true>), g, b, 0, s, p);  \
-                break;                                                                                          \
-            }                                                                                                   \
-        hipLaunchKernelGGL((gemm_f32_kernel<CORE, BM, BN, BK, P1, P2, false, A, B, LOAD_STEPS, 1, false, true>), g, b, 0, s, p); \
+#define KS_V(A, B)                                                                                                           \
+    do {                                                                                                                     \
+        if constexpr (f32_parts_member(CORE, BM, BN, BK, 1, false))                                                          \
+            hipLaunchKernelGGL((gemm_f32_parts_kernel<BM, BN, P1, P2, false, A, B, 1, true>), g, b, 0, s, p);                \
+        else                                                                                                                 \
+            hipLaunchKernelGGL((gemm_f32_kernel<CORE, BM, BN, BK, P1, P2, false, A, B, LOAD_STEPS, 1, false, true>), g, b, 0, s, p); \
     } while (0)
     switch ((variant >> 1) & 3) {
         case 0: KS_V(false, false); break;

@@ -125,6 +125,13 @@ def test_balanced_persistent_form_is_taken_where_its_rule_says(planner):
         ks.set_balanced_groups(0)
 
 
+def test_balanced_form_of_the_128_x_128_member_is_on_the_bf16_matrix_pipe_alone(planner):
+    ks.set_balanced_groups(1)
+    for kid, K, groups in ((47, 48, 0), (47, 49, 256), (60, 48, 256), (60, 49, 256)):
+        got = planner(ks.F32, kid, 0, 0, 24 * 128, 12 * 128, K)
+        assert got["balanced_groups"] == groups and (got["path"] == 3) == (kid == 47 and K == 49), (kid, K, got)
+
+
 def test_hybrid_launch_and_cut_of_k_for_the_16_bit_members(planner):
     big = [k for k in range(ks.num_kernels(ks.BF16)) if ks.kernel_info(ks.BF16, k)["split_k"] == 0 and
            ks.kernel_info(ks.BF16, k)["bm"] == 256 and ks.kernel_info(ks.BF16, k)["bn"] == 256][-1]
