@@ -132,6 +132,56 @@ def test_balanced_form_of_the_128_x_128_member_is_on_the_bf16_matrix_pipe_alone(
         assert got["balanced_groups"] == groups and (got["path"] == 3) == (kid == 47 and K == 49), (kid, K, got)
 
 
+def test_fp32_members_on_the_bf16_matrix_pipe(planner):
+    """Restated: 128 x 128 x 32 tiles, and 64 x 64 x 16 ones that have two K groups or no K partitions, from a K range of a work-group
+    of 49 on (two K groups: 360); the unsplit 64 x 64 x 16 member then takes 2 x 2 tiles as one where their rounds of 512
+    are not over 23 / 160 of the single ones' rounds of 256, from K = 80 on."""
+    def member(ki, split):
+        if ki["core_name"] != "mfma32":
+            return False
+        tile = (ki["bm"], ki["bn"], ki["bk"])
+        return (tile == (128, 128, 32) and ki["k_waves"] == 1) or (tile == (64, 64, 16) and (ki["k_waves"] == 2 or split == 1))
+    ks.lib().ks_set_workspace(None, 0)
+    taken = set()
+    for kid in range(ks.num_kernels(ks.F32)):
+        ki = ks.kernel_info(ks.F32, kid)
+        if ki["split_k"] > 1:
+            continue                                           # (needs scratch)
+        for K in (16, 48, 49, 80, 359, 360, 1024):
+            for tA, tB in ((0, 0), (1, 1)):
+                got = planner(ks.F32, kid, tA, tB, 300, 200, K)
+                want = member(ki, 1) and K >= (360 if ki["k_waves"] == 2 else 49)
+                assert got["split_k"] == 1 and (got["path"] == 3) == want, (kid, K, got)
+                taken |= {kid} if want else set()
+    assert taken == {13, 28, 32, 42, 47, 59}
+    # K partitions: the range of one counts, and a 64 x 64 tile with one K group has the form without them only
+    ks.lib().ks_set_workspace(ctypes.c_void_p(1 << 21), ctypes.c_size_t(256 << 20))
+    for kid in (32, 42):
+        ki = ks.kernel_info(ks.F32, kid)
+        for parts in (1, 2, 3, 5):
+            ks.set_split_partitions(parts)
+            for K in (700, 719, 720, 721, 1087, 1088, 1800):
+                got = planner(ks.F32, kid, 0, 1, 300, 200, K)
+                chunk = min(K, -(-(-(-K // 16)) // got["split_k"]) * 16)
+                want = member(ki, got["split_k"]) and chunk >= (360 if ki["k_waves"] == 2 else 49)
+                assert (got["path"] == 3) == want, (kid, parts, K, got)
+    ks.set_split_partitions(0)
+    # 2 x 2 tiles of 64 x 64 as one
+    both = set()
+    for (M, N, K) in ((2816, 2560, 79), (2816, 2560, 80), (2753, 2497, 129), (1024, 1024, 512), (2048, 1024, 512), (64, 57000, 96),
+                      (4096, 4096, 256), (57000, 97, 96), (1280, 1280, 200), (8192, 512, 64), (3000, 2944, 700)):
+        t64, t128 = -(-M // 64) * -(-N // 64), -(-M // 128) * -(-N // 128)
+        want = K >= 80 and 160 * -(-t128 // 512) <= 23 * -(-t64 // 256)
+        for kid in (28, 42):
+            got = planner(ks.F32, kid, 0, 1, M, N, K)
+            want_here = want and kid == 28                     # (42: its partitions are chosen per call)
+            if got["split_k"] == 1:
+                assert got["tiles_per_workgroup"] == (4 if want_here else 1), (kid, M, N, K, got)
+                assert got["workgroups"] == (t128 if want_here else t64)
+        both.add(want)
+    assert both == {True, False}
+
+
 def test_hybrid_launch_and_cut_of_k_for_the_16_bit_members(planner):
     big = [k for k in range(ks.num_kernels(ks.BF16)) if ks.kernel_info(ks.BF16, k)["split_k"] == 0 and
            ks.kernel_info(ks.BF16, k)["bm"] == 256 and ks.kernel_info(ks.BF16, k)["bn"] == 256][-1]
