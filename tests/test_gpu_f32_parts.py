@@ -1,6 +1,6 @@
 """fp32 members on the bf16 matrix pipe (128 x 128 tiles plain and balanced, 64 x 64 with one and two K groups, with and without
-K partitions): sizes around the edges of tiles and K-steps against an fp64 product, and operands that three bf16 parts cannot
-hold, which come out as from fp32 arithmetic."""
+K partitions): sizes around the edges of tiles, K-steps and the lines from which the form runs against an fp64 product, its
+error against the fp32 pipe's, and operands that it cannot hold, which come out as from fp32 arithmetic."""
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -18,6 +18,7 @@ def ks():
     scratch = torch.empty(68 << 20, dtype=torch.uint8, device="cuda")
     ks.set_workspace(scratch)
     yield ks
+    ks.set_split_partitions(0)
     ks.set_workspace(None)
     gpu_util.ensure_workspace.__defaults__[0].clear()
 
@@ -57,26 +58,58 @@ def bound(A, B, K):
 
 
 @pytest.mark.parametrize("tA,tB", LAYOUTS)
-@pytest.mark.parametrize("kid", [LARGE, PLAIN, SMALL, GROUPS])
+@pytest.mark.parametrize("kid", [LARGE, PLAIN, SMALL, UNSPLIT_GROUPS, GROUPS])
 def test_edges(ks, kid, tA, tB):
     import torch
     g = torch.Generator(device="cuda").manual_seed(3)
-    for n, (M, N, K) in enumerate([(1, 1, 49), (127, 129, 63), (128, 128, 64), (129, 65, 97), (63, 200, 255), (65, 63, 361),
-                                   (192, 131, 1025), (3, 260, 2047), (300, 257, 4001)]):
+    line, on = (360 if kid in (UNSPLIT_GROUPS, GROUPS) else 49), 0
+    for n, (M, N, K) in enumerate([(1, 1, 49), (127, 129, 63), (128, 128, 64), (129, 65, 97), (63, 200, 255), (65, 63, 361), (67, 63, 360),
+                                   (192, 131, 1025), (3, 260, 2047), (300, 257, 4001), (129, 127, 48), (70, 66, 359)]):
+        if kid == GROUPS:
+            ks.set_split_partitions(max(1, min(3, K // 400)))
+        X = torch.empty(16, device="cuda")
+        plan = ks.gemm_plan(ks.F32, kid, tA, tB, M, N, K, 1.0, X, M if tA else K, X, K if tB else N, 0.0, X, N)
+        assert plan["path"] == (3 if -(-K // plan["split_k"]) >= line else 0) and (kid == GROUPS or plan["split_k"] == 1)
+        on += plan["path"] == 3
         A = torch.rand(M, K, generator=g, device="cuda") * 2 - 1
         B = torch.rand(K, N, generator=g, device="cuda") * 2 - 1
         C0 = torch.rand(M, N, generator=g, device="cuda") if n % 2 else None
         got = run(ks, kid, tA, tB, A, B, 0.5 if n % 2 else 0.0, C0, pad=(0, 3, 8)[n % 3])
         ref = A.double() @ B.double() + (0.5 * C0.double() if n % 2 else 0.0)
         assert ((got.double() - ref).abs() <= bound(A, B, K) + 2.0 ** -23).all(), (kid, M, N, K)
+    assert on == (5 if line == 360 else 11)
 
 
 @pytest.mark.parametrize("tA,tB", LAYOUTS)
-@pytest.mark.parametrize("kid", [LARGE, SMALL, GROUPS])
+def test_two_groups_whose_last_partition_is_one_slice(ks, tA, tB):
+    """23 partitions of 368 k, and the four k that are left over: the second K group of the last one has none."""
+    import torch
+    g = torch.Generator(device="cuda").manual_seed(12)
+    M, N, K = 70, 90, 8100
+    ks.set_split_partitions(23)
+    plan = assert_parts(ks, GROUPS, tA, tB, M, N, K)
+    assert plan["split_k"] == 23
+    A = torch.rand(M, K, generator=g, device="cuda") * 2 - 1
+    B = torch.rand(K, N, generator=g, device="cuda") * 2 - 1
+    for at, value in ((K // 3, 0.25), (K - 1, float("inf")), (K // 3, float("inf"))):
+        A[3, at] = value
+        got, ref = run(ks, GROUPS, tA, tB, A, B), A.double() @ B.double()
+        near = ((got.double() - ref).abs() <= bound(A.nan_to_num(0, 1, 1), B, K)) | (got == ref.float()) | (got.isnan() & ref.isnan())
+        assert near.all() and got[torch.arange(M, device="cuda") != 3].isfinite().all(), at
+        A[3, at] = 0.25
+
+
+@pytest.mark.parametrize("tA,tB", LAYOUTS)
+@pytest.mark.parametrize("kid", [LARGE, SMALL, UNSPLIT_GROUPS, GROUPS])
 def test_what_three_parts_cannot_hold(ks, kid, tA, tB):
     import torch
     g = torch.Generator(device="cuda").manual_seed(4)
     M, N, K = 300, 260, 1100
+    if kid == GROUPS:
+        ks.set_split_partitions(2)
+    plan = assert_parts(ks, kid, tA, tB, M, N, K)
+    assert plan["split_k"] == (2 if kid == GROUPS else 1)
+    assert_parts(ks, kid, tA, tB, N, M, K)
     A = torch.rand(M, K, generator=g, device="cuda") * 2 - 1
     B = torch.rand(K, N, generator=g, device="cuda") * 2 - 1
     inf, nan, most = float("inf"), float("nan"), torch.finfo(torch.float32).max
@@ -91,7 +124,9 @@ def test_what_three_parts_cannot_hold(ks, kid, tA, tB):
                  (ref32.isfinite() & ((got.double() - ref).abs() <= bound(P.nan_to_num(0, most, -most), Q.nan_to_num(0, most, -most), K)))
             # a sum beyond the largest float may overflow a step earlier or later in another order
             assert ok[ref.abs().nan_to_num(0, 0) < 0.9 * most].all(), (kid, value, swap)
-    for scale, other in ((2.0 ** -110, 1.0), (2.0 ** -126, 2.0 ** 100), (2.0 ** -140, 2.0 ** 120)):
+    # sums and operands on both sides of what is held, and magnitudes that are all held
+    for scale, other in ((2.0 ** 40, 2.0 ** 34), (2.0 ** 40, 2.0 ** 44), (2.0 ** 104, 2.0 ** -104), (2.0 ** 106, 2.0 ** -106),
+                         (2.0 ** -110, 1.0), (2.0 ** -126, 2.0 ** 100), (2.0 ** -140, 2.0 ** 120)):
         X, Y = A * scale, B * other
         ref = X.double() @ Y.double()
         assert ((run(ks, kid, tA, tB, X, Y).double() - ref).abs() <= bound(X, Y, K)).all(), (kid, scale)
