@@ -51,10 +51,10 @@ __global__ __launch_bounds__(512) void mfma_sustained_kernel(const uintx4 *src, 
                         continue;
                     }
                     floatx16 &c = acc[KIND >= 3 ? 0 : q * 2 + m];
-                    if constexpr (KIND == 2)
-                        c = __builtin_amdgcn_mfma_f32_32x32x2f32(__builtin_bit_cast(float, a[m * 4 + ks][q]),
-                                                                 __builtin_bit_cast(float, b[ks][q]), c, 0, 0, 0);
-                    else
+                    if constexpr (KIND == 2) {
+                        const unsigned ae = a[m * 4 + ks][q], be = b[ks][q];      // (a bit cast of a vector's element takes element 0)
+                        c = __builtin_amdgcn_mfma_f32_32x32x2f32(__builtin_bit_cast(float, ae), __builtin_bit_cast(float, be), c, 0, 0, 0);
+                    } else
                         c = mfma_32x32x16<KIND == 1>(__builtin_bit_cast(bf16x8, a[m * 4 + ks]),
                                                      __builtin_bit_cast(bf16x8, b[ks]), c);
                 }
