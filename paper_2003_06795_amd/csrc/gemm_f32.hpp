@@ -244,6 +244,90 @@ struct TileLoader {
     }
 };
 
+// The tiles and K-steps of one work-group of the balanced persistent form (SK below): body(tile, first K-step, last K-step + 1,
+// K-steps of a tile, work-group, whether it is the head of the share of left-over tiles) for each.  Everything that describes
+// the share is the same for all lanes; the integer divisions run on the vector unit, so their results are moved
+// to scalar registers explicitly.
+template <int BK, class Body>
+__device__ __forceinline__ void sk_for_each_tile(const GemmParams &p, Body body) {
+    auto uni = [](long long v) -> long long {
+        const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(unsigned long long)v);
+        const unsigned hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)((unsigned long long)v >> 32));
+        return (long long)(((unsigned long long)hi << 32) | lo);
+    };
+    const unsigned lw = (unsigned)__builtin_amdgcn_readfirstlane((int)logical_of_block());
+    const long long groups = (long long)gridDim.x;
+    const int nkT = (p.K + BK - 1) / BK;
+    const long long units = (long long)p.skTailTiles * nkT;
+    const long long ub = uni(sk_share_begin(lw, units, groups)), ue = uni(sk_share_begin(lw + 1, units, groups));
+    const long long t0 = uni(ub / nkT);                      // first left-over tile of the share
+    const int r0 = (int)(ub - t0 * nkT);                      // and the K-step it starts at
+    const int tailSegs = ue > ub ? (int)(uni((ue - 1) / nkT) - t0) + 1 : 0;
+    const int nSeg = p.skRounds + tailSegs;
+    for (int sg = 0; sg < nSeg; ++sg) {
+        unsigned logical;
+        int ks0 = 0, ks1 = nkT;
+        if (sg < p.skRounds) {
+            logical = (unsigned)sg * (unsigned)groups + lw;
+        } else {
+            const long long t = t0 + (sg - p.skRounds);
+            logical = (unsigned)p.skRounds * (unsigned)groups + (unsigned)t;
+            ks0 = sg == p.skRounds ? r0 : 0;
+            ks1 = (int)min((long long)nkT, ue - t * nkT);
+        }
+        TileCoord tc = tile_of_logical(p, logical);
+        tc.batch = __builtin_amdgcn_readfirstlane(tc.batch);
+        tc.tm = __builtin_amdgcn_readfirstlane(tc.tm);
+        tc.tn = __builtin_amdgcn_readfirstlane(tc.tn);
+        tc.split = 0;
+        body(tc, ks0, ks1, nkT, lw, sg == p.skRounds);
+    }
+}
+
+// raw accumulators of 32x32 fragments, in register order: float4 unit (wave, i, j, chunk) of lane l
+template <int FM, int FN, class Acc>
+__device__ __forceinline__ void store_units32(floatx4 *units, int wave, int lane, const Acc &acc) {
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                units[(((wave * FM + i) * FN + j) * 4 + c) * 64 + lane] =
+                    floatx4{acc[i][j][4 * c], acc[i][j][4 * c + 1], acc[i][j][4 * c + 2], acc[i][j][4 * c + 3]};
+}
+// ... of a part of a tile in the balanced form: at most two per work-group, the head and the tail of its share
+template <int BM, int BN, int FM, int FN, class Acc>
+__device__ __forceinline__ void sk_store_part(const GemmParams &p, unsigned group, bool head, int wave, int lane, const Acc &acc) {
+    store_units32<FM, FN>(reinterpret_cast<floatx4 *>(p.ws) + ((long long)group * 2 + (head ? 0 : 1)) * (BM * BN / 4), wave, lane, acc);
+}
+
+// Sums the accumulators of the K groups in group order, from float4 units [group][wave][i][j][chunk][lane] in LDS that are
+// dealt out over all threads, and stores the tile at (row, col).  FRG: fragment edge, CH: chunks of a fragment and lane.
+template <bool SPLIT, int FRG, int CH, int FM, int FN, int P1, int P2, int BN, int NT, int KW>
+__device__ __forceinline__ void store_sum_of_groups(const floatx4 *part, const GemmParams &p, const TileCoord &tc, float *Cb, int row, int col) {
+    constexpr int UNITS = (NT / 64) * FM * FN * CH * 64;
+    const OutTarget o = out_target<SPLIT>(p, tc, Cb);
+    for (int u = (int)threadIdx.x; u < UNITS; u += NT * KW) {
+        floatx4 sum = part[u];
+#pragma unroll
+        for (int g = 1; g < KW; ++g) sum += part[g * UNITS + u];
+        const int ul = u & 63;
+        int q = __builtin_amdgcn_readfirstlane(u >> 6);
+        const int c = q % CH; q /= CH;
+        const int j = q % FN; q /= FN;
+        const int i = q % FM;
+        const int w = q / FM;
+        const int fr0 = row + (w / (BN / P2)) * P1 + i * FRG, fc0 = col + (w % (BN / P2)) * P2 + j * FRG;
+        const bool full = fr0 + FRG <= o.M && fc0 + FRG <= o.N;
+        const float v[4] = {sum[0], sum[1], sum[2], sum[3]};
+        if constexpr (FRG == 16)
+            store_lane_column<SPLIT, 4>(o, fr0 + 4 * (ul >> 4), fc0 + (ul & 15), full, v, [](int e) { return e; });
+        else
+            store_lane_column<SPLIT, 4>(o, fr0 + 8 * c + 4 * (ul >> 5), fc0 + (ul & 31), full, v, [](int e) { return e; });
+    }
+}
+
 // KW > 1 (MFMA cores): the work-group holds KW groups of waves, each a complete copy of the
 // BM x BN wave arrangement with its own LDS stages, and each takes one slice of the work-group's
 // K range (rounded to whole K-steps).  The groups run the same number of K-steps in lock-step (a
@@ -520,38 +604,7 @@ __global__ __launch_bounds__((F32Shape<CORE, BM, BN, P1, P2>::threads * KW), (SK
     }
 
     if constexpr (SK) {
-        // Everything that describes the share is the same for all lanes; the integer divisions run
-        // on the vector unit, so their results are moved to scalar registers explicitly.
-        auto uni = [](long long v) -> long long {
-            const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(unsigned long long)v);
-            const unsigned hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)((unsigned long long)v >> 32));
-            return (long long)(((unsigned long long)hi << 32) | lo);
-        };
-        const unsigned lw = (unsigned)__builtin_amdgcn_readfirstlane((int)logical_of_block());
-        const long long groups = (long long)gridDim.x;
-        const int nkT = (p.K + BK - 1) / BK;
-        const long long units = (long long)p.skTailTiles * nkT;
-        const long long ub = uni(sk_share_begin(lw, units, groups)), ue = uni(sk_share_begin(lw + 1, units, groups));
-        const long long t0 = uni(ub / nkT);                  // first left-over tile of the share
-        const int r0 = (int)(ub - t0 * nkT);                  // and the K-step it starts at
-        const int tailSegs = ue > ub ? (int)(uni((ue - 1) / nkT) - t0) + 1 : 0;
-        const int nSeg = p.skRounds + tailSegs;
-        for (int sg = 0; sg < nSeg; ++sg) {
-            unsigned logical;
-            int ks0 = 0, ks1 = nkT;
-            if (sg < p.skRounds) {
-                logical = (unsigned)sg * (unsigned)groups + lw;
-            } else {
-                const long long t = t0 + (sg - p.skRounds);
-                logical = (unsigned)p.skRounds * (unsigned)groups + (unsigned)t;
-                ks0 = sg == p.skRounds ? r0 : 0;
-                ks1 = (int)min((long long)nkT, ue - t * nkT);
-            }
-            TileCoord tcS = tile_of_logical(p, logical);
-            tcS.batch = __builtin_amdgcn_readfirstlane(tcS.batch);
-            tcS.tm = __builtin_amdgcn_readfirstlane(tcS.tm);
-            tcS.tn = __builtin_amdgcn_readfirstlane(tcS.tn);
-            tcS.split = 0;
+        sk_for_each_tile<BK>(p, [&](const TileCoord &tcS, int ks0, int ks1, int nkT, unsigned group, bool head) {
             const int rowS = tcS.tm * BM, colS = tcS.tn * BN;
             const float *AbS = static_cast<const float *>(p.A) + (long long)tcS.batch * p.strideA;
             const float *BbS = static_cast<const float *>(p.B) + (long long)tcS.batch * p.strideB;
@@ -590,18 +643,7 @@ __global__ __launch_bounds__((F32Shape<CORE, BM, BN, P1, P2>::threads * KW), (SK
                 float *CbS = p.C + (long long)tcS.batch * p.strideC;
                 write_tile_mfma32<false, FM, FN>(p, tcS, CbS, rowS + subM, colS + subN, laneE, acc32);
             } else {
-                // raw accumulators, in register order: float4 unit (wave, i, j, chunk) of lane l
-                floatx4 *part = reinterpret_cast<floatx4 *>(p.ws) +
-                                ((long long)lw * 2 + (sg == p.skRounds ? 0 : 1)) * (BM * BN / 4);
-#pragma unroll
-                for (int i = 0; i < FM; ++i)
-#pragma unroll
-                    for (int j = 0; j < FN; ++j)
-#pragma unroll
-                        for (int c = 0; c < 4; ++c)
-                            part[(((wave * FM + i) * FN + j) * 4 + c) * 64 + laneE] =
-                                floatx4{acc32[i][j][4 * c], acc32[i][j][4 * c + 1], acc32[i][j][4 * c + 2],
-                                        acc32[i][j][4 * c + 3]};
+                sk_store_part<BM, BN, FM, FN>(p, group, head, wave, laneE, acc32);
             }
 #pragma unroll
             for (int i = 0; i < FM; ++i)
@@ -609,7 +651,7 @@ __global__ __launch_bounds__((F32Shape<CORE, BM, BN, P1, P2>::threads * KW), (SK
                 for (int j = 0; j < FN; ++j)
 #pragma unroll
                     for (int e = 0; e < 16; ++e) acc32[i][j][e] = 0.f;
-        }
+        });
         return;
     }
 
@@ -653,47 +695,19 @@ __global__ __launch_bounds__((F32Shape<CORE, BM, BN, P1, P2>::threads * KW), (SK
                 for (int j = 0; j < P2; ++j) emit(row0 + subM + i, col0 + subN + j, accF[i][j]);
         });
     } else if constexpr (KW > 1) {
-        // every wave publishes its accumulators as float4 units [group][wave][i][j][chunk][lane];
-        // the units are then dealt out over all threads, summed in group order and stored
-        constexpr int CH = CORE == CORE_MFMA32 ? 4 : 1;       // float4 chunks per fragment and lane
-        constexpr int FRG = CORE == CORE_MFMA32 ? 32 : 16;
+        constexpr int CH = CORE == CORE_MFMA32 ? 4 : 1, FRG = CORE == CORE_MFMA32 ? 32 : 16;
         constexpr int UNITS = (NT / 64) * FM * FN * CH * 64;
         __shared__ floatx4 part[KW][UNITS];
+        if constexpr (CORE == CORE_MFMA16) {
 #pragma unroll
-        for (int i = 0; i < FM; ++i)
+            for (int i = 0; i < FM; ++i)
 #pragma unroll
-            for (int j = 0; j < FN; ++j) {
-                const int base = (((wave * FM + i) * FN + j) * CH) * 64 + lane;
-                if constexpr (CORE == CORE_MFMA16) {
-                    part[grp][base] = acc16[i][j];
-                } else {
-#pragma unroll
-                    for (int c = 0; c < 4; ++c)
-                        part[grp][base + c * 64] = floatx4{acc32[i][j][4 * c], acc32[i][j][4 * c + 1],
-                                                           acc32[i][j][4 * c + 2], acc32[i][j][4 * c + 3]};
-                }
-            }
-        __syncthreads();
-        const OutTarget o = out_target<SPLIT>(p, tc, Cb);
-        for (int u = (int)threadIdx.x; u < UNITS; u += NT * KW) {
-            floatx4 sum = part[0][u];
-#pragma unroll
-            for (int g = 1; g < KW; ++g) sum += part[g][u];
-            const int ul = u & 63;
-            int q = __builtin_amdgcn_readfirstlane(u >> 6);
-            const int c = q % CH; q /= CH;
-            const int j = q % FN; q /= FN;
-            const int i = q % FM;
-            const int w = q / FM;
-            const int fr0 = row0 + (w / (BN / P2)) * P1 + i * FRG, fc0 = col0 + (w % (BN / P2)) * P2 + j * FRG;
-            const bool full = fr0 + FRG <= o.M && fc0 + FRG <= o.N;
-            const float v[4] = {sum[0], sum[1], sum[2], sum[3]};
-            if constexpr (CORE == CORE_MFMA16)
-                store_lane_column<SPLIT, 4>(o, fr0 + 4 * (ul >> 4), fc0 + (ul & 15), full, v, [](int e) { return e; });
-            else
-                store_lane_column<SPLIT, 4>(o, fr0 + 8 * c + 4 * (ul >> 5), fc0 + (ul & 31), full, v,
-                                            [](int e) { return e; });
+                for (int j = 0; j < FN; ++j) part[grp][((wave * FM + i) * FN + j) * 64 + lane] = acc16[i][j];
+        } else {
+            store_units32<FM, FN>(part[grp], wave, lane, acc32);
         }
+        __syncthreads();
+        store_sum_of_groups<SPLIT, FRG, CH, FM, FN, P1, P2, BN, NT, KW>(&part[0][0], p, tc, Cb, row0, col0);
     } else if constexpr (CORE == CORE_MFMA16) {
         write_tile_mfma16<SPLIT, FM, FN>(p, tc, Cb, row0 + subM, col0 + subN, lane, acc16);
     } else {

@@ -283,55 +283,16 @@ __global__ __launch_bounds__(64 * (BM / P1) * (BN / P2) * KW, 4) void gemm_f32_p
     };
 
     if constexpr (SK) {
-        // shares as in gemm_f32_kernel
-        auto uni = [](long long v) -> long long {
-            const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(unsigned long long)v);
-            const unsigned hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)((unsigned long long)v >> 32));
-            return (long long)(((unsigned long long)hi << 32) | lo);
-        };
-        const unsigned lw = (unsigned)__builtin_amdgcn_readfirstlane((int)logical_of_block());
-        const long long groups = (long long)gridDim.x;
-        const int nkT = (p.K + BK - 1) / BK;
-        const long long units = (long long)p.skTailTiles * nkT;
-        const long long ub = uni(sk_share_begin(lw, units, groups)), ue = uni(sk_share_begin(lw + 1, units, groups));
-        const long long t0 = uni(ub / nkT);
-        const int r0 = (int)(ub - t0 * nkT);
-        const int tailSegs = ue > ub ? (int)(uni((ue - 1) / nkT) - t0) + 1 : 0;
-        const int nSeg = p.skRounds + tailSegs;
-        for (int sg = 0; sg < nSeg; ++sg) {
-            unsigned logical;
-            int ks0 = 0, ks1 = nkT;
-            if (sg < p.skRounds) {
-                logical = (unsigned)sg * (unsigned)groups + lw;
-            } else {
-                const long long t = t0 + (sg - p.skRounds);
-                logical = (unsigned)p.skRounds * (unsigned)groups + (unsigned)t;
-                ks0 = sg == p.skRounds ? r0 : 0;
-                ks1 = (int)min((long long)nkT, ue - t * nkT);
-            }
-            TileCoord tc = tile_of_logical(p, logical);
-            tc.batch = __builtin_amdgcn_readfirstlane(tc.batch);
-            tc.tm = __builtin_amdgcn_readfirstlane(tc.tm);
-            tc.tn = __builtin_amdgcn_readfirstlane(tc.tn);
-            tc.split = 0;
+        sk_for_each_tile<BK>(p, [&](const TileCoord &tc, int ks0, int ks1, int nkT, unsigned group, bool head) {
             const int row = tc.tm * BM, col = tc.tn * BN;
             range(static_cast<const float *>(p.A) + (long long)tc.batch * p.strideA,
                   static_cast<const float *>(p.B) + (long long)tc.batch * p.strideB, row, col, ks0 * BK, min(p.K, ks1 * BK));
             const int laneE = this_lane();
-            if (ks0 == 0 && ks1 == nkT) {
+            if (ks0 == 0 && ks1 == nkT)
                 write_tile_mfma32<false, FM, FN>(p, tc, p.C + (long long)tc.batch * p.strideC, row + subM, col + subN, laneE, acc);
-            } else {
-                floatx4 *part = reinterpret_cast<floatx4 *>(p.ws) + ((long long)lw * 2 + (sg == p.skRounds ? 0 : 1)) * (BM * BN / 4);
-#pragma unroll
-                for (int i = 0; i < FM; ++i)
-#pragma unroll
-                    for (int j = 0; j < FN; ++j)
-#pragma unroll
-                        for (int c = 0; c < 4; ++c)
-                            part[(((wave * FM + i) * FN + j) * 4 + c) * 64 + laneE] =
-                                floatx4{acc[i][j][4 * c], acc[i][j][4 * c + 1], acc[i][j][4 * c + 2], acc[i][j][4 * c + 3]};
-            }
-        }
+            else
+                sk_store_part<BM, BN, FM, FN>(p, group, head, wave, laneE, acc);
+        });
     } else {
         const TileCoord tc = tile_of_block(p);
         const int row = __builtin_amdgcn_readfirstlane(tc.tm) * BM, col = __builtin_amdgcn_readfirstlane(tc.tn) * BN;
@@ -342,34 +303,11 @@ __global__ __launch_bounds__(64 * (BM / P1) * (BN / P2) * KW, 4) void gemm_f32_p
         if constexpr (KW == 1) {
             write_tile_mfma32<SPLIT, FM, FN>(p, tc, Cb, row + subM, col + subN, (int)threadIdx.x & 63, acc);
         } else {
-            // float4 units [group][wave][i][j][chunk][lane], dealt out over all threads and summed in group order
             constexpr int UNITS = (NT / 64) * FM * FN * 4 * 64;
             floatx4 *part = reinterpret_cast<floatx4 *>(ldsAll);
-#pragma unroll
-            for (int i = 0; i < FM; ++i)
-#pragma unroll
-                for (int j = 0; j < FN; ++j)
-#pragma unroll
-                    for (int c = 0; c < 4; ++c)
-                        part[grp * UNITS + (((wave * FM + i) * FN + j) * 4 + c) * 64 + ((int)threadIdx.x & 63)] =
-                            floatx4{acc[i][j][4 * c], acc[i][j][4 * c + 1], acc[i][j][4 * c + 2], acc[i][j][4 * c + 3]};
+            store_units32<FM, FN>(part + grp * UNITS, wave, (int)threadIdx.x & 63, acc);
             __syncthreads();
-            const OutTarget o = out_target<SPLIT>(p, tc, Cb);
-            for (int u = (int)threadIdx.x; u < UNITS; u += NT * KW) {
-                floatx4 sum = part[u];
-#pragma unroll
-                for (int g = 1; g < KW; ++g) sum += part[g * UNITS + u];
-                const int ul = u & 63;
-                int q = __builtin_amdgcn_readfirstlane(u >> 6);
-                const int c = q % 4; q /= 4;
-                const int j = q % FN; q /= FN;
-                const int i = q % FM;
-                const int w = q / FM;
-                const int fr0 = row + (w / (BN / P2)) * P1 + i * 32, fc0 = col + (w % (BN / P2)) * P2 + j * 32;
-                const bool full = fr0 + 32 <= o.M && fc0 + 32 <= o.N;
-                const float v[4] = {sum[0], sum[1], sum[2], sum[3]};
-                store_lane_column<SPLIT, 4>(o, fr0 + 8 * c + 4 * (ul >> 5), fc0 + (ul & 31), full, v, [](int e) { return e; });
-            }
+            store_sum_of_groups<SPLIT, 32, 4, FM, FN, P1, P2, BN, NT, KW>(part, p, tc, Cb, row, col);
         }
     }
 }

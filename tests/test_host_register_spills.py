@@ -35,3 +35,11 @@ def test_unsplit_256_x_256_tile(tmp_path, layout, most):
 def test_fp32_units_form_on_16_wide_fragments(tmp_path, tile, layout):
     """Sixteen waves of 64 x 64 hold two work-groups a compute unit, 32 x 32 x 16 eight: eight waves per SIMD, no spills."""
     assert resources(tmp_path, "gemm_f32.hpp", "gemm_f32_kernel<1, %s, 16, 16, false, %s, 1, 1, false, false>" % (tile, layout)) == (0, 8)
+
+
+@pytest.mark.parametrize("balanced", ["false", "true"])
+@pytest.mark.parametrize("layout", ["false, false", "false, true", "true, false", "true, true"])
+def test_fp32_parts_on_128_x_128_tiles(tmp_path, layout, balanced):
+    """Two work-groups of eight waves a compute unit take 128 registers a wave, 64 of them accumulators: none over that, in the
+    balanced form's loop over tiles neither."""
+    assert resources(tmp_path, "gemm_f32_parts.hpp", "gemm_f32_parts_kernel<128, 128, 64, 32, false, %s, 1, %s>" % (layout, balanced)) == (0, 4)
