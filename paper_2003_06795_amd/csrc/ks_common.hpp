@@ -129,10 +129,10 @@ constexpr bool f32_parts_member(int core, int bm, int bn, int bk, int kw, bool s
                          (bm == 64 && bn == 64 && bk == 16 && (kw == 2 || (kw == 1 && !split))));
 }
 // It takes K ranges (of a work-group) from these on.  Time against the fp32 matrix pipe over drawn problems of 16 to 4096 in each
-// dimension and im2col ones, all layouts, with and without scratch: 128 x 128 tiles 0.68 (110 problems; 1.03 once, at K = 31), 64 x 64
-// 0.845 (110; up to K = 48 half of them slower by up to 1.10, from 56 on 0.80 and none over 0.99), two K groups 0.86 (500; of those
-// with ranges below 360 half slower, up to 1.15, 0.95 in all: a few steps to a slice and one work-group to a compute unit wait
-// for memory, which the fp32 form has four steps in flight for; from 360 on 0.84, four over 1.02, 1.05 at most).
+// dimension and im2col ones, all layouts, with and without scratch: 128 x 128 tiles 0.67 (98 problems; K of 49 to 64 0.89, 0.96 at
+// most), 64 x 64 0.77 (101; 49 to 64 0.94, four of 40 over 1.02, and up to 48 half of them slower by up to 1.10), two K groups 0.87
+// (101; ranges of 360 to 420 0.905, five of 40 over 1.02, 1.055 at most; below 360 half slower, up to 1.15, 0.95 in all: a few
+// steps to a slice and one work-group to a compute unit wait for memory, which the fp32 form has four steps in flight for).
 constexpr int f32_parts_least_k(int kw) { return kw == 2 ? 360 : 49; }
 // In that form an unsplit 64 x 64 x 16 member computes 2 x 2 tiles per work-group, on the 128 x 128 tile of eight waves, where a
 // work-group's sum of splitting and LDS traffic is half as long per product: the bits are the same.  Two of them fill a unit, so
