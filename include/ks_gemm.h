@@ -134,7 +134,7 @@ typedef struct {
  * partitions, multiply a K range of at least 49 (360 with two K groups) on the bf16 matrix pipe, each float as the exact sum of
  * three bf16 numbers, accumulated in fp32: rms errors are 0.3 to 0.9 of the fp32 pipe's for dense and sparse sums, 1.03 for one term
  * (2^-23 of it at most), 1.2 for sums that a few terms nearly are.  Entries that the accumulators cannot hold (infinities, NaN,
- * magnitudes from 2^104 on, sums from 2^82 on) are computed once more on the fp32 pipe, in the same launch: the results are fp32
+ * magnitudes from 2^105 on, sums from 2^82 on) are computed once more on the fp32 pipe, in the same launch: the results are fp32
  * arithmetic's, in up to 2.6 times the time of a call without them.  On which pipe an entry is computed depends on its row of
  * op(A) and its column of op(B) alone.
  * Degenerate sizes: M, N or batch == 0 -> success, nothing launched; K == 0 -> C = beta*C.
@@ -338,7 +338,8 @@ int ks_set_tiles_per_workgroup(int n);
  * kernel); a 512-thread member with two per compute unit launches 256 when the problem has at
  * most 96 tiles.  1 <= per_cu <= 8 forces another count per compute unit for testing and tuning, and
  * makes those members take the form on every call whose scratch is there (or that divides no
- * tile; the 128 x 128 x 32 one, which has it on the bf16 matrix pipe, from K = 49 on); 0 restores the members' own count and the per-call choice.  ks_workspace_bytes_needed
+ * tile; the 128 x 128 x 32 one, which has it on the bf16 matrix pipe, from K = 49 on); 0 restores
+ * the members' own count and the per-call choice.  ks_workspace_bytes_needed
  * follows the forced count.  Results stay within the stated bound but the summation order of
  * divided tiles changes with the count.  Not thread-safe. */
 int ks_set_balanced_groups(int per_cu);
