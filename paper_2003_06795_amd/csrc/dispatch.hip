@@ -823,6 +823,7 @@ int run_ws(Workspace wsp, int dtype, int id, int transA, int transB, int64_t M, 
                              : 1;
         return KS_OK;
     }
+    set_tile_order(p);
     if (tailS) {
         const int layoutBits = (akc ? 2 : 0) + (bkc ? 1 : 0) + f16Bit;
         g_bf16_dma[id](p, (int)mainGrid, layoutBits, stream);
@@ -833,6 +834,7 @@ int run_ws(Workspace wsp, int dtype, int id, int transA, int transB, int64_t M, 
         q.tileBase = (int)mainGrid;
         q.tileSpan = (int)tailTiles;
         q.ws = static_cast<float *>(wsp.ptr);
+        set_tile_order(q);
         g_bf16_dma[id](q, (int)(tailTiles * tailS), layoutBits + 8, stream);
         if (hipGetLastError() != hipSuccess) return KS_ERR_LAUNCH;
         hipLaunchKernelGGL(tail_reduce_kernel,

@@ -24,7 +24,28 @@ __device__ __forceinline__ uintx4 load16_any(const uint16_t *src) {
     return reinterpret_cast<const AnyUintx4 *>(src)->v;
 }
 
+// n / d for n < 2^31, as a multiplication and a shift that the scalar unit does: there is no integer division, and what the
+// compiler puts in its place, some 25 dependent instructions of the vector unit for each of the four that find a tile, was
+// most of the time from the kernel's arguments to its first load.  1024 x 32x64x16 fp32 on 32 x 32 tiles 6.55 -> 5.86 us, 700 x
+// 60x52x33 11.1 -> 10.2, 401408 x 64 x 27 39.8 -> 38.3, 480 x 1184 x 2592 TN 31.5 -> 30.4; level from 50 us on.
+// m = ceil(2^(31 + s) / d) with 2^(s - 1) < d <= 2^s: m d exceeds 2^(31 + s) by less than 2^s, which n < 2^31 makes less than one
+// part in d of a quotient's unit.
+struct Divisor {
+    unsigned mul, shift;
+};
+inline Divisor divisor_of(unsigned d) {
+    const unsigned s = d > 1 ? 32 - (unsigned)__builtin_clz(d - 1) : 0;
+    return Divisor{(unsigned)(((1ULL << (31 + s)) + d - 1) / d), 31 + s};
+}
+__host__ __device__ __forceinline__ unsigned divide(unsigned n, Divisor d) {
+    return (unsigned)((unsigned long long)n * d.mul >> d.shift);
+}
+
+// (arguments lie in memory that no cache of the device holds at a launch; what a three-dimensional launch reads before its first
+// loads stays in the first 144 bytes and in one group of loads: with perSplit at byte 188, or with C further back, which the compiler
+// then fetched in a second group, every launch took 0.2 us more)
 struct GemmParams {
+    Divisor perSplit;                // K partitions (tile order, set_tile_order)
     const void *A;
     const void *B;
     float *C;
@@ -44,6 +65,8 @@ struct GemmParams {
                                      //    then 0 and the batch stride, in elements, is strideC16
     long long strideC16;
     float alpha, beta;
+    // tile order: tiles of a unit, tiles of a band, rows of a band and of the last one
+    Divisor perUnit, perBand, perRow, perLastRow;
     // balanced persistent form (fp32 members that have one; 0 everywhere else): the launch holds
     // skGroups work-groups; each computes skRounds whole tiles (logical tiles round * skGroups + its
     // own logical id) and then an equal share of the K-steps of the skTailTiles tiles that are left
@@ -54,6 +77,18 @@ struct GemmParams {
     // bm x bn tiles [partition][tile - tileBase].  tileSpan == 0 everywhere else.
     int tileBase, tileSpan, bm, bn;
 };
+// from the tile counts, the partitions and the band height, once they are final (a three-dimensional launch reads its tile)
+inline void set_tile_order(GemmParams &p) {
+    if (p.grid3d) {
+        if (p.splitK > 1) p.perSplit = divisor_of((unsigned)p.splitK);
+        return;
+    }
+    p.perUnit = divisor_of(p.tileSpan ? (unsigned)p.tileSpan : (unsigned)p.tilesM * (unsigned)p.tilesN);
+    p.perSplit = divisor_of((unsigned)p.splitK);
+    p.perBand = divisor_of((unsigned)p.bandRows * (unsigned)p.tilesN);
+    p.perRow = divisor_of((unsigned)p.bandRows);
+    p.perLastRow = divisor_of((unsigned)((p.tilesM - 1) % p.bandRows + 1));
+}
 
 // K-steps [first, last) of the left-over tiles (flattened as tile * steps-per-tile + step) that
 // work-group `w` of `groups` computes in the balanced persistent form; shares differ by at most one
@@ -179,16 +214,17 @@ __device__ __forceinline__ unsigned logical_of_block() {
 // order, inside a unit bands of p.bandRows tile-rows walked column-major
 __device__ __forceinline__ TileCoord tile_of_logical(const GemmParams &p, unsigned logical) {
     const unsigned per = p.tileSpan ? (unsigned)p.tileSpan : (unsigned)p.tilesM * (unsigned)p.tilesN;
-    const unsigned unit = logical / per, t = logical - unit * per + (unsigned)p.tileBase;
+    const unsigned unit = divide(logical, p.perUnit), t = logical - unit * per + (unsigned)p.tileBase;
     TileCoord c;
-    c.batch = (int)(unit / (unsigned)p.splitK);
+    c.batch = (int)divide(unit, p.perSplit);
     c.split = (int)(unit - (unsigned)c.batch * (unsigned)p.splitK);
     const unsigned h = (unsigned)p.bandRows;
     const unsigned band = h * (unsigned)p.tilesN;
-    const unsigned g = t / band, in = t - g * band;
+    const unsigned g = divide(t, p.perBand), in = t - g * band;
     const unsigned first = g * h;
-    const unsigned rows = ((unsigned)p.tilesM - first) < h ? ((unsigned)p.tilesM - first) : h;
-    c.tn = (int)(in / rows);
+    const bool last = (unsigned)p.tilesM - first < h;
+    const unsigned rows = last ? (unsigned)p.tilesM - first : h;
+    c.tn = (int)divide(in, Divisor{last ? p.perLastRow.mul : p.perRow.mul, last ? p.perLastRow.shift : p.perRow.shift});
     c.tm = (int)(first + (in - (unsigned)c.tn * rows));
     return c;
 }
@@ -196,7 +232,7 @@ __device__ __forceinline__ TileCoord tile_of_logical(const GemmParams &p, unsign
 // inverse of the tile walk above: position of tile (tm, tn) in the one-dimensional order of a unit
 __device__ __forceinline__ unsigned logical_of_tile(const GemmParams &p, int tm, int tn) {
     const unsigned h = (unsigned)p.bandRows;
-    const unsigned g = (unsigned)tm / h, first = g * h;
+    const unsigned g = divide((unsigned)tm, p.perRow), first = g * h;
     const unsigned rows = ((unsigned)p.tilesM - first) < h ? ((unsigned)p.tilesM - first) : h;
     return g * h * (unsigned)p.tilesN + (unsigned)tn * rows + ((unsigned)tm - first);
 }
@@ -226,7 +262,7 @@ __device__ __forceinline__ TileCoord tile_of_block(const GemmParams &p) {
         if (p.splitK == 1) {
             c.batch = (int)unit; c.split = 0;
         } else {
-            c.batch = (int)(unit / (unsigned)p.splitK);
+            c.batch = (int)divide(unit, p.perSplit);
             c.split = (int)(unit - (unsigned)c.batch * (unsigned)p.splitK);
         }
         return c;

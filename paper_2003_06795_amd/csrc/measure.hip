@@ -135,6 +135,7 @@ extern "C" int ks_bf16_ablation(int mode, const uint16_t *A, const uint16_t *B, 
     p.tilesM = (int)(M / 256); p.tilesN = (int)(N / 256);
     p.splitK = 1; p.kChunk = (int)K; p.grid3d = 0; p.tilesPerWG = 1; p.bandRows = 8;
     p.alpha = 1.0f; p.beta = 0.0f;
+    set_tile_order(p);
     const dim3 grid((unsigned)(p.tilesM * p.tilesN)), block(512);
     hipStream_t s = static_cast<hipStream_t>(stream);
     hipEvent_t e0, e1;
