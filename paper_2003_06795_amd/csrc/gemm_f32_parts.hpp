@@ -47,7 +47,6 @@ namespace ks {
 
 typedef float floatx2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef unsigned uintx2 __attribute__((ext_vector_type(2)));
 
 // what the operands are multiplied by: the last bit of the smallest float, 2^-149, becomes 2^-126
 constexpr float kPartsScale = 8388608.f;

@@ -23,6 +23,11 @@ struct __attribute__((packed, aligned(2))) AnyUintx4 {
 __device__ __forceinline__ uintx4 load16_any(const uint16_t *src) {
     return reinterpret_cast<const AnyUintx4 *>(src)->v;
 }
+// and four, of an output kept in bf16
+typedef unsigned int uintx2 __attribute__((ext_vector_type(2)));
+struct __attribute__((packed, aligned(2))) AnyUintx2 {
+    uintx2 v;
+};
 
 // n / d for n < 2^31, as a multiplication and a shift that the scalar unit does: there is no integer division, and what the
 // compiler puts in its place, some 25 dependent instructions of the vector unit for each of the four that find a tile, was
@@ -431,6 +436,73 @@ __device__ __forceinline__ void write_tile_mfma16(const GemmParams &p, const Til
             store_lane_column<SPLIT, 4>(o, rb + i * 16 + 4 * (lane >> 4), cb + j * 16 + (lane & 15), full, v,
                                         [](int e) { return e; });
         }
+}
+
+// Four consecutive entries of a row of C, columns col .. col + 3: what a lane holds of a 16x16 fragment that is computed with the
+// operands exchanged, B op(A): register e of lane l is then C[l%16][4*(l/16) + e], a neighbour in a row and not in a column, and
+// the entries are one access of sixteen bytes (eight in bf16) where they were four of four (two).  For the kernels whose epilogue
+// counts, those in two groups of waves (gemm_bf16_pp.hpp); members of a few microseconds lost 0.1 - 0.2 us by the longer code.
+// `full` as above.  old_entries() is apart from store_entries() so that old values can be requested before the first store.
+__device__ __forceinline__ floatx4 old_entries(const OutTarget &o, int row, int col, bool full) {
+    floatx4 old = {0.f, 0.f, 0.f, 0.f};
+    const long long at = (long long)row * o.ld + col;
+    if (o.out16) {
+        const uint16_t *c = reinterpret_cast<const uint16_t *>(o.base) + o.off16 + at;
+        if (full) {
+            const uintx2 u = reinterpret_cast<const AnyUintx2 *>(c)->v;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) old[e] = bf16_bits_to_float((uint16_t)(u[e >> 1] >> (16 * (e & 1))));
+        } else if (row < o.M) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (col + e < o.N) old[e] = bf16_bits_to_float(c[e]);
+        }
+    } else if (full) {
+        old = load_float4_any(o.base + at);
+    } else if (row < o.M) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (col + e < o.N) old[e] = o.base[at + e];
+    }
+    return old;
+}
+template <bool SPLIT>
+__device__ __forceinline__ void store_entries(const OutTarget &o, int row, int col, bool full, floatx4 v, floatx4 old) {
+    const long long at = (long long)row * o.ld + col;
+    if constexpr (!SPLIT) {
+        v = o.alpha * v;
+        if (o.beta != 0.0f) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = fmaf(o.beta, old[e], v[e]);
+        }
+        if (o.bias != nullptr) {
+            if (full) v += load_float4_any(o.bias + col);
+            else
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (col + e < o.N) v[e] += o.bias[col + e];
+        }
+        if (o.out16) {
+            uint16_t *c = reinterpret_cast<uint16_t *>(o.base) + o.off16 + at;
+            const unsigned h[4] = {float_to_bf16_bits(v[0]), float_to_bf16_bits(v[1]), float_to_bf16_bits(v[2]),
+                                   float_to_bf16_bits(v[3])};
+            if (full) {
+                reinterpret_cast<AnyUintx2 *>(c)->v = uintx2{h[0] | h[1] << 16, h[2] | h[3] << 16};
+            } else if (row < o.M) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (col + e < o.N) c[e] = (uint16_t)h[e];
+            }
+            return;
+        }
+    }
+    if (full) {
+        reinterpret_cast<AnyFloatx4 *>(o.base + at)->v = v;
+    } else if (row < o.M) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (col + e < o.N) o.base[at + e] = v[e];
+    }
 }
 
 // accumulator register e of lane l of a 32x32 MFMA fragment holds C[8*(e/4) + 4*(l/32) + e%4][l%32]
