@@ -49,7 +49,7 @@ def _jobs(kept_only=False):
             src = os.path.join(CSRC, "instances_%s.hip" % kind)
             jobs.append((src, os.path.join(obj, "inst_%s_%02d.o" % (kind, n)),
                          [HIPCC] + HIP_FLAGS + extra + ["-DKS_SHARD=%d" % n, "-c", src]))
-    for name in ("dispatch", "measure"):
+    for name in ("instances_bf16_slices", "dispatch", "measure"):
         src = os.path.join(CSRC, name + ".hip")
         jobs.append((src, os.path.join(obj, name + ".o"), [HIPCC] + HIP_FLAGS + extra + ["-c", src]))
     for name in ("selector", "tune"):

@@ -7,6 +7,7 @@
 
 #include "../../include/ks_gemm.h"
 #include "registry.hpp"
+#include "slices.hpp"
 
 #ifndef KS_GRID3D_MAX
 #define KS_GRID3D_MAX 2048      // work-groups up to which the grid is launched three-dimensional
@@ -17,7 +18,9 @@
 
 namespace ks {
 
-int select_member(int dtype, int64_t M, int64_t N, int64_t K, int64_t batch, int transA, int transB, bool scratch);   // selector.cpp
+// selector.cpp
+int select_member(int dtype, int64_t M, int64_t N, int64_t K, int64_t batch, int transA, int transB, bool scratch);
+bool custom_tree(int dtype);
 
 #define KS_DECL(n)                              \
     void register_f32_shard_##n(LaunchFn *);    \
@@ -567,7 +570,7 @@ int run_ws(Workspace wsp, int dtype, int id, int transA, int transB, int64_t M, 
            const void *A, int64_t lda, const void *B, int64_t ldb, float beta, float *C, int64_t ldc,
            int64_t batch, int64_t strideA, int64_t strideB, int64_t strideC, hipStream_t stream,
            const float *bias = nullptr, int out16 = 0, ks_launch_plan_t *planOnly = nullptr, bool own = false,
-           bool copied = false) {
+           bool copied = false, bool selected = false) {
     const InstanceDesc *d = desc_of(dtype, id);
     if (!d) return KS_ERR_INVALID_ARG;
     const int rc = validate(transA, transB, M, N, K, A, lda, B, ldb, C, ldc, batch, strideC);
@@ -595,6 +598,46 @@ int run_ws(Workspace wsp, int dtype, int id, int transA, int transB, int64_t M, 
 
     // a pruned build holds only the kept members
     if ((dtype == KS_F32 ? g_f32[id] : g_bf16[id]) == nullptr) return KS_ERR_UNSUPPORTED;
+
+    // A call that names no member and would run one of the skinny or square ones with few tiles takes the K-slices form
+    // where its estimate is the lower one (slices.hpp).  Named members, a caller's own tree and forced partitions are followed as they
+    // are.  The form takes no scratch; what the member would do with the scratch at hand is what it is compared with.
+    // 1300 drawn problems (64 .. 4096 in each dimension, skinny and tall ones, four layouts): 495 take it, 0.755 of the time.
+    if (selected && dtype != KS_F32 && batch == 1 && g_splitForced == 0 && !custom_tree(dtype)) {
+        const bool akc = transA == 0, bkc = transB == 1;
+        if (dma_operands(akc, bkc, M, N, K, A, lda, B, ldb, 1, 0, 0)) {
+            const int64_t parts = d->splitK > 0 ? 1 : partitions(d, false, M, N, K, 1, wsp), kTiles = (K + d->bk - 1) / d->bk;
+            const int64_t groups = ((M + d->bm - 1) / d->bm) * ((N + d->bn - 1) / d->bn) * parts;
+            const int t = slices_tile(akc, bkc, M, N, K, slices_other_us(id, M, N, K, groups, (kTiles + parts - 1) / parts, parts,
+                                                                          4.0 * (double)parts * (double)M * (double)N));
+            if (t >= 0) {
+                const SliceTile &tile = kSliceTiles[t];
+                GemmParams p{};
+                p.A = A; p.B = B; p.C = C; p.bias = bias; p.out16 = out16;
+                p.lda = lda; p.ldb = ldb; p.ldc = ldc;
+                p.M = (int)M; p.N = (int)N; p.K = (int)K; p.batch = 1;
+                p.tilesM = (int)((M + tile.bm - 1) / tile.bm);
+                p.tilesN = (int)((N + tile.bn - 1) / tile.bn);
+                p.splitK = 1; p.kChunk = (int)K; p.tilesPerWG = 1; p.bandRows = 8;
+                p.bm = tile.bm; p.bn = tile.bn;
+                p.alpha = alpha; p.beta = beta;
+                const int grid = p.tilesM * p.tilesN;
+                p.grid3d = (double)(M + N) * (double)K * 2 <= (double)KS_GRID3D_BYTES ? 1 : 0;
+                set_tile_order(p);
+                if (planOnly) {
+                    planOnly->kernel_id = select_member(dtype, M, N, K, 1, transA, transB, true);   // whatever the scratch, which is not used
+                    planOnly->path = 16 + t;
+                    planOnly->vector_loads = 1;
+                    planOnly->grid_3d = p.grid3d;
+                    planOnly->workgroups = grid;
+                    return KS_OK;
+                }
+                const int pastCache = (slices_past_cache(M, K, p.tilesN) ? 1 : 0) + (slices_past_cache(N, K, p.tilesM) ? 2 : 0);
+                launch_bf16_slices(t, p, grid, (akc ? 2 : 0) + (bkc ? 1 : 0) + (dtype == KS_F16 ? 16 : 0), pastCache, stream);
+                return hipGetLastError() == hipSuccess ? KS_OK : KS_ERR_LAUNCH;
+            }
+        }
+    }
 
     // 16-bit operands whose K is not a whole number of K-steps (of half ones for members of K-step 128)
     // would take the member's register-staged path for all of K.  Where everything else qualifies for the
@@ -858,9 +901,9 @@ int run_ws(Workspace wsp, int dtype, int id, int transA, int transB, int64_t M, 
 int run(int dtype, int id, int transA, int transB, int64_t M, int64_t N, int64_t K, float alpha,
         const void *A, int64_t lda, const void *B, int64_t ldb, float beta, float *C, int64_t ldc,
         int64_t batch, int64_t strideA, int64_t strideB, int64_t strideC, hipStream_t stream,
-        const float *bias = nullptr, int out16 = 0) {
+        const float *bias = nullptr, int out16 = 0, bool selected = false) {
     return run_ws(registered_ws(), dtype, id, transA, transB, M, N, K, alpha, A, lda, B, ldb, beta, C, ldc, batch,
-                  strideA, strideB, strideC, stream, bias, out16);
+                  strideA, strideB, strideC, stream, bias, out16, nullptr, false, false, selected);
 }
 
 }  // namespace
@@ -1053,7 +1096,7 @@ extern "C" int ks_gemm_bf16(int transA, int transB, int64_t M, int64_t N, int64_
                             int64_t strideC, void *stream) {
     const int id = select_checked(KS_BF16, M, N, K, batch, transA, transB);
     if (id < 0) return id;
-    return run(KS_BF16, id, KS_GEMM_PASS);
+    return run(KS_BF16, id, KS_GEMM_PASS, nullptr, 0, true);
 }
 
 extern "C" int ks_gemm_f16(int transA, int transB, int64_t M, int64_t N, int64_t K, float alpha,
@@ -1062,7 +1105,7 @@ extern "C" int ks_gemm_f16(int transA, int transB, int64_t M, int64_t N, int64_t
                            int64_t strideC, void *stream) {
     const int id = select_checked(KS_F16, M, N, K, batch, transA, transB);
     if (id < 0) return id;
-    return run(KS_F16, id, KS_GEMM_PASS);
+    return run(KS_F16, id, KS_GEMM_PASS, nullptr, 0, true);
 }
 
 extern "C" int ks_gemm_f16_with_kernel(int kernel_id, int transA, int transB, int64_t M, int64_t N,
@@ -1079,11 +1122,12 @@ extern "C" int ks_gemm_bias(int dtype, int kernel_id, int transA, int transB, in
                             int64_t batch, int64_t strideA, int64_t strideB, int64_t strideC,
                             void *stream) {
     if (dtype != KS_F32 && dtype != KS_BF16 && dtype != KS_F16) return KS_ERR_INVALID_ARG;
-    if (kernel_id < 0) {
+    const bool selected = kernel_id < 0;
+    if (selected) {
         kernel_id = select_checked(dtype, M, N, K, batch, transA, transB);
         if (kernel_id < 0) return kernel_id;
     }
-    return run(dtype, kernel_id, KS_GEMM_PASS, bias);
+    return run(dtype, kernel_id, KS_GEMM_PASS, bias, 0, selected);
 }
 
 extern "C" int ks_gemm_out_bf16(int dtype, int kernel_id, int transA, int transB, int64_t M, int64_t N,
@@ -1092,12 +1136,13 @@ extern "C" int ks_gemm_out_bf16(int dtype, int kernel_id, int transA, int transB
                                 int64_t batch, int64_t strideA, int64_t strideB, int64_t strideC,
                                 void *stream) {
     if (dtype != KS_F32 && dtype != KS_BF16 && dtype != KS_F16) return KS_ERR_INVALID_ARG;
-    if (kernel_id < 0) {
+    const bool selected = kernel_id < 0;
+    if (selected) {
         kernel_id = select_checked(dtype, M, N, K, batch, transA, transB);
         if (kernel_id < 0) return kernel_id;
     }
     float *C = reinterpret_cast<float *>(C16);        // element size is carried by the out16 flag
-    return run(dtype, kernel_id, KS_GEMM_PASS, bias, 1);
+    return run(dtype, kernel_id, KS_GEMM_PASS, bias, 1, selected);
 }
 
 // Entry point for callers that cannot allocate device memory (HIP graph capture, serving loops):
@@ -1139,11 +1184,12 @@ extern "C" int ks_gemm_static_scratch(int dtype, int kernel_id, int transA, int 
     Workspace w{nullptr, 0};
     const int rc = static_scratch(&w);
     if (rc != KS_OK) return rc;
-    if (kernel_id < 0) {
+    const bool selected = kernel_id < 0;
+    if (selected) {
         kernel_id = select_checked(dtype, M, N, K, batch, transA, transB, w);
         if (kernel_id < 0) return kernel_id;
     }
-    return run_ws(w, dtype, kernel_id, KS_GEMM_PASS);
+    return run_ws(w, dtype, kernel_id, KS_GEMM_PASS, nullptr, 0, nullptr, false, false, selected);
 }
 
 extern "C" int ks_gemm_with_workspace(int dtype, int kernel_id, int transA, int transB, int64_t M, int64_t N,
@@ -1155,11 +1201,12 @@ extern "C" int ks_gemm_with_workspace(int dtype, int kernel_id, int transA, int 
     if ((workspace_device == nullptr) != (workspace_bytes == 0)) return KS_ERR_INVALID_ARG;
     if (reinterpret_cast<uintptr_t>(workspace_device) % sizeof(float)) return KS_ERR_INVALID_ARG;
     const Workspace w{workspace_device, workspace_bytes};
-    if (kernel_id < 0) {
+    const bool selected = kernel_id < 0;
+    if (selected) {
         kernel_id = select_checked(dtype, M, N, K, batch, transA, transB, w);
         if (kernel_id < 0) return kernel_id;
     }
-    return run_ws(w, dtype, kernel_id, KS_GEMM_PASS, nullptr, 0, nullptr, true);
+    return run_ws(w, dtype, kernel_id, KS_GEMM_PASS, nullptr, 0, nullptr, true, false, selected);
 }
 
 extern "C" int ks_gemm_plan(int dtype, int kernel_id, int transA, int transB, int64_t M, int64_t N, int64_t K,
@@ -1168,12 +1215,13 @@ extern "C" int ks_gemm_plan(int dtype, int kernel_id, int transA, int transB, in
                             int64_t strideC, ks_launch_plan_t *out) {
     if (dtype != KS_F32 && dtype != KS_BF16 && dtype != KS_F16) return KS_ERR_INVALID_ARG;
     if (!out) return KS_ERR_INVALID_ARG;
-    if (kernel_id < 0) {
+    const bool selected = kernel_id < 0;
+    if (selected) {
         kernel_id = select_checked(dtype, M, N, K, batch, transA, transB);
         if (kernel_id < 0) return kernel_id;
     }
     void *stream = nullptr;
-    return run_ws(registered_ws(), dtype, kernel_id, KS_GEMM_PASS, nullptr, 0, out);
+    return run_ws(registered_ws(), dtype, kernel_id, KS_GEMM_PASS, nullptr, 0, out, false, false, selected);
 }
 
 extern "C" int ks_time_gemm(int dtype, int kernel_id, int transA, int transB, int64_t M, int64_t N,
@@ -1183,7 +1231,8 @@ extern "C" int ks_time_gemm(int dtype, int kernel_id, int transA, int transB, in
                             int warmup, int iters, int reps, float *ms_out) {
     if (dtype != KS_F32 && dtype != KS_BF16 && dtype != KS_F16) return KS_ERR_INVALID_ARG;
     if (iters < 1 || iters > 1024 || reps < 1 || warmup < 0 || !ms_out) return KS_ERR_INVALID_ARG;
-    if (kernel_id < 0) {
+    const bool selected = kernel_id < 0;
+    if (selected) {
         kernel_id = select_checked(dtype, M, N, K, batch, transA, transB);
         if (kernel_id < 0) return kernel_id;
     }
@@ -1198,13 +1247,13 @@ extern "C" int ks_time_gemm(int dtype, int kernel_id, int transA, int transB, in
     // the first launch also proves the arguments: if it is refused nothing else is enqueued
     int rc = KS_OK;
     for (int i = 0; i < warmup; ++i) {
-        rc = run(dtype, kernel_id, KS_GEMM_PASS);
+        rc = run(dtype, kernel_id, KS_GEMM_PASS, nullptr, 0, selected);
         if (rc != KS_OK) return rc;
     }
     for (int i = 0; i < iters; ++i) {
         if (hipEventRecord(ev[2 * i], s) != hipSuccess) return KS_ERR_LAUNCH;
         for (int r = 0; r < reps; ++r) {
-            rc = run(dtype, kernel_id, KS_GEMM_PASS);
+            rc = run(dtype, kernel_id, KS_GEMM_PASS, nullptr, 0, selected);
             if (rc != KS_OK) return rc;
         }
         if (hipEventRecord(ev[2 * i + 1], s) != hipSuccess) return KS_ERR_LAUNCH;

@@ -247,6 +247,7 @@ extern "C" int ks_features(int64_t M, int64_t N, int64_t K, int64_t batch, int t
 }
 
 namespace ks {
+bool custom_tree(int dtype) { return g_tree[dtype == KS_F32 ? KS_F32 : KS_BF16].custom; }
 // The member for these sizes; without scratch (for the partitions it takes) the rules that count on a K split are left out.
 int select_member(int dtype, int64_t M, int64_t N, int64_t K, int64_t batch, int transA, int transB, bool scratch) {
     if (dtype == KS_F16) dtype = KS_BF16;          // the fp16 form runs the 16-bit family with its tree

@@ -1,0 +1,74 @@
+"""The K-slices form of the 16-bit products against fp64: every tile of it that a layout's sizes lead to, edges of tiles in both
+directions, K-steps that do not deal out evenly over the waves (and fewer of them than waves), old values, bias, a bf16 output and
+operands that are loaded past the last-level cache."""
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+# M, N, K: small ones, edges of 16 .. 64 in either direction, one to seventeen K-steps of 64 for the waves, wide operands
+SIZES = [(128, 128, 1024), (120, 72, 2048), (8, 8, 576), (1, 24, 1088), (200, 1000, 1536), (1000, 200, 1152), (520, 504, 2112),
+         (1024, 1000, 1024), (1000, 1016, 2048), (4096, 8, 1024), (16, 4000, 2048), (6000, 32, 1024), (32, 5000, 2048), (3200, 24, 576),
+         (12000, 16, 1024), (24, 9000, 2048), (8, 16384, 1024), (40, 2040, 4096), (7000, 40, 2048), (4584, 8, 512), (1880, 8, 576),
+         (1248, 8, 512), (9272, 8, 1216), (3144, 8, 512), (3464, 8, 576), (8, 3464, 576), (4936, 72, 1024), (5000, 64, 960), (3536, 72, 704),
+         (1896, 144, 768), (3368, 152, 3008), (1144, 456, 1984), (2208, 264, 3840), (3032, 176, 2496)]
+
+
+def operands(torch, g, tA, tB, M, N, K, kind):
+    A = torch.randn((K, M) if tA else (M, K), generator=g, device="cuda").mul_(K ** -0.5).to(kind)
+    B = torch.randn((N, K) if tB else (K, N), generator=g, device="cuda").mul_(K ** -0.5).to(kind)
+    return A, B
+
+
+@pytest.mark.parametrize("tA,tB", [(0, 0), (0, 1), (1, 0), (1, 1)])
+def test_against_fp64(tA, tB):
+    import torch
+    import paper_2003_06795_amd as ks
+    g = torch.Generator(device="cuda").manual_seed(7 + 2 * tA + tB)
+    tiles = set()
+    for i, (M, N, K) in enumerate(SIZES):
+        if (tA and M % 8) or (not tB and N % 8):
+            continue
+        dtype, kind = ((ks.BF16, torch.bfloat16), (ks.F16, torch.float16))[i % 2]
+        A, B = operands(torch, g, tA, tB, M, N, K, kind)
+        ldc = N + (0, 1, 4)[i % 3]
+        out16, beta, with_bias = i % 4 == 3, (0.0, 0.5)[i % 2], i % 3 == 1
+        C0 = torch.rand((M, ldc), generator=g, device="cuda").mul_(2).sub_(1)
+        C = C0.bfloat16() if out16 else C0.clone()
+        old = C.double()
+        bias = torch.rand(N, generator=g, device="cuda")
+        args = (tA, tB, M, N, K, 1.5, A, A.shape[1], B, B.shape[1], beta, C, ldc)
+        plan = ks.binding.gemm_plan(dtype, -1, *args)
+        if plan["path"] < 16:
+            continue
+        tiles.add(plan["path"] - 16)
+        if out16:
+            ks.gemm_out_bf16(dtype, -1, *args, bias if with_bias else None)
+        elif with_bias:
+            ks.gemm_bias(dtype, -1, *args, bias)
+        else:
+            (ks.gemm_bf16 if dtype == ks.BF16 else ks.gemm_f16)(*args)
+        torch.cuda.synchronize()
+        a, b = (A.t() if tA else A).double().contiguous(), (B.t() if tB else B).double().contiguous()
+        want = 1.5 * (a @ b) + beta * old[:, :N] + (bias.double() if with_bias else 0)
+        # fp32 sums of K exact products, at most K + 16 roundings of 2^-24 of the sum of magnitudes, and three of the epilogue
+        bound = (1.5 * (a.abs() @ b.abs())) * (K + 16) * 2.0 ** -24 + 3 * 2.0 ** -24 * (want.abs() + 2) + 1e-12
+        if out16:
+            bound = bound + 2.0 ** -8 * (want.abs() + bound)
+        assert bool(((C[:, :N].double() - want).abs() <= bound).all()), (M, N, K, plan["path"])
+        assert torch.equal(C[:, N:].double(), old[:, N:])
+    assert tiles == set(range(10)), tiles
+
+
+def test_operand_past_the_last_level_cache():
+    import torch
+    import paper_2003_06795_amd as ks
+    g = torch.Generator(device="cuda").manual_seed(3)
+    for tA, tB, M, N, K in ((0, 0, 8192, 16, 6208), (0, 1, 8, 8000, 6400)):
+        A, B = operands(torch, g, tA, tB, M, N, K, torch.bfloat16)
+        C = torch.full((M, N), float("nan"), device="cuda")
+        args = (tA, tB, M, N, K, 1.0, A, A.shape[1], B, B.shape[1], 0.0, C, N)
+        assert ks.binding.gemm_plan(ks.BF16, -1, *args)["path"] >= 16 and max(M, N) * K * 2 >= 96 << 20
+        ks.gemm_bf16(*args)
+        a, b = A.double(), (B.t() if tB else B).double().contiguous()
+        bound = (a.abs() @ b.abs()) * (K + 16) * 2.0 ** -24 + 1e-12
+        assert bool(((C.double() - a @ b).abs() <= bound).all()), (M, N, K)

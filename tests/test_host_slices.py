@@ -1,0 +1,74 @@
+"""Where a selecting call takes the K-slices form of the 16-bit products (ks_launch_plan_t::path 16 + tile): one round of work-groups
+on aligned operands with whole K-steps of 64, and never for a named member, forced partitions, a caller's own tree, batches, fp32
+or operands the direct-to-LDS path does not take.  No GPU: ks_gemm_plan reads sizes and addresses only."""
+import ctypes
+
+import pytest
+
+import paper_2003_06795_amd.binding as ks
+
+TILES = [(16, 16), (32, 16), (16, 32), (32, 32), (64, 16), (16, 64), (64, 32), (32, 64), (64, 64), (64, 64)]
+PTR = 1 << 20
+
+
+@pytest.fixture()
+def planner():
+    L = ks.lib()
+    assert L.ks_set_workspace(ctypes.c_void_p(1 << 21), ctypes.c_size_t(256 << 20)) == 0
+
+    def plan(dtype, kid, tA, tB, M, N, K, batch=1, lda=None, ldb=None, a=PTR):
+        return ks.gemm_plan(dtype, kid, tA, tB, M, N, K, 1.0, a, lda or (M if tA else K), PTR, ldb or (K if tB else N), 0.0, PTR, N,
+                            batch, M * K, K * N, M * N)
+    yield plan
+    L.ks_set_workspace(None, 0)
+
+
+def test_the_form_is_one_round_of_its_tiles(planner):
+    seen = set()
+    for tA in (0, 1):
+        for tB in (0, 1):
+            for M in (8, 64, 256, 1024, 3368, 4096, 8192, 16384):
+                for N in (8, 40, 64, 152, 512, 1024, 12000):
+                    for K in (448, 512, 1024, 2048, 3008, 4096, 8192):
+                        for dtype in (ks.BF16, ks.F16):
+                            got = planner(dtype, -1, tA, tB, M, N, K)
+                            if got["path"] < 16:
+                                continue
+                            bm, bn = TILES[got["path"] - 16]
+                            tiles = -(-M // bm) * -(-N // bn)
+                            assert K >= 512 and tiles <= 256 and got["workgroups"] == tiles and got["split_k"] == 1, got
+                            assert got["kernel_id"] == ks.select(dtype, M, N, K, 1, tA, tB)
+                            assert not (got["tail_split"] or got["k_remainder"] or got["operand_copies"] or got["balanced_groups"])
+                            seen.add(got["path"] - 16)
+    assert seen == set(range(len(TILES)))
+
+
+def test_calls_that_do_not_take_it(planner):
+    size = (0, 1, 512, 512, 2048)
+    assert planner(ks.BF16, -1, *size)["path"] == 16 + 3
+    assert planner(ks.BF16, ks.select(ks.BF16, 512, 512, 2048, 1, 0, 1), *size)["path"] < 16
+    assert planner(ks.F32, -1, *size)["path"] < 16
+    assert planner(ks.BF16, -1, *size, batch=2)["path"] < 16
+    assert planner(ks.BF16, -1, *size, a=PTR + 2)["path"] < 16
+    assert planner(ks.BF16, -1, *size, lda=2052)["path"] < 16
+    assert planner(ks.BF16, -1, 0, 1, 512, 512, 2080)["path"] < 16
+    assert planner(ks.BF16, -1, 0, 0, 512, 516, 2048)["path"] < 16          # rows of B end inside sixteen bytes
+    assert planner(ks.BF16, -1, 0, 1, 512, 507, 2048)["path"] == 16 + 3     # columns of C may end anywhere
+    ks.set_split_partitions(2)
+    try:
+        assert planner(ks.BF16, -1, *size)["path"] < 16
+    finally:
+        ks.set_split_partitions(0)
+    ks.set_fast_path(False)
+    try:
+        assert planner(ks.BF16, -1, *size)["path"] < 16
+    finally:
+        ks.set_fast_path(True)
+    tree = ks.get_selector(ks.BF16)
+    ks.set_selector(ks.BF16, tree)
+    try:
+        assert planner(ks.BF16, -1, *size)["path"] < 16
+    finally:
+        ks.set_selector(ks.BF16, [])
+    ks.lib().ks_set_workspace(None, 0)                                       # it needs no scratch
+    assert planner(ks.BF16, -1, *size)["path"] == 16 + 3
