@@ -248,7 +248,8 @@ typedef struct {
                                      at all (operand_copies); 1: direct-to-LDS 16-bit kernel; 2: the same in its
                                      two-groups-of-waves form; 3: by the fp32 member's form on the bf16 matrix pipe;
                                      16 + t: not by the member but in the K-slices form, tile t of its list (selecting
-                                     16-bit calls with few tiles and aligned operands; no scratch is used) */
+                                     16-bit calls with few tiles; no scratch is used; from 26 on operands that the
+                                     direct-to-LDS kernels do not take) */
     int32_t vector_loads;         /* 16-byte global accesses are legal for these operands */
     int32_t grid_3d;              /* launched (tilesN, tilesM, batch * split_k) instead of one-dimensional */
     int32_t tiles_per_workgroup;  /* > 1: the multi-tile form of the large fp32 members; 4 on a 64 x 64 one: 2 x 2 tiles as one */

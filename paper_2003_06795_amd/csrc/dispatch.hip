@@ -602,40 +602,44 @@ int run_ws(Workspace wsp, int dtype, int id, int transA, int transB, int64_t M, 
     // A call that names no member and would run one of the skinny or square ones with few tiles takes the K-slices form
     // where its estimate is the lower one (slices.hpp).  Named members, a caller's own tree and forced partitions are followed as they
     // are.  The form takes no scratch; what the member would do with the scratch at hand is what it is compared with.
-    // 1300 drawn problems (64 .. 4096 in each dimension, skinny and tall ones, four layouts): 495 take it, 0.755 of the time.
-    if (selected && dtype != KS_F32 && batch == 1 && g_splitForced == 0 && !custom_tree(dtype)) {
+    // Drawn problems (64 .. 4096 in each dimension, skinny and tall ones, four layouts): aligned 495 of 1300 take it, 0.755 of the
+    // time; with rows that nothing aligns 521 of 1597, 0.70.
+    if (selected && dtype != KS_F32 && batch == 1 && g_splitForced == 0 && g_forceGeneric == 0 && slices_possible(id, M, N, K) &&
+        !custom_tree(dtype)) {
         const bool akc = transA == 0, bkc = transB == 1;
-        if (dma_operands(akc, bkc, M, N, K, A, lda, B, ldb, 1, 0, 0)) {
-            const int64_t parts = d->splitK > 0 ? 1 : partitions(d, false, M, N, K, 1, wsp), kTiles = (K + d->bk - 1) / d->bk;
-            const int64_t groups = ((M + d->bm - 1) / d->bm) * ((N + d->bn - 1) / d->bn) * parts;
-            const int t = slices_tile(akc, bkc, M, N, K, slices_other_us(id, M, N, K, groups, (kTiles + parts - 1) / parts, parts,
-                                                                          4.0 * (double)parts * (double)M * (double)N));
-            if (t >= 0) {
-                const SliceTile &tile = kSliceTiles[t];
-                GemmParams p{};
-                p.A = A; p.B = B; p.C = C; p.bias = bias; p.out16 = out16;
-                p.lda = lda; p.ldb = ldb; p.ldc = ldc;
-                p.M = (int)M; p.N = (int)N; p.K = (int)K; p.batch = 1;
-                p.tilesM = (int)((M + tile.bm - 1) / tile.bm);
-                p.tilesN = (int)((N + tile.bn - 1) / tile.bn);
-                p.splitK = 1; p.kChunk = (int)K; p.tilesPerWG = 1; p.bandRows = 8;
-                p.bm = tile.bm; p.bn = tile.bn;
-                p.alpha = alpha; p.beta = beta;
-                const int grid = p.tilesM * p.tilesN;
-                p.grid3d = (double)(M + N) * (double)K * 2 <= (double)KS_GRID3D_BYTES ? 1 : 0;
-                set_tile_order(p);
-                if (planOnly) {
-                    planOnly->kernel_id = select_member(dtype, M, N, K, 1, transA, transB, true);   // whatever the scratch, which is not used
-                    planOnly->path = 16 + t;
-                    planOnly->vector_loads = 1;
-                    planOnly->grid_3d = p.grid3d;
-                    planOnly->workgroups = grid;
-                    return KS_OK;
-                }
-                const int pastCache = (slices_past_cache(M, K, p.tilesN) ? 1 : 0) + (slices_past_cache(N, K, p.tilesM) ? 2 : 0);
-                launch_bf16_slices(t, p, grid, (akc ? 2 : 0) + (bkc ? 1 : 0) + (dtype == KS_F16 ? 16 : 0), pastCache, stream);
-                return hipGetLastError() == hipSuccess ? KS_OK : KS_ERR_LAUNCH;
+        const bool staged = K % 64 != 0 || !dma_operands(akc, bkc, M, N, K, A, lda, B, ldb, 1, 0, 0);
+        const int64_t parts = d->splitK > 0 ? 1 : partitions(d, false, M, N, K, 1, wsp), kTiles = (K + d->bk - 1) / d->bk;
+        const int64_t groups = ((M + d->bm - 1) / d->bm) * ((N + d->bn - 1) / d->bn) * parts;
+        const double other = slices_other_us(staged, id, M, N, K, groups, (kTiles + parts - 1) / parts, parts,
+                                             4.0 * (double)parts * (double)M * (double)N);
+        const int t = slices_tile(staged, akc, bkc, M, N, K, lda, ldb, other);
+        if (t >= 0) {
+            const SliceTile &tile = kSliceTiles[t];
+            GemmParams p{};
+            p.A = A; p.B = B; p.C = C; p.bias = bias; p.out16 = out16;
+            p.lda = lda; p.ldb = ldb; p.ldc = ldc;
+            p.M = (int)M; p.N = (int)N; p.K = (int)K; p.batch = 1;
+            p.tilesM = (int)((M + tile.bm - 1) / tile.bm);
+            p.tilesN = (int)((N + tile.bn - 1) / tile.bn);
+            p.splitK = 1; p.kChunk = (int)K; p.tilesPerWG = 1; p.bandRows = 8;
+            p.bm = tile.bm; p.bn = tile.bn;
+            p.alpha = alpha; p.beta = beta;
+            const int grid = p.tilesM * p.tilesN;
+            p.grid3d = (double)(M + N) * (double)K * 2 <= (double)KS_GRID3D_BYTES ? 1 : 0;
+            set_tile_order(p);
+            if (planOnly) {
+                // the form uses no scratch: the member named is ks_select's from one partition's worth on, as for split_k == 1
+                if (wsp.ptr && wsp.bytes >= (size_t)M * (size_t)N * sizeof(float))
+                    planOnly->kernel_id = select_member(dtype, M, N, K, 1, transA, transB, true);
+                planOnly->path = 16 + t;
+                planOnly->vector_loads = vector_operands(8, akc, bkc, M, N, K, A, lda, B, ldb, 1, 0, 0) ? 1 : 0;
+                planOnly->grid_3d = p.grid3d;
+                planOnly->workgroups = grid;
+                return KS_OK;
             }
+            const int pastCache = (slices_past_cache(M, K, p.tilesN) ? 1 : 0) + (slices_past_cache(N, K, p.tilesM) ? 2 : 0);
+            launch_bf16_slices(t, p, grid, (akc ? 2 : 0) + (bkc ? 1 : 0) + (dtype == KS_F16 ? 16 : 0), pastCache, stream);
+            return hipGetLastError() == hipSuccess ? KS_OK : KS_ERR_LAUNCH;
         }
     }
 

@@ -15,6 +15,10 @@
 // `stream`): 8192 x 16 x 8192 26.5 -> 23.1 us, 16384 x 16 x 8192 48.9 -> 43.8 (6.1 TB/s); smaller ones that the cache does hold
 // lose by it (4096 x 16 x 8192 12.5 -> 17.0).
 // Preconditions are those of gemm_bf16_dma.hpp, K a multiple of 64, no K partitions over work-groups.
+//
+// gemm_bf16_slices_staged_kernel is the same for operands that nothing aligns: a wave holds PF K-steps in registers, as the members'
+// register-staged path loads them (Bf16Staging), and passes them through one stage of its own.  1000 x 777 x 1509 fp16 NN 17.4 -> 13.7 us;
+// 1597 drawn products (64 .. 4096, skinny and tall, rows padded by up to three) of which 521 take it 0.70 of the time.
 #pragma once
 #include "gemm_bf16_dma.hpp"
 #include "slices.hpp"
@@ -136,6 +140,98 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_slices_kernel(const GemmPar
         sum[0][0] = reinterpret_cast<const floatx4 *>(lds[0][0])[f * 64 + lane];
 #pragma unroll
         for (int w = 1; w < NW; ++w) sum[0][0] += reinterpret_cast<const floatx4 *>(lds[w][0])[f * 64 + lane];
+        write_tile_mfma16<false, 1, 1>(p, tc, p.C, row0 + (f / FN) * 16, col0 + (f % FN) * 16, lane, sum);
+    }
+}
+
+template <int BM, int BN, int BK, int NW, int PF, bool AKC, bool BKC, bool F16>
+__global__ __launch_bounds__(64 * NW) void gemm_bf16_slices_staged_kernel(const GemmParams p) {
+    constexpr int FM = BM / 16, FN = BN / 16, NF = FM * FN;
+    constexpr int A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2, STAGE = A_BYTES + B_BYTES;
+    constexpr int OWN = STAGE > NF * 1024 ? STAGE : NF * 1024;       // a K-step, later the wave's sums
+    static_assert(NW * OWN <= 160 * 1024, "LDS");
+    __shared__ __attribute__((aligned(1024))) char lds[NW][OWN];
+    using LoadA = Bf16Staging<BM, BK, 64, AKC, 16>;
+    using LoadB = Bf16Staging<BN, BK, 64, BKC, 16>;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const TileCoord tc = tile_of_block(p);
+    const int row0 = tc.tm * BM, col0 = tc.tn * BN;
+    const uint16_t *Ab = static_cast<const uint16_t *>(p.A), *Bb = static_cast<const uint16_t *>(p.B);
+    // K-steps whose chunks may all be read whole (see Bf16Staging; rows of less than seven elements do not come here)
+    const int fullA = AKC ? p.K / BK : (p.K - 1) / BK, fullB = BKC ? p.K / BK : (p.K - 1) / BK;
+    const int full = min(fullA, fullB), steps = (p.K + BK - 1) / BK;
+    const int n = wave < full ? (full - wave + NW - 1) / NW : 0;
+    const long long aStep = (AKC ? (long long)BK : BK * p.lda) * NW, bStep = (BKC ? (long long)BK : BK * p.ldb) * NW;
+    LoadA la;
+    LoadB lb;
+    la.init(Ab, p.lda, row0, p.M, wave * BK, lane);
+    lb.init(Bb, p.ldb, col0, p.N, wave * BK, lane);
+    uintx4 ra[PF][LoadA::PER], rb[PF][LoadB::PER];
+    floatx4 acc[FM][FN];
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    char *const as = lds[wave], *const bs = as + A_BYTES;
+    auto multiply = [&]() {
+#pragma unroll
+        for (int kk = 0; kk < BK; kk += 32) {
+            bf16x8 a[FM], b[FN];
+#pragma unroll
+            for (int i = 0; i < FM; ++i) a[i] = read_fragment<16, BM, BK, AKC>(as, i * 16, kk, lane);
+#pragma unroll
+            for (int j = 0; j < FN; ++j) b[j] = read_fragment<16, BN, BK, BKC>(bs, j * 16, kk, lane);
+#pragma unroll
+            for (int i = 0; i < FM; ++i)
+#pragma unroll
+                for (int j = 0; j < FN; ++j) acc[i][j] = mfma_16x16x32<F16>(a[i], b[j], acc[i][j]);
+        }
+    };
+#pragma unroll
+    for (int s = 0; s < PF; ++s)
+        if (s < n) { la.load(ra[s], s * aStep, lane); lb.load(rb[s], s * bStep, lane); }
+    for (int t0 = 0; t0 < n; t0 += PF) {
+#pragma unroll
+        for (int s = 0; s < PF; ++s) {
+            const int t = t0 + s;
+            if (t >= n) break;
+            LoadA::store(ra[s], as, lane);
+            LoadB::store(rb[s], bs, lane);
+            if (t + PF < n) { la.load(ra[s], (t + PF) * aStep, lane); lb.load(rb[s], (t + PF) * bStep, lane); }
+            multiply();
+        }
+    }
+    // the steps that hold the end of K, as a rule one, are dealt out after the whole ones
+    for (int t = full + (wave - full % NW + NW) % NW; t < steps; t += NW) {
+        const int k0 = t * BK;
+        if ((AKC ? p.K : p.M) >= 8 && (BKC ? p.K : p.N) >= 8) {
+            LoadA::load_edge_back(ra[0], Ab, p.lda, row0, p.M, k0, p.K, lane);
+            LoadB::load_edge_back(rb[0], Bb, p.ldb, col0, p.N, k0, p.K, lane);
+            LoadA::fit_edge(ra[0], row0, p.M, k0, p.K, lane);
+            LoadB::fit_edge(rb[0], col0, p.N, k0, p.K, lane);
+        } else {
+            LoadA::load_edge(ra[0], Ab, p.lda, row0, p.M, k0, p.K, lane);
+            LoadB::load_edge(rb[0], Bb, p.ldb, col0, p.N, k0, p.K, lane);
+        }
+        LoadA::store(ra[0], as, lane);
+        LoadB::store(rb[0], bs, lane);
+        multiply();
+    }
+    // the sums of the waves in wave order
+    floatx4 *const mine = reinterpret_cast<floatx4 *>(lds[wave]);
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) mine[(i * FN + j) * 64 + lane] = acc[i][j];
+    __syncthreads();
+#pragma unroll
+    for (int f0 = 0; f0 < NF; f0 += NW) {
+        const int f = f0 + wave;
+        if (f >= NF) break;
+        floatx4 sum[1][1];
+        sum[0][0] = reinterpret_cast<const floatx4 *>(lds[0])[f * 64 + lane];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) sum[0][0] += reinterpret_cast<const floatx4 *>(lds[w])[f * 64 + lane];
         write_tile_mfma16<false, 1, 1>(p, tc, p.C, row0 + (f / FN) * 16, col0 + (f % FN) * 16, lane, sum);
     }
 }

@@ -18,66 +18,89 @@ namespace ks {
     X(7, 32, 64, 64, 4, 3, 3.53)       \
     X(8, 64, 64, 32, 8, 2, 3.49)       \
     X(9, 64, 64, 64, 4, 2, 6.59)
+// and of the form for any operands: K-steps in registers in place of the stages
+#define KS_SLICES_STAGED_TILES(X)      \
+    X(10, 16, 16, 64, 16, 4, 2.80)     \
+    X(11, 32, 16, 64, 8, 3, 2.93)      \
+    X(12, 16, 32, 64, 8, 3, 2.90)      \
+    X(13, 32, 32, 64, 8, 3, 3.12)      \
+    X(14, 64, 16, 64, 8, 3, 3.52)      \
+    X(15, 16, 64, 64, 8, 3, 3.36)      \
+    X(16, 64, 32, 64, 8, 2, 3.84)      \
+    X(17, 32, 64, 64, 8, 2, 3.76)      \
+    X(18, 64, 64, 32, 8, 3, 4.49)
 struct SliceTile {
     int bm, bn, bk, waves, stages;
     double fixed;
 };
 constexpr SliceTile kSliceTiles[] = {
 #define KS_ROW(i, BM, BN, BK, NW, ST, FIXED) {BM, BN, BK, NW, ST, FIXED},
-    KS_SLICES_TILES(KS_ROW)
+    KS_SLICES_TILES(KS_ROW) KS_SLICES_STAGED_TILES(KS_ROW)
 #undef KS_ROW
 };
-constexpr int kSliceTileCount = sizeof(kSliceTiles) / sizeof(kSliceTiles[0]);
+constexpr int kSliceTileCount = sizeof(kSliceTiles) / sizeof(kSliceTiles[0]), kSliceTilesAligned = 10;
 
 // variant: 1 bkc, 2 akc, 16 binary16; stream: which operands are loaded past the last-level cache
 void launch_bf16_slices(int tile, const GemmParams &p, int grid, int variant, int stream, hipStream_t s);
 
+// Members that the form may stand in for, and sizes that may be one round of its largest tiles.
+inline int slices_member(int id) { return id == 13 ? 0 : id == 27 ? 1 : id == 38 ? 2 : id == 39 ? 3 : -1; }
+inline bool slices_possible(int id, int64_t M, int64_t N, int64_t K) {
+    return slices_member(id) >= 0 && K >= 256 && M <= (1 << 14) && N <= (1 << 14) && ((M + 63) / 64) * ((N + 63) / 64) <= 256;
+}
+
 // us per 1024 of K that a compute unit's memory pipe takes for one operand of a tile of `extent` rows (of columns): a K-contiguous
-// one by its bytes, of a row-contiguous one with less than 64 every k takes as long as a whole line
-inline double slice_operand_us(int extent, bool kc, int bk) {
-    if (bk == 32) return kc ? 2.09 : 2.03;            // (K-contiguous pieces of 64 bytes)
+// one by its bytes, of a row-contiguous one with less than 64 every k takes as long as a whole line; K-steps of 32 have
+// K-contiguous pieces of 64 bytes.  staged: the form for any operands.
+inline double slice_operand_us(bool staged, int extent, bool kc, int bk) {
+    if (staged) {
+        if (bk == 32) return kc ? 3.12 : 2.77;
+        return extent == 16 ? (kc ? 0.58 : 1.35) : extent == 32 ? (kc ? 1.15 : 1.64) : (kc ? 2.29 : 2.40);
+    }
+    if (bk == 32) return kc ? 2.09 : 2.03;
     return extent == 16 ? (kc ? 0.34 : 1.12) : extent == 32 ? (kc ? 0.66 : 1.33) : (kc ? 1.23 : 1.61);
 }
 // Estimate for one round of work-groups of tile `t`, us: the longest of a unit's memory pipe, memory (a row-contiguous operand in
 // pieces of less than a line is fetched as often as a line has pieces), what a work-group has in flight of an operand that comes
 // from memory behind its 2 us (one of 64 MiB and more: 2944 x 2 x 14976 NT 18.4 us by the member, 22.7 in 184 tiles of 16 x 16), and the
-// L2s.
-inline double slices_us(const SliceTile &t, bool akc, bool bkc, int64_t M, int64_t N, int64_t K) {
+// L2s.  The constants are fitted to the times of all tiles over 1300 (any operands: 1597) drawn products, 14 % (17 %) rms.
+inline double slices_us(bool staged, const SliceTile &t, bool akc, bool bkc, int64_t M, int64_t N, int64_t K) {
     const double k = (double)K, tiles = (double)((M + t.bm - 1) / t.bm) * (double)((N + t.bn - 1) / t.bn);
-    const double pipe = k / 1024 * (slice_operand_us(t.bm, akc, t.bk) + slice_operand_us(t.bn, bkc, t.bk));
-    const double memory = k * 2e-6 * ((double)M * (akc ? 1 : 64 / t.bm) + (double)N * (bkc ? 1 : 64 / t.bn)) / 5.99;
-    const double l2 = tiles * (t.bm + t.bn) * k * 2e-6 / 17.02;
+    const double pipe = k / 1024 * (slice_operand_us(staged, t.bm, akc, t.bk) + slice_operand_us(staged, t.bn, bkc, t.bk));
+    const double memory = k * 2e-6 * ((double)M * (akc ? 1 : 64 / t.bm) + (double)N * (bkc ? 1 : 64 / t.bn)) / (staged ? 6.14 : 5.99);
+    const double l2 = tiles * (t.bm + t.bn) * k * 2e-6 / (staged ? 10.66 : 17.02);
     const double latency = M * K >= (32LL << 20) || N * K >= (32LL << 20) ? 2.0 * k / (t.waves * (t.stages - 1) * t.bk) : 0;
     double longest = pipe > memory ? pipe : memory;
     longest = longest > l2 ? longest : l2;
     return t.fixed + (longest > latency ? longest : latency);
 }
-// The same for the member (id) that the call would run otherwise, `steps` K-steps in each of `groups` work-groups, 0 where the
-// form does not stand in for it; partitions > 1: their sums are `partialBytes` and a second launch adds them.
-inline double slices_other_us(int id, int64_t M, int64_t N, int64_t K, int64_t groups, int64_t steps, int64_t partitions,
+// The same for the member (id) that the call would run otherwise, `steps` K-steps in each of `groups` work-groups;
+// partitions > 1: their sums are `partialBytes` and a second launch adds them.
+inline double slices_other_us(bool staged, int id, int64_t M, int64_t N, int64_t K, int64_t groups, int64_t steps, int64_t partitions,
                               double partialBytes) {
-    const double *c = nullptr;
-    static constexpr double k13[] = {2.17, 0.51, 0.3}, k27[] = {3.19, 0.84, 0.39}, k38[] = {3.47, 0.52, 0.32}, k39[] = {3.67, 0.67, 0.67};
-    if (id == 13) c = k13;
-    else if (id == 27) c = k27;
-    else if (id == 38) c = k38;
-    else if (id == 39) c = k39;
-    if (!c) return 0;
+    static constexpr double fit[2][4][3] = {{{2.17, 0.51, 0.3}, {3.19, 0.84, 0.39}, {3.47, 0.52, 0.32}, {3.67, 0.67, 0.67}},
+                                            {{2.95, 0.67, 0.47}, {7.49, 0.02, 0.74}, {6.14, 0.57, 0.42}, {7.68, 0.83, 0.29}}};
+    const double *c = fit[staged][slices_member(id)];
     const double rounds = (double)((groups + 255) / 256);
     const double chain = (double)steps * (c[1] > c[2] * rounds ? c[1] : c[2] * rounds);
-    const double memory = (double)(M + N) * (double)K * 2e-6 / 5.91;
-    return c[0] + (chain > memory ? chain : memory) + (partitions > 1 ? 1.64 + 0.59e-6 * partialBytes : 0);
+    const double memory = (double)(M + N) * (double)K * 2e-6 / (staged ? 4.9 : 5.91);
+    const double sums = partitions > 1 ? (staged ? -0.11 + 0.18e-6 * partialBytes : 1.64 + 0.59e-6 * partialBytes) : 0;
+    return c[0] + (chain > memory ? chain : memory) + sums;
 }
 // Tile for this call, or -1: the members as they are.  One round of work-groups (a second one costs more than the estimate knows:
-// up to 2.0 of the time), K from 512 on (below, level) and an estimate 8 % below the other one.
-inline int slices_tile(bool akc, bool bkc, int64_t M, int64_t N, int64_t K, double other) {
-    if (K < 512 || K % 64 != 0 || M > (1 << 24) || N > (1 << 24)) return -1;
+// up to 2.0 of the time), K from 512 (any operands: 256) on, below which it is level, and an estimate 8 % below the other one.  Any
+// operands: rows of seven elements at least; none of 64 MiB and more (up to 1.39), nor 1e10 flop, where copies pay.
+inline int slices_tile(bool staged, bool akc, bool bkc, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, double other) {
+    if (K < (staged ? 256 : 512)) return -1;
+    if (staged && ((!akc && lda < 7) || (!bkc && ldb < 7) || M * K >= (32LL << 20) || N * K >= (32LL << 20) ||
+                   2.0 * (double)M * (double)N * (double)K >= 1e10))
+        return -1;
     int best = -1;
     double us = 0.92 * other;
-    for (int i = 0; i < kSliceTileCount; ++i) {
+    for (int i = staged ? kSliceTilesAligned : 0; i < (staged ? kSliceTileCount : kSliceTilesAligned); ++i) {
         const SliceTile &t = kSliceTiles[i];
         if (((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) > 256) continue;
-        const double x = slices_us(t, akc, bkc, M, N, K);
+        const double x = slices_us(staged, t, akc, bkc, M, N, K);
         if (x < us) { us = x; best = i; }
     }
     return best;

@@ -1,5 +1,5 @@
-"""The K-slices form of the 16-bit products against fp64: every tile of it that a layout's sizes lead to, edges of tiles in both
-directions, K-steps that do not deal out evenly over the waves (and fewer of them than waves), old values, bias, a bf16 output and
+"""The K-slices form of the 16-bit products against fp64: every tile of it in every layout, on aligned operands and on others (odd
+sizes, padded rows, addresses inside sixteen bytes), edges of tiles in both directions, K-steps that do not deal out evenly over the waves (and fewer of them than waves), old values, bias, a bf16 output and
 operands that are loaded past the last-level cache."""
 import pytest
 
@@ -13,23 +13,34 @@ SIZES = [(128, 128, 1024), (120, 72, 2048), (8, 8, 576), (1, 24, 1088), (200, 10
          (1896, 144, 768), (3368, 152, 3008), (1144, 456, 1984), (2208, 264, 3840), (3032, 176, 2496)]
 
 
-def operands(torch, g, tA, tB, M, N, K, kind):
-    A = torch.randn((K, M) if tA else (M, K), generator=g, device="cuda").mul_(K ** -0.5).to(kind)
-    B = torch.randn((N, K) if tB else (K, N), generator=g, device="cuda").mul_(K ** -0.5).to(kind)
-    return A, B
+# the same for operands that nothing aligns: ends of K in every place of a chunk, a K-step of which one k is left, short edges
+ODD_SIZES = [(127, 129, 1025), (121, 71, 2047), (9, 7, 575), (1, 23, 1089), (199, 1001, 1537), (1001, 199, 1151), (521, 503, 2113),
+             (1000, 777, 1509), (777, 1000, 509), (4095, 9, 1023), (15, 4001, 2044), (6001, 31, 1022), (31, 5003, 2050), (3201, 23, 257),
+             (12001, 15, 1027), (23, 9001, 2041), (7, 16383, 1021), (41, 2041, 4091), (7001, 39, 2042), (1871, 149, 769), (3001, 170, 1301),
+             (64, 64, 2052), (250, 250, 300), (65, 33, 8193), (2500, 64, 700), (48, 3000, 500), (1300, 130, 330), (130, 1300, 330),
+             (4517, 10, 300), (4111, 12, 317), (8205, 19, 322), (8331, 18, 444), (9, 4147, 307), (13, 4256, 335)]
+
+
+def operands(torch, g, tA, tB, M, N, K, kind, pad=0, offset=0):
+    """rows of a wider buffer, `offset` elements from its beginning"""
+    def one(rows, cols, scale):
+        flat = torch.randn(offset + rows * (cols + pad) + 8, generator=g, device="cuda").mul_(scale).to(kind)
+        return flat[offset:offset + rows * (cols + pad)].view(rows, cols + pad)
+    return one(*((K, M) if tA else (M, K)), K ** -0.5), one(*((N, K) if tB else (K, N)), K ** -0.5)
 
 
 @pytest.mark.parametrize("tA,tB", [(0, 0), (0, 1), (1, 0), (1, 1)])
-def test_against_fp64(tA, tB):
+@pytest.mark.parametrize("aligned", [True, False])
+def test_against_fp64(tA, tB, aligned):
     import torch
     import paper_2003_06795_amd as ks
     g = torch.Generator(device="cuda").manual_seed(7 + 2 * tA + tB)
     tiles = set()
-    for i, (M, N, K) in enumerate(SIZES):
-        if (tA and M % 8) or (not tB and N % 8):
+    for i, (M, N, K) in enumerate(SIZES if aligned else ODD_SIZES):
+        if aligned and ((tA and M % 8) or (not tB and N % 8)):
             continue
         dtype, kind = ((ks.BF16, torch.bfloat16), (ks.F16, torch.float16))[i % 2]
-        A, B = operands(torch, g, tA, tB, M, N, K, kind)
+        A, B = operands(torch, g, tA, tB, M, N, K, kind, *((0, 0) if aligned else (i % 4, i % 3)))
         ldc = N + (0, 1, 4)[i % 3]
         out16, beta, with_bias = i % 4 == 3, (0.0, 0.5)[i % 2], i % 3 == 1
         C0 = torch.rand((M, ldc), generator=g, device="cuda").mul_(2).sub_(1)
@@ -48,7 +59,8 @@ def test_against_fp64(tA, tB):
         else:
             (ks.gemm_bf16 if dtype == ks.BF16 else ks.gemm_f16)(*args)
         torch.cuda.synchronize()
-        a, b = (A.t() if tA else A).double().contiguous(), (B.t() if tB else B).double().contiguous()
+        a = (A[:, :M].t() if tA else A[:, :K]).double().contiguous()
+        b = (B[:, :K].t() if tB else B[:, :N]).double().contiguous()
         want = 1.5 * (a @ b) + beta * old[:, :N] + (bias.double() if with_bias else 0)
         # fp32 sums of K exact products, at most K + 16 roundings of 2^-24 of the sum of magnitudes, and three of the epilogue
         bound = (1.5 * (a.abs() @ b.abs())) * (K + 16) * 2.0 ** -24 + 3 * 2.0 ** -24 * (want.abs() + 2) + 1e-12
@@ -56,7 +68,7 @@ def test_against_fp64(tA, tB):
             bound = bound + 2.0 ** -8 * (want.abs() + bound)
         assert bool(((C[:, :N].double() - want).abs() <= bound).all()), (M, N, K, plan["path"])
         assert torch.equal(C[:, N:].double(), old[:, N:])
-    assert tiles == set(range(10)), tiles
+    assert tiles == (set(range(10)) if aligned else set(range(10, 19))), tiles
 
 
 def test_operand_past_the_last_level_cache():

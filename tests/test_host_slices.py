@@ -1,6 +1,7 @@
-"""Where a selecting call takes the K-slices form of the 16-bit products (ks_launch_plan_t::path 16 + tile): one round of work-groups
-on aligned operands with whole K-steps of 64, and never for a named member, forced partitions, a caller's own tree, batches, fp32
-or operands the direct-to-LDS path does not take.  No GPU: ks_gemm_plan reads sizes and addresses only."""
+"""Where a selecting call takes the K-slices form of the 16-bit products (ks_launch_plan_t::path 16 + tile): one round of work-groups,
+by direct-to-LDS loads (tiles 0 to 9) on aligned operands with whole K-steps of 64, through registers (10 to 18) on others, and
+never for a named member, forced partitions, a caller's own tree, batches or fp32.  No GPU: ks_gemm_plan reads sizes and addresses
+only."""
 import ctypes
 
 import pytest
@@ -8,6 +9,7 @@ import pytest
 import paper_2003_06795_amd.binding as ks
 
 TILES = [(16, 16), (32, 16), (16, 32), (32, 32), (64, 16), (16, 64), (64, 32), (32, 64), (64, 64), (64, 64)]
+TILES += [(16, 16), (32, 16), (16, 32), (32, 32), (64, 16), (16, 64), (64, 32), (32, 64), (64, 64)]
 PTR = 1 << 20
 
 
@@ -23,24 +25,26 @@ def planner():
     L.ks_set_workspace(None, 0)
 
 
-def test_the_form_is_one_round_of_its_tiles(planner):
+@pytest.mark.parametrize("odd", [0, 1])
+def test_the_form_is_one_round_of_its_tiles(planner, odd):
     seen = set()
     for tA in (0, 1):
         for tB in (0, 1):
             for M in (8, 64, 256, 1024, 3368, 4096, 8192, 16384):
                 for N in (8, 40, 64, 152, 512, 1024, 12000):
-                    for K in (448, 512, 1024, 2048, 3008, 4096, 8192):
+                    for K in (192, 256, 448, 512, 1024, 2048, 3008, 4096, 8192):
                         for dtype in (ks.BF16, ks.F16):
-                            got = planner(dtype, -1, tA, tB, M, N, K)
+                            got = planner(dtype, -1, tA, tB, M - odd, N - odd, K - odd)
                             if got["path"] < 16:
                                 continue
                             bm, bn = TILES[got["path"] - 16]
-                            tiles = -(-M // bm) * -(-N // bn)
-                            assert K >= 512 and tiles <= 256 and got["workgroups"] == tiles and got["split_k"] == 1, got
-                            assert got["kernel_id"] == ks.select(dtype, M, N, K, 1, tA, tB)
+                            tiles = -(-(M - odd) // bm) * -(-(N - odd) // bn)
+                            assert K >= (256 if odd else 512) and (got["path"] >= 26) == bool(odd)
+                            assert tiles <= 256 and got["workgroups"] == tiles and got["split_k"] == 1, got
+                            assert got["kernel_id"] == ks.select(dtype, M - odd, N - odd, K - odd, 1, tA, tB)
                             assert not (got["tail_split"] or got["k_remainder"] or got["operand_copies"] or got["balanced_groups"])
                             seen.add(got["path"] - 16)
-    assert seen == set(range(len(TILES)))
+    assert seen == (set(range(10, 19)) if odd else set(range(10)))
 
 
 def test_calls_that_do_not_take_it(planner):
@@ -49,11 +53,15 @@ def test_calls_that_do_not_take_it(planner):
     assert planner(ks.BF16, ks.select(ks.BF16, 512, 512, 2048, 1, 0, 1), *size)["path"] < 16
     assert planner(ks.F32, -1, *size)["path"] < 16
     assert planner(ks.BF16, -1, *size, batch=2)["path"] < 16
-    assert planner(ks.BF16, -1, *size, a=PTR + 2)["path"] < 16
-    assert planner(ks.BF16, -1, *size, lda=2052)["path"] < 16
-    assert planner(ks.BF16, -1, 0, 1, 512, 512, 2080)["path"] < 16
-    assert planner(ks.BF16, -1, 0, 0, 512, 516, 2048)["path"] < 16          # rows of B end inside sixteen bytes
+    assert planner(ks.BF16, -1, *size, a=PTR + 2)["path"] >= 26
+    assert planner(ks.BF16, -1, *size, lda=2052)["path"] >= 26
+    assert planner(ks.BF16, -1, 0, 1, 512, 512, 2080)["path"] >= 26
+    assert planner(ks.BF16, -1, 0, 0, 512, 516, 2048)["path"] >= 26         # rows of B end inside sixteen bytes
     assert planner(ks.BF16, -1, 0, 1, 512, 507, 2048)["path"] == 16 + 3     # columns of C may end anywhere
+    assert planner(ks.BF16, -1, 0, 0, 3000, 6, 2001)["path"] < 16           # rows of six elements: B from further back does not work
+    assert planner(ks.BF16, -1, 0, 0, 3000, 6, 2001, ldb=7)["path"] >= 26
+    assert planner(ks.BF16, -1, 1, 0, 1024, 1024, 5001)["path"] < 16        # copies of the operands pay
+    assert planner(ks.BF16, -1, 0, 0, 8001, 9, 4195)["path"] < 16           # 2^25 entries of A
     ks.set_split_partitions(2)
     try:
         assert planner(ks.BF16, -1, *size)["path"] < 16
