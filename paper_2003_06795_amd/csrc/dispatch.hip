@@ -604,11 +604,12 @@ int run_ws(Workspace wsp, int dtype, int id, int transA, int transB, int64_t M, 
     // are.  The form takes no scratch; what the member would do with the scratch at hand is what it is compared with.
     // Drawn problems (64 .. 4096 in each dimension, skinny and tall ones, four layouts): aligned 495 of 1300 take it, 0.755 of the
     // time; with rows that nothing aligns 521 of 1597, 0.70.
+    int64_t estimated = 0;                            // K partitions of this member and call, once known
     if (selected && dtype != KS_F32 && batch == 1 && g_splitForced == 0 && g_forceGeneric == 0 && slices_possible(id, M, N, K) &&
         !custom_tree(dtype)) {
         const bool akc = transA == 0, bkc = transB == 1;
         const bool staged = K % 64 != 0 || !dma_operands(akc, bkc, M, N, K, A, lda, B, ldb, 1, 0, 0);
-        const int64_t parts = d->splitK > 0 ? 1 : partitions(d, false, M, N, K, 1, wsp), kTiles = (K + d->bk - 1) / d->bk;
+        const int64_t parts = d->splitK > 0 ? 1 : (estimated = partitions(d, false, M, N, K, 1, wsp)), kTiles = (K + d->bk - 1) / d->bk;
         const int64_t groups = ((M + d->bm - 1) / d->bm) * ((N + d->bn - 1) / d->bn) * parts;
         const double other = slices_other_us(staged, id, M, N, K, groups, (kTiles + parts - 1) / parts, parts,
                                              4.0 * (double)parts * (double)M * (double)N);
@@ -746,7 +747,7 @@ int run_ws(Workspace wsp, int dtype, int id, int transA, int transB, int64_t M, 
     p.tilesN = (int)((N + d->bn - 1) / d->bn);
     const int64_t kTiles = (K + d->bk - 1) / d->bk;
     p.splitK = d->splitK;
-    if (d->splitK == 0) p.splitK = (int)partitions(d, dtype == KS_F32, M, N, K, batch, wsp);
+    if (d->splitK == 0) p.splitK = (int)(estimated > 0 ? estimated : partitions(d, dtype == KS_F32, M, N, K, batch, wsp));
     p.kChunk = (int)(((kTiles + p.splitK - 1) / p.splitK) * d->bk);
     p.alpha = alpha; p.beta = beta;
 

@@ -38,7 +38,7 @@ constexpr SliceTile kSliceTiles[] = {
     KS_SLICES_TILES(KS_ROW) KS_SLICES_STAGED_TILES(KS_ROW)
 #undef KS_ROW
 };
-constexpr int kSliceTileCount = sizeof(kSliceTiles) / sizeof(kSliceTiles[0]), kSliceTilesAligned = 10;
+constexpr int kSliceTilesAligned = 10;
 
 // variant: 1 bkc, 2 akc, 16 binary16; stream: which operands are loaded past the last-level cache
 void launch_bf16_slices(int tile, const GemmParams &p, int grid, int variant, int stream, hipStream_t s);
@@ -52,7 +52,7 @@ inline bool slices_possible(int id, int64_t M, int64_t N, int64_t K) {
 // us per 1024 of K that a compute unit's memory pipe takes for one operand of a tile of `extent` rows (of columns): a K-contiguous
 // one by its bytes, of a row-contiguous one with less than 64 every k takes as long as a whole line; K-steps of 32 have
 // K-contiguous pieces of 64 bytes.  staged: the form for any operands.
-inline double slice_operand_us(bool staged, int extent, bool kc, int bk) {
+constexpr double slice_operand_us(bool staged, int extent, bool kc, int bk) {
     if (staged) {
         if (bk == 32) return kc ? 3.12 : 2.77;
         return extent == 16 ? (kc ? 0.58 : 1.35) : extent == 32 ? (kc ? 1.15 : 1.64) : (kc ? 2.29 : 2.40);
@@ -64,15 +64,32 @@ inline double slice_operand_us(bool staged, int extent, bool kc, int bk) {
 // pieces of less than a line is fetched as often as a line has pieces), what a work-group has in flight of an operand that comes
 // from memory behind its 2 us (one of 64 MiB and more: 2944 x 2 x 14976 NT 18.4 us by the member, 22.7 in 184 tiles of 16 x 16), and the
 // L2s.  The constants are fitted to the times of all tiles over 1300 (any operands: 1597) drawn products, 14 % (17 %) rms.
-inline double slices_us(bool staged, const SliceTile &t, bool akc, bool bkc, int64_t M, int64_t N, int64_t K) {
-    const double k = (double)K, tiles = (double)((M + t.bm - 1) / t.bm) * (double)((N + t.bn - 1) / t.bn);
-    const double pipe = k / 1024 * (slice_operand_us(staged, t.bm, akc, t.bk) + slice_operand_us(staged, t.bn, bkc, t.bk));
-    const double memory = k * 2e-6 * ((double)M * (akc ? 1 : 64 / t.bm) + (double)N * (bkc ? 1 : 64 / t.bn)) / (staged ? 6.14 : 5.99);
-    const double l2 = tiles * (t.bm + t.bn) * k * 2e-6 / (staged ? 10.66 : 17.02);
-    const double latency = M * K >= (32LL << 20) || N * K >= (32LL << 20) ? 2.0 * k / (t.waves * (t.stages - 1) * t.bk) : 0;
-    double longest = pipe > memory ? pipe : memory;
-    longest = longest > l2 ? longest : l2;
-    return t.fixed + (longest > latency ? longest : latency);
+// (The tile is a template argument: a small call waits for the host, and with the constants folded ten estimates take it
+// 30 ns where a loop over the table took 250.)
+struct SliceCall {
+    bool akc, bkc;
+    int64_t M, N;
+    double k, latency;               // latency: K / 1024 steps' worth of 2 us, 0 where no operand comes from memory
+};
+template <int T>
+inline bool slices_us(const SliceCall &c, double &us) {
+    constexpr SliceTile t = kSliceTiles[T];
+    constexpr bool staged = T >= kSliceTilesAligned;
+    const int64_t tiles = ((c.M + t.bm - 1) / t.bm) * ((c.N + t.bn - 1) / t.bn);
+    if (tiles > 256) return false;
+    constexpr double aKc = slice_operand_us(staged, t.bm, true, t.bk), aRc = slice_operand_us(staged, t.bm, false, t.bk),
+                     bKc = slice_operand_us(staged, t.bn, true, t.bk), bRc = slice_operand_us(staged, t.bn, false, t.bk);
+    double longest = c.k * (1.0 / 1024) * ((c.akc ? aKc : aRc) + (c.bkc ? bKc : bRc));
+    const double memory = c.k * (2e-6 / (staged ? 6.14 : 5.99)) * ((double)c.M * (c.akc ? 1 : 64 / t.bm) + (double)c.N * (c.bkc ? 1 : 64 / t.bn));
+    if (memory > longest) longest = memory;
+    const double l2 = (double)tiles * c.k * ((t.bm + t.bn) * 2e-6 / (staged ? 10.66 : 17.02));
+    if (l2 > longest) longest = l2;
+    const double latency = c.latency * (1.0 / (t.waves * (t.stages - 1) * t.bk));
+    if (latency > longest) longest = latency;
+    const double x = t.fixed + longest;
+    if (x >= us) return false;
+    us = x;
+    return true;
 }
 // The same for the member (id) that the call would run otherwise, `steps` K-steps in each of `groups` work-groups;
 // partitions > 1: their sums are `partialBytes` and a second launch adds them.
@@ -95,14 +112,17 @@ inline int slices_tile(bool staged, bool akc, bool bkc, int64_t M, int64_t N, in
     if (staged && ((!akc && lda < 7) || (!bkc && ldb < 7) || M * K >= (32LL << 20) || N * K >= (32LL << 20) ||
                    2.0 * (double)M * (double)N * (double)K >= 1e10))
         return -1;
+    const bool far = M * K >= (32LL << 20) || N * K >= (32LL << 20);
+    const SliceCall c{akc, bkc, M, N, (double)K, far ? 2.0 * (double)K : 0};
     int best = -1;
     double us = 0.92 * other;
-    for (int i = staged ? kSliceTilesAligned : 0; i < (staged ? kSliceTileCount : kSliceTilesAligned); ++i) {
-        const SliceTile &t = kSliceTiles[i];
-        if (((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) > 256) continue;
-        const double x = slices_us(staged, t, akc, bkc, M, N, K);
-        if (x < us) { us = x; best = i; }
+#define KS_TRY(i, BM, BN, BK, NW, ST, FIXED) if (slices_us<i>(c, us)) best = i;
+    if (staged) {
+        KS_SLICES_STAGED_TILES(KS_TRY)
+    } else {
+        KS_SLICES_TILES(KS_TRY)
     }
+#undef KS_TRY
     return best;
 }
 // An operand of 96 MiB and more that one row (column) of tiles reads does not outlast in the last-level cache of 256 MiB what comes
