@@ -98,7 +98,8 @@ __device__ __forceinline__ void wait_vmcnt() {
 
 template <int F, int BM, int BN, int BK, int WM, int WN, int STAGES, bool SPLIT, bool AKC, bool BKC,
           bool F16 = false, bool CUT = false>
-__global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) void gemm_bf16_dma_kernel(const GemmParams p) {
+__global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) void gemm_bf16_dma_kernel(KS_PARAMS) {
+    KS_PARAMS_TOGETHER;
     constexpr int NW = (BM / WM) * (BN / WN);
     constexpr int FM = WM / F, FN = WN / F;
     constexpr int KSTEP = F == 32 ? 16 : 32;
@@ -123,9 +124,9 @@ __global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) void gemm_bf16_dma_kern
     const int whole = (kEnd - kBegin) / BK;                   // K-steps, and half a one where K ends in one
     const bool half = CUT && kEnd > kBegin && (kEnd - kBegin) % BK != 0;
     const int nk = whole + (half ? 1 : 0);
-    const uint16_t *Ab = static_cast<const uint16_t *>(p.A) + (long long)tc.batch * p.strideA;
-    const uint16_t *Bb = static_cast<const uint16_t *>(p.B) + (long long)tc.batch * p.strideB;
-    float *Cb = p.C + (long long)tc.batch * p.strideC;
+    const uint16_t *Ab = batch_origin(static_cast<const uint16_t *>(p.A), tc.batch, p.strideA);
+    const uint16_t *Bb = batch_origin(static_cast<const uint16_t *>(p.B), tc.batch, p.strideB);
+    float *Cb = batch_origin(p.C, tc.batch, p.strideC);
     // tile origins at k = kBegin and their advance per K-step, in bytes
     const char *aTile = reinterpret_cast<const char *>(AKC ? Ab + (long long)row0 * p.lda + kBegin
                                                             : Ab + (long long)kBegin * p.lda + row0);

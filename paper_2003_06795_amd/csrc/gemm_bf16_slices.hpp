@@ -46,7 +46,8 @@ __device__ __forceinline__ void wait_for_stage() {
 }
 
 template <int BM, int BN, int BK, int NW, int STAGES, bool AKC, bool BKC, bool F16>
-__global__ __launch_bounds__(64 * NW) void gemm_bf16_slices_kernel(const GemmParams p, const int stream) {
+__global__ __launch_bounds__(64 * NW) void gemm_bf16_slices_kernel(KS_PARAMS, const int stream) {
+    KS_PARAMS_TOGETHER;
     constexpr int FM = BM / 16, FN = BN / 16, NF = FM * FN;
     constexpr int A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2, STAGE = A_BYTES + B_BYTES;
     static_assert(NW * STAGES * STAGE <= 160 * 1024 && STAGES >= 2 && STAGES <= 4, "LDS");

@@ -61,16 +61,17 @@ __device__ __forceinline__ floatx4 direct_fetch_full(const float *lanePtr, long 
 }
 
 template <int BM, int BN, int BK, int WM, int WN, bool SPLIT, bool AKC, bool BKC, bool UNITS>
-__global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) void gemm_f32_direct_kernel(const GemmParams p) {
+__global__ __launch_bounds__(64 * (BM / WM) * (BN / WN)) void gemm_f32_direct_kernel(KS_PARAMS) {
+    KS_PARAMS_TOGETHER;
     constexpr int FM = WM / 16, FN = WN / 16, NG = BK / 16;       // fragments per wave; k-groups per step
     static_assert(BK % 16 == 0 && WM % 16 == 0 && WN % 16 == 0, "direct core shape");
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const TileCoord tc = tile_of_block(p);
     const int row0 = tc.tm * BM + (wave / (BN / WN)) * WM;
     const int col0 = tc.tn * BN + (wave % (BN / WN)) * WN;
-    const float *Ab = static_cast<const float *>(p.A) + (long long)tc.batch * p.strideA;
-    const float *Bb = static_cast<const float *>(p.B) + (long long)tc.batch * p.strideB;
-    float *Cb = p.C + (long long)tc.batch * p.strideC;
+    const float *Ab = batch_origin(static_cast<const float *>(p.A), tc.batch, p.strideA);
+    const float *Bb = batch_origin(static_cast<const float *>(p.B), tc.batch, p.strideB);
+    float *Cb = batch_origin(p.C, tc.batch, p.strideC);
     const int kBegin = tc.split * p.kChunk;
     const int kEnd = min(p.K, kBegin + p.kChunk);
     const int nk = (kEnd - kBegin + BK - 1) / BK;

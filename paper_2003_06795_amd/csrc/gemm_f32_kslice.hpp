@@ -17,7 +17,8 @@
 namespace ks {
 
 template <int BM, int BN, int BK, int KW, int W, bool SPLIT, bool AKC, bool BKC, bool UNITS>
-__global__ __launch_bounds__(64 * KW * (BM / W) * (BN / W)) void gemm_f32_kslice_kernel(const GemmParams p) {
+__global__ __launch_bounds__(64 * KW * (BM / W) * (BN / W)) void gemm_f32_kslice_kernel(KS_PARAMS) {
+    KS_PARAMS_TOGETHER;
     constexpr int FM = W / 16, FN = W / 16, NG = BK / 16;
     constexpr int TW = (BM / W) * (BN / W);                   // wave tiles per work-group tile
     constexpr int NF = TW * FM * FN;                          // 16x16 fragments per work-group tile
@@ -27,9 +28,9 @@ __global__ __launch_bounds__(64 * KW * (BM / W) * (BN / W)) void gemm_f32_kslice
     const int tid = threadIdx.x, lane = tid & 63, wave = (tid >> 6) / TW, tw = (tid >> 6) % TW;
     const TileCoord tc = tile_of_block(p);
     const int row0 = tc.tm * BM + (tw / (BN / W)) * W, col0 = tc.tn * BN + (tw % (BN / W)) * W;
-    const float *Ab = static_cast<const float *>(p.A) + (long long)tc.batch * p.strideA;
-    const float *Bb = static_cast<const float *>(p.B) + (long long)tc.batch * p.strideB;
-    float *Cb = p.C + (long long)tc.batch * p.strideC;
+    const float *Ab = batch_origin(static_cast<const float *>(p.A), tc.batch, p.strideA);
+    const float *Bb = batch_origin(static_cast<const float *>(p.B), tc.batch, p.strideB);
+    float *Cb = batch_origin(p.C, tc.batch, p.strideC);
     const int kLo = tc.split * p.kChunk;
     const int kHi = min(p.K, kLo + p.kChunk);
     const int slice = (((kHi - kLo + KW - 1) / KW) + 15) & ~15;

@@ -35,11 +35,11 @@ static void launch_bf16_dma_fixed(const GemmParams &p, int grid, int variant, hi
         } else {                                                                                                    \
             constexpr bool MAY_CUT = BK == 128;                                                                     \
             if (MAY_CUT && p.K % BK != 0) {                                                                         \
-                if (variant & 16) hipLaunchKernelGGL((gemm_bf16_dma_kernel<F, BM, BN, BK, WM, WN, STAGES, SPLIT, A, B, true, MAY_CUT>), g, b, 0, s, p); \
-                else hipLaunchKernelGGL((gemm_bf16_dma_kernel<F, BM, BN, BK, WM, WN, STAGES, SPLIT, A, B, false, MAY_CUT>), g, b, 0, s, p); \
+                if (variant & 16) hipLaunchKernelGGL((gemm_bf16_dma_kernel<F, BM, BN, BK, WM, WN, STAGES, SPLIT, A, B, true, MAY_CUT>), g, b, 0, s, KS_ARGUMENTS(p)); \
+                else hipLaunchKernelGGL((gemm_bf16_dma_kernel<F, BM, BN, BK, WM, WN, STAGES, SPLIT, A, B, false, MAY_CUT>), g, b, 0, s, KS_ARGUMENTS(p)); \
             } else if (variant & 16)                                                                                \
-                hipLaunchKernelGGL((gemm_bf16_dma_kernel<F, BM, BN, BK, WM, WN, STAGES, SPLIT, A, B, true>), g, b, 0, s, p);  \
-            else hipLaunchKernelGGL((gemm_bf16_dma_kernel<F, BM, BN, BK, WM, WN, STAGES, SPLIT, A, B, false>), g, b, 0, s, p); \
+                hipLaunchKernelGGL((gemm_bf16_dma_kernel<F, BM, BN, BK, WM, WN, STAGES, SPLIT, A, B, true>), g, b, 0, s, KS_ARGUMENTS(p));  \
+            else hipLaunchKernelGGL((gemm_bf16_dma_kernel<F, BM, BN, BK, WM, WN, STAGES, SPLIT, A, B, false>), g, b, 0, s, KS_ARGUMENTS(p)); \
         }                                                                                                           \
     } while (0)
     switch (variant & 3) {

@@ -9,8 +9,8 @@ static void launch(const GemmParams &p, int grid, int variant, int stream, hipSt
     const dim3 g = launch_grid(p, grid), b(64 * NW);
 #define KS_V(A, B)                                                                                                            \
     do {                                                                                                                      \
-        if (variant & 16) hipLaunchKernelGGL((gemm_bf16_slices_kernel<BM, BN, BK, NW, STAGES, A, B, true>), g, b, 0, s, p, stream); \
-        else hipLaunchKernelGGL((gemm_bf16_slices_kernel<BM, BN, BK, NW, STAGES, A, B, false>), g, b, 0, s, p, stream);       \
+        if (variant & 16) hipLaunchKernelGGL((gemm_bf16_slices_kernel<BM, BN, BK, NW, STAGES, A, B, true>), g, b, 0, s, KS_ARGUMENTS(p), stream); \
+        else hipLaunchKernelGGL((gemm_bf16_slices_kernel<BM, BN, BK, NW, STAGES, A, B, false>), g, b, 0, s, KS_ARGUMENTS(p), stream);       \
     } while (0)
     switch (variant & 3) {
         case 0: KS_V(false, false); break;

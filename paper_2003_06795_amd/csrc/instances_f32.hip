@@ -49,9 +49,9 @@ static void launch_f32_fixed(const GemmParams &p, int grid, int variant, hipStre
 #define KS_V(A, B, L)                                                                                   \
     do {                                                                                                \
         if constexpr (CORE == CORE_KSLICE)                                                              \
-            hipLaunchKernelGGL((gemm_f32_kslice_kernel<BM, BN, BK, P1, P2, SPLIT, A, B, L == LOAD_UNITS && (A || B)>), g, b, 0, s, p); \
+            hipLaunchKernelGGL((gemm_f32_kslice_kernel<BM, BN, BK, P1, P2, SPLIT, A, B, L == LOAD_UNITS && (A || B)>), g, b, 0, s, KS_ARGUMENTS(p)); \
         else if constexpr (CORE == CORE_DIRECT)                                                         \
-            hipLaunchKernelGGL((gemm_f32_direct_kernel<BM, BN, BK, P1, P2, SPLIT, A, B, L == LOAD_UNITS && (A || B)>), g, b, 0, s, p); \
+            hipLaunchKernelGGL((gemm_f32_direct_kernel<BM, BN, BK, P1, P2, SPLIT, A, B, L == LOAD_UNITS && (A || B)>), g, b, 0, s, KS_ARGUMENTS(p)); \
         else if constexpr (MULTI_OK) {                                                                  \
             if (p.tilesPerWG > 1)                                                                       \
                 hipLaunchKernelGGL((gemm_f32_kernel<CORE, BM, BN, BK, P1, P2, SPLIT, A, B, LOAD_STEPS, KW, true>), g, b, 0, s, p); \

@@ -95,6 +95,34 @@ inline void set_tile_order(GemmParams &p) {
     p.perLastRow = divisor_of((unsigned)((p.tilesM - 1) % p.bandRows + 1));
 }
 
+// What a launch of one batch item and no K partitions that reads its tile needs before its first loads, as three arguments in front
+// of the others: the build has the compiler put the first fourteen dwords into scalar registers when a wave starts
+// (-amdgpu-kernarg-preload-count), where all others come from memory that no cache holds at a launch.  Three vectors, because the
+// runtime copies argument by argument (eleven scalars cost the host 0.15 us a call).  For the kernels of short calls, us:
+// fp32 200 x 300 x 700 NT (K-sliced) 4.87 -> 4.53, bf16 128 x 128 x 2048 NT (K slices) 3.52 -> 3.26, 512 x 512 x 512 NT (direct-to-LDS)
+// 3.67 -> 3.42; level to 1 % the other way elsewhere.
+typedef unsigned long long HotPointers __attribute__((ext_vector_type(2)));
+typedef int HotInts __attribute__((ext_vector_type(4)));
+#define KS_PARAMS const HotPointers hotAB, const HotInts hotSizes, const HotInts hotForm, const GemmParams rest
+#define KS_ARGUMENTS(p)                                                                                                          \
+    HotPointers{(unsigned long long)(uintptr_t)(p).A, (unsigned long long)(uintptr_t)(p).B},                                  \
+        HotInts{(int)(p).lda, (int)(p).ldb, (p).M, (p).N}, HotInts{(p).K, (p).kChunk, (p).grid3d, (p).splitK}, (p)
+#define KS_PARAMS_TOGETHER                                                                                                        \
+    GemmParams p = rest;                                                                                                          \
+    p.A = reinterpret_cast<const void *>((uintptr_t)hotAB.x); p.B = reinterpret_cast<const void *>((uintptr_t)hotAB.y);           \
+    p.lda = hotSizes.x; p.ldb = hotSizes.y; p.M = hotSizes.z; p.N = hotSizes.w;                                                   \
+    p.K = hotForm.x; p.kChunk = hotForm.y; p.grid3d = hotForm.z; p.splitK = hotForm.w
+
+// origin of a batch item; the stride of the first one is not waited for
+template <class T>
+__device__ __forceinline__ T *batch_origin(T *base, int batch, long long stride) {
+    if (batch != 0) {
+        asm volatile("");                                    // (keeps the stride, and the wait for it, in here)
+        base += batch * stride;
+    }
+    return base;
+}
+
 // K-steps [first, last) of the left-over tiles (flattened as tile * steps-per-tile + step) that
 // work-group `w` of `groups` computes in the balanced persistent form; shares differ by at most one
 __host__ __device__ inline long long sk_share_begin(long long w, long long units, long long groups) {
