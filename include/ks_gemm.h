@@ -128,7 +128,10 @@ typedef struct {
  * ks_gemm_*_with_kernel(ks_select(...), ...) whenever the registered workspace can hold the
  * chosen kernel's split-K partial sums; if it cannot (or none is registered) the instance with
  * the same tiles and split_k == 1 runs instead, and for 16-bit products of up to 32 rows or 16 columns without scratch for the
- * K partitions that the chosen member would take, the member that gains without them.  A, B, C: device pointers.
+ * K partitions that the chosen member would take, the member that gains without them.  Not so 16-bit products with few output tiles
+ * and K from 256 on that ks_gemm_plan reports with a path of 16 and more: the built-in selection runs them in the K-slices form,
+ * which no kernel id names (every wave of a work-group sums its own part of K, the parts are added in a fixed order: the same bound
+ * on the error, other last bits), unless the estimate for the member is the lower one.  A, B, C: device pointers.
  * bf16 operands are raw bfloat16 bit patterns; accumulation and C are fp32.
  * fp32 members of core KS_CORE_MFMA32 with 128 x 128 x 32 tiles, and those with 64 x 64 x 16 ones that have two K groups or no K
  * partitions, multiply a K range of at least 49 (360 with two K groups) on the bf16 matrix pipe, each float as the exact sum of
