@@ -69,7 +69,7 @@ constexpr double slice_operand_us(bool staged, int extent, bool kc, int bk) {
 struct SliceCall {
     bool akc, bkc;
     int64_t M, N;
-    double k, latency;               // latency: K / 1024 steps' worth of 2 us, 0 where no operand comes from memory
+    double k, latency;               // latency: 2 us x K (a wave's round trips to memory), 0 where no operand comes from there
 };
 template <int T>
 inline bool slices_us(const SliceCall &c, double &us) {

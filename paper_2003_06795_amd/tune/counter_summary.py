@@ -16,7 +16,7 @@ import sys
 
 
 def short(name):
-    return re.sub(r"^void ks::|\(ks::GemmParams\)$", "", name)
+    return re.sub(r"^void ks::|(?<=>)\((unsigned long long|ks::GemmParams).*$", "", name)
 
 
 def main(path, min_share=0.01):

@@ -25,7 +25,7 @@ def per_kernel(path, counter):
 
 
 def short(name):
-    return re.sub(r"^void ks::|\(ks::GemmParams\)$", "", name)
+    return re.sub(r"^void ks::|(?<=>)\((unsigned long long|ks::GemmParams).*$", "", name)
 
 
 def main(fetch_csv, write_csv, workload):

@@ -13,10 +13,11 @@ bench line) is always printed too.
 import argparse
 import csv
 import json
+import re
 
 
 def short(name):
-    return name.replace("void ks::", "").replace("(ks::GemmParams)", "")
+    return re.sub(r"^void ks::|(?<=>)\((unsigned long long|ks::GemmParams).*$", "", name)
 
 
 def main(argv=None):
