@@ -245,7 +245,8 @@ int ks_gemm_with_workspace(int dtype, int kernel_id, int transA, int transB, int
  * (a member whose split is chosen per call runs another kernel, plus the reduction pass, when it
  * splits).  Arguments and statuses as for the GEMM calls; out: host. */
 typedef struct {
-    int32_t kernel_id;            /* the member that runs (after selection and the no-workspace fallback) */
+    int32_t kernel_id;            /* the member that runs (after selection and the no-workspace fallback); with a path of 16
+                                     and more the one that the K-slices form stands in for */
     int32_t split_k;              /* K partitions taken; > 1 means partial-sum kernel + reduction pass */
     int32_t path;                 /* how the operands are read as they are.  0: by the member's general kernel, or not
                                      at all (operand_copies); 1: direct-to-LDS 16-bit kernel; 2: the same in its

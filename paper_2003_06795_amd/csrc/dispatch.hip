@@ -629,9 +629,6 @@ int run_ws(Workspace wsp, int dtype, int id, int transA, int transB, int64_t M, 
             p.grid3d = (double)(M + N) * (double)K * 2 <= (double)KS_GRID3D_BYTES ? 1 : 0;
             set_tile_order(p);
             if (planOnly) {
-                // the form uses no scratch: the member named is ks_select's from one partition's worth on, as for split_k == 1
-                if (wsp.ptr && wsp.bytes >= (size_t)M * (size_t)N * sizeof(float))
-                    planOnly->kernel_id = select_member(dtype, M, N, K, 1, transA, transB, true);
                 planOnly->path = 16 + t;
                 planOnly->vector_loads = vector_operands(8, akc, bkc, M, N, K, A, lda, B, ldb, 1, 0, 0) ? 1 : 0;
                 planOnly->grid_3d = p.grid3d;

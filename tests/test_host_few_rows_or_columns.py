@@ -110,16 +110,17 @@ def test_scratch_that_holds_fewer_partitions_is_none():
     the member it has without any."""
     ptr = 1 << 20                                                        # never dereferenced
 
-    def plan(M, N, K):
-        return ks.gemm_plan(ks.BF16, -1, 0, 1, M, N, K, 1.0, ptr, K, ptr, K, 0.0, ptr, N)
+    def plan(M, N, K, kid=-1):
+        return ks.gemm_plan(ks.BF16, kid, 0, 1, M, N, K, 1.0, ptr, K, ptr, K, 0.0, ptr, N)
     try:
         for M, N, K in ((6, 6163, 5041), (12, 3000, 2100), (5000, 7, 2100), (8192, 1, 8192), (5, 4096, 16384)):
             ks.set_workspace(None)
             without = plan(M, N, K)["kernel_id"]
             ks.set_workspace(ptr, 256 << 20)
             full = plan(M, N, K)
-            used = 4 * M * N * full["split_k"]
-            assert full["kernel_id"] == ks.select(ks.BF16, M, N, K, 1, 0, 1)
+            # partitions of the member: these calls run in the K-slices form, which stands in for it without any
+            used = 4 * M * N * plan(M, N, K, full["kernel_id"])["split_k"]
+            assert full["kernel_id"] == ks.select(ks.BF16, M, N, K, 1, 0, 1) and used > 4 * M * N
             for size in (4096, 65536, used - 4, used):
                 ks.set_workspace(ptr, size)
                 assert plan(M, N, K)["kernel_id"] == (full["kernel_id"] if size >= used else without), (M, N, K, size)
