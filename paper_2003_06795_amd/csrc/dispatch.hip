@@ -600,8 +600,8 @@ int run_ws(Workspace wsp, int dtype, int id, int transA, int transB, int64_t M, 
     if ((dtype == KS_F32 ? g_f32[id] : g_bf16[id]) == nullptr) return KS_ERR_UNSUPPORTED;
 
     // A call that names no member and would run one of the skinny or square ones with few tiles takes the K-slices form
-    // where its estimate is the lower one (slices.hpp).  Named members, a caller's own tree and forced partitions are followed as they
-    // are.  The form takes no scratch; what the member would do with the scratch at hand is what it is compared with.
+    // where its estimate is the lower one (slices.hpp).  Named members, a caller's own tree, forced partitions and forced copies are
+    // followed as they are.  The form takes no scratch; what the member would do with the scratch at hand is what it is compared with.
     // Drawn problems (64 .. 4096 in each dimension, skinny and tall ones, four layouts): aligned 495 of 1300 take it, 0.755 of the
     // time; with rows that nothing aligns 521 of 1597, 0.70.
     int64_t estimated = 0;                            // K partitions of this member and call, once known
@@ -613,7 +613,8 @@ int run_ws(Workspace wsp, int dtype, int id, int transA, int transB, int64_t M, 
         const int64_t groups = ((M + d->bm - 1) / d->bm) * ((N + d->bn - 1) / d->bn) * parts;
         const double other = slices_other_us(staged, id, M, N, K, groups, (kTiles + parts - 1) / parts, parts,
                                              4.0 * (double)parts * (double)M * (double)N);
-        const int t = slices_tile(staged, akc, bkc, M, N, K, lda, ldb, other);
+        // (copies of the operands asked for wherever they can be made are the member's)
+        const int t = staged && g_operandCopies > 0 ? -1 : slices_tile(staged, akc, bkc, M, N, K, lda, ldb, other);
         if (t >= 0) {
             const SliceTile &tile = kSliceTiles[t];
             GemmParams p{};

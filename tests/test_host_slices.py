@@ -67,6 +67,18 @@ def test_calls_that_do_not_take_it(planner):
         assert planner(ks.BF16, -1, *size)["path"] < 16
     finally:
         ks.set_split_partitions(0)
+    ks.set_operand_copies(1)                                                 # copies wherever they can be made: by the member
+    try:
+        got = planner(ks.BF16, -1, 0, 1, 975, 675, 3392, lda=3396)
+        assert got["path"] < 16 and got["operand_copies"] == 1
+        got = planner(ks.BF16, -1, 0, 1, 975, 675, 3365, a=PTR + 2)
+        assert got["path"] < 16 and got["operand_copies"] == 3
+        assert planner(ks.BF16, -1, *size)["path"] == 16 + 3                 # none to be made
+        for mode in (0, -1):
+            ks.set_operand_copies(mode)
+            assert planner(ks.BF16, -1, 0, 1, 975, 675, 3392, lda=3396)["path"] >= 26
+    finally:
+        ks.set_operand_copies(-1)
     ks.set_fast_path(False)
     try:
         assert planner(ks.BF16, -1, *size)["path"] < 16
