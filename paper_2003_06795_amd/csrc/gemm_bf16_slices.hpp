@@ -45,6 +45,9 @@ __device__ __forceinline__ void wait_for_stage() {
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
+// the LDS reads issued so far have returned; what they read may be overwritten
+__device__ __forceinline__ void wait_for_reads() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+
 template <int BM, int BN, int BK, int NW, int STAGES, bool AKC, bool BKC, bool F16>
 __global__ __launch_bounds__(64 * NW) void gemm_bf16_slices_kernel(KS_PARAMS, const int stream) {
     KS_PARAMS_TOGETHER;
@@ -107,7 +110,8 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_slices_kernel(KS_PARAMS, co
     };
 
     // Step t lives in stage t % STAGES.  Before it is read at most the loads of the younger steps are in flight; the stage that
-    // step t - 1 left, whose fragments have entered their MFMAs, is refilled with step t + STAGES - 1.
+    // step t - 1 left is refilled with step t + STAGES - 1 once its fragments are in registers.  (They are where the MFMAs of
+    // step t - 1 stand in front of the refill, which nothing but the wait here makes the compiler do.)
 #pragma unroll
     for (int s = 0; s < STAGES - 1; ++s)
         if (s < n) issue(s, s);
@@ -120,7 +124,10 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_slices_kernel(KS_PARAMS, co
             if (STAGES > 3 && younger >= 2) wait_for_stage<2 * LOADS>();
             else if (STAGES > 2 && younger >= 1) wait_for_stage<LOADS>();
             else wait_for_stage<0>();
-            if (t + STAGES - 1 < n) issue(t + STAGES - 1, (s + STAGES - 1) % STAGES);
+            if (t + STAGES - 1 < n) {
+                wait_for_reads();
+                issue(t + STAGES - 1, (s + STAGES - 1) % STAGES);
+            }
             multiply(lds[wave][s]);
         }
     }

@@ -3,10 +3,14 @@ by direct-to-LDS loads (tiles 0 to 9) on aligned operands with whole K-steps of 
 never for a named member, forced partitions, a caller's own tree, batches or fp32.  No GPU: ks_gemm_plan reads sizes and addresses
 only."""
 import ctypes
+import re
+import shutil
+import subprocess
 
 import pytest
 
 import paper_2003_06795_amd.binding as ks
+from paper_2003_06795_amd import build as lib_build
 
 TILES = [(16, 16), (32, 16), (16, 32), (32, 32), (64, 16), (16, 64), (64, 32), (32, 64), (64, 64), (64, 64)]
 TILES += [(16, 16), (32, 16), (16, 32), (32, 32), (64, 16), (16, 64), (64, 32), (32, 64), (64, 64)]
@@ -92,3 +96,28 @@ def test_calls_that_do_not_take_it(planner):
         ks.set_selector(ks.BF16, [])
     ks.lib().ks_set_workspace(None, 0)                                       # it needs no scratch
     assert planner(ks.BF16, -1, *size)["path"] == 16 + 3
+
+
+@pytest.mark.skipif(shutil.which(lib_build.HIPCC) is None, reason="needs the device compiler")
+@pytest.mark.parametrize("tile,layout", [("16, 16, 64, 8, 4", "true, true"), ("32, 32, 64, 8, 2", "false, true"),
+                                         ("64, 64, 64, 4, 2", "true, false"), ("64, 32, 64, 4, 3", "false, false")])
+def test_a_stage_is_refilled_behind_its_reads(tmp_path, tile, layout):
+    """The direct-to-LDS loads of the K loop overwrite the stage that the step before has read: between the wait that opens
+    a step and its loads the code waits for the LDS reads too."""
+    src, asm = tmp_path / "one.hip", tmp_path / "one.s"
+    src.write_text('#include "gemm_bf16_slices.hpp"\ntemplate __global__ void ks::gemm_bf16_slices_kernel<%s, %s, false>(const '
+                   'ks::HotPointers, const ks::HotInts, const ks::HotInts, const ks::GemmParams, const int);\n' % (tile, layout))
+    subprocess.run([lib_build.HIPCC] + lib_build.HIP_FLAGS + ["-I", lib_build.CSRC, "--cuda-device-only", "-S", str(src), "-o",
+                                                              str(asm)], check=True, capture_output=True)
+    step, waited, refills = False, False, 0
+    for line in asm.read_text().splitlines():
+        if re.search(r"s_waitcnt vmcnt\(\d+\)", line):
+            step, waited = True, "lgkmcnt(0)" in line
+        elif "s_waitcnt" in line and "lgkmcnt(0)" in line:
+            waited = True
+        elif "ds_read" in line:
+            waited = False
+        elif "global_load_lds" in line and step:
+            refills += 1
+            assert waited, line
+    assert refills > 0
