@@ -614,7 +614,7 @@ int run_ws(Workspace wsp, int dtype, int id, int transA, int transB, int64_t M, 
         const double other = slices_other_us(staged, id, M, N, K, groups, (kTiles + parts - 1) / parts, parts,
                                              4.0 * (double)parts * (double)M * (double)N);
         // (copies of the operands asked for wherever they can be made are the member's)
-        const int t = staged && g_operandCopies > 0 ? -1 : slices_tile(staged, akc, bkc, M, N, K, lda, ldb, other);
+        const int t = staged && g_operandCopies > 0 ? -1 : slices_tile(staged, id, akc, bkc, M, N, K, lda, ldb, other);
         if (t >= 0) {
             const SliceTile &tile = kSliceTiles[t];
             GemmParams p{};

@@ -62,14 +62,18 @@ constexpr double slice_operand_us(bool staged, int extent, bool kc, int bk) {
 }
 // Estimate for one round of work-groups of tile `t`, us: the longest of a unit's memory pipe, memory (a row-contiguous operand in
 // pieces of less than a line is fetched as often as a line has pieces), what a work-group has in flight of an operand that comes
-// from memory behind its 2 us (one of 64 MiB and more: 2944 x 2 x 14976 NT 18.4 us by the member, 22.7 in 184 tiles of 16 x 16), and the
-// L2s.  The constants are fitted to the times of all tiles over 1300 (any operands: 1597) drawn products, 14 % (17 %) rms.
+// from memory behind its 2 us (one of 64 MiB and more: 2944 x 2 x 14976 NT 18.4 us by the member, 22.7 in 184 tiles of 16 x 16) or from
+// the last-level cache behind 0.8 (32 MiB: 2944 x 52 x 8960 NT 14.7 and 15.8), and the L2s.  Where the rows of an aligned K-contiguous
+// operand do not begin at lines of 128 bytes, the piece of a K-step lies in one line more, which shows in tiles of 32 of its
+// rows and more (1984 x 448 x 3584 NT, rows of 3592, 20.2 and 24.5).  The constants are fitted to the times of all tiles over 1300 (any
+// operands: 1597) drawn products, 14 % (17 %) rms.
 // (The tile is a template argument: a small call waits for the host, and with the constants folded ten estimates take it
 // 30 ns where a loop over the table took 250.)
 struct SliceCall {
     bool akc, bkc;
     int64_t M, N;
-    double k, latency;               // latency: 2 us x K (a wave's round trips to memory), 0 where no operand comes from there
+    double k, latency;               // latency: us of a wave's round trip x K, 0 where all operands come from the L2s
+    double aLines, bLines;           // what rows that do not begin at lines add to an operand's part
 };
 template <int T>
 inline bool slices_us(const SliceCall &c, double &us) {
@@ -79,7 +83,8 @@ inline bool slices_us(const SliceCall &c, double &us) {
     if (tiles > 256) return false;
     constexpr double aKc = slice_operand_us(staged, t.bm, true, t.bk), aRc = slice_operand_us(staged, t.bm, false, t.bk),
                      bKc = slice_operand_us(staged, t.bn, true, t.bk), bRc = slice_operand_us(staged, t.bn, false, t.bk);
-    double longest = c.k * (1.0 / 1024) * ((c.akc ? aKc : aRc) + (c.bkc ? bKc : bRc));
+    double longest = c.k * (1.0 / 1024) * ((c.akc ? (t.bm >= 32 ? aKc * c.aLines : aKc) : aRc) +
+                                           (c.bkc ? (t.bn >= 32 ? bKc * c.bLines : bKc) : bRc));
     const double memory = c.k * (2e-6 / (staged ? 6.14 : 5.99)) * ((double)c.M * (c.akc ? 1 : 64 / t.bm) + (double)c.N * (c.bkc ? 1 : 64 / t.bn));
     if (memory > longest) longest = memory;
     const double l2 = (double)tiles * c.k * ((t.bm + t.bn) * 2e-6 / (staged ? 10.66 : 17.02));
@@ -105,15 +110,21 @@ inline double slices_other_us(bool staged, int id, int64_t M, int64_t N, int64_t
     return c[0] + (chain > memory ? chain : memory) + sums;
 }
 // Tile for this call, or -1: the members as they are.  One round of work-groups (a second one costs more than the estimate knows:
-// up to 2.0 of the time), K from 512 (any operands: 256) on, below which it is level, and an estimate 8 % below the other one.  Any
-// operands: rows of seven elements at least; none of 64 MiB and more (up to 1.39), nor 1e10 flop, where copies pay.
-inline int slices_tile(bool staged, bool akc, bool bkc, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, double other) {
+// up to 2.0 of the time), K from 512 (any operands: 256) on, below which it is level, and an estimate 8 % below the other one; 18 %
+// for the largest tile in place of the 64 x 64 x 128 member, whose two work-groups a unit the estimate of one flatters (51 calls
+// between the two lines: 17 slower by over 3 %, 17 faster, 0.99 in the mean).  Any operands: rows of seven elements at least; none of
+// 64 MiB and more (up to 1.39), nor 1e10 flop, where copies pay.
+// Of 6150 drawn aligned calls that took the form without the last three of these terms (the caches' trip, lines, the largest tile)
+// 102 were slower than with the member by over 3 %, 41 by over 10; 40 and 22 of those now stay with it, with 25 level ones and
+// 20 that were faster.  Of 3083 drawn afterwards 53 and 21 were, 38 and 15 are, and 0.6848 of the member's time in the mean was 0.6843.
+inline int slices_tile(bool staged, int id, bool akc, bool bkc, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, double other) {
     if (K < (staged ? 256 : 512)) return -1;
     if (staged && ((!akc && lda < 7) || (!bkc && ldb < 7) || M * K >= (32LL << 20) || N * K >= (32LL << 20) ||
                    2.0 * (double)M * (double)N * (double)K >= 1e10))
         return -1;
-    const bool far = M * K >= (32LL << 20) || N * K >= (32LL << 20);
-    const SliceCall c{akc, bkc, M, N, (double)K, far ? 2.0 * (double)K : 0};
+    const int64_t larger = (M > N ? M : N) * K;
+    const double trip = staged || larger < (16LL << 20) ? 0 : larger < (32LL << 20) ? 0.8 : 2;
+    const SliceCall c{akc, bkc, M, N, (double)K, trip * (double)K, staged || lda % 64 == 0 ? 1 : 1.35, staged || ldb % 64 == 0 ? 1 : 1.35};
     int best = -1;
     double us = 0.92 * other;
 #define KS_TRY(i, BM, BN, BK, NW, ST, FIXED) if (slices_us<i>(c, us)) best = i;
@@ -123,7 +134,7 @@ inline int slices_tile(bool staged, bool akc, bool bkc, int64_t M, int64_t N, in
         KS_SLICES_TILES(KS_TRY)
     }
 #undef KS_TRY
-    return best;
+    return best == 9 && id == 27 && us > 0.82 * other ? -1 : best;
 }
 // An operand of 96 MiB and more that one row (column) of tiles reads does not outlast in the last-level cache of 256 MiB what comes
 // between two of its uses: 6000 x 16 x 8192 (94 MiB) is level, 8192 x 16 x 8192 0.87 of the time, 4096 x 16 x 8192 1.36.

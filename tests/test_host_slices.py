@@ -66,6 +66,12 @@ def test_calls_that_do_not_take_it(planner):
     assert planner(ks.BF16, -1, 0, 0, 3000, 6, 2001, ldb=7)["path"] >= 26
     assert planner(ks.BF16, -1, 1, 0, 1024, 1024, 5001)["path"] < 16        # copies of the operands pay
     assert planner(ks.BF16, -1, 0, 0, 8001, 9, 4195)["path"] < 16           # 2^25 entries of A
+    # that the member is faster at (time of the form over its): rows between lines 1.21, what is in flight of 50 MiB 1.08, the
+    # largest tile for the 64 x 64 x 128 member 1.17
+    assert planner(ks.BF16, -1, 0, 1, 1984, 448, 3584, lda=3592, ldb=3592)["path"] < 16
+    assert planner(ks.BF16, -1, 0, 1, 1984, 448, 3584)["path"] == 16 + 8
+    assert planner(ks.BF16, -1, 0, 1, 2944, 52, 8960)["path"] < 16
+    assert planner(ks.BF16, -1, 1, 1, 2816, 212, 7808)["path"] < 16
     ks.set_split_partitions(2)
     try:
         assert planner(ks.BF16, -1, *size)["path"] < 16
