@@ -21,6 +21,7 @@ namespace ks {
 // selector.cpp
 int select_member(int dtype, int64_t M, int64_t N, int64_t K, int64_t batch, int transA, int transB, bool scratch);
 bool custom_tree(int dtype);
+bool split_decides(int dtype, int64_t M, int64_t N, int64_t K, int64_t batch);
 
 #define KS_DECL(n)                              \
     void register_f32_shard_##n(LaunchFn *);    \
@@ -609,12 +610,15 @@ int run_ws(Workspace wsp, int dtype, int id, int transA, int transB, int64_t M, 
         !custom_tree(dtype)) {
         const bool akc = transA == 0, bkc = transB == 1;
         const bool staged = K % 64 != 0 || !dma_operands(akc, bkc, M, N, K, A, lda, B, ldb, 1, 0, 0);
-        const int64_t parts = d->splitK > 0 ? 1 : (estimated = partitions(d, false, M, N, K, 1, wsp)), kTiles = (K + d->bk - 1) / d->bk;
-        const int64_t groups = ((M + d->bm - 1) / d->bm) * ((N + d->bn - 1) / d->bn) * parts;
-        const double other = slices_other_us(staged, id, M, N, K, groups, (kTiles + parts - 1) / parts, parts,
-                                             4.0 * (double)parts * (double)M * (double)N);
+        int t = -1;
         // (copies of the operands asked for wherever they can be made are the member's)
-        const int t = staged && g_operandCopies > 0 ? -1 : slices_tile(staged, id, akc, bkc, M, N, K, lda, ldb, other);
+        if (slices_worth(staged, akc, bkc, M, N, K, lda, ldb) && !(staged && g_operandCopies > 0)) {
+            const int64_t parts = d->splitK > 0 ? 1 : (estimated = partitions(d, false, M, N, K, 1, wsp)), kTiles = (K + d->bk - 1) / d->bk;
+            const int64_t groups = ((M + d->bm - 1) / d->bm) * ((N + d->bn - 1) / d->bn) * parts;
+            const double other = slices_other_us(staged, id, M, N, K, groups, (kTiles + parts - 1) / parts, parts,
+                                                 4.0 * (double)parts * (double)M * (double)N);
+            t = slices_tile(staged, id, akc, bkc, M, N, K, lda, ldb, other);
+        }
         if (t >= 0) {
             const SliceTile &tile = kSliceTiles[t];
             GemmParams p{};
@@ -1033,7 +1037,7 @@ static int select_checked(int dtype, int64_t M, int64_t N, int64_t K, int64_t ba
     int id = ks::select_member(dtype, M, N, K, batch, tA, tB, true);
     if (id < 0) return id;
     const InstanceDesc *d = desc_of(dtype, id);
-    const int unsplit = ks::select_member(dtype, M, N, K, batch, tA, tB, false);
+    const int unsplit = ks::split_decides(dtype, M, N, K, batch) ? ks::select_member(dtype, M, N, K, batch, tA, tB, false) : id;
     if (unsplit != id && d && d->splitK == 0 &&
         (!w.ptr || partitions(d, dtype == KS_F32, M, N, K, batch, w) <
                        partitions(d, dtype == KS_F32, M, N, K, batch, Workspace{w.ptr, SIZE_MAX}))) {

@@ -247,6 +247,10 @@ extern "C" int ks_features(int64_t M, int64_t N, int64_t K, int64_t batch, int t
 }
 
 namespace ks {
+// whether a rule that counts on a K split looks at these sizes (by_few_rows_or_columns): elsewhere scratch changes nothing below
+bool split_decides(int dtype, int64_t M, int64_t N, int64_t K, int64_t batch) {
+    return dtype != KS_F32 && batch == 1 && K >= 1024 && ((M >= 1024 && N <= 32) || (M <= 32 && N >= 1024));
+}
 bool custom_tree(int dtype) { return g_tree[dtype == KS_F32 ? KS_F32 : KS_BF16].custom; }
 // The member for these sizes; without scratch (for the partitions it takes) the rules that count on a K split are left out.
 int select_member(int dtype, int64_t M, int64_t N, int64_t K, int64_t batch, int transA, int transB, bool scratch) {

@@ -46,7 +46,13 @@ void launch_bf16_slices(int tile, const GemmParams &p, int grid, int variant, in
 // Members that the form may stand in for, and sizes that may be one round of its largest tiles.
 inline int slices_member(int id) { return id == 13 ? 0 : id == 27 ? 1 : id == 38 ? 2 : id == 39 ? 3 : -1; }
 inline bool slices_possible(int id, int64_t M, int64_t N, int64_t K) {
-    return slices_member(id) >= 0 && K >= 256 && M <= (1 << 14) && N <= (1 << 14) && ((M + 63) / 64) * ((N + 63) / 64) <= 256;
+    return slices_member(id) >= 0 && K >= 256 && ((M + 63) / 64) * ((N + 63) / 64) <= 256;
+}
+// K from 512 (any operands: 256) on, below which it is level.  Any operands: rows of seven elements at least; none of 64 MiB and more
+// (up to 1.39 of the time), nor 1e10 flop, where copies pay.
+inline bool slices_worth(bool staged, bool akc, bool bkc, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb) {
+    if (!staged) return K >= 512;
+    return (akc || lda >= 7) && (bkc || ldb >= 7) && M * K < (32LL << 20) && N * K < (32LL << 20) && 2.0 * (double)M * (double)N * (double)K < 1e10;
 }
 
 // us per 1024 of K that a compute unit's memory pipe takes for one operand of a tile of `extent` rows (of columns): a K-contiguous
@@ -110,18 +116,13 @@ inline double slices_other_us(bool staged, int id, int64_t M, int64_t N, int64_t
     return c[0] + (chain > memory ? chain : memory) + sums;
 }
 // Tile for this call, or -1: the members as they are.  One round of work-groups (a second one costs more than the estimate knows:
-// up to 2.0 of the time), K from 512 (any operands: 256) on, below which it is level, and an estimate 8 % below the other one; 18 %
-// for the largest tile in place of the 64 x 64 x 128 member, whose two work-groups a unit the estimate of one flatters (51 calls
-// between the two lines: 17 slower by over 3 %, 17 faster, 0.99 in the mean).  Any operands: rows of seven elements at least; none of
-// 64 MiB and more (up to 1.39), nor 1e10 flop, where copies pay.
+// up to 2.0 of the time) and an estimate 8 % below the other one; 18 % for the largest tile in place of the 64 x 64 x 128 member,
+// whose two work-groups a unit the estimate of one flatters (51 calls between the two lines: 17 slower by over 3 %, 17 faster, 0.99
+// in the mean).
 // Of 6150 drawn aligned calls that took the form without the last three of these terms (the caches' trip, lines, the largest tile)
 // 102 were slower than with the member by over 3 %, 41 by over 10; 40 and 22 of those now stay with it, with 25 level ones and
 // 20 that were faster.  Of 3083 drawn afterwards 53 and 21 were, 38 and 15 are, and 0.6848 of the member's time in the mean was 0.6843.
 inline int slices_tile(bool staged, int id, bool akc, bool bkc, int64_t M, int64_t N, int64_t K, int64_t lda, int64_t ldb, double other) {
-    if (K < (staged ? 256 : 512)) return -1;
-    if (staged && ((!akc && lda < 7) || (!bkc && ldb < 7) || M * K >= (32LL << 20) || N * K >= (32LL << 20) ||
-                   2.0 * (double)M * (double)N * (double)K >= 1e10))
-        return -1;
     const int64_t larger = (M > N ? M : N) * K;
     const double trip = staged || larger < (16LL << 20) ? 0 : larger < (32LL << 20) ? 0.8 : 2;
     const SliceCall c{akc, bkc, M, N, (double)K, trip * (double)K, staged || lda % 64 == 0 ? 1 : 1.35, staged || ldb % 64 == 0 ? 1 : 1.35};
