@@ -48,6 +48,10 @@ __device__ __forceinline__ void wait_for_stage() {
 // the LDS reads issued so far have returned; what they read may be overwritten
 __device__ __forceinline__ void wait_for_reads() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
+// Lanes of a wave pass each other what they write to LDS: the LDS serves a wave's accesses in order, and the compiler, which sees the
+// addresses of one lane only, keeps them in that order across this (no instruction).
+__device__ __forceinline__ void lanes_meet() { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
+
 template <int BM, int BN, int BK, int NW, int STAGES, bool AKC, bool BKC, bool F16>
 __global__ __launch_bounds__(64 * NW) void gemm_bf16_slices_kernel(KS_PARAMS, const int stream) {
     KS_PARAMS_TOGETHER;
@@ -203,8 +207,10 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_slices_staged_kernel(const 
         for (int s = 0; s < PF; ++s) {
             const int t = t0 + s;
             if (t >= n) break;
+            lanes_meet();
             LoadA::store(ra[s], as, lane);
             LoadB::store(rb[s], bs, lane);
+            lanes_meet();
             if (t + PF < n) { la.load(ra[s], (t + PF) * aStep, lane); lb.load(rb[s], (t + PF) * bStep, lane); }
             multiply();
         }
@@ -221,11 +227,14 @@ __global__ __launch_bounds__(64 * NW) void gemm_bf16_slices_staged_kernel(const 
             LoadA::load_edge(ra[0], Ab, p.lda, row0, p.M, k0, p.K, lane);
             LoadB::load_edge(rb[0], Bb, p.ldb, col0, p.N, k0, p.K, lane);
         }
+        lanes_meet();
         LoadA::store(ra[0], as, lane);
         LoadB::store(rb[0], bs, lane);
+        lanes_meet();
         multiply();
     }
     // the sums of the waves in wave order
+    lanes_meet();
     floatx4 *const mine = reinterpret_cast<floatx4 *>(lds[wave]);
 #pragma unroll
     for (int i = 0; i < FM; ++i)

@@ -104,19 +104,24 @@ def test_calls_that_do_not_take_it(planner):
     assert planner(ks.BF16, -1, *size)["path"] == 16 + 3
 
 
+def assembly(tmp_path, kernel):
+    src, asm = tmp_path / "one.hip", tmp_path / "one.s"
+    src.write_text('#include "gemm_bf16_slices.hpp"\ntemplate __global__ void ks::%s;\n' % kernel)
+    subprocess.run([lib_build.HIPCC] + lib_build.HIP_FLAGS + ["-I", lib_build.CSRC, "--cuda-device-only", "-S", str(src), "-o",
+                                                              str(asm)], check=True, capture_output=True)
+    return asm.read_text().splitlines()
+
+
 @pytest.mark.skipif(shutil.which(lib_build.HIPCC) is None, reason="needs the device compiler")
 @pytest.mark.parametrize("tile,layout", [("16, 16, 64, 8, 4", "true, true"), ("32, 32, 64, 8, 2", "false, true"),
                                          ("64, 64, 64, 4, 2", "true, false"), ("64, 32, 64, 4, 3", "false, false")])
 def test_a_stage_is_refilled_behind_its_reads(tmp_path, tile, layout):
     """The direct-to-LDS loads of the K loop overwrite the stage that the step before has read: between the wait that opens
     a step and its loads the code waits for the LDS reads too."""
-    src, asm = tmp_path / "one.hip", tmp_path / "one.s"
-    src.write_text('#include "gemm_bf16_slices.hpp"\ntemplate __global__ void ks::gemm_bf16_slices_kernel<%s, %s, false>(const '
-                   'ks::HotPointers, const ks::HotInts, const ks::HotInts, const ks::GemmParams, const int);\n' % (tile, layout))
-    subprocess.run([lib_build.HIPCC] + lib_build.HIP_FLAGS + ["-I", lib_build.CSRC, "--cuda-device-only", "-S", str(src), "-o",
-                                                              str(asm)], check=True, capture_output=True)
+    lines = assembly(tmp_path, "gemm_bf16_slices_kernel<%s, %s, false>(const ks::HotPointers, const ks::HotInts, const ks::HotInts, const "
+                               "ks::GemmParams, const int)" % (tile, layout))
     step, waited, refills = False, False, 0
-    for line in asm.read_text().splitlines():
+    for line in lines:
         if re.search(r"s_waitcnt vmcnt\(\d+\)", line):
             step, waited = True, "lgkmcnt(0)" in line
         elif "s_waitcnt" in line and "lgkmcnt(0)" in line:
@@ -127,3 +132,22 @@ def test_a_stage_is_refilled_behind_its_reads(tmp_path, tile, layout):
             refills += 1
             assert waited, line
     assert refills > 0
+
+
+@pytest.mark.skipif(shutil.which(lib_build.HIPCC) is None, reason="needs the device compiler")
+@pytest.mark.parametrize("bm,bn,bk,rest,layout", [(16, 16, 64, "16, 4", "false, false"), (16, 16, 64, "16, 4", "true, true"),
+                                                  (32, 16, 64, "8, 3", "false, true"), (64, 64, 32, "8, 3", "true, false")])
+def test_lanes_read_a_step_behind_all_writes_of_it(tmp_path, bm, bn, bk, rest, layout):
+    """The lanes of a wave read from LDS what others of them have written, where the compiler looks at one lane's addresses: no
+    read stands between the writes of a K-step (nor of the sums, one a fragment, at the end)."""
+    lines = assembly(tmp_path, "gemm_bf16_slices_staged_kernel<%d, %d, %d, %s, %s, false>(const ks::GemmParams)" % (bm, bn, bk, rest, layout))
+    runs, run = [], 0
+    for line in lines + [".L"]:
+        if "ds_write" in line:
+            run += 1
+        elif "ds_read" in line or line.startswith(".L"):
+            runs += [run] if run else []
+            run = 0
+    step, sums = (bm + bn) * bk * 2 // 1024, bm * bn // 256
+    runs.remove(sums)
+    assert len(runs) > 1 and all(n % step == 0 for n in runs), runs
