@@ -137,8 +137,16 @@ inline int slices_tile(bool staged, int id, bool akc, bool bkc, int64_t M, int64
 #undef KS_TRY
     return best == 9 && id == 27 && us > 0.82 * other ? -1 : best;
 }
-// An operand of 96 MiB and more that one row (column) of tiles reads does not outlast in the last-level cache of 256 MiB what comes
-// between two of its uses: 6000 x 16 x 8192 (94 MiB) is level, 8192 x 16 x 8192 0.87 of the time, 4096 x 16 x 8192 1.36.
-inline bool slices_past_cache(int64_t extent, int64_t K, int64_t tilesOther) { return tilesOther == 1 && extent * K * 2 >= (96LL << 20); }
+// An operand of 104 MiB and more that one row (column) of tiles reads is taken not to outlast in the last-level cache of 256 MiB what
+// comes between two of its uses.  That counts on other operands in between, as a model's layers are, which the call cannot know.
+// M x 16 x 8192 NN, us past the cache and through it, by how many sets of operands take turns (one: the same again and again):
+//   M                   1              2              3              6
+//    6144 ( 96 MiB)  18.1 / 15.8    18.6 / 15.9    18.8 / 19.0    19.0 / 20.9
+//    7168 (112 MiB)  19.3 / 18.0    20.2 / 18.0    20.4 / 23.2    20.7 / 23.1
+//    8192 (128 MiB)  21.5 / 20.1    22.5 / 21.2    22.9 / 26.6    23.3 / 26.7
+//   12288 (192 MiB)  33.2 / 28.5    35.2 / 40.0    36.0 / 40.4    36.8 / 41.3
+//   14336 (224 MiB)  38.4 / 33.1    40.9 / 46.4    41.8 / 46.8    42.2 / 46.9
+// (4096, 64 MiB, in turns of three 17.0 / 12.5.)
+inline bool slices_past_cache(int64_t extent, int64_t K, int64_t tilesOther) { return tilesOther == 1 && extent * K * 2 >= (104LL << 20); }
 
 }  // namespace ks
