@@ -91,10 +91,8 @@ def kernel_symbol(ks, dt, plan, tA, tB, M, N, K):
             b(plan["tiles_per_workgroup"] > 1), b(plan["balanced_groups"] > 0))
     f = 16 if ki["core_name"] == "mfma16" else 32
     if plan["path"] >= 16:                             # K slices, by the number of the tile
-        tile = [(16, 16, 64, 8, 4), (32, 16, 64, 8, 3), (16, 32, 64, 8, 3), (32, 32, 64, 8, 2), (64, 16, 64, 4, 3), (16, 64, 64, 4, 3),
-                (64, 32, 64, 4, 3), (32, 64, 64, 4, 3), (64, 64, 32, 8, 2), (64, 64, 64, 4, 2), (16, 16, 64, 16, 4), (32, 16, 64, 8, 3),
-                (16, 32, 64, 8, 3), (32, 32, 64, 8, 3), (64, 16, 64, 8, 3), (16, 64, 64, 8, 3), (64, 32, 64, 8, 2), (32, 64, 64, 8, 2),
-                (64, 64, 32, 8, 3)][plan["path"] - 16]
+        from paper_2003_06795_amd.build import slice_tiles
+        tile = slice_tiles()[plan["path"] - 16]
         return "gemm_bf16_slices_%skernel<%d, %d, %d, %d, %d, %s, %s, false>" % (("staged_" if plan["path"] >= 26 else "",) + tile + (b(akc), b(bkc)))
     if plan["path"] == 2:
         return "gemm_bf16_pp_kernel<%d, %s, %s, %s, false, 0, %d, %d, %s>" % (f, b(split), b(akc), b(bkc), ki["bm"], ki["bk"],

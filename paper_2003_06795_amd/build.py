@@ -14,6 +14,7 @@ import argparse
 import concurrent.futures as cf
 import glob
 import os
+import re
 import subprocess
 import sys
 import sysconfig
@@ -56,6 +57,15 @@ def _jobs(kept_only=False):
         src = os.path.join(CSRC, name + ".cpp")
         jobs.append((src, os.path.join(obj, name + ".o"), ["g++"] + CXX_FLAGS + ["-c", src]))
     return jobs
+
+
+def slice_tiles():
+    """Tiles of the K-slices form in the order of ks_launch_plan_t::path - 16, as csrc/slices.hpp lists them: rows, columns,
+    K-step, waves, stages (from the eleventh on K-steps in registers)."""
+    with open(os.path.join(CSRC, "slices.hpp")) as f:
+        rows = re.findall(r"X\((\d+), (\d+), (\d+), (\d+), (\d+), (\d+), [\d.]+\)", f.read())
+    assert [int(r[0]) for r in rows] == list(range(len(rows)))
+    return [tuple(int(v) for v in r[1:]) for r in rows]
 
 
 def _compile(job):

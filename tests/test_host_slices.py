@@ -12,8 +12,7 @@ import pytest
 import paper_2003_06795_amd.binding as ks
 from paper_2003_06795_amd import build as lib_build
 
-TILES = [(16, 16), (32, 16), (16, 32), (32, 32), (64, 16), (16, 64), (64, 32), (32, 64), (64, 64), (64, 64)]
-TILES += [(16, 16), (32, 16), (16, 32), (32, 32), (64, 16), (16, 64), (64, 32), (32, 64), (64, 64)]
+TILES = [tile[:2] for tile in lib_build.slice_tiles()]
 PTR = 1 << 20
 
 
