@@ -131,7 +131,9 @@ typedef struct {
  * K partitions that the chosen member would take, the member that gains without them.  Not so 16-bit products with few output tiles
  * and K from 256 on that ks_gemm_plan reports with a path of 16 and more: the built-in selection runs them in the K-slices form,
  * which no kernel id names (every wave of a work-group sums its own part of K, the parts are added in a fixed order: the same bound
- * on the error, other last bits), unless the estimate for the member is the lower one.  A, B, C: device pointers.
+ * on the error, other last bits), unless the estimate for the member is the lower one.  Which tile they take, and with it the last
+ * bits, follows from the sizes, the layout, the leading dimensions, whether the direct-to-LDS kernels can read the operands where
+ * they lie, and what partitions the scratch would give the member.  A, B, C: device pointers.
  * bf16 operands are raw bfloat16 bit patterns; accumulation and C are fp32.
  * fp32 members of core KS_CORE_MFMA32 with 128 x 128 x 32 tiles, and those with 64 x 64 x 16 ones that have two K groups or no K
  * partitions, multiply a K range of at least 49 (360 with two K groups) on the bf16 matrix pipe, each float as the exact sum of
@@ -283,7 +285,7 @@ int ks_gemm_plan(int dtype, int kernel_id, int transA, int transB, int64_t M, in
  * `reps` back-to-back launches bracketed by one pair of HIP events on `stream`.  Synchronises and
  * writes the per-launch time of each sample (elapsed / reps) in milliseconds to
  * ms_out[0 .. iters-1] (host).  dtype selects the f32 / bf16 entry point; A and B are device
- * pointers of that type.  kernel_id < 0 times the selected kernel (ks_select).
+ * pointers of that type.  kernel_id < 0 times what ks_gemm_* would run for the call (ks_gemm_plan).
  * 1 <= iters <= 1024, reps >= 1, warmup >= 0. */
 int ks_time_gemm(int dtype, int kernel_id, int transA, int transB, int64_t M, int64_t N, int64_t K,
                  float alpha, const void *A, int64_t lda, const void *B, int64_t ldb,
@@ -311,7 +313,8 @@ int ks_features(int64_t M, int64_t N, int64_t K, int64_t batch, int transA, int 
 /* Replace the deployed tree of `dtype` by a copy of nodes[0 .. n-1] (host; node 0 is the root).
  * The tree is validated (child indices in range and acyclic by construction: children must have
  * larger indices than their parent; leaf values must be kernel ids).  n == 0 restores the tree
- * compiled into the library and its rules.  Not thread-safe against concurrent ks_select / ks_gemm calls. */
+ * compiled into the library and its rules.  A tree that is set, be it a copy of that one, names the members that run: the K-slices
+ * form (ks_gemm_*) belongs to the built-in selection alone.  Not thread-safe against concurrent ks_select / ks_gemm calls. */
 int ks_set_selector(int dtype, const ks_tree_node_t *nodes, int n);
 /* Copy the deployed tree out (host).  Returns the node count, or a negative status if cap is
  * too small. */
@@ -324,7 +327,7 @@ int ks_get_selector(int dtype, ks_tree_node_t *nodes, int cap);
  * K-contiguous, where the generic path is at its best, only for outputs of 2^24 entries or more), the call runs as
  * two launches: the remainder of K beyond the whole K-steps through the generic path first, with
  * alpha, beta and the bias, then the whole K-steps through the direct-to-LDS path with beta = 1
- * (ks_launch_plan_t::k_remainder).  enabled == 0 forces the generic path for all of K (for testing
+ * (ks_launch_plan_t::k_remainder), unless it takes the K-slices form, which reads any K as it is.  enabled == 0 forces the generic path for all of K (for testing
  * it at aligned shapes); nonzero restores the default. */
 int ks_set_fast_path(int enabled);
 
@@ -381,7 +384,8 @@ int ks_set_split_partitions(int partitions);
  * the call brings (ks_gemm_with_workspace: any member) or shares (the registered workspace and the static array: members
  * with split_k != 1 only; the others never touch them).  mode == -1 (the default) does so where a cost estimate by
  * flops and bytes says it pays and the scratch holds the copies beside the partial sums of the K partitions that the
- * call takes without them; 0 never; 1 wherever the scratch allows (for testing and tuning).  Not thread-safe. */
+ * call takes without them; 0 never; 1 wherever the scratch allows (for testing and tuning; a selecting call with operands to copy
+ * then runs the member and not the K-slices form).  Not thread-safe. */
 int ks_set_operand_copies(int mode);
 
 /* Measurement aid: copies `bytes` (a multiple of 16; both device pointers 16-byte aligned) with a

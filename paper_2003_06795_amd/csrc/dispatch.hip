@@ -653,7 +653,8 @@ int run_ws(Workspace wsp, int dtype, int id, int transA, int transB, int64_t M, 
     // beta = 1.  The partial result passes through C in fp32 (one more rounding per entry, far inside the
     // bound), so an output kept in bf16 is not served this way.  The line (every layout but NT, and NT from 2^24
     // entries of output on) is a published one: ks_set_fast_path in the header states it, ks_launch_plan_t
-    // reports it, and the bits of every such call, named member or selected, hang on it.  It was drawn when the
+    // reports it, and the bits of every such call that runs a member, named or selected, hang on it (a selecting call that takes the
+    // K-slices form has returned above: 512 x 512 x 1032 TN).  It was drawn when the
     // register-staged path loaded two bytes per lane.  By today's times, cut against register-staged over all of
     // K with a remainder of 24, it would lie at 2^24 entries for NN, TN and TT and nowhere for NT: 4096^3 NN 150 / 165
     // us, TN 140 / 155, TT 142 / 155, NT 160 / 152; 2048^3 NN 39 / 35, TN 35 / 33; 1024^3 NN 14.7 / 12.4.

@@ -30,8 +30,8 @@
 // in flight.  Past the end of the K range the same loads are issued on the last K-step's
 // addresses into halves nobody reads any more: every step is the same straight-line code.
 // Epilogue of the 16x16x32 form: a lane holds four entries of a row (store_entries) and the old values of one to three quadrants
-// are under way while one is stored.  Of one entry per access, us: 2048^3 NT with bias and bf16 output 24.4 -> 22.5, 4096^3 the same
-// without bias 110.7 -> 104.4, 4096 x 4096 x 2048 TN with beta and bias 90.9 -> 80.6, 1500 x 2500 x 3072 TT with beta in bf16 46.9 -> 40.1; level
+// are under way while one is stored.  Of one entry per access, us: 2048^3 NT with bias and bf16 output 24.9 -> 23.3, 4096^3 the same
+// without bias 113.3 -> 107.1, 4096 x 4096 x 2048 TN with beta and bias 92.0 -> 80.7, 1500 x 2500 x 3072 TT with beta in bf16 47.8 -> 41.3; level
 // to 2 % with neither.  Old values requested ahead of the last compute slots, in place of the loads past the end, held those up:
 // 2048^3 NT with beta 24.2 -> 26.4.
 // Preconditions are those of gemm_bf16_dma.hpp.  CUT (BK = 128): K is an odd multiple of 64, and the second

@@ -5,19 +5,20 @@
 // partitions up (4 us of calls that take 6 to 40), or leave the device to a chain of K-steps at memory latency behind a barrier
 // each.  Here wave w of NW takes K-steps w, w + NW, ... of BK, so that the waves read neighbouring pieces of the same rows at
 // the same time; each has a ring of STAGES K-steps in LDS of its own, filled by direct-to-LDS loads, and waits for nobody: no
-// barrier before the sums of the waves meet in LDS and are added in wave order (the bits follow from the sizes and the tile alone).
-// One work-group to a compute unit (120 to 144 KB of stages, 64 to 108 KB in flight).  Bound by what the unit's memory pipe
+// barrier before the sums of the waves meet in LDS and are added in wave order (the bits follow from the sizes and the tile, the
+// tile from slices_tile: layout, strides, alignment and the member's partitions have a say in it).
+// One work-group to a compute unit (120 to 144 KB of stages, 64 to 96 KB in flight).  Bound by what the unit's memory pipe
 // takes, 0.95 to 1.05 us per 100 KB of operands from L2 and about 6 TB/s from memory.
-// us, members as selected before -> here, operands rotated through three sets: 8192 x 16 x 8192 NN 34.7 -> 23.1, 2048 x 16 x 2048 NT 6.4 -> 3.8,
-// 4096 x 32 x 4096 NT 10.9 -> 8.0, 512 x 512 x 2048 NN 10.5 -> 6.5, 128 x 128 x 2048 NN 6.4 -> 3.9, 1024 x 1024 x 4096 NT 18.9 -> 16.6.
+// us, members as selected before -> here, operands rotated through three sets: 8192 x 16 x 8192 NN 34.7 -> 22.8, 2048 x 16 x 2048 NT 6.0 -> 3.4
+// (launches of a graph), 4096 x 32 x 4096 NT 10.8 -> 7.7, 512 x 512 x 2048 NN 10.6 -> 6.7, 128 x 128 x 2048 NN 6.4 -> 4.1, 1024 x 1024 x 4096 NT 19.8 -> 19.4.
 //
-// An operand that only one work-group reads and that is larger than the last-level cache keeps is loaded past it (NT_A, NT_B of
-// `stream`): 8192 x 16 x 8192 26.5 -> 23.1 us, 16384 x 16 x 8192 48.9 -> 43.8 (6.1 TB/s); smaller ones that the cache does hold
-// lose by it (4096 x 16 x 8192 12.5 -> 17.0).
+// An operand whose pieces one work-group each reads and that is large enough to be gone from the last-level cache before it is used
+// again is loaded past it (NT_A, NT_B of `stream`): 8192 x 16 x 8192 26.6 -> 22.9 us, 14336 x 16 x 8192 46.8 -> 41.8 (5.6 TB/s); slices.hpp
+// has the line and what it costs where nothing else comes in between.
 // Preconditions are those of gemm_bf16_dma.hpp, K a multiple of 64, no K partitions over work-groups.
 //
 // gemm_bf16_slices_staged_kernel is the same for operands that nothing aligns: a wave holds PF K-steps in registers, as the members'
-// register-staged path loads them (Bf16Staging), and passes them through one stage of its own.  1000 x 777 x 1509 fp16 NN 17.4 -> 13.7 us;
+// register-staged path loads them (Bf16Staging), and passes them through one stage of its own (48 to 128 KB of LDS).  1000 x 777 x 1509 fp16 NN 17.6 -> 13.7 us;
 // 1597 drawn products (64 .. 4096, skinny and tall, rows padded by up to three) of which 521 take it 0.70 of the time.
 #pragma once
 #include "gemm_bf16_dma.hpp"

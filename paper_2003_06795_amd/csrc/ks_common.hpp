@@ -32,7 +32,8 @@ struct __attribute__((packed, aligned(2))) AnyUintx2 {
 // n / d for n < 2^31, as a multiplication and a shift that the scalar unit does: there is no integer division, and what the
 // compiler puts in its place, some 25 dependent instructions of the vector unit for each of the four that find a tile, was
 // most of the time from the kernel's arguments to its first load.  1024 x 32x64x16 fp32 on 32 x 32 tiles 6.55 -> 5.86 us, 700 x
-// 60x52x33 11.1 -> 10.2, 401408 x 64 x 27 39.8 -> 38.3, 480 x 1184 x 2592 TN 31.5 -> 30.4; level from 50 us on.
+// 60x52x33 11.2 -> 10.3, 401408 x 64 x 27 39.0 -> 38.2; level from 20 us on where tiles have more than a few K-steps
+// (480 x 1184 x 2592 TN 31.7 -> 31.6).
 // m = ceil(2^(31 + s) / d) with 2^(s - 1) < d <= 2^s: m d exceeds 2^(31 + s) by less than 2^s, which n < 2^31 makes less than one
 // part in d of a quotient's unit.
 struct Divisor {
@@ -98,9 +99,10 @@ inline void set_tile_order(GemmParams &p) {
 // What a launch of one batch item and no K partitions that reads its tile needs before its first loads, as three arguments in front
 // of the others: the build has the compiler put the first fourteen dwords into scalar registers when a wave starts
 // (-amdgpu-kernarg-preload-count), where all others come from memory that no cache holds at a launch.  Three vectors, because the
-// runtime copies argument by argument (eleven scalars cost the host 0.15 us a call).  For the kernels of short calls, us:
-// fp32 200 x 300 x 700 NT (K-sliced) 4.87 -> 4.53, bf16 128 x 128 x 2048 NT (K slices) 3.52 -> 3.26, 512 x 512 x 512 NT (direct-to-LDS)
-// 3.67 -> 3.42; level to 1 % the other way elsewhere.
+// runtime copies argument by argument (eleven scalars cost the host 0.15 us a call).  For the kernels of short calls, us, launches
+// of a graph: fp32 73 x 57 x 232 NT (K-sliced) 3.09 -> 2.66, 359 x 69 x 24 NT (direct) 2.48 -> 2.18, 200 x 300 x 700 NT 5.05 -> 4.65, 37 x 1001 x 515
+// NT 4.82 -> 4.75; bf16 128 x 128 x 2048 NT (K slices) 3.29 -> 3.21, 512 x 512 x 512 NT 3.14 -> 3.07; level to 1 % the other way elsewhere.
+// Calls that wait for the host (128 x 128 x 128 fp32: kernel 3.1, call 4.1) show nothing of it.
 typedef unsigned long long HotPointers __attribute__((ext_vector_type(2)));
 typedef int HotInts __attribute__((ext_vector_type(4)));
 #define KS_PARAMS const HotPointers hotAB, const HotInts hotSizes, const HotInts hotForm, const GemmParams rest

@@ -47,7 +47,8 @@ int64_t sat_mul(int64_t a, int64_t b) {
 // corrected, from the sizes alone: every caller of ks_select and every selecting entry point gets the same
 // member, whatever the alignment of its operands, and whatever its scratch but for the rules that count on a K split
 // (by_few_rows_or_columns): a call whose scratch does not hold the partitions gets what it would without them.  A caller's own
-// tree is followed as it is.
+// tree is followed as it is.  (Whether the K-slices form then runs in place of a 16-bit member, slices.hpp, follows from alignment and
+// scratch too.)
 struct Tile {
     int id, bm, bn, bk;
 };
